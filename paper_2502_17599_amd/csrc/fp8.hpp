@@ -28,6 +28,18 @@ __device__ __forceinline__ uint32_t float_to_e4m3(float y) {
   return sign | code;
 }
 
+// Codes of four floats with magnitudes up to 448 (nearest representable value, ties to even), packed in element order.
+__device__ __forceinline__ uint32_t floats_to_e4m3x4(float f0, float f1, float f2, float f3) {
+#if __HIP_DEVICE_COMPILE__
+  int w = 0;
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(f0, f1, w, false);
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(f2, f3, w, true);
+  return (uint32_t)w;
+#else
+  return 0u;
+#endif
+}
+
 // Two codes (bytes 0,1 or bytes 2,3 of `word`) as floats.
 __device__ __forceinline__ void e4m3x2_to_float(uint32_t word, bool upper, float& f0, float& f1) {
 #if __HIP_DEVICE_COMPILE__
