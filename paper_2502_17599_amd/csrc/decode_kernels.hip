@@ -3,12 +3,12 @@
 // compression pass kept for the layer (S_l per kv head, Section 3.2) followed by the rows appended
 // since (K = [K, k_t], V = [V, v_t]).
 //
-// The step reads every cached key and value once and does 4*G*d flops per (key, value) pair, so for
-// the group sizes of the workloads it is bound by HBM: the kernels are plain streaming kernels (no
-// LDS staging of the cache, no matrix unit).  The rows of one (layer, kv head) are cut into NS
-// equal chunks; one workgroup takes one chunk for all G query heads of the group (flash-decoding
-// style: a running maximum, normaliser and weighted value sum per head), a second small kernel merges
-// the chunks.
+// The step reads every cached key and value once and does 4*G*d flops per (key, value) pair, so it is bound by HBM
+// as long as the instructions per byte stay few: fp32 caches take a plain streaming kernel on the vector unit, bf16
+// and 8-bit caches put both products on the matrix unit.  The rows of every (layer, kv head) are cut into chunks of
+// about the same size over all layers (budgets differ by more than a factor of ten between layers); one workgroup
+// takes one chunk for all G query heads of the group (flash-decoding style: a running maximum, normaliser and
+// weighted value sum per head), a second small kernel merges the chunks.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -23,8 +23,14 @@ namespace meda {
 
 constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / 64;
-constexpr int kDecRowsPerGroup = 128;  // rows a workgroup should get at the average layer budget, per query head of the group (up to 4)
-constexpr int kDecMaxSplit = 64;
+// Rows per chunk: the rows of the whole cache over kDecTargetGroups workgroups (256 CUs, three workgroups each, two
+// rounds), between one step of a workgroup's four waves and a size that bounds the unevenness.  Measured over 524288
+// bf16 rows (one head per kv head) with 1024 / 1536 / 2048 / 3072 workgroups: 52 / 48 / 52 / 52 us; over 838856 8-bit
+// rows: 53 / 50 / 51 / 53 us.
+constexpr int kDecTargetGroups = 1536;
+constexpr int kDecMinRows = 128, kDecMaxRows = 2048;
+constexpr int kDecInlineNew = 128;  // so many appended rows ride with the layer's last chunk instead of chunks of their own
+constexpr int kDecMaxSplit = 64;  // average number of chunks per layer, at most
 
 struct DecodeArgs {
   const char* q;            // [L][Hq][d]
@@ -35,16 +41,103 @@ struct DecodeArgs {
   const char* k_new;        // [L][Hkv][n_new][d] or null
   const char* v_new;
   char* out;                // [L][Hq][d]
-  float* part;              // [L][Hq][NP][d + 2]: weighted value sum, maximum (base-2 logits), normaliser
+  float* part;              // [NC + L*NSN][Hq][d + 2]: weighted value sum, maximum (base-2 logits), normaliser
   int L, Hq, Hkv, G, n_new;
-  int NS, NSN, NP;          // chunks of the cached rows, chunks of the appended rows, NS + NSN
+  int R;                    // rows per chunk aimed at
+  int NC, NSN;              // chunk ids of the cached rows (at most), chunks of a layer's appended rows
   float scale_log2;
   // 8-bit cache (FP8 instantiation): k_cache / v_cache hold E4M3 codes, one scale per row
   const float* k_scale;     // [B*Hkv]
   const float* v_scale;
-  int sp0;                  // chunk index of the launch's first workgroup (the appended rows of an 8-bit cache
-                            // are taken by a second launch of the plain kernel, which starts at NS)
 };
+
+// The chunks of the cached rows are numbered layer after layer: layer l has ceil(S_l / R) of them, at least one.  The host sizes
+// the launch for NC = floor(B / R) + L ids, which bounds their number for S_1 + .. + S_L <= B; should the lengths
+// exceed B, R is doubled until they fit (every workgroup computes the same R).  Evaluated by every wave on its own:
+// lane i holds layer base + i.
+struct LayerChunks {
+  int layer;      // the layer asked for, or the one that owns the chunk id asked for (-1: id past the last chunk)
+  int first;      // id of its first chunk
+  int n;          // its number of chunks
+  int rows;       // S_l
+  long long off;  // layer_off[layer]
+};
+// Inclusive sum over the lanes of the wave (data-parallel primitives, no LDS traffic).
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8: inside the rows of 16
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // lane 15 of rows 0, 2 to rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2, 3
+  return v;
+}
+// by_layer >= 0: the chunks of that layer; otherwise the owner of chunk `id`
+__device__ __forceinline__ LayerChunks find_chunks(const DecodeArgs& a, int by_layer, int id) {
+  const int lane = threadIdx.x & 63;
+  LayerChunks out{-1, 0, 0, 0, 0};
+  for (int R = a.R;; R *= 2) {
+    int total = 0;
+    for (int base = 0; base < a.L; base += 64) {
+      const int lc = min(base + lane, a.L - 1);
+      const int s = (base + lane < a.L) ? a.layer_len[lc] : 0;
+      const long long off = a.layer_off[lc];
+      const int n = base + lane < a.L ? max(1, (int)(((unsigned)s + (unsigned)R - 1u) / (unsigned)R)) : 0;
+      const int inc = wave_inclusive_sum(n);
+      const int first = total + inc - n;
+      const bool mine = by_layer >= 0 ? base + lane == by_layer : (id >= first && id < first + n);
+      const unsigned long long b = __ballot(mine);
+      if (b != 0ull) {
+        const int src = __ffsll((unsigned long long)b) - 1;
+        out.layer = base + src;
+        out.first = __builtin_amdgcn_readlane(first, src);
+        out.n = __builtin_amdgcn_readlane(n, src);
+        out.rows = __builtin_amdgcn_readlane(s, src);
+        out.off = (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(off >> 32), src) << 32) |
+                              (unsigned)__builtin_amdgcn_readlane((int)off, src));
+      }
+      total += __builtin_amdgcn_readlane(inc, 63);
+    }
+    if (total <= a.NC || R > (1 << 29)) return out;
+    out.layer = -1;
+  }
+}
+
+// What one workgroup works on.
+struct DecodeChunk {
+  int l;         // layer
+  size_t row0;   // first row of the chunk, of head 0 (cached or appended rows) ...
+  size_t head;   // ... and rows from one head to the next
+  int rows;      // its length
+  bool fresh;    // appended rows
+  bool last;     // last chunk of the layer's cached rows: the appended rows follow it when they have no chunks (NSN = 0)
+};
+__device__ __forceinline__ bool chunk_of_group(const DecodeArgs& a, int id, DecodeChunk& c) {
+  if (id >= a.NC) {
+    const int k = id - a.NC, s = k % a.NSN;  // (NSN > 0: the launch has ids past NC)
+    const int rows = (a.n_new + a.NSN - 1) / a.NSN;
+    const int beg = min(s * rows, a.n_new);
+    c.l = k / a.NSN;
+    c.rows = min(a.n_new - beg, rows);
+    c.row0 = (size_t)c.l * a.Hkv * a.n_new + beg;
+    c.head = a.n_new;
+    c.fresh = true;
+    c.last = false;
+    return true;
+  }
+  const LayerChunks lc = find_chunks(a, -1, id);
+  if (lc.layer < 0) return false;
+  const int per = (lc.rows + lc.n - 1) / lc.n;
+  const int rows = (per + 31) & ~31;  // whole steps of a wave
+  const int beg = min((id - lc.first) * rows, lc.rows);
+  c.l = lc.layer;
+  c.rows = min(lc.rows - beg, rows);
+  c.row0 = (size_t)lc.off * a.Hkv + beg;
+  c.head = lc.rows;
+  c.fresh = false;
+  c.last = id - lc.first == lc.n - 1;
+  return true;
+}
 
 // 8-byte load of data that is read once (see load16_stream)
 __device__ __forceinline__ uint2 load8_stream(const void* p) {
@@ -53,50 +146,48 @@ __device__ __forceinline__ uint2 load8_stream(const void* p) {
   return make_uint2(t.x, t.y);
 }
 
-template <typename T>
-struct Elems;
-template <>
-struct Elems<bf16_t> {
-  static constexpr int kPerPiece = 8;
-  static __device__ __forceinline__ void unpack(const uint4& v, float (&f)[8]) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+__device__ __forceinline__ void store_elem(char* dst, float x, bf16_t) {
+  *reinterpret_cast<uint16_t*>(dst) = (uint16_t)float_to_bf16_rne(x);
+}
+__device__ __forceinline__ void store_elem(char* dst, float x, float) { *reinterpret_cast<float*>(dst) = x; }
+
+__device__ __forceinline__ void unpack4(const uint4& v, float (&f)[4]) {
+  f[0] = __uint_as_float(v.x);
+  f[1] = __uint_as_float(v.y);
+  f[2] = __uint_as_float(v.z);
+  f[3] = __uint_as_float(v.w);
+}
+__device__ __forceinline__ float dot4(const uint4& a, const uint4& b) {
+  float d = __uint_as_float(a.x) * __uint_as_float(b.x);
+  d = fmaf(__uint_as_float(a.y), __uint_as_float(b.y), d);
+  d = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), d);
+  return fmaf(__uint_as_float(a.w), __uint_as_float(b.w), d);
+}
+
+// Chunk `id` of head h of a workgroup: the waves' results (red_*) merged and written.
+template <int H, int D>
+__device__ __forceinline__ void write_partial(const DecodeArgs& a, int id, int l, int g, const float (&red_o)[kDecWaves][H][D],
+                                              const float (&red_m)[kDecWaves][H], const float (&red_z)[kDecWaves][H]) {
+  for (int i = threadIdx.x; i < a.G * D; i += kDecThreads) {
+    const int h = i / D, j = i - h * D;
+    float mn = red_m[0][h];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = __uint_as_float(w[i] << 16);
-      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    for (int w = 1; w < kDecWaves; ++w) mn = fmaxf(mn, red_m[w][h]);
+    float zs = 0.f, os = 0.f;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) {
+      const float c = __builtin_amdgcn_exp2f(red_m[w][h] - mn);
+      zs = fmaf(red_z[w][h], c, zs);
+      os = fmaf(red_o[w][h][j], c, os);
+    }
+    float* dst = a.part + ((size_t)id * a.Hq + g * a.G + h) * (D + 2);
+    dst[j] = os;
+    if (j == 0) {
+      dst[D] = mn;
+      dst[D + 1] = zs;
     }
   }
-  // sum of the 8 products of two packed pieces (packed dot instruction: exact products, fp32 sums)
-  static __device__ __forceinline__ float dot(const uint4& a, const uint4& b) {
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
-    float d = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x[i]), __builtin_bit_cast(bf16x2_t, y[i]), d, false);
-    return d;
-  }
-  static __device__ __forceinline__ void store(char* dst, float x) {
-    *reinterpret_cast<uint16_t*>(dst) = (uint16_t)float_to_bf16_rne(x);
-  }
-};
-template <>
-struct Elems<float> {
-  static constexpr int kPerPiece = 4;
-  static __device__ __forceinline__ void unpack(const uint4& v, float (&f)[4]) {
-    f[0] = __uint_as_float(v.x);
-    f[1] = __uint_as_float(v.y);
-    f[2] = __uint_as_float(v.z);
-    f[3] = __uint_as_float(v.w);
-  }
-  static __device__ __forceinline__ float dot(const uint4& a, const uint4& b) {
-    float d = __uint_as_float(a.x) * __uint_as_float(b.x);
-    d = fmaf(__uint_as_float(a.y), __uint_as_float(b.y), d);
-    d = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), d);
-    return fmaf(__uint_as_float(a.w), __uint_as_float(b.w), d);
-  }
-  static __device__ __forceinline__ void store(char* dst, float x) { *reinterpret_cast<float*>(dst) = x; }
-};
+}
 
 // Value of a partner lane whose lane-index bit X differs (X = 1, 2, 4, 8 inside a row of 16 lanes: data-parallel
 // primitives, no LDS traffic; the partners of 4 and 8 are the mirrored lanes of the half row / row, which differ
@@ -175,62 +266,28 @@ __device__ __forceinline__ void row_all_gather(float mine, float (&w)[GP], int c
   RowAllGather<GP, 1, LPR / GP>::run(w, cc);   // the last halving step of the reduce-scatter had distance LPR / GP
 }
 
-// grid (NP, Hkv, L), 256 threads.  A row is read by LPR = row bytes / 16 lanes (16 bytes each), so a
-// wave takes 64 / LPR rows per step; every lane group keeps, per query head of the group, the running
-// maximum, the normaliser and its piece of the weighted value sum over the rows it has seen.  GP is
-// the group size rounded up to a power of two (heads past G repeat head 0 and are not stored).
-// FP8: the cached rows are E4M3 codes with one scale per row (8-byte pieces, converted to packed bf16 on
-// arrival, which is exact; the key's scale multiplies the logit, the value's scale the softmax weight); the
-// queries stay bf16 and the launch covers the cached rows only.
-template <typename T, int D, int GP, bool FP8>
+// fp32 cache.  grid (NC + L*NSN, Hkv), 256 threads.  A row is read by LPR = row bytes / 16 lanes (16 bytes each), so
+// a wave takes 64 / LPR rows per step; every lane group keeps, per query head of the group, the running maximum, the
+// normaliser and its piece of the weighted value sum over the rows it has seen.  GP is the group size rounded up to a
+// power of two (heads past G repeat head 0 and are not stored).
+template <int D, int GP>
 __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeArgs a) {
-  using TL = Tile<T, D>;
-  using EL = Elems<T>;
+  using TL = Tile<float, D>;
   constexpr int LPR = TL::kChunksPerRow;
   constexpr int MS = 64 / LPR;
-  constexpr int E = EL::kPerPiece;
+  constexpr int E = 4;
   constexpr int U = 2;  // steps whose loads are issued together
-  static_assert(!FP8 || sizeof(T) == 2, "the 8-bit cache is read with bf16 queries");
-  constexpr size_t kCacheRowBytes = FP8 ? (size_t)D : (size_t)TL::kRowBytes;
-  constexpr int kCachePieceBytes = FP8 ? E : 16;
   __shared__ float red_o[kDecWaves][GP][D];
   __shared__ float red_m[kDecWaves][GP], red_z[kDecWaves][GP];
 
-  const int sp = blockIdx.x + a.sp0, g = blockIdx.y, l = blockIdx.z;
+  const int id = blockIdx.x, g = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sub = lane / LPR, cc = lane - sub * LPR;
 
-  // the rows of this workgroup
-  const char *kb, *vb;
-  const float *ksc = nullptr, *vsc = nullptr;
-  int r_beg, r_end;
-  size_t row_bytes = kCacheRowBytes;
-  int piece_bytes = kCachePieceBytes;
-  if (FP8 || sp < a.NS) {
-    const int S = a.layer_len[l];
-    const int chunk = (S + a.NS - 1) / a.NS;
-    r_beg = sp * chunk;
-    r_end = min(S, r_beg + chunk);
-    const size_t row0 = (size_t)a.layer_off[l] * a.Hkv + (size_t)g * S;
-    kb = a.k_cache + row0 * kCacheRowBytes;
-    vb = a.v_cache + row0 * kCacheRowBytes;
-    if (FP8) {
-      ksc = a.k_scale + row0;
-      vsc = a.v_scale + row0;
-    }
-  } else {
-    const int chunk = (a.n_new + a.NSN - 1) / a.NSN;
-    r_beg = (sp - a.NS) * chunk;
-    r_end = min(a.n_new, r_beg + chunk);
-    const size_t base = ((size_t)(l * a.Hkv + g) * a.n_new) * TL::kRowBytes;
-    kb = a.k_new + base;
-    vb = a.v_new + base;
-    row_bytes = TL::kRowBytes;
-    piece_bytes = 16;
-  }
-  kb += cc * piece_bytes;
-  vb += cc * piece_bytes;
+  DecodeChunk ch;
+  if (!chunk_of_group(a, id, ch)) return;
+  const int l = ch.l;
 
   // this lane's piece of the G queries, kept packed
   uint4 qp[GP];
@@ -246,66 +303,57 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
 #pragma unroll
     for (int e = 0; e < E; ++e) o[h][e] = 0.f;
 
-  for (int r0 = r_beg + wave * MS; r0 < r_end; r0 += U * kDecWaves * MS) {
-    uint4 kv[U], vv[U];
-    float sck[U], scv[U];
-    bool ok[U];
+  auto walk = [&](const char* k, const char* v, size_t row0, int r_end) {
+    const char *kb = k + row0 * TL::kRowBytes + cc * 16, *vb = v + row0 * TL::kRowBytes + cc * 16;
+    for (int r0 = wave * MS; r0 < r_end; r0 += U * kDecWaves * MS) {
+      uint4 kv[U], vv[U];
+      bool ok[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = r0 + u * kDecWaves * MS + sub;
-      ok[u] = r < r_end;
-      const int rc = min(r, r_end - 1);  // rows past the end repeat the last one
-      const size_t ro = (size_t)rc * row_bytes;
-      if constexpr (FP8) {
-        const uint2 kc = load8_stream(kb + ro), vc = load8_stream(vb + ro);
-        sck[u] = ksc[rc];
-        scv[u] = vsc[rc];
-        kv[u] = e4m3x8_to_bf16x8(kc);          // keys as packed bf16 for the dot instruction
-        vv[u] = make_uint4(vc.x, vc.y, 0u, 0u);  // values stay codes until they are needed as floats
-      } else {
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * kDecWaves * MS + sub;
+        ok[u] = r < r_end;
+        const size_t ro = (size_t)min(r, r_end - 1) * TL::kRowBytes;  // rows past the end repeat the last one
         kv[u] = load16_stream(kb + ro);
         vv[u] = load16_stream(vb + ro);
-        sck[u] = scv[u] = 1.0f;
       }
-    }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float s[GP];
+      for (int u = 0; u < U; ++u) {
+        float s[GP];
 #pragma unroll
-      for (int h = 0; h < GP; ++h) s[h] = EL::dot(qp[h], kv[u]);
-      row_reduce_scatter<GP, LPR>(s, cc);
-      const float s1 = ok[u] ? (FP8 ? s[0] * sck[u] * a.scale_log2 : s[0] * a.scale_log2) : kNegBig;
-      // a new maximum of some head in some lane group: rescale what that head has so far (rare after
-      // the first rows)
-      if (__ballot(s1 > m1) != 0ull) {
-        const float mn = fmaxf(m1, s1);
-        const float c1 = __builtin_amdgcn_exp2f(m1 - mn);
-        z1 *= c1;
-        m1 = mn;
-        float c[GP];
-        row_all_gather<GP, LPR>(c1, c, cc);
+        for (int h = 0; h < GP; ++h) s[h] = dot4(qp[h], kv[u]);
+        row_reduce_scatter<GP, LPR>(s, cc);
+        const float s1 = ok[u] ? s[0] * a.scale_log2 : kNegBig;
+        // a new maximum of some head in some lane group: rescale what that head has so far (rare after
+        // the first rows)
+        if (__ballot(s1 > m1) != 0ull) {
+          const float mn = fmaxf(m1, s1);
+          const float c1 = __builtin_amdgcn_exp2f(m1 - mn);
+          z1 *= c1;
+          m1 = mn;
+          float c[GP];
+          row_all_gather<GP, LPR>(c1, c, cc);
+#pragma unroll
+          for (int h = 0; h < GP; ++h)
+#pragma unroll
+            for (int e = 0; e < E; ++e) o[h][e] *= c[h];
+        }
+        const float p1 = ok[u] ? __builtin_amdgcn_exp2f(s1 - m1) : 0.f;
+        z1 += p1;
+        float p[GP], vf[E];
+        row_all_gather<GP, LPR>(p1, p, cc);
+        unpack4(vv[u], vf);
 #pragma unroll
         for (int h = 0; h < GP; ++h)
 #pragma unroll
-          for (int e = 0; e < E; ++e) o[h][e] *= c[h];
+          for (int e = 0; e < E; ++e) o[h][e] = fmaf(p[h], vf[e], o[h][e]);
       }
-      const float p1 = ok[u] ? __builtin_amdgcn_exp2f(s1 - m1) : 0.f;
-      z1 += p1;
-      float p[GP], vf[E];
-      row_all_gather<GP, LPR>(FP8 ? p1 * scv[u] : p1, p, cc);   // the value row's scale rides on its weight
-      if constexpr (FP8) {
-        e4m3x2_to_float(vv[u].x, false, vf[0], vf[1]);
-        e4m3x2_to_float(vv[u].x, true, vf[2], vf[3]);
-        e4m3x2_to_float(vv[u].y, false, vf[4], vf[5]);
-        e4m3x2_to_float(vv[u].y, true, vf[6], vf[7]);
-      } else {
-        EL::unpack(vv[u], vf);
-      }
-#pragma unroll
-      for (int h = 0; h < GP; ++h)
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[h][e] = fmaf(p[h], vf[e], o[h][e]);
     }
+  };
+  if (ch.fresh) {
+    walk(a.k_new, a.v_new, ch.row0 + g * ch.head, ch.rows);
+  } else {
+    walk(a.k_cache, a.v_cache, ch.row0 + g * ch.head, ch.rows);
+    if (ch.last && a.n_new > 0 && a.NSN == 0) walk(a.k_new, a.v_new, (size_t)(l * a.Hkv + g) * a.n_new, a.n_new);
   }
   float m[GP], z[GP];
   row_all_gather<GP, LPR>(m1, m, cc);
@@ -337,249 +385,370 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
     }
   }
   __syncthreads();
-  for (int i = tid; i < a.G * D; i += kDecThreads) {
-    const int h = i / D, j = i - h * D;
-    float mn = red_m[0][h];
-#pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) mn = fmaxf(mn, red_m[w][h]);
-    float zs = 0.f, os = 0.f;
-#pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-      const float c = __builtin_amdgcn_exp2f(red_m[w][h] - mn);
-      zs = fmaf(red_z[w][h], c, zs);
-      os = fmaf(red_o[w][h][j], c, os);
-    }
-    float* dst = a.part + ((size_t)(l * a.Hq + g * a.G + h) * a.NP + sp) * (D + 2);
-    dst[j] = os;
-    if (j == 0) {
-      dst[D] = mn;
-      dst[D + 1] = zs;
-    }
+  write_partial<GP, D>(a, id, l, g, red_o, red_m, red_z);
+}
+
+// bf16 and 8-bit caches, on the matrix unit.  grid (NC + L*NSN, Hkv), 4 waves, each taking every fourth step of 32
+// rows (keys) of the chunk.
+//   logits  D[key][col] = sum_d K[key][d] Q[col][d]     2 x d/32 x v_mfma_f32_16x16x32_bf16 (exact products, fp32 sums)
+//   output  O[row][col] += sum_key P[row][key] V[key][col]   d/16 x v_mfma_f32_16x16x32_bf16
+// The softmax weights are not rounded: a weight p in fp32 is the exact sum of three bf16 numbers (the upper 8, the
+// next 8 and the last 8 significant bits), and the second product takes the three parts as rows of its own, which
+// the 16 rows of the instruction have room for: column c of the first product is query head c % GP, so lane column c
+// holds the weights of that head and passes on part c / GP (GP heads, rounded up to a power of two).  Groups of 5 to
+// 8 heads fill the 16 rows with two parts and take a second instruction for the third.
+//
+// Lane (c, g) = (l % 16, l / 16).  First product: it holds, for every k-step, 8 elements of key c (and 16 + c) and the
+// same 8 of query head c % GP (any assignment of elements to (lane group, step) gives the same sum: step k takes
+// the elements 32 k + 8 g .. + 7, or 64 (k / 2) + 16 g + 8 (k % 2) .. + 7 with FP8, so that a load brings 16 bytes of a
+// row in either case), and receives that head's logits for the keys 4 g + i and 16 + 4 g + i, i = 0..3.  The second
+// product contracts over keys, in the order (lane group, register): its weight operand is then exactly what the lane
+// has (no movement between lanes), and its value operand the same 8 keys at one column: the lane loads piece c (d/16
+// elements) of these 8 rows and transposes them in registers (one byte permutation per two elements; unpacking to
+// fp32 would cost one instruction per element).
+// FP8: the cached rows are E4M3 codes with one scale per row, converted to packed bf16 on arrival (exact); the key's
+// scale multiplies the logit and the value's scale the weight.  The appended rows of a step are bf16 in either case.
+//
+// Bound by HBM: 524288 bf16 rows, one head per kv head, in 47 us (5.7 TB/s); 650000 rows, seven heads, in 62 us
+// (5.4 TB/s); 838856 8-bit rows, four heads, in 50 us (4.6 TB/s).  The kernels this one replaced took 47, 79 and 90 us:
+// they spent about 160 vector instructions per 16 rows and wave (up to four heads) or 32 fp32 matrix instructions of
+// 32 clocks (five to eight), and cut every layer into the same number of chunks, so that the layer with the largest
+// budget had the longest ones.
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// out[i] = the value of lane FIRST + i of this lane's row of 16 lanes, i = 0..7 (0x150 + n: broadcast of lane n)
+template <int FIRST>
+__device__ __forceinline__ void row_broadcast(float v, float (&out)[8]) {
+  const int i = __float_as_int(v);
+  out[0] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 0, 0xF, 0xF, true));
+  out[1] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 1, 0xF, 0xF, true));
+  out[2] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 2, 0xF, 0xF, true));
+  out[3] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 3, 0xF, 0xF, true));
+  out[4] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 4, 0xF, 0xF, true));
+  out[5] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 5, 0xF, 0xF, true));
+  out[6] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 6, 0xF, 0xF, true));
+  out[7] = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x150 + FIRST + 7, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ float group_max(float v) {  // over the four lane groups of 16
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float group_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// N bytes of a row that is read once, as dwords (see load16_stream)
+template <int N>
+__device__ __forceinline__ void load_piece(const char* p, uint32_t (&w)[N / 4]) {
+  if constexpr (N == 16) {
+    const uint4 v = load16_stream(p);
+    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+  } else if constexpr (N == 8) {
+    const uint2 v = load8_stream(p);
+    w[0] = v.x; w[1] = v.y;
+  } else {
+    w[0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p));
   }
 }
 
-// The same partial step on the matrix unit, for bf16 rows of 128 elements and groups of 5 to 8 query heads, where
-// the kernel above is bound by the vector ALU (about 160 vector instructions per 32 bytes a lane reads) and not by
-// HBM.  A wave takes 16 rows per step:
-//   logits  D[key][head] = sum_d K[key][d] Q[head][d]    4 x v_mfma_f32_16x16x32_bf16 (exact products, fp32 sums)
-//   output  O[head][col] += sum_key P[key][head] V[key][col]   32 x v_mfma_f32_16x16x4_f32 (fp32 weights and values)
-// Lane l = (c, g) = (l % 16, l / 16).  For the logits it holds the pieces g, 4+g, 8+g, 12+g (16 bytes each) of key c
-// and of query head c, and receives the logits of head c for the keys 4g .. 4g+3.  The second product runs over the
-// keys in four instructions i = 0..3, instruction i taking the keys {4g' + i} with g' as its k index: its weight
-// operand is then this lane's own register i (no cross-lane movement), and its value operand element j of piece c of
-// key 4g + i, which the lane loads itself.  Output column 8c + j of the heads 4g .. 4g+3 accumulates in this lane.
-// The running maximum of a head is kept common to the four lane groups (they hold different keys of the same
-// head); the normaliser is summed per group and merged at the end.
-constexpr int kDecMfmaRows = 16;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+// State of a wave while it walks its rows.
+template <int D>
+struct DecodeState {
+  float m_run, z_run;   // of head c % GP; m_run is the same in the four lane groups
+  f32x4_t acc[D / 16];  // acc[j][r]: output column (d/16) c + j, row 4 g + r
+};
 
-// FP8: the cached rows are E4M3 codes with one scale per row (pieces of 8 bytes; keys become packed bf16 on arrival,
-// which is exact, and the key's scale multiplies the logit; values become fp32 and their scale rides on the weight);
-// the launch then covers the cached rows only.
-template <int D, bool FP8>
-__global__ void __launch_bounds__(kDecThreads, 2) decode_partial_mfma_kernel(DecodeArgs a) {
-  static_assert(D == 128, "16 pieces per row: one per lane of a lane group");
-  constexpr int kRowBytes = D * 2;                     // bf16 rows (queries, appended rows, the bf16 cache)
-  constexpr int kCacheRowBytes = FP8 ? D : kRowBytes;  // rows of the cache this launch reads
-  constexpr int kPiece = FP8 ? 8 : 16;
-  constexpr int GPM = 16;  // heads the matrix shapes hold (a.G <= 8 of them are real)
-  __shared__ float red_o[kDecWaves][8][D];
-  __shared__ float red_m[kDecWaves][8], red_z[kDecWaves][8];
+// The r_end rows of one chunk.  kb, vb (ksc, vsc): its first row.  LEAN: keys and values are never held together
+// (fewer registers, more waiting).
+template <int D, int GP, bool FP8, bool LEAN>
+__device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp)[D / 32], const char* kb, const char* vb,
+                                            const float* ksc, const float* vsc, int r_end, float scale_log2) {
+  constexpr int KS = D / 32;                  // k-steps of the first product
+  constexpr int PE = D / 16;                  // elements of a value piece = instructions of the second product
+  constexpr int kEl = FP8 ? 1 : 2;            // bytes per element
+  constexpr int kRowBytes = D * kEl;
+  constexpr int kStep = 32, kStride = kDecWaves * kStep;
+  const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = c / GP;
 
-  const int sp = blockIdx.x + a.sp0, g = blockIdx.y, l = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 15, grp = lane >> 4;
-
-  const char *kb, *vb;
-  const float *ksc = nullptr, *vsc = nullptr;
-  int r_beg, r_end;
-  if (FP8 || sp < a.NS) {
-    const int S = a.layer_len[l];
-    const int chunk = (S + a.NS - 1) / a.NS;
-    r_beg = sp * chunk;
-    r_end = min(S, r_beg + chunk);
-    const size_t row0 = (size_t)a.layer_off[l] * a.Hkv + (size_t)g * S;
-    kb = a.k_cache + row0 * kCacheRowBytes;
-    vb = a.v_cache + row0 * kCacheRowBytes;
-    if (FP8) {
-      ksc = a.k_scale + row0;
-      vsc = a.v_scale + row0;
+  constexpr int KL = D * kEl / 64;            // 16-byte loads per key and lane
+  // One step's rows.
+  struct Rows {
+    uint32_t k[2][KL][4], v[8][PE * kEl / 4];
+    float scale;
+  };
+  const float* sc = c < 8 ? ksc : vsc;
+  auto load_keys = [&](Rows& t, int r0) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      // rows past the end repeat the last one (their weights are zero).  No streaming hint here: a load instruction
+      // takes half a cache line of every row (with the hint the line was fetched again for the other half: 5.3
+      // instead of 5.6 TB/s)
+      const unsigned ro = (unsigned)min(r0 + 16 * b + c, r_end - 1) * (unsigned)kRowBytes + (unsigned)(16 * g);
+#pragma unroll
+      for (int k = 0; k < KL; ++k) {
+        const uint4 x = *reinterpret_cast<const uint4*>(kb + (ro + 64 * k));
+        t.k[b][k][0] = x.x; t.k[b][k][1] = x.y; t.k[b][k][2] = x.z; t.k[b][k][3] = x.w;
+      }
     }
-  } else {
-    const int chunk = (a.n_new + a.NSN - 1) / a.NSN;
-    r_beg = (sp - a.NS) * chunk;
-    r_end = min(a.n_new, r_beg + chunk);
-    const size_t base = ((size_t)(l * a.Hkv + g) * a.n_new) * kRowBytes;
-    kb = a.k_new + base;
-    vb = a.v_new + base;
-  }
-
-  // query head c of the group (heads past G: zeros, their columns are dropped)
-  uint4 qp[4];
+  };
+  auto load_values = [&](Rows& t, int r0) {
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    qp[ks] = make_uint4(0u, 0u, 0u, 0u);
-    if (c < a.G) qp[ks] = *reinterpret_cast<const uint4*>(a.q + (size_t)(l * a.Hq + g * a.G + c) * kRowBytes + (4 * ks + grp) * 16);
-  }
-
-  float m_run = kNegBig, z_run = 0.f;  // of head c; m_run is the same in the four lane groups
-  f32x4_t acc[8];                      // acc[j][r]: output column 8c + j of head 4 grp + r
+    for (int e = 0; e < 8; ++e) {
+      const unsigned ro = (unsigned)min(r0 + 16 * (e >> 2) + 4 * g + (e & 3), r_end - 1) * (unsigned)kRowBytes;
+      load_piece<PE * kEl>(vb + (ro + c * PE * kEl), t.v[e]);
+    }
+    // the scales of the 8 keys this row of 16 lanes has logits and weights for: lanes 0..7 the keys', 8..15 the
+    // values', handed to the other lanes of the row by broadcasts
+    if constexpr (FP8) t.scale = sc[min(r0 + 16 * ((c >> 2) & 1) + 4 * g + (c & 3), r_end - 1)];
+  };
+  auto logits = [&](const Rows& rows, float (&t)[8]) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // a step's loads: four key pieces (packed bf16 after the load), four value pieces (codes stay codes until they
-  // are needed as floats), and with FP8 the scales of the keys 4 grp + i this lane has logits and weights for
-  auto load_step = [&](int r0, uint4 (&kv)[4], uint4 (&vv)[4], float (&sk)[4], float (&sv)[4]) {
-    const int rk = min(r0 + c, r_end - 1);  // rows past the end repeat the last one (their weights are zero)
+    for (int b = 0; b < 2; ++b) {
+      f32x4_t s4 = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const char* src = kb + (size_t)rk * kCacheRowBytes + (4 * ks + grp) * kPiece;
-      if constexpr (FP8) kv[ks] = e4m3x8_to_bf16x8(load8_stream(src)); else kv[ks] = load16_stream(src);
+      for (int k = 0; k < KS; ++k) {
+        uint4 kp;
+        if constexpr (FP8) kp = e4m3x8_to_bf16x8(make_uint2(rows.k[b][k / 2][2 * (k & 1)], rows.k[b][k / 2][2 * (k & 1) + 1]));
+        else kp = make_uint4(rows.k[b][k][0], rows.k[b][k][1], rows.k[b][k][2], rows.k[b][k][3]);
+        s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kp), __builtin_bit_cast(bf16x8_t, qp[k]), s4, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[4 * b + i] = s4[i];
+    }
+  };
+  auto finish = [&](const Rows& rows, int r0, float (&t)[8]) {
+    float bm = kNegBig;
+    float sk[8], sv[8];
+    if constexpr (FP8) {
+      row_broadcast<0>(rows.scale * scale_log2, sk);
+      row_broadcast<8>(rows.scale, sv);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rv = min(r0 + 4 * grp + i, r_end - 1);
-      const char* src = vb + (size_t)rv * kCacheRowBytes + c * kPiece;
-      if constexpr (FP8) {
-        const uint2 vc = load8_stream(src);
-        vv[i] = make_uint4(vc.x, vc.y, 0u, 0u);
-        sk[i] = ksc[rv];
-        sv[i] = vsc[rv];
-      } else {
-        vv[i] = load16_stream(src);
-        sk[i] = sv[i] = 1.0f;
+    for (int e = 0; e < 8; ++e) t[e] *= FP8 ? sk[e] : scale_log2;
+    if (r0 + kStep > r_end) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = (r0 + 16 * (e >> 2) + 4 * g + (e & 3) < r_end) ? t[e] : kNegBig;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bm = fmaxf(bm, t[e]);
+    bm = group_max(bm);
+    if (__ballot(bm > st.m_run) != 0ull) {  // a new maximum of some head: rescale what that head has so far (rare)
+      const float mn = fmaxf(st.m_run, bm);
+      const float c1 = __builtin_amdgcn_exp2f(st.m_run - mn);
+      st.z_run *= c1;
+      st.m_run = mn;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float cr = __shfl(c1, 4 * g + r, kWave);  // row 4 g + r belongs to the head of lane column 4 g + r
+#pragma unroll
+        for (int j = 0; j < PE; ++j) st.acc[j][r] *= cr;
+      }
+    }
+    // the weights, their parts as packed bf16 (parts past the third do not exist: zeros)
+    uint32_t pa[4], pl[4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      uint32_t x[2], y[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        float p = __builtin_amdgcn_exp2f(t[e + u] - st.m_run);
+        if (r0 + kStep > r_end) p = (r0 + 16 * ((e + u) >> 2) + 4 * g + ((e + u) & 3) < r_end) ? p : 0.f;
+        st.z_run += p;
+        const float w = FP8 ? p * sv[e + u] : p;
+        const float hi = __uint_as_float(__float_as_uint(w) & 0xffff0000u), r1 = w - hi;
+        const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u), lo = r1 - mid;
+        if constexpr (GP == 8) {
+          x[u] = __float_as_uint(part == 0 ? hi : mid);
+          y[u] = __float_as_uint(part == 0 ? lo : 0.f);
+        } else {
+          x[u] = __float_as_uint(part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : 0.f)));
+          y[u] = 0u;
+        }
+      }
+      pa[e / 2] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
+      pl[e / 2] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302u);
+    }
+    const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, make_uint4(pa[0], pa[1], pa[2], pa[3]));
+    const bf16x8_t wl = __builtin_bit_cast(bf16x8_t, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+#pragma unroll
+    for (int j2 = 0; j2 < PE / 2; ++j2) {  // two columns at a time: one dword of every row
+      uint32_t d[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (FP8) d[e] = e4m3x2_to_bf16x2(rows.v[e][j2 / 2], (j2 & 1) != 0);
+        else d[e] = rows.v[e][j2];
+      }
+      uint32_t lo[4], hi[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        lo[u] = __builtin_amdgcn_perm(d[2 * u + 1], d[2 * u], 0x05040100u);
+        hi[u] = __builtin_amdgcn_perm(d[2 * u + 1], d[2 * u], 0x07060302u);
+      }
+      const bf16x8_t v0 = __builtin_bit_cast(bf16x8_t, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+      const bf16x8_t v1 = __builtin_bit_cast(bf16x8_t, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+      st.acc[2 * j2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, v0, st.acc[2 * j2], 0, 0, 0);
+      st.acc[2 * j2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, v1, st.acc[2 * j2 + 1], 0, 0, 0);
+      if constexpr (GP == 8) {
+        st.acc[2 * j2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, v0, st.acc[2 * j2], 0, 0, 0);
+        st.acc[2 * j2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, v1, st.acc[2 * j2 + 1], 0, 0, 0);
       }
     }
   };
 
-  constexpr int kStepStride = kDecWaves * kDecMfmaRows;
-  int r0 = r_beg + wave * kDecMfmaRows;
-  uint4 kv[4], vv[4];
-  float sk[4], sv[4];
-  if (r0 < r_end) load_step(r0, kv, vv, sk, sv);
-  for (; r0 < r_end; r0 += kStepStride) {
-    uint4 kn[4], vn[4];
-    float skn[4], svn[4];
-    const bool more = r0 + kStepStride < r_end;
-    if (more) load_step(r0 + kStepStride, kn, vn, skn, svn);  // in flight while this step is computed
-
-    f32x4_t s4 = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv[ks]), __builtin_bit_cast(bf16x8_t, qp[ks]),
-                                                   s4, 0, 0, 0);
-    // this lane: head c, keys r0 + 4 grp + i
-    float t[4];
-    float bm = kNegBig;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      t[i] = (r0 + 4 * grp + i < r_end) ? (FP8 ? s4[i] * sk[i] * a.scale_log2 : s4[i] * a.scale_log2) : kNegBig;
-      bm = fmaxf(bm, t[i]);
+  int r0 = wave * kStep;
+  if (r0 >= r_end) return;
+  float t[8];
+  Rows rows;
+  if constexpr (LEAN) {
+    for (; r0 < r_end; r0 += kStride) {
+      load_keys(rows, r0);
+      logits(rows, t);
+      load_values(rows, r0);
+      finish(rows, r0, t);
     }
-    bm = fmaxf(bm, __shfl_xor(bm, 16, kWave));
-    bm = fmaxf(bm, __shfl_xor(bm, 32, kWave));
-    if (__ballot(bm > m_run) != 0ull) {  // a new maximum of some head: rescale what that head has so far (rare)
-      const float mn = fmaxf(m_run, bm);
-      const float c1 = __builtin_amdgcn_exp2f(m_run - mn);
-      z_run *= c1;
-      m_run = mn;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float cr = __shfl(c1, 4 * grp + r, kWave);  // the factor of head 4 grp + r (lane 4 grp + r of group 0)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j][r] *= cr;
-      }
-    }
-    float p[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p[i] = (r0 + 4 * grp + i < r_end) ? __builtin_amdgcn_exp2f(t[i] - m_run) : 0.f;
-      z_run += p[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float vf[8];
-      if constexpr (FP8) {
-        e4m3x2_to_float(vv[i].x, false, vf[0], vf[1]);
-        e4m3x2_to_float(vv[i].x, true, vf[2], vf[3]);
-        e4m3x2_to_float(vv[i].y, false, vf[4], vf[5]);
-        e4m3x2_to_float(vv[i].y, true, vf[6], vf[7]);
-      } else {
-        Elems<bf16_t>::unpack(vv[i], vf);
-      }
-      const float w = FP8 ? p[i] * sv[i] : p[i];  // the value row's scale rides on its weight
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, vf[j], acc[j], 0, 0, 0);
-    }
-    if (more) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        kv[i] = kn[i];
-        vv[i] = vn[i];
-        sk[i] = skn[i];
-        sv[i] = svn[i];
-      }
-    }
-  }
-  // the four lane groups saw different keys of head c: one normaliser
-  z_run += __shfl_xor(z_run, 16, kWave);
-  z_run += __shfl_xor(z_run, 32, kWave);
-
-  // merge the waves through LDS (as in the kernel above)
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int h = 4 * grp + r;
-    if (h < 8) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) red_o[wave][h][8 * c + j] = acc[j][r];
-    }
-  }
-  if (grp == 0 && c < 8) {
-    red_m[wave][c] = m_run;
-    red_z[wave][c] = z_run;
-  }
-  __syncthreads();
-  for (int i = tid; i < a.G * D; i += kDecThreads) {
-    const int h = i / D, j = i - h * D;
-    float mn = red_m[0][h];
-#pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) mn = fmaxf(mn, red_m[w][h]);
-    float zs = 0.f, os = 0.f;
-#pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-      const float cw = __builtin_amdgcn_exp2f(red_m[w][h] - mn);
-      zs = fmaf(red_z[w][h], cw, zs);
-      os = fmaf(red_o[w][h][j], cw, os);
-    }
-    float* dst = a.part + ((size_t)(l * a.Hq + g * a.G + h) * a.NP + sp) * (D + 2);
-    dst[j] = os;
-    if (j == 0) {
-      dst[D] = mn;
-      dst[D + 1] = zs;
+  } else {
+    load_keys(rows, r0);
+    for (; r0 < r_end; r0 += kStride) {
+      load_values(rows, r0);
+      logits(rows, t);
+      if (r0 + kStride < r_end) load_keys(rows, r0 + kStride);  // in flight while this step is finished
+      finish(rows, r0, t);
     }
   }
 }
 
-// grid (Hq, L), D threads: merges the NP chunks of one query head and writes the output row.
+// Three waves per SIMD (145 registers with rows of 256 bytes; four spill, and took twice the time).
+template <int D, int GP, bool FP8>
+__global__ void __launch_bounds__(kDecThreads, 3) decode_matrix_kernel(DecodeArgs a) {
+  constexpr int PE = D / 16;
+  __shared__ float red_o[kDecWaves][GP][D];
+  __shared__ float red_m[kDecWaves][GP], red_z[kDecWaves][GP];
+
+  const int id = blockIdx.x, g = blockIdx.y;
+  const int lane = threadIdx.x & 63, c = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  DecodeChunk ch;
+  if (!chunk_of_group(a, id, ch)) return;
+  const int l = ch.l;
+
+  // query head c % GP of the group (heads past G: zeros, their rows are dropped)
+  uint4 qp[D / 32];
+  auto load_queries = [&](bool codes) {
+#pragma unroll
+    for (int k = 0; k < D / 32; ++k) {
+      qp[k] = make_uint4(0u, 0u, 0u, 0u);
+      const int e0 = codes ? 64 * (k / 2) + 16 * grp + 8 * (k & 1) : 32 * k + 8 * grp;
+      if (c % GP < a.G) qp[k] = *reinterpret_cast<const uint4*>(a.q + ((size_t)(l * a.Hq + g * a.G + c % GP) * D + e0) * 2);
+    }
+  };
+  load_queries(FP8 && !ch.fresh);
+  DecodeState<D> st;
+  st.m_run = kNegBig;
+  st.z_run = 0.f;
+#pragma unroll
+  for (int j = 0; j < PE; ++j) st.acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  if (!ch.fresh) {
+    const size_t row0 = ch.row0 + g * ch.head;
+    if constexpr (FP8)
+      decode_rows<D, GP, true, false>(st, qp, a.k_cache + row0 * D, a.v_cache + row0 * D, a.k_scale + row0, a.v_scale + row0,
+                                      ch.rows, a.scale_log2);
+    else
+      decode_rows<D, GP, false, false>(st, qp, a.k_cache + row0 * (D * 2), a.v_cache + row0 * (D * 2), nullptr, nullptr,
+                                       ch.rows, a.scale_log2);
+  }
+  if (ch.fresh || (ch.last && a.n_new > 0 && a.NSN == 0)) {
+    const size_t row0 = ch.fresh ? ch.row0 + g * ch.head : (size_t)(l * a.Hkv + g) * a.n_new;
+    if (FP8 && !ch.fresh) load_queries(false);
+    decode_rows<D, GP, false, true>(st, qp, a.k_new + row0 * (D * 2), a.v_new + row0 * (D * 2), nullptr, nullptr,
+                                    ch.fresh ? ch.rows : a.n_new, a.scale_log2);
+  }
+
+  // the four lane groups saw different keys of the same head: one normaliser
+  const float z = group_sum(st.z_run);
+  if (lane < GP) {
+    red_m[wave][lane] = st.m_run;
+    red_z[wave][lane] = z;
+  }
+  // row R = 4 grp + r is part R / GP of head R % GP: the parts are summed
+#pragma unroll
+  for (int j = 0; j < PE; ++j) {
+    float* dst = &red_o[wave][0][PE * c + j];
+    if constexpr (GP == 8) {  // rows 0..7: first and third part, rows 8..15: second part
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.acc[j][r]), __float_as_uint(st.acc[j][r]), false, false);
+        if (grp < 2) dst[(4 * grp + r) * D] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+      }
+    } else if constexpr (GP == 4) {  // lane groups 0, 1, 2: the three parts, 3: zeros
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float s = group_sum(st.acc[j][r]);
+        if (grp == 0) dst[r * D] = s;
+      }
+    } else if constexpr (GP == 2) {  // rows 0, 1 | 2, 3 in group 0, rows 4, 5 in group 1
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float s = group_sum(st.acc[j][h] + st.acc[j][2 + h]);
+        if (grp == 0) dst[h * D] = s;
+      }
+    } else {  // rows 0, 1, 2 in group 0
+      const float s = st.acc[j][0] + st.acc[j][1] + st.acc[j][2];
+      if (grp == 0) dst[0] = s;
+    }
+  }
+  __syncthreads();
+  write_partial<GP, D>(a, id, l, g, red_o, red_m, red_z);
+}
+
+// grid (Hq, L), D threads: merges the chunks of one query head and writes the output row.  Four chunks are in flight
+// together.
 template <typename T, int D>
 __global__ void __launch_bounds__(D) decode_combine_kernel(DecodeArgs a) {
   const int h = blockIdx.x, l = blockIdx.y, j = threadIdx.x;
-  const float* p = a.part + (size_t)(l * a.Hq + h) * a.NP * (D + 2);
-  float mn = kNegBig;
-  for (int s = 0; s < a.NP; ++s) mn = fmaxf(mn, p[(size_t)s * (D + 2) + D]);
-  float zs = 0.f, os = 0.f;
-  for (int s = 0; s < a.NP; ++s) {
-    const float* ps = p + (size_t)s * (D + 2);
-    const float c = __builtin_amdgcn_exp2f(ps[D] - mn);
-    zs = fmaf(ps[D + 1], c, zs);
-    os = fmaf(ps[j], c, os);
+  const LayerChunks lc = find_chunks(a, l, 0);
+  const int n = lc.n + a.NSN;
+  constexpr int U = 4;
+  float mn = kNegBig, zs = 0.f, os = 0.f;
+  for (int s0 = 0; s0 < n; s0 += U) {
+    float m[U], z[U], o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = min(s0 + u, n - 1);
+      const int id = s < lc.n ? lc.first + s : a.NC + l * a.NSN + (s - lc.n);
+      const float* p = a.part + ((size_t)id * a.Hq + h) * (D + 2);
+      m[u] = (s0 + u < n) ? p[D] : kNegBig;
+      z[u] = (s0 + u < n) ? p[D + 1] : 0.f;
+      o[u] = p[j];
+    }
+    float top = mn;
+#pragma unroll
+    for (int u = 0; u < U; ++u) top = fmaxf(top, m[u]);
+    const float c0 = __builtin_amdgcn_exp2f(mn - top);
+    zs *= c0;
+    os *= c0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float c = (s0 + u < n) ? __builtin_amdgcn_exp2f(m[u] - top) : 0.f;
+      zs = fmaf(z[u], c, zs);
+      os = fmaf(o[u], c, os);
+    }
+    mn = top;
   }
-  Elems<T>::store(a.out + ((size_t)(l * a.Hq + h) * D + j) * sizeof(T), os / zs);
+  store_elem(a.out + ((size_t)(l * a.Hq + h) * D + j) * sizeof(T), os / zs, T{});
 }
 
 struct DecodePlan {
-  int L, Hq, Hkv, G, GP, d, dtype, n_new, NS, NSN, NP;
+  int L, Hq, Hkv, G, GP, d, dtype, n_new, R, NC, NSN;
   float scale_log2;
   size_t ws_bytes;
 };
@@ -598,55 +767,34 @@ static meda_status make_decode_plan(const meda_decode_params* p, DecodePlan* pl)
   pl->L = p->n_layers; pl->Hq = p->n_q_heads; pl->Hkv = p->n_kv_heads; pl->G = G; pl->d = p->head_dim;
   pl->GP = G <= 1 ? 1 : (G <= 2 ? 2 : (G <= 4 ? 4 : 8));
   pl->dtype = p->dtype; pl->n_new = p->n_new;
-  // the per-head state a workgroup merges at its end grows with the group size: give it more rows then
-  const int rows_per_group = kDecRowsPerGroup * (pl->GP < 4 ? pl->GP : 4);
-  const int64_t avg = p->total_budget / p->n_layers;
-  int64_t ns = (avg + rows_per_group - 1) / rows_per_group;
-  pl->NS = (int)(ns < 1 ? 1 : (ns > kDecMaxSplit ? kDecMaxSplit : ns));
-  int64_t nsn = ((int64_t)p->n_new + kDecRowsPerGroup - 1) / kDecRowsPerGroup;
+  int64_t rows = p->total_budget * p->n_kv_heads / kDecTargetGroups;
+  rows = (rows + 127) / 128 * 128;
+  rows = rows < kDecMinRows ? kDecMinRows : (rows > kDecMaxRows ? kDecMaxRows : rows);
+  // at most kDecMaxSplit chunks per layer on average (the chunk partials are workspace)
+  const int64_t least = p->total_budget / ((int64_t)(kDecMaxSplit - 1) * p->n_layers) + 1;
+  if (rows < least) rows = least;
+  if (rows > (1 << 28)) return MEDA_ERR_UNSUPPORTED;
+  pl->R = (int)rows;
+  pl->NC = (int)(p->total_budget / rows) + p->n_layers;
+  const int64_t nsn = p->n_new <= kDecInlineNew ? 0 : ((int64_t)p->n_new + rows - 1) / rows;
   pl->NSN = (int)(nsn > kDecMaxSplit ? kDecMaxSplit : nsn);
-  pl->NP = pl->NS + pl->NSN;
   const double scale = p->softmax_scale > 0.0f ? (double)p->softmax_scale : 1.0 / sqrt((double)p->head_dim);
   pl->scale_log2 = (float)(scale * 1.4426950408889634074);
-  pl->ws_bytes = ((size_t)pl->L * pl->Hq * pl->NP * (pl->d + 2) * sizeof(float) + 255) / 256 * 256;
+  const size_t chunks = (size_t)pl->NC + (size_t)pl->L * pl->NSN;
+  pl->ws_bytes = (chunks * pl->Hq * (pl->d + 2) * sizeof(float) + 255) / 256 * 256;
   return MEDA_OK;
 }
 
 template <typename T, int D, int GP>
-static hipError_t launch_decode_g(const DecodePlan& pl, const DecodeArgs& a_in, hipStream_t s) {
-  DecodeArgs a = a_in;
-  hipError_t e;
+static hipError_t launch_decode_g(const DecodePlan& pl, const DecodeArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)(pl.NC + pl.L * pl.NSN), pl.Hkv), block(kDecThreads);
   if constexpr (sizeof(T) == 2) {
-    if (a.k_scale) {  // 8-bit cache: its rows first, then the appended bf16 rows with the plain kernel
-      constexpr bool kMfma = D == 128 && GP == 8;  // groups of 5 to 8 heads: the matrix form (see its comment)
-      a.sp0 = 0;
-      if constexpr (kMfma)
-        hipLaunchKernelGGL((decode_partial_mfma_kernel<D, true>), dim3(pl.NS, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
-      else
-        hipLaunchKernelGGL((decode_partial_kernel<T, D, GP, true>), dim3(pl.NS, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      if (pl.NSN > 0) {
-        a.sp0 = pl.NS;
-        if constexpr (kMfma)
-          hipLaunchKernelGGL((decode_partial_mfma_kernel<D, false>), dim3(pl.NSN, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
-        else
-          hipLaunchKernelGGL((decode_partial_kernel<T, D, GP, false>), dim3(pl.NSN, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
-      hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(pl.Hq, pl.L), dim3(D), 0, s, a);
-      return hipGetLastError();
-    }
-  }
-  a.sp0 = 0;
-  if constexpr (sizeof(T) == 2 && D == 128 && GP == 8) {
-    // groups of 5 to 8 heads: the vector form is bound by its instruction count, the matrix form by HBM
-    hipLaunchKernelGGL((decode_partial_mfma_kernel<D, false>), dim3(pl.NP, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
+    if (a.k_scale) hipLaunchKernelGGL((decode_matrix_kernel<D, GP, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((decode_matrix_kernel<D, GP, false>), grid, block, 0, s, a);
   } else {
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, GP, false>), dim3(pl.NP, pl.Hkv, pl.L), dim3(kDecThreads), 0, s, a);
+    hipLaunchKernelGGL((decode_partial_kernel<D, GP>), grid, block, 0, s, a);
   }
-  e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(pl.Hq, pl.L), dim3(D), 0, s, a);
   return hipGetLastError();
@@ -732,11 +880,10 @@ static meda_status decode_common(const meda_decode_params* params, const void* q
   a.out = static_cast<char*>(out);
   a.part = static_cast<float*>(workspace);
   a.L = pl.L; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.n_new = pl.n_new;
-  a.NS = pl.NS; a.NSN = pl.NSN; a.NP = pl.NP;
+  a.R = pl.R; a.NC = pl.NC; a.NSN = pl.NSN;
   a.scale_log2 = pl.scale_log2;
   a.k_scale = fp8 ? k_scale : nullptr;
   a.v_scale = fp8 ? v_scale : nullptr;
-  a.sp0 = 0;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
   if (pl.dtype == MEDA_BF16) e = pl.d == 128 ? launch_decode_t<bf16_t, 128>(pl, a, s) : launch_decode_t<bf16_t, 64>(pl, a, s);
@@ -762,7 +909,7 @@ meda_status meda_decode_attention_noalloc(const meda_decode_params* params, cons
   hipError_t err = hipSuccess;
   void* ptr = meda::scratch_of_current_device(&err);
   if (!ptr) return MEDA_ERR_HIP;
-  // every chunk partial the combine kernel reads is written by the partial kernel of the same call (also for
+  // every chunk partial the combine kernel reads is written by the kernel before it in the same call (also for
   // chunks without rows), so nothing in the array has to be cleared between calls
   return decode_common(params, q, k_cache, v_cache, nullptr, nullptr, false, layer_len, layer_off, k_new, v_new, out,
                        ptr, meda::kDecodeScratchBytes, hip_stream);

@@ -53,21 +53,21 @@ __device__ __forceinline__ void e4m3x2_to_float(uint32_t word, bool upper, float
 #endif
 }
 
-// Eight codes (8 bytes) as eight bf16 values packed in 16 bytes, element order kept.  Exact: every E4M3 value
-// is a bf16 value (3 mantissa bits, exponents -9 .. 8).
+// Two codes (bytes 0,1 or bytes 2,3 of `word`) as two packed bf16 values.  Exact: every E4M3 value is a bf16 value
+// (3 mantissa bits, exponents -9 .. 8).
+__device__ __forceinline__ uint32_t e4m3x2_to_bf16x2(uint32_t word, bool upper) {
+#if __HIP_DEVICE_COMPILE__
+  return upper ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(word, 1.0f, true))
+               : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(word, 1.0f, false));
+#else
+  return 0u;
+#endif
+}
+
+// Eight codes (8 bytes) as eight packed bf16 values, element order kept.
 __device__ __forceinline__ uint4 e4m3x8_to_bf16x8(uint2 c) {
-  float f[8];
-  e4m3x2_to_float(c.x, false, f[0], f[1]);
-  e4m3x2_to_float(c.x, true, f[2], f[3]);
-  e4m3x2_to_float(c.y, false, f[4], f[5]);
-  e4m3x2_to_float(c.y, true, f[6], f[7]);
-  uint4 o;
-  // upper halves of two floats side by side: bytes 2,3 of the first, bytes 2,3 of the second
-  o.x = __builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u);
-  o.y = __builtin_amdgcn_perm(__float_as_uint(f[3]), __float_as_uint(f[2]), 0x07060302u);
-  o.z = __builtin_amdgcn_perm(__float_as_uint(f[5]), __float_as_uint(f[4]), 0x07060302u);
-  o.w = __builtin_amdgcn_perm(__float_as_uint(f[7]), __float_as_uint(f[6]), 0x07060302u);
-  return o;
+  return make_uint4(e4m3x2_to_bf16x2(c.x, false), e4m3x2_to_bf16x2(c.x, true), e4m3x2_to_bf16x2(c.y, false),
+                    e4m3x2_to_bf16x2(c.y, true));
 }
 
 }  // namespace meda

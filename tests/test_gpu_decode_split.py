@@ -1,0 +1,79 @@
+"""How a decoding step cuts the rows into chunks: lengths around the 32-row step of a wave, the 128-row workgroup
+step and the chunk size, very uneven layers, more than 64 layers, appended rows with and without chunks of their own,
+and lengths whose sum exceeds the budget the launch was sized for.  Against the fp64 oracle; the bound is that of
+parity.decode_error (exact products, fp32 sums, one rounding)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decode_oracle as D
+from oracle import fp8_oracle
+
+from parity import decode_error
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(lens, hq, hkv, d, dtype, n_new, budget=None, fp8=False, seed=0):
+    import paper_2502_17599_amd as pkg
+    print(f"\n[decode split] L={len(lens)} Hq={hq} Hkv={hkv} d={d} {dtype} n_new={n_new} fp8={fp8}", flush=True)
+    dev = torch.device("cuda:0")
+    L, rows = len(lens), sum(lens) * hkv
+    g = torch.Generator().manual_seed(seed)
+    k = torch.randn(rows, d, generator=g).to(dtype).to(dev)
+    v = torch.randn(rows, d, generator=g).to(dtype).to(dev)
+    q = (3 * torch.randn(L, hq, d, generator=g)).to(dtype).to(dev)
+    kn = vn = None
+    if n_new:
+        kn = torch.randn(L, hkv, n_new, d, generator=g).to(dtype).to(dev)
+        vn = torch.randn(L, hkv, n_new, d, generator=g).to(dtype).to(dev)
+    s = torch.tensor(lens, dtype=torch.int32, device=dev)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64, device=dev)
+    dec = pkg.Decoder(pkg.make_decode_params(L, hq, hkv, d, sum(lens) if budget is None else budget, dtype, n_new), dev)
+    if fp8:
+        kc, ks = pkg.meda_quantize_fp8(k)
+        vc, vs = pkg.meda_quantize_fp8(v)
+        out = dec.fp8(q, kc, vc, ks, vs, s, off, kn, vn)
+        kr = fp8_oracle.dequantize_rows(kc.cpu().numpy(), ks.cpu().numpy())
+        vr = fp8_oracle.dequantize_rows(vc.cpu().numpy(), vs.cpu().numpy())
+    else:
+        out = dec(q, k, v, s, off, kn, vn)
+        kr, vr = k.double().cpu().numpy(), v.double().cpu().numpy()
+    torch.cuda.synchronize()
+    ref = D.decode_step(q.double().cpu().numpy(), kr, vr, np.array(lens), off.cpu().numpy(), hkv,
+                        None if kn is None else kn.double().cpu().numpy(), None if vn is None else vn.double().cpu().numpy())
+    vmax = max(np.abs(vr).max(), 0.0 if vn is None else float(vn.abs().max()))
+    decode_error(out.double().cpu().numpy(), ref, vmax, dtype == torch.bfloat16)
+
+
+EDGES = [1, 31, 32, 33, 127, 128, 129, 255, 257, 1000]
+
+
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (3, 1), (8, 2), (5, 1), (8, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_lengths_around_the_steps(hq, hkv, d):
+    for n_new in (0, 1, 33, 128, 129, 300):
+        _case(EDGES, hq, hkv, d, torch.bfloat16, n_new)
+    _case(EDGES, hq, hkv, d, torch.bfloat16, 5, fp8=True)
+    _case(EDGES, hq, hkv, d, torch.bfloat16, 140, fp8=True)
+    _case(EDGES, hq, hkv, d, torch.float32, 5)
+    _case(EDGES, hq, hkv, d, torch.float32, 140)
+
+
+def test_more_layers_than_lanes_and_uneven_lengths():
+    lens = [1 + (37 * i * i) % 400 for i in range(130)]
+    lens[70] = 9000
+    _case(lens, 4, 1, 64, torch.bfloat16, 2)
+    _case(lens, 2, 1, 64, torch.float32, 0)
+
+
+def test_lengths_beyond_the_budget_of_the_launch():
+    # 20 layers of up to 2000 rows, sized for 20 rows: the chunks grow until their number fits
+    lens = [2000, 1, 700] * 6 + [129, 128]
+    _case(lens, 4, 2, 128, torch.bfloat16, 3, budget=20)
+    _case(lens, 2, 2, 64, torch.float32, 200, budget=20)
+
+
+def test_rows_enough_for_chunks_of_several_hundred_rows():
+    # 2 kv heads, 500000 rows: chunks of 384 rows at 1536 workgroups
+    _case([120000, 70000, 33333, 26667], 8, 2, 64, torch.bfloat16, 0)
