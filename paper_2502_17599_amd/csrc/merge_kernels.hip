@@ -36,12 +36,6 @@ __device__ __forceinline__ size_t less_base_of(int l, int g, int T, int Hkv, lon
   return ((size_t)l * T - (size_t)off_l) * Hkv + (size_t)g * (T - S);
 }
 
-// number of 5-bit passes the segment sort needs for slots in [0, S)
-__device__ __forceinline__ int sort_passes(int S) {
-  const int nbits = (S > 1) ? (32 - __clz(S - 1)) : 1;
-  return (nbits + 4) / 5;
-}
-
 // ------------------------------------------------------------------------ similarity + argmax
 // Layers whose conserved set fits into LDS go to the resident-set kernel (one workgroup of 8 waves per
 // (layer, head) part, all 160 KB of LDS), the others to the tiled kernel; both are launched and every
@@ -462,131 +456,126 @@ __global__ void __launch_bounds__(256) pack_conserved_kernel(MergeArgs a) {
 }
 
 // ------------------------------------------------------------------------------- segment sort
-// grid (Hkv, L).  Stable least-significant-digit radix sort (5 bits per pass) of the pairs
+// grid (Hkv, L), 1024 threads.  Stable least-significant-digit radix sort (at most 8 bits per pass) of the pairs
 // (slot, row id) of one (layer, head) by slot; row ids enter ascending, so every slot's members come
-// out ascending and the merge adds them in one fixed order.  The last pass always writes buffer 0.
-// Per tile of blockDim elements: a lane finds the lanes of its wave with the same digit (one ballot
-// per digit bit) and its rank among them, the per-wave digit counts go to LDS, wave 0 turns them into exclusive prefixes over the
-// waves (and advances the running digit bases), and every element is written to its final place.
-// Then seg_beg / seg_end of every slot = its range in the sorted array.
-constexpr int kSortMaxThreads = 1024;
-constexpr int kSortMaxWaves = kSortMaxThreads / 64;
-constexpr int kSortBits = 5;  // 6-bit digits (one pass fewer on long sets) measured slower: wave 0's prefix over the waves per tile weighs more
+// out ascending and the merge adds them in one fixed order.  Then seg_beg / seg_end of every slot = its range in the
+// sorted array (sort_val[0]).
+// Every wave owns a contiguous part of the input and a histogram of its own: a pass is one count over the parts, one
+// prefix over (digit, wave), and one scatter in which a wave walks its part in order, 64 elements at a time, without
+// a barrier (a lane finds its equals with one ballot per digit bit).  Bound by the scattered 4-byte stores: slot and
+// position travel as one 32-bit word where their bits fit (PACKED: slot above position), which halves them.
+// Before (5 bits per pass, a barrier-separated prefix over the waves per 1024 elements) and now, in us: 256 pairs of
+// 118000 rows 781 / 621, 256 of 13000 91 / 50, 1024 of 3600 62 / 52, 360 of 2300 39 / 21, 8 of 770 12 / 8.
+constexpr int kSortThreads = 1024;
+constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kSortBits = 8;
 constexpr int kSortDigits = 1 << kSortBits;
-constexpr int kSortItems = 4;  // tiles whose loads are issued together
+constexpr int kSortItems = 8;  // groups of 64 elements whose loads are issued together
 
-// Lanes of the wave whose 5-bit digit equals this lane's (invalid lanes match nobody): one ballot per
+struct SortShared {
+  int cnt[kSortWaves][kSortDigits];
+  int wave_total[kSortDigits / 64];
+};
+
+// Lanes of the wave whose digit equals this lane's (invalid lanes match nobody): one ballot per
 // digit bit, each lane keeps the side of the ballot it is on.
-__device__ __forceinline__ unsigned long long digit_peers(int dgt, bool valid) {
+__device__ __forceinline__ unsigned long long digit_peers(int dgt, int bits, bool valid) {
   unsigned long long peers = __ballot(valid);
 #pragma unroll
   for (int b = 0; b < kSortBits; ++b) {
-    const unsigned long long set = __ballot((dgt >> b) & 1);
-    peers &= ((dgt >> b) & 1) ? set : ~set;
+    if (b < bits) {
+      const unsigned long long set = __ballot((dgt >> b) & 1);
+      peers &= ((dgt >> b) & 1) ? set : ~set;
+    }
   }
   return valid ? peers : 0ull;
 }
 
-__global__ void __launch_bounds__(kSortMaxThreads, 8) segment_sort_kernel(MergeArgs a) {
-  __shared__ int base[2][kSortDigits];
-  __shared__ int wcnt[2][kSortMaxWaves][kSortDigits];
+__device__ __forceinline__ int bits_below(int n) { return n > 1 ? 32 - __clz(n - 1) : 1; }  // bits of 0 .. n-1
 
-  const int g = blockIdx.x, l = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nthr = blockDim.x, nwaves = nthr >> 6;
-  const int S = a.alloc[4 * l];
+template <bool PACKED>
+__device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh, int S, size_t lbase, int row0, int32_t* beg,
+                                             int32_t* end) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.T - S;
-  const long long off_l = a.off[l];
-  const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
-  const int passes = sort_passes(S);
+  const int slot_bits = bits_below(S), pos_bits = PACKED ? bits_below(a.T) : 0;
+  const int passes = (slot_bits + kSortBits - 1) / kSortBits;
+  const int bits = (slot_bits + passes - 1) / passes, digit_mask = (1 << bits) - 1;
+  const int part = ((n + kSortWaves - 1) / kSortWaves + 63) & ~63;  // elements per wave
+  const int p_beg = min(wave * part, n), p_end = min(p_beg + part, n);
+  volatile int* mine = sh.cnt[wave];  // the wave's histogram, later the next output position per digit
 
-  const int32_t* in_key = a.less_slot + lbase;
-  const int32_t* in_val = a.less_idx + lbase;
+  const int32_t* slots = a.less_slot + lbase;
+  const int32_t* rows = a.less_idx + lbase;
+  const int32_t *in_key = slots, *in_val = rows;
   for (int p = 0; p < passes; ++p) {
     const int ob = (passes - 1 - p) & 1;
     int32_t* out_key = a.sort_key[ob] + lbase;
     int32_t* out_val = a.sort_val[ob] + lbase;
-    const int shift = kSortBits * p;
-    if (tid < kSortDigits) base[0][tid] = 0;
-    __syncthreads();
-    // digit histogram: lane q of every wave counts digit q.  Four tiles are loaded at a time so
-    // that their loads are in flight together.
-    for (int t0 = 0; t0 < n; t0 += kSortItems * nthr) {
+    const bool packed_in = PACKED && p > 0;
+    const int shift_in = bits * p + (packed_in ? pos_bits : 0);
+    for (int i = lane; i < kSortDigits; i += 64) mine[i] = 0;
+    for (int t0 = p_beg; t0 < p_end; t0 += kSortItems * 64) {
       int keys[kSortItems];
 #pragma unroll
-      for (int j = 0; j < kSortItems; ++j) {
-        const int i = t0 + j * nthr + tid;
-        keys[j] = (i < n) ? in_key[i] : -1;
-      }
+      for (int j = 0; j < kSortItems; ++j)
+        if (t0 + j * 64 < p_end) keys[j] = in_key[min(t0 + j * 64 + lane, p_end - 1)];
 #pragma unroll
-      for (int j = 0; j < kSortItems; ++j) {
-        if (t0 + j * nthr < n) {
-          const bool valid = keys[j] >= 0;
-          const int dgt = (keys[j] >> shift) & (kSortDigits - 1);
-          const unsigned long long peers = digit_peers(dgt, valid);
-          if (valid && (peers & lt_mask) == 0ull) atomicAdd(&base[0][dgt], __popcll(peers));  // group leader
-        }
-      }
+      for (int j = 0; j < kSortItems; ++j)
+        if (t0 + j * 64 + lane < p_end) atomicAdd(&sh.cnt[wave][((unsigned)keys[j] >> shift_in) & digit_mask], 1);
     }
     __syncthreads();
-    if (wave == 0) {  // exclusive scan of the 32 digit totals
-      const int c = (lane < kSortDigits) ? base[0][lane] : 0;
-      int inc = c;
+    // exclusive prefix in the order (digit, wave): thread q < 256 has digit q
+    int c[kSortWaves], total = 0, inc = 0;
+    if (tid < kSortDigits) {
 #pragma unroll
-      for (int o = 1; o < kSortDigits; o <<= 1) {
+      for (int w = 0; w < kSortWaves; ++w) {
+        c[w] = sh.cnt[w][tid];
+        total += c[w];
+      }
+      inc = total;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
         const int t = __shfl_up(inc, o, kWave);
         if (lane >= o) inc += t;
       }
-      if (lane < kSortDigits) base[0][lane] = inc - c;
+      if (lane == 63) sh.wave_total[wave] = inc;
     }
     __syncthreads();
-    // stable scatter, blockDim elements at a time in input order (loads of four tiles in flight)
-    int it = 0;
-    for (int s0 = 0; s0 < n; s0 += kSortItems * nthr) {
+    if (tid < kSortDigits) {
+      int pos = inc - total;
+#pragma unroll
+      for (int w = 0; w < kSortDigits / 64; ++w) pos += (w < wave) ? sh.wave_total[w] : 0;
+#pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) {
+        sh.cnt[w][tid] = pos;
+        pos += c[w];
+      }
+    }
+    __syncthreads();
+    for (int t0 = p_beg; t0 < p_end; t0 += kSortItems * 64) {
       int keys[kSortItems], vals[kSortItems];
 #pragma unroll
       for (int j = 0; j < kSortItems; ++j) {
-        const int i = s0 + j * nthr + tid;
-        keys[j] = (i < n) ? in_key[i] : -1;
-        vals[j] = (i < n) ? in_val[i] : 0;
+        if (t0 + j * 64 >= p_end) break;
+        const int i = min(t0 + j * 64 + lane, p_end - 1);
+        keys[j] = in_key[i];
+        vals[j] = packed_in ? 0 : in_val[i];
       }
 #pragma unroll
       for (int j = 0; j < kSortItems; ++j) {
-        if (s0 + j * nthr < n) {
-          const int cur = it & 1;
-          ++it;
-          const int key = keys[j], val = vals[j];
-          const bool valid = key >= 0;
-          const int dgt = (key >> shift) & (kSortDigits - 1);
-          const unsigned long long peers = digit_peers(dgt, valid);
-          const int my_rank = __popcll(peers & lt_mask);
-          if (lane < kSortDigits) wcnt[cur][wave][lane] = 0;
-          if (valid && my_rank == 0) wcnt[cur][wave][dgt] = __popcll(peers);  // after the zeroing: same wave, in order
-          __syncthreads();
-          if (wave == 0) {  // (a scan spread over all waves, 16 lanes per digit, measured slower than this walk by one wave)
-            // lane (q, half): digit q = lane / 2, waves half*8 .. half*8+7; exclusive prefix over the waves
-            const int q = lane >> 1, w0 = (lane & 1) * (kSortMaxWaves / 2);
-            int run = 0, c[kSortMaxWaves / 2];
-#pragma unroll
-            for (int w2 = 0; w2 < kSortMaxWaves / 2; ++w2) {
-              c[w2] = (w0 + w2 < nwaves) ? wcnt[cur][w0 + w2][q] : 0;
-              run += c[w2];
-            }
-            const int other = __shfl_xor(run, 1, kWave);
-            int pre = (lane & 1) ? other : 0;  // counts of the lower half of the waves
-#pragma unroll
-            for (int w2 = 0; w2 < kSortMaxWaves / 2; ++w2) {
-              if (w0 + w2 < nwaves) wcnt[cur][w0 + w2][q] = pre;
-              pre += c[w2];
-            }
-            if ((lane & 1) == 0) base[cur ^ 1][q] = base[cur][q] + run + other;
-          }
-          __syncthreads();
-          if (valid) {
-            const int pos = base[cur][dgt] + wcnt[cur][wave][dgt] + my_rank;
-            out_key[pos] = key;
-            out_val[pos] = val;
-          }
+        if (t0 + j * 64 >= p_end) break;
+        const bool valid = t0 + j * 64 + lane < p_end;
+        const int dgt = (int)((unsigned)keys[j] >> shift_in) & digit_mask;
+        const unsigned long long peers = digit_peers(dgt, bits, valid);
+        const int rank = __popcll(peers & lt_mask);
+        if (valid) {
+          const int base = mine[dgt];  // LDS operations of a wave stay in order: every lane reads before the group's
+          if (rank == 0) mine[dgt] = base + __popcll(peers);  // first lane moves the position on
+          out_key[base + rank] = PACKED && !packed_in ? (int)(((unsigned)keys[j] << pos_bits) | (unsigned)(vals[j] - row0)) : keys[j];
+          if (!PACKED) out_val[base + rank] = vals[j];
         }
       }
     }
@@ -596,19 +585,32 @@ __global__ void __launch_bounds__(kSortMaxThreads, 8) segment_sort_kernel(MergeA
   }
 
   // member range of every slot, as absolute indices into the sorted array
-  const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
-  int32_t* beg = a.seg_beg + cbase;
-  int32_t* end = a.seg_end + cbase;
   const int ib = (int)lbase;
-  for (int i = tid; i < n; i += nthr) {
-    const int kcur = in_key[i];
-    const int kprev = (i > 0) ? in_key[i - 1] : -1;
+  auto slot_at = [&](int i) { return PACKED ? (int)((unsigned)in_key[i] >> pos_bits) : in_key[i]; };
+  for (int i = tid; i < n; i += kSortThreads) {
+    const int kcur = slot_at(i);
+    const int kprev = (i > 0) ? slot_at(i - 1) : -1;
+    if (PACKED) a.sort_val[0][lbase + i] = row0 + (int)((unsigned)in_key[i] & ((1u << pos_bits) - 1u));
     for (int s = kprev + 1; s <= kcur; ++s) beg[s] = ib + i;
     for (int s = max(kprev, 0); s < kcur; ++s) end[s] = ib + i;
   }
-  const int klast = (n > 0) ? in_key[n - 1] : -1;
-  for (int s = klast + 1 + tid; s < S; s += nthr) beg[s] = ib + n;
-  for (int s = max(klast, 0) + tid; s < S; s += nthr) end[s] = ib + n;
+  const int klast = (n > 0) ? slot_at(n - 1) : -1;
+  for (int s = klast + 1 + tid; s < S; s += kSortThreads) beg[s] = ib + n;
+  for (int s = max(klast, 0) + tid; s < S; s += kSortThreads) end[s] = ib + n;
+}
+
+__global__ void __launch_bounds__(kSortThreads, 8) segment_sort_kernel(MergeArgs a) {
+  __shared__ SortShared sh;
+  const int g = blockIdx.x, l = blockIdx.y;
+  const int S = a.alloc[4 * l];
+  const long long off_l = a.off[l];
+  const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
+  const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
+  const int row0 = (l * a.Hkv + g) * a.T;  // row id of position 0
+  if (bits_below(S) + bits_below(a.T) <= 32)
+    segment_sort<true>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
+  else
+    segment_sort<false>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
 }
 
 // ------------------------------------------------------------------------------ merge + write
@@ -956,8 +958,7 @@ hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {
 
 hipError_t launch_segment_sort(const Plan& p, const Buffers& b, hipStream_t s) {
   const MergeArgs a = make_args(p, b);
-  const int nthr = p.T >= 16384 ? 1024 : (p.T >= 4096 ? 512 : 256);  // measured at T = 4096: 512 threads 65 us, 1024 or 256 threads 75 us
-  hipLaunchKernelGGL(segment_sort_kernel, dim3(p.Hkv, p.L), dim3(nthr), 0, s, a);
+  hipLaunchKernelGGL(segment_sort_kernel, dim3(p.Hkv, p.L), dim3(kSortThreads), 0, s, a);
   return hipGetLastError();
 }
 
