@@ -28,6 +28,7 @@ struct MergeArgs {
   int L, Hkv, T, flags;
   int merge_members;        // 0: every output row is a plain copy (no merge requested or nothing to merge)
   long long total_slots;    // B * Hkv
+  int merge_rows;           // output rows a wave of the merge walks
   int use_resident;         // layers whose conserved set fits into LDS go to the resident-set kernel
   int n_members;            // keys that are not conserved, all layers and heads: (L * T - B) * Hkv
 };
@@ -708,8 +709,12 @@ struct OutConv<float> {
   }
 };
 
-// Output rows one wave walks; a lane of the wave holds the list range of one of them.
+// Output rows one wave walks; a lane of the wave holds the list range of one of them.  Short outputs are spread over
+// more waves (2048 rows: 14.7 -> 6.6 us): below kMergeShortRows sixteen rows per wave leave the chip's 4096 wave
+// slots of the kernel unfilled.
 constexpr int kMergeRowsPerWave = 16;
+constexpr int kMergeRowsPerWaveShort = 4;
+constexpr long long kMergeShortRows = 65536;
 
 // Where a wave is in the flat sequence of load steps of its output rows: row r of the wave, element t
 // of that row's list (element 0 is the conserved row itself, the others its members), and the row's
@@ -724,9 +729,12 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
   using CV = OutConv<T>;
   constexpr int LPR = TL::kChunksPerRow;  // lanes per row
   constexpr int MS = 64 / LPR;            // rows per load
-  constexpr int STEP = 2 * MS;            // rows per step (two loads per lane and tensor)
+  // loads per lane and tensor in a step: a list holds four to nine rows on average, so rows of 128 bytes (eight per
+  // load) take one (360 pairs of 3001: 145 -> 121 us), longer rows two (with one, rows of 256 bytes 13-25 % slower)
+  constexpr int U = MS >= 8 ? 1 : 2;
+  constexpr int STEP = U * MS;            // rows per step
   constexpr int E = CV::kElems;
-  constexpr int R = kMergeRowsPerWave;
+  const int R = a.merge_rows;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -768,18 +776,20 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
   // list are clamped into the list array, and their lanes load the conserved row again, which the
   // sum then skips.
   const int last_member = a.n_members - 1;
-  auto step_ids = [&](const MergeCursor& c, int& i0, int& i1) {
-    const int e0 = c.t + sub, e1 = e0 + MS;
-    const int p0 = min(max(c.beg - 1 + e0, 0), last_member), p1 = min(c.beg - 1 + e1, last_member);
-    const int m0 = members[p0], m1 = members[p1];
-    i0 = (e0 != 0 && e0 < c.cnt) ? m0 : c.sel;
-    i1 = (e1 < c.cnt) ? m1 : c.sel;
+  auto step_ids = [&](const MergeCursor& c, int (&ids)[U]) {
+    const int e0 = c.t + sub;
+    int m[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m[u] = members[min(max(c.beg - 1 + e0 + u * MS, 0), last_member)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ids[u] = ((u > 0 || e0 != 0) && e0 + u * MS < c.cnt) ? m[u] : c.sel;
   };
-  auto fetch = [&](int i0, int i1, uint4 (&k)[2], uint4 (&v)[2]) {
-    k[0] = load16_stream(kb + (size_t)i0 * TL::kRowBytes);
-    v[0] = load16_stream(vb + (size_t)i0 * TL::kRowBytes);
-    k[1] = load16_stream(kb + (size_t)i1 * TL::kRowBytes);
-    v[1] = load16_stream(vb + (size_t)i1 * TL::kRowBytes);
+  auto fetch = [&](const int (&ids)[U], uint4 (&k)[U], uint4 (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      k[u] = load16_stream(kb + (size_t)ids[u] * TL::kRowBytes);
+      v[u] = load16_stream(vb + (size_t)ids[u] * TL::kRowBytes);
+    }
   };
 
   double ak[E], av[E];
@@ -789,13 +799,13 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
     av[i] = 0.0;
   }
   // sums the rows of the step at c (already loaded into k, v); finishes the output row on its last step
-  auto consume = [&](const MergeCursor& c, const uint4 (&k)[2], const uint4 (&v)[2]) {
+  auto consume = [&](const MergeCursor& c, const uint4 (&k)[U], const uint4 (&v)[U]) {
     // One unconditional use of everything the step loaded: the wait for these loads then sits here on
     // every path, instead of inside the branches below (which would leave them formally in flight on
     // the other paths and force wider waits later).
-    asm volatile("" ::"v"(k[0].x), "v"(k[0].y), "v"(k[0].z), "v"(k[0].w), "v"(k[1].x), "v"(k[1].y), "v"(k[1].z),
-                 "v"(k[1].w), "v"(v[0].x), "v"(v[0].y), "v"(v[0].z), "v"(v[0].w), "v"(v[1].x), "v"(v[1].y),
-                 "v"(v[1].z), "v"(v[1].w));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      asm volatile("" ::"v"(k[u].x), "v"(k[u].y), "v"(k[u].z), "v"(k[u].w), "v"(v[u].x), "v"(v[u].y), "v"(v[u].z), "v"(v[u].w));
     const long long w = w_lo + c.r;
     if (c.cnt == 1) {  // nothing merges into this row: bit-exact copy
       if (sub == 0) {
@@ -806,7 +816,7 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
       return;
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
       if (c.t + u * MS + sub < c.cnt) {  // lanes past the end of the list hold a row that does not count
         double tk[E], tv[E];
         CV::unpack(k[u], tk);
@@ -854,16 +864,15 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
   advance(c1);
   MergeCursor c2 = c1;
   advance(c2);
-  int ida0, ida1, idb0, idb1;
-  uint4 ka[2], va[2], kb2[2], vb2[2];
-  step_ids(c0, ida0, ida1);
-  step_ids(c1, idb0, idb1);
-  fetch(ida0, ida1, kb2, vb2);
+  int ida[U], idb[U];
+  uint4 ka[U], va[U], kb2[U], vb2[U];
+  step_ids(c0, ida);
+  step_ids(c1, idb);
+  fetch(ida, kb2, vb2);
   // one step: true when the wave's last row is done
-  auto round = [&](int& new0, int& new1, int old0, int old1, uint4 (&nk)[2], uint4 (&nv)[2], const uint4 (&ok)[2],
-                   const uint4 (&ov)[2]) {
-    step_ids(c2, new0, new1);
-    fetch(old0, old1, nk, nv);
+  auto round = [&](int (&fresh)[U], const int (&old)[U], uint4 (&nk)[U], uint4 (&nv)[U], const uint4 (&ok)[U], const uint4 (&ov)[U]) {
+    step_ids(c2, fresh);
+    fetch(old, nk, nv);
     consume(c0, ok, ov);
     c0 = c1;
     c1 = c2;
@@ -871,10 +880,10 @@ __global__ void __launch_bounds__(256) merge_write_kernel(MergeArgs a) {
     return c0.r >= n_out;
   };
   while (true) {
-    if (round(ida0, ida1, idb0, idb1, ka, va, kb2, vb2)) break;
-    if (round(idb0, idb1, ida0, ida1, kb2, vb2, ka, va)) break;
-    if (round(ida0, ida1, idb0, idb1, ka, va, kb2, vb2)) break;
-    if (round(idb0, idb1, ida0, ida1, kb2, vb2, ka, va)) break;
+    if (round(ida, idb, ka, va, kb2, vb2)) break;
+    if (round(idb, ida, kb2, vb2, ka, va)) break;
+    if (round(ida, idb, ka, va, kb2, vb2)) break;
+    if (round(idb, ida, kb2, vb2, ka, va)) break;
   }
 }
 
@@ -917,6 +926,7 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   a.merge_assign = b.merge_assign;
   a.L = p.L; a.Hkv = p.Hkv; a.T = p.T; a.flags = p.flags;
   a.total_slots = (long long)p.B * p.Hkv;
+  a.merge_rows = a.total_slots < kMergeShortRows ? kMergeRowsPerWaveShort : kMergeRowsPerWave;
   a.use_resident = 0;
   a.merge_members = !((p.flags & MEDA_FLAG_NO_MERGE) || p.B == (int64_t)p.L * p.T);
   a.n_members = (int)(((int64_t)p.L * p.T - p.B) * p.Hkv);
@@ -969,7 +979,7 @@ static hipError_t launch_merge_t(const Plan& p, const MergeArgs& a, hipStream_t 
     hipLaunchKernelGGL((copy_rows_kernel<T, D>), dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
   }
-  const long long waves = (a.total_slots + kMergeRowsPerWave - 1) / kMergeRowsPerWave;
+  const long long waves = (a.total_slots + a.merge_rows - 1) / a.merge_rows;
   hipLaunchKernelGGL((merge_write_kernel<T, D>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
