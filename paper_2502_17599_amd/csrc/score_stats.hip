@@ -259,25 +259,50 @@ __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2
   }
 }
 
-// One thread per (layer, query head, row of the statistics arrays): merge the partials of the row.
-__global__ void __launch_bounds__(256) stats_combine_kernel(ScoreArgs a) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// Merges the partials of every (layer, query head, row of the statistics arrays): one thread per row, which walks
+// its partials in order.  STAGED: a workgroup takes `rows` rows and first copies all their partials (contiguous) into
+// LDS, all loads in flight together: with one load after the other the memory latency of every partial bound the
+// kernel (32 partials 11 -> 6 us, 37 partials 25 -> 17 us; at 12 and 16 partials the staging costs more than it saves,
+// 7 and 8 us without it, 14 and 11 us with it).
+constexpr int kCombineThreads = 256;
+constexpr int kCombineDirect = 16;
+constexpr int kCombineStaged = 2048;  // partials of a workgroup in LDS (each row padded by one: its lanes spread over the banks)
+
+template <bool STAGED>
+__global__ void __launch_bounds__(kCombineThreads) stats_combine_kernel(ScoreArgs a, int rows) {
+  __shared__ float4 staged[STAGED ? kCombineStaged + kCombineThreads : 1];
   const int total = a.L * a.Hq * a.stats_rows;
-  if (idx >= total) return;
+  const int idx0 = blockIdx.x * rows, idx = idx0 + threadIdx.x;
+  const int n_part = a.NPART, pad = (n_part & 1) ^ 1;  // an odd number of 16-byte pieces per row
   const int row = idx % a.stats_rows;
-  const int n_part = a.NPART;
-  int position;  // the row's position in the sequence
-  if (a.blocks) {
-    position = a.Tk - a.q_rows + row;  // one chunk of keys per row block: every partial of the row exists
-  } else {
-    if (row >= a.W) {  // padding rows of the window: no weight
-      float* plane = reinterpret_cast<float*>(a.stats) + (size_t)(idx / a.stats_rows) * 4 * a.stats_rows + row;
-      plane[0] = plane[(size_t)a.stats_rows] = plane[2 * (size_t)a.stats_rows] = plane[3 * (size_t)a.stats_rows] = 0.f;
-      return;
-    }
-    position = a.T - a.W + row;
+  // the row's position in the sequence (row-block mode: one chunk of keys per row block, every partial of the row
+  // exists; else the rows from W on are padding)
+  const int position = a.blocks ? a.Tk - a.q_rows + row : a.T - a.W + row;
+  uint8_t row_mask = 0;
+  if ((int)threadIdx.x < rows && idx < total && (a.blocks || row < a.W))
+    row_mask = a.mask[(size_t)(idx / (a.Hq * a.stats_rows) / a.Lseq) * a.Tk + position];
+  if (STAGED) {
+    const float4* src = a.stats_part + (size_t)idx0 * n_part;
+    const int n = min(rows, total - idx0) * n_part;
+    float4 v[kCombineStaged / kCombineThreads];
+#pragma unroll
+    for (int i = 0; i < kCombineStaged / kCombineThreads; ++i)
+      if (i * kCombineThreads < n) v[i] = src[min((int)threadIdx.x + i * kCombineThreads, n - 1)];
+#pragma unroll
+    for (int i = 0; i < kCombineStaged / kCombineThreads; ++i)
+      if ((int)threadIdx.x + i * kCombineThreads < n) {
+        const unsigned at = threadIdx.x + i * kCombineThreads;
+        staged[at + at / (unsigned)n_part * (unsigned)pad] = v[i];
+      }
+    __syncthreads();
   }
-  const float4* part = a.stats_part + (size_t)idx * a.NPART;
+  if ((int)threadIdx.x >= rows || idx >= total) return;
+  if (!a.blocks && row >= a.W) {  // padding rows of the window: no weight
+    float* plane = reinterpret_cast<float*>(a.stats) + (size_t)(idx / a.stats_rows) * 4 * a.stats_rows + row;
+    plane[0] = plane[(size_t)a.stats_rows] = plane[2 * (size_t)a.stats_rows] = plane[3 * (size_t)a.stats_rows] = 0.f;
+    return;
+  }
+  const float4* part = STAGED ? staged + threadIdx.x * (n_part + pad) : a.stats_part + (size_t)idx * n_part;
   float M = kNegBig;
   for (int i = 0; i < n_part; ++i) M = fmaxf(M, part[i].x);
   float zv = 0.f, zt = 0.f;
@@ -287,8 +312,7 @@ __global__ void __launch_bounds__(256) stats_combine_kernel(ScoreArgs a) {
     zv = fmaf(p.y, f, zv);
     zt = fmaf(p.z, f, zt);
   }
-  const int l = idx / (a.Hq * a.stats_rows);
-  const bool row_is_vision = a.mask[(size_t)(l / a.Lseq) * a.Tk + position] != 0;
+  const bool row_is_vision = row_mask != 0;
   const float coef_v = (!row_is_vision && zv > 0.f) ? 1.0f / zv : 0.f;  // text row: attends to vision columns
   const float coef_t = (row_is_vision && zt > 0.f) ? 1.0f / zt : 0.f;   // vision row: attends to text columns
   if (a.blocks) {
@@ -365,7 +389,13 @@ hipError_t launch_score_stats(const Plan& p, const Buffers& b, hipStream_t s) {
 hipError_t launch_stats_combine(const Plan& p, const Buffers& b, hipStream_t s) {
   const ScoreArgs a = make_args(p, b);
   const int total = p.L * p.Hq * (p.blocks ? p.R : p.Wp);
-  hipLaunchKernelGGL(stats_combine_kernel, dim3((total + 255) / 256), dim3(256), 0, s, a);
+  if (a.NPART > kCombineDirect && a.NPART <= kCombineStaged) {
+    const int fit = kCombineStaged / a.NPART, rows = fit < kCombineThreads ? fit : kCombineThreads;
+    hipLaunchKernelGGL((stats_combine_kernel<true>), dim3((total + rows - 1) / rows), dim3(kCombineThreads), 0, s, a, rows);
+  } else {
+    hipLaunchKernelGGL((stats_combine_kernel<false>), dim3((total + kCombineThreads - 1) / kCombineThreads),
+                       dim3(kCombineThreads), 0, s, a, kCombineThreads);
+  }
   return hipGetLastError();
 }
 
