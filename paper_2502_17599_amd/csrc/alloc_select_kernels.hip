@@ -26,11 +26,11 @@ __device__ __forceinline__ double clampd(double v, double lo, double hi) { retur
 // [min(W,T), T] by water-filling (x_l = clamp(lambda * w_l), sum x_l = B) and rounded by largest
 // remainder, so that sum_l S_l = B exactly.  All real arithmetic is double precision.
 __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
-  __shared__ double E[kMaxLayers], w[kMaxLayers], x[kMaxLayers], frac[kMaxLayers];
+  __shared__ double E[kMaxLayers], w[kMaxLayers], frac[kMaxLayers];
   __shared__ double kink[2 * kMaxLayers], filled[2 * kMaxLayers];
   __shared__ int S[kMaxLayers], order[kMaxLayers];
   __shared__ double s_lambda;
-  const int tid = threadIdx.x, L = a.L;
+  const int tid = threadIdx.x, lane = tid & 63, L = a.L;
   const double lo = (double)min(a.W, a.T), hi = (double)a.T, B = (double)a.B;
   // sequence n: its layers are the layers n*L .. n*L + L-1 of the batch, its output rows start at n*B
   const int n = blockIdx.x;
@@ -45,15 +45,17 @@ __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
   const int n_text = a.R - n_vis;
   // per-tile entropy partials of a layer are summed by one wave (lanes stride over the tiles)
   for (int l = tid >> 6; l < L; l += blockDim.x >> 6) {
-    const double* p = a.ent_part + (size_t)l * a.NT * 2;
+    const double2* p = reinterpret_cast<const double2*>(a.ent_part + (size_t)l * a.NT * 2);
     double tv = 0.0, vt = 0.0;
-    for (int t = tid & 63; t < a.NT; t += 64) {
-      tv += p[2 * t];
-      vt += p[2 * t + 1];
+#pragma unroll 4
+    for (int t = lane; t < a.NT; t += 64) {
+      const double2 v = p[t];
+      tv += v.x;
+      vt += v.y;
     }
     tv = wave_sum(tv);
     vt = wave_sum(vt);
-    if ((tid & 63) == 0) {
+    if (lane == 0) {
       const double e = (n_text ? tv / n_text : 0.0) + (n_vis ? vt / n_vis : 0.0);
       E[l] = e;
       if (a.entropy) a.entropy[l] = e;
@@ -61,9 +63,13 @@ __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
   }
   __syncthreads();
 
+  // From here on the kernel is a chain of short steps over L values, bound by the latency of LDS and of the fp64
+  // operations: everything that can be is done by a wave (reductions over the lanes) or by a thread per value (32
+  // layers: 22 -> 11 us against one thread walking the kinks and the remainders).
   const bool uniform = (a.flags & MEDA_FLAG_UNIFORM_BUDGET) != 0;
   if (tid < L) {
     double emax = E[0];
+#pragma unroll 8
     for (int i = 1; i < L; ++i) emax = fmax(emax, E[i]);
     w[tid] = uniform ? 1.0 : exp(E[tid] - emax);
   }
@@ -72,30 +78,38 @@ __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
   for (int i = tid; i < 2 * L; i += blockDim.x) {
     const double b = (i < L) ? lo / w[i] : hi / w[i - L];
     double f = 0.0;
+#pragma unroll 8
     for (int j = 0; j < L; ++j) f += clampd(b * w[j], lo, hi);
     kink[i] = b;
     filled[i] = f;
   }
   __syncthreads();
-  if (tid == 0) {
-    double upper = -1.0, lower = 0.0;
-    for (int i = 0; i < 2 * L; ++i) {
-      if (filled[i] >= B) {
-        if (upper < 0.0 || kink[i] < upper) upper = kink[i];
-      } else if (kink[i] > lower) {
-        lower = kink[i];
-      }
+  if (tid < 64) {  // first kink at or above the budget, last one below it
+    double upper = INFINITY, lower = 0.0;
+    for (int i = lane; i < 2 * L; i += 64) {
+      const double k = kink[i];
+      if (filled[i] >= B) upper = fmin(upper, k);
+      else lower = fmax(lower, k);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      upper = fmin(upper, __shfl_xor(upper, o, kWave));
+      lower = fmax(lower, __shfl_xor(lower, o, kWave));
+    }
+    if (upper == INFINITY) upper = -1.0;
     const double mid = 0.5 * (lower + upper);
     double wsum = 0.0;
     int n_lo = 0, n_hi = 0;
-    for (int j = 0; j < L; ++j) {
+    for (int j = lane; j < L; j += 64) {
       const double v = mid * w[j];
       if (v <= lo) ++n_lo;
       else if (v >= hi) ++n_hi;
       else wsum += w[j];
     }
-    s_lambda = (wsum > 0.0) ? (B - lo * n_lo - hi * n_hi) / wsum : upper;
+    wsum = wave_sum(wsum);
+    n_lo = wave_sum(n_lo);
+    n_hi = wave_sum(n_hi);
+    if (lane == 0) s_lambda = (wsum > 0.0) ? (B - lo * n_lo - hi * n_hi) / wsum : upper;
   }
   __syncthreads();
   if (tid < L) {
@@ -103,7 +117,6 @@ __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
     if (a.B == (long long)L * a.T) xv = hi;
     if (a.B == (long long)L * min(a.W, a.T)) xv = lo;
     const double fl = floor(xv);
-    x[tid] = xv;
     frac[tid] = xv - fl;
     S[tid] = (int)clampd(fl, lo, hi);
   }
@@ -111,40 +124,56 @@ __global__ void __launch_bounds__(1024) allocate_kernel(AllocArgs a) {
   if (tid < L) {
     int rank = 0;
     const double f = frac[tid];
+#pragma unroll 8
     for (int j = 0; j < L; ++j) rank += (frac[j] > f || (frac[j] == f && j < tid)) ? 1 : 0;
     order[rank] = tid;  // decreasing fractional part, ties towards the lower layer
   }
   __syncthreads();
-  if (tid == 0) {
+  if (tid < 64) {
     long long sum = 0;
-    for (int j = 0; j < L; ++j) sum += S[j];
+    bool full = false;  // a layer that cannot take another slot
+    for (int j = lane; j < L; j += 64) {
+      sum += S[j];
+      full = full || S[j] >= a.T;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
     long long rest = a.B - sum;
-    for (int round = 0; round < 4 && rest > 0; ++round)
-      for (int r = 0; r < L && rest > 0; ++r) {
-        const int lyr = order[r];
-        if (S[lyr] < a.T) { ++S[lyr]; --rest; }
-      }
-    for (int round = 0; round < 4 && rest < 0; ++round)  // only reachable through rounding fuzz
-      for (int r = L - 1; r >= 0 && rest < 0; --r) {
-        const int lyr = order[r];
-        if (S[lyr] > min(a.W, a.T)) { --S[lyr]; ++rest; }
-      }
+    if (rest >= 0 && rest <= L && __ballot(full) == 0ull) {
+      // the usual case: the first `rest` layers of the order take one slot each
+      for (int r = lane; r < (int)rest; r += 64) ++S[order[r]];
+    } else if (lane == 0) {
+      for (int round = 0; round < 4 && rest > 0; ++round)
+        for (int r = 0; r < L && rest > 0; ++r) {
+          const int lyr = order[r];
+          if (S[lyr] < a.T) { ++S[lyr]; --rest; }
+        }
+      for (int round = 0; round < 4 && rest < 0; ++round)  // only reachable through rounding fuzz
+        for (int r = L - 1; r >= 0 && rest < 0; --r) {
+          const int lyr = order[r];
+          if (S[lyr] > min(a.W, a.T)) { --S[lyr]; ++rest; }
+        }
+    }
   }
   __syncthreads();
   if (tid < L) {
     const int s = S[tid];
     const int m = max(min(a.W, s), (int)(((long long)s * a.num) / a.den));
     long long o = (long long)n * a.B;
-    for (int j = 0; j < tid; ++j) o += S[j];
-    const int lv = n * L + tid;  // layer of the batch
-    a.alloc[4 * lv + 0] = s;
-    a.alloc[4 * lv + 1] = m;
-    a.alloc[4 * lv + 2] = s - m;
     // layers ranked by decreasing budget (ties: lower layer first), for kernels that launch the
     // longest workgroups first; in a batch the ranks of the sequences are interleaved (rank r of
     // sequence n is entry r*N + n), which keeps the order of one sequence and is decreasing on average
     int rank = 0;
-    for (int j = 0; j < L; ++j) rank += (S[j] > s || (S[j] == s && j < tid)) ? 1 : 0;
+#pragma unroll 8
+    for (int j = 0; j < L; ++j) {
+      const int sj = S[j];
+      o += j < tid ? sj : 0;
+      rank += (sj > s || (sj == s && j < tid)) ? 1 : 0;
+    }
+    const int lv = n * L + tid;  // layer of the batch
+    a.alloc[4 * lv + 0] = s;
+    a.alloc[4 * lv + 1] = m;
+    a.alloc[4 * lv + 2] = s - m;
     a.alloc[4 * (rank * a.N + n) + 3] = lv;
     a.off[lv] = o;
     a.layer_len[lv] = s;
