@@ -202,34 +202,62 @@ struct SelectArgs {
 };
 
 constexpr int kSelMaxThreads = 1024;
-constexpr int kSelBatch = 4;  // loads a thread has in flight in the counting passes
 constexpr int kSelMaxWaves = kSelMaxThreads / 64;
+constexpr int kSelBins = 2048;  // 11-bit digits
 
-// Exclusive rank of a one-bit flag over the workgroup (ballots inside a wave, wave totals in LDS).
-// `totals` has 2*kSelWaves ints; `slot` selects which half.  Returns rank; *block_total = number of set flags.
-__device__ __forceinline__ int flag_rank_in_wave(bool flag, int lane, int* wave_total) {
-  const unsigned long long b = __ballot(flag);
-  *wave_total = __popcll(b);
-  return __popcll(b & ((1ull << lane) - 1ull));
+struct SelectShared {
+  int hist[2][kSelBins];      // text, vision (the later digits use the first half)
+  int wsum[2][kSelMaxWaves];
+  int bin, rest;
+};
+
+// The digit of the `want`-th largest key of a histogram (want >= 1, at most the histogram's total) and how many of
+// that digit's keys are still wanted.  Every thread takes kSelBins / threads adjacent bins, from the top.
+__device__ __forceinline__ void find_digit(SelectShared& sh, const int* hist, int want) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
+  const int per = kSelBins / (int)blockDim.x, top = kSelBins - 1 - tid * per;
+  int own = 0;
+  for (int b = 0; b < per; ++b) own += hist[top - b];
+  int inc = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, kWave);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) sh.wsum[0][wave] = inc;
+  __syncthreads();
+  int before = inc - own;
+  for (int w = 0; w < n_waves; ++w) before += w < wave ? sh.wsum[0][w] : 0;
+  if (before < want && before + own >= want) {
+    int bin = top;
+    while (before + hist[bin] < want) before += hist[bin--];
+    sh.bin = bin;
+    sh.rest = want - before;
+  }
+  __syncthreads();
 }
 
 // grid (Hkv, L).  Adding max(A_s) to every text score puts all text candidates above all vision
 // candidates and keeps the order inside each modality, so the Top-N of the boosted scores is:
 // all text candidates plus the best vision ones if N exceeds the number of text candidates, else
 // the best N text candidates.  The order inside one modality is found exactly on the unboosted
-// fp32 scores (no bits are lost to the addition) with a 4 x 8-bit radix select on their bit
-// patterns (scores are >= 0, so the unsigned order of the bits is the order of the values); equal
-// scores go to the smaller position.
-template <int kSelItems>  // consecutive positions a thread takes per iteration of the output pass
+// fp32 scores (no bits are lost to the addition) with a radix select over their bit patterns, 11 + 11 + 10 bits
+// (scores are >= 0, so the unsigned order of the bits is the order of the values); equal scores go to the smaller
+// position.  The first sweep counts both modalities, so the number of text candidates needs no sweep of its own.
+//
+// Bound by the latency of its sweeps and, before, by histogram atomics: with 8-bit digits the first one (two octaves
+// of score per bin) put nearly all of a wave's adds on one or two addresses.  A wave takes ITEMS x 64 consecutive
+// positions per iteration, lane by lane (loads and stores coalesced, ranks from ballots).  Up to ITEMS positions per
+// thread (SINGLE) the scores are read once and stay in registers.  One barrier per iteration of the output sweep:
+// the positions a tie may take before p are min(ties before p, ties taken), so one prefix over (certain, tied)
+// counts places everything.  Before and now, in us: 256 (layer, head) pairs of 131072 positions 370 / 233, 112 of 37376
+// 92 / 64, 256 of 16384 45 / 32, 1024 of 4096 31 / 29, 360 of 3001 23 / 16.5.
+template <int ITEMS, bool SINGLE>
 __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
-  __shared__ int hist[256];
-  __shared__ int wtot[2][kSelMaxWaves];
-  __shared__ int s_red[kSelMaxWaves];
-  __shared__ unsigned s_prefix;
-  __shared__ int s_remaining;
-
-  const int g = blockIdx.x, l = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kSelThreads = blockDim.x, kSelWaves = kSelThreads >> 6;
+  __shared__ SelectShared sh;
+  const int g = blockIdx.x, l = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_thr = blockDim.x, n_waves = n_thr >> 6;
   const int T = a.T;
   const uint8_t* mask = a.mask + (size_t)(l / a.Lseq) * T;  // this layer's sequence
   const int S = a.alloc[4 * l + 0], M = a.alloc[4 * l + 1], N = a.alloc[4 * l + 2];
@@ -240,177 +268,121 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
   const size_t c_base = (size_t)off_l * a.Hkv + (size_t)g * S;
   const size_t less_base = ((size_t)l * T - (size_t)off_l) * a.Hkv + (size_t)g * (T - S);
 
-  // number of text candidates (kSelBatch loads in flight per thread: a pass over the scores of one head is bound by
-  // the latency of its loads, not by their bytes)
-  int cnt = 0;
-  for (int j0 = tid; j0 < ncand; j0 += kSelBatch * kSelThreads) {
-    uint8_t mk[kSelBatch];
+  const int span = ITEMS * n_thr;           // positions per iteration of the workgroup
+  const int w0 = wave * ITEMS * 64 + lane;  // this lane's first position of an iteration
+  unsigned key[ITEMS];
+  uint8_t mk[ITEMS];
+  auto load = [&](int base) {
 #pragma unroll
-    for (int i = 0; i < kSelBatch; ++i) mk[i] = mask[min(j0 + i * kSelThreads, ncand - 1)];
+    for (int i = 0; i < ITEMS; ++i) {
+      const int j = min(base + w0 + i * 64, T - 1);
+      mk[i] = mask[j];
+      key[i] = __float_as_uint(scores[j]);
+    }
+  };
+  // f(position, key, class) for every candidate
+  auto sweep = [&](auto f) {
+    for (int base = 0; base < ncand; base += span) {
+      if (!SINGLE) load(base);
 #pragma unroll
-    for (int i = 0; i < kSelBatch; ++i) cnt += (j0 + i * kSelThreads < ncand && mk[i] == 0) ? 1 : 0;
-  }
-  cnt = wave_sum(cnt);
-  if (lane == 0) s_red[wave] = cnt;
+      for (int i = 0; i < ITEMS; ++i)
+        if (base + w0 + i * 64 < ncand) f(key[i], mk[i] != 0 ? 1 : 0);
+    }
+  };
+  if (SINGLE) load(0);
+
+  for (int b = tid; b < 2 * kSelBins; b += n_thr) (&sh.hist[0][0])[b] = 0;
+  __syncthreads();
+  sweep([&](unsigned k, int c) { atomicAdd(&sh.hist[c][k >> 21], 1); });
   __syncthreads();
   int n_text = 0;
-  for (int i = 0; i < kSelWaves; ++i) n_text += s_red[i];
+  for (int b = tid; b < kSelBins; b += n_thr) n_text += sh.hist[0][b];
+  n_text = wave_sum(n_text);
+  if (lane == 0) sh.wsum[1][wave] = n_text;
+  __syncthreads();
+  n_text = 0;
+  for (int w = 0; w < n_waves; ++w) n_text += sh.wsum[1][w];
 
   const bool pick_text = N <= n_text;            // class in which the cut falls
   const int K = pick_text ? N : N - n_text;      // how many of that class are taken
   const bool other_taken = !pick_text;           // vision cut: every text candidate is taken
-  const uint8_t cls = pick_text ? 0 : 1;
+  const int cls = pick_text ? 0 : 1;
 
   unsigned threshold = 0xffffffffu;
   int ties_taken = 0;
   if (K > 0) {
-    if (tid == 0) { s_prefix = 0u; s_remaining = K; }
-    unsigned prefix_mask = 0u;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) hist[tid] = 0;
-      __syncthreads();
-      const unsigned prefix = s_prefix;
-      for (int j0 = tid; j0 < ncand; j0 += kSelBatch * kSelThreads) {
-        uint8_t mk[kSelBatch];
-        unsigned key[kSelBatch];
+    find_digit(sh, sh.hist[cls], K);
+    unsigned prefix = (unsigned)sh.bin;
+    int want = sh.rest;
 #pragma unroll
-        for (int i = 0; i < kSelBatch; ++i) {
-          const int j = min(j0 + i * kSelThreads, ncand - 1);
-          mk[i] = mask[j];
-          key[i] = __float_as_uint(scores[j]);
-        }
-#pragma unroll
-        for (int i = 0; i < kSelBatch; ++i) {
-          if (j0 + i * kSelThreads < ncand && (mk[i] != 0) == (cls != 0) && (key[i] & prefix_mask) == prefix)
-            atomicAdd(&hist[(key[i] >> shift) & 255u], 1);
-        }
-      }
+    for (int step = 0; step < 2; ++step) {
+      const int shift = step == 0 ? 10 : 0, bits = step == 0 ? 11 : 10;
+      for (int b = tid; b < kSelBins; b += n_thr) sh.hist[0][b] = 0;
       __syncthreads();
-      if (wave == 0) {
-        // bins from the top: lane i looks at bins 255-4i .. 252-4i; the lane whose running count
-        // first reaches `remaining` holds the digit of the K-th largest key
-        const int remaining = s_remaining;
-        const int b0 = 255 - 4 * lane;
-        const int c0 = hist[b0], c1 = hist[b0 - 1], c2 = hist[b0 - 2], c3 = hist[b0 - 3];
-        const int tot = c0 + c1 + c2 + c3;
-        int inc = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int t = __shfl_up(inc, o, kWave);
-          if (lane >= o) inc += t;
-        }
-        const int exc = inc - tot;
-        if (exc < remaining && inc >= remaining) {
-          int cum = exc, digit = b0;
-          if (cum + c0 < remaining) {
-            cum += c0; digit = b0 - 1;
-            if (cum + c1 < remaining) {
-              cum += c1; digit = b0 - 2;
-              if (cum + c2 < remaining) { cum += c2; digit = b0 - 3; }
-            }
-          }
-          s_remaining = remaining - cum;
-          s_prefix = prefix | ((unsigned)digit << shift);
-        }
-      }
-      prefix_mask |= 255u << shift;
+      sweep([&](unsigned k, int c) {
+        if (c == cls && (k >> (shift + bits)) == prefix) atomicAdd(&sh.hist[0][(k >> shift) & ((1u << bits) - 1u)], 1);
+      });
       __syncthreads();
+      find_digit(sh, sh.hist[0], want);
+      prefix = (prefix << bits) | (unsigned)sh.bin;
+      want = sh.rest;
     }
-    threshold = s_prefix;
-    ties_taken = s_remaining;
+    threshold = prefix;
+    ties_taken = want;
   }
 
-  // ordered output: conserved positions ascending, the rest ascending.  A thread takes kSelItems consecutive
-  // positions per iteration (two barriers per kSelItems * blockDim positions); their mask, score and 1/|k| are
-  // requested one iteration ahead, so that the barriers do not sit behind the loads.
-  int run_c = 0, run_tie = 0;
+  // ordered output: conserved positions ascending, the rest ascending
+  int run_sure = 0, run_tie = 0;  // certain and tied positions before this iteration
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
-  uint8_t mk_n[kSelItems];
-  unsigned key_n[kSelItems];
-  float inv_n[kSelItems];
-  auto fetch = [&](int j0) {
+  float inv[ITEMS];
+  auto load_inv = [&](int base) {
 #pragma unroll
-    for (int i = 0; i < kSelItems; ++i) {
-      const int jj = min(j0 + i, T - 1);
-      mk_n[i] = mask[jj];
-      key_n[i] = __float_as_uint(scores[jj]);
-      inv_n[i] = a.inv_norm[head_row0 + jj];
-    }
+    for (int i = 0; i < ITEMS; ++i) inv[i] = a.inv_norm[head_row0 + min(base + w0 + i * 64, T - 1)];
   };
-  fetch(tid * kSelItems);
-  for (int base = 0; base < T; base += kSelItems * kSelThreads) {
-    const int j0 = base + tid * kSelItems;
-    uint8_t mk[kSelItems];
-    unsigned key[kSelItems];
-    float inv[kSelItems];
+  int buf = 0;
+  for (int base = 0; base < T; base += span, buf ^= 1) {
+    if (!SINGLE) load(base);
+    load_inv(base);
+    unsigned long long sure[ITEMS], tie[ITEMS];  // uniform over the wave
+    int n_sure = 0, n_tie = 0;
 #pragma unroll
-    for (int i = 0; i < kSelItems; ++i) {
-      mk[i] = mk_n[i];
-      key[i] = key_n[i];
-      inv[i] = inv_n[i];
+    for (int i = 0; i < ITEMS; ++i) {
+      const int j = base + w0 + i * 64;
+      const bool cand = j < ncand, in_cls = (mk[i] != 0 ? 1 : 0) == cls;
+      sure[i] = __ballot(j < T && (!cand || (in_cls ? key[i] > threshold : other_taken)));
+      tie[i] = __ballot(cand && in_cls && key[i] == threshold);
+      n_sure += __popcll(sure[i]);
+      n_tie += __popcll(tie[i]);
     }
-    fetch(j0 + kSelItems * kSelThreads);
-    bool valid[kSelItems], in_cls[kSelItems], is_tie[kSelItems], above[kSelItems];
-    int tie_before = 0, tie_wave = 0;
-#pragma unroll
-    for (int i = 0; i < kSelItems; ++i) {
-      const int j = j0 + i;
-      valid[i] = j < T;
-      in_cls[i] = is_tie[i] = above[i] = false;
-      if (valid[i] && j < ncand) {
-        in_cls[i] = (mk[i] != 0) == (cls != 0);
-        if (in_cls[i]) {
-          above[i] = key[i] > threshold;
-          is_tie[i] = key[i] == threshold;
-        }
-      }
-      const unsigned long long b = __ballot(is_tie[i]);
-      tie_before += __popcll(b & lt_mask);  // ties at the positions of the lanes below
-      tie_wave += __popcll(b);
-    }
-    if (lane == 0) wtot[0][wave] = tie_wave;
+    if (lane == 0) sh.wsum[buf][wave] = n_sure | (n_tie << 16);  // at most 16384 positions per iteration
     __syncthreads();
-    int tie_rank = run_tie + tie_before, tie_total = 0;
-    for (int i = 0; i < kSelWaves; ++i) {
-      const int v = wtot[0][i];
-      tie_rank += (i < wave) ? v : 0;
-      tie_total += v;
+    int before = 0, total = 0;
+    for (int w = 0; w < n_waves; ++w) {
+      const int v = sh.wsum[buf][w];
+      before += w < wave ? v : 0;
+      total += v;
     }
-    bool sel[kSelItems];
-    int sel_before = 0, sel_wave = 0;
+    int sure_b = run_sure + (before & 0xffff), tie_b = run_tie + (before >> 16);
 #pragma unroll
-    for (int i = 0; i < kSelItems; ++i) {
-      const int j = j0 + i;
-      sel[i] = valid[i] && (j >= ncand || (in_cls[i] ? (above[i] || (is_tie[i] && tie_rank < ties_taken)) : other_taken));
-      tie_rank += is_tie[i] ? 1 : 0;  // this thread's positions are consecutive
-      const unsigned long long b = __ballot(sel[i]);
-      sel_before += __popcll(b & lt_mask);
-      sel_wave += __popcll(b);
-    }
-    if (lane == 0) wtot[1][wave] = sel_wave;
-    __syncthreads();
-    int pos_c = run_c + sel_before, sel_total = 0;
-    for (int i = 0; i < kSelWaves; ++i) {
-      const int v = wtot[1][i];
-      pos_c += (i < wave) ? v : 0;
-      sel_total += v;
-    }
-#pragma unroll
-    for (int i = 0; i < kSelItems; ++i) {
-      const int j = j0 + i;  // pos_c conserved positions lie before j
-      if (sel[i]) {
+    for (int i = 0; i < ITEMS; ++i) {
+      const int j = base + w0 + i * 64;
+      const int my_tie = tie_b + __popcll(tie[i] & lt_mask);
+      const int pos_c = sure_b + __popcll(sure[i] & lt_mask) + min(my_tie, ties_taken);  // conserved positions before j
+      const bool sel = ((sure[i] >> lane) & 1ull) || (((tie[i] >> lane) & 1ull) && my_tie < ties_taken);
+      if (sel) {
         a.sel_idx[c_base + pos_c] = head_row0 + j;
         a.sel_inv_norm[c_base + pos_c] = inv[i];
         if (a.sel_idx_user) a.sel_idx_user[c_base + pos_c] = j;
         if (a.merge_assign) a.merge_assign[head_row0 + j] = pos_c;
-        ++pos_c;
-      } else if (valid[i]) {
+      } else if (j < T) {
         a.less_idx[less_base + (j - pos_c)] = head_row0 + j;
         if (a.merge_assign && a.no_merge) a.merge_assign[head_row0 + j] = -1;
       }
+      sure_b += __popcll(sure[i]);
+      tie_b += __popcll(tie[i]);
     }
-    run_c += sel_total;
-    run_tie += tie_total;
+    run_sure += total & 0xffff;
+    run_tie += total >> 16;
   }
 }
 
@@ -446,11 +418,12 @@ hipError_t launch_select(const Plan& p, const Buffers& b, hipStream_t s) {
   a.merge_assign = b.merge_assign;
   a.L = p.L; a.Hkv = p.Hkv; a.T = p.T; a.no_merge = (p.flags & MEDA_FLAG_NO_MERGE) ? 1 : 0;
   a.Lseq = p.Lseq;
-  const int nthr = p.T >= 16384 ? 1024 : (p.T >= 4096 ? 512 : 256);
-  // long sequences: four positions per thread and iteration in the output pass (a quarter of the barriers); short
-  // ones have too few iterations for that to pay
-  if (p.T >= 16384) hipLaunchKernelGGL(select_kernel<4>, dim3(p.Hkv, p.L), dim3(nthr), 0, s, a);
-  else hipLaunchKernelGGL(select_kernel<1>, dim3(p.Hkv, p.L), dim3(nthr), 0, s, a);
+  const dim3 grid(p.Hkv, p.L);
+  if (p.T <= 1024) hipLaunchKernelGGL((select_kernel<4, true>), grid, dim3(256), 0, s, a);
+  else if (p.T <= 4096) hipLaunchKernelGGL((select_kernel<8, true>), grid, dim3(512), 0, s, a);
+  else if (p.T <= 8192) hipLaunchKernelGGL((select_kernel<8, true>), grid, dim3(1024), 0, s, a);
+  else if (p.T <= 16384) hipLaunchKernelGGL((select_kernel<16, true>), grid, dim3(1024), 0, s, a);
+  else hipLaunchKernelGGL((select_kernel<8, false>), grid, dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

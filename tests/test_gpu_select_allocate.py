@@ -1,0 +1,82 @@
+"""Selection and budgets at their edges.  Selection: lengths around the sizes at which a workgroup changes its shape
+(1024, 4096, 8192, 16384 positions) and beyond, text or vision cuts, many equal scores; the reference is a sort of the
+kernel's own column scores (text candidates first, then by score, equal scores by position), so it is exact.
+Budgets: one layer to more layers than a wave has lanes, with and without active bounds; the reference is the oracle's
+allocator on the kernel's own entropies.
+Nearest neighbours of the kernel that works without an LDS copy of the conserved set: against float64 cosines; a
+slot counts as right if its cosine is within 1e-5 of the best (sums of up to 128 exact products in fp32, times 1/|k|)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import meda_oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _run(T, L, hkv, d, dtype, B, W=16, p_text=0.3, duplicates=0, flat=False, seed=0):
+    import paper_2502_17599_amd as pkg
+    print(f"\n[select/allocate] T={T} L={L} Hkv={hkv} d={d} {dtype} B={B} W={W} text={p_text} dup={duplicates}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    k = torch.randn(L, hkv, T, d, generator=g, device=DEV)
+    if duplicates:
+        k[:, :, torch.randperm(T, generator=g, device=DEV)[:duplicates]] = k[:, :, :1]
+    q = torch.randn(L, hkv, W, d, generator=g, device=DEV)
+    if not flat:
+        q *= torch.linspace(0.2, 6.0, L, device=DEV)[:, None, None, None]
+    mask = (torch.rand(T, generator=g, device=DEV) >= p_text).to(torch.uint8)
+    comp = pkg.Compressor(pkg.make_params(L, hkv, hkv, d, T, W, B, dtype), DEV, want_merge_assign=True)
+    k = k.to(dtype)
+    out = comp(q.to(dtype), k, k.clone(), mask)
+    torch.cuda.synchronize()
+    S, M, N, off = meda_oracle.allocate_budgets(out.entropy.cpu().numpy(), B, T, W)
+    assert out.layer_len.cpu().tolist() == S.tolist() and out.layer_off.cpu().tolist() == off.tolist()
+    scores = comp.region("col_scores", torch.float32).view(L, hkv, T)
+    for l in range(L):
+        _, _, idx = out.layer(l)
+        s, m = int(S[l]), int(M[l])
+        order_class = mask[:T - m].long()
+        for h in range(hkv):
+            cand = scores[l, h, :T - m]
+            order = torch.sort(-cand, stable=True).indices                  # by score, equal ones by position
+            order = order[torch.sort(order_class[order], stable=True).indices]  # text first
+            want = torch.cat([order[:s - m].sort().values, torch.arange(T - m, T, device=DEV)])
+            assert torch.equal(idx[h].long(), want), (l, h)
+    return out, k, S
+
+
+@pytest.mark.parametrize("T", [33, 1023, 1024, 1025, 4095, 4097, 8192, 8193, 16384, 16385, 40001])
+@pytest.mark.parametrize("p_text", [0.02, 0.6])
+def test_selection_around_the_shapes(T, p_text):
+    _run(T, 2, 2, 64, torch.bfloat16, 2 * max(16, T // 5), p_text=p_text)
+    _run(T, 2, 1, 64, torch.bfloat16, 2 * max(16, T // 5), p_text=p_text, duplicates=T // 3)
+
+
+def test_selection_of_one_modality_and_of_nearly_everything():
+    for p in (0.0, 1.0):
+        _run(1500, 2, 1, 64, torch.float32, 2 * 300, p_text=p)
+    _run(5000, 2, 1, 64, torch.bfloat16, 2 * 4999)
+    _run(5000, 2, 1, 64, torch.bfloat16, 2 * 16)
+
+
+@pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 200])
+def test_budgets(L):
+    _run(200, L, 1, 64, torch.bfloat16, L * 60 + L // 2)
+    _run(200, L, 1, 64, torch.bfloat16, L * 60 + L // 2, flat=True)
+    _run(100, L, 1, 64, torch.bfloat16, L * 90 + L // 3)       # layers at the cap
+    _run(200, L, 1, 64, torch.bfloat16, L * 17)                # layers at the floor
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("T,L,hkv", [(40, 1, 1), (97, 2, 3), (1000, 2, 1), (2048, 3, 1), (2049, 3, 1), (700, 5, 8)])
+def test_nearest_neighbours(dtype, d, T, L, hkv):
+    out, k, S = _run(T, L, hkv, d, dtype, L * max(17, T // 4))
+    for l in range(L):
+        _, _, idx = out.layer(l)
+        for h in range(hkv):
+            u = k[l, h].double()
+            u = u / u.norm(dim=1, keepdim=True)
+            cos = u @ u[idx[h].long()].T
+            got = cos.gather(1, out.merge_assign[l, h].long()[:, None])[:, 0]
+            assert (got >= cos.max(dim=1).values - 1e-5).all()
