@@ -425,6 +425,104 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   }
 }
 
+// Direct kernel: no conserved set in LDS, no packed copy.  grid over (row block of 32 F, kv head, layer), XCD-aware
+// as the tiled kernel; the NW waves of a workgroup take the same 32 F rows and every NW-th block of 32 conserved keys,
+// whose fragments come from the key cache itself (L2), one block ahead; the waves' bests are merged at the end.
+// For fp32 keys, whose matrix instructions are sixteen times slower than bf16's per byte, so that the loads hide
+// behind them (256 pairs of 1024 positions: 110 us, against 105 for one workgroup per pair with its set in LDS plus
+// 16 for packing the set and an empty launch), and for problems that leave CUs empty with 256 rows per workgroup, where
+// the serial chain of one wave bounds the kernel (8 pairs of 1024 positions, fp32: 27 + 6 us for packing -> 9.6 us).
+template <typename T, int D, int F, int NW>
+__global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs a) {
+  using TL = Tile<T, D>;
+  constexpr int kRows = 32 * F;
+  __shared__ __align__(16) float inv_lds[NW][2][32];
+  __shared__ float best_v[NW][kRows];
+  __shared__ int best_s[NW][kRows];
+
+  const unsigned nrb = (a.T + kRows - 1) / kRows;
+  const unsigned xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
+  const unsigned pair = xcd + 8u * (seq / nrb);
+  if (pair >= (unsigned)(a.L * a.Hkv)) return;
+  const int l = a.alloc[4 * (pair / a.Hkv) + 3], g = pair % a.Hkv;  // layers by decreasing budget
+  const int S = a.alloc[4 * l];
+  const int n_less = a.T - S;
+  const int row_base = (seq % nrb) * kRows;
+  if (row_base >= n_less) return;
+
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long long off_l = a.off[l];
+  const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
+  const int32_t* sel = a.sel_idx + cbase;
+  const float* sinv = a.sel_inv_norm + cbase;
+  const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
+  const int32_t* less = a.less_idx + lbase;
+
+  const int nblocks = (S + 31) / 32;
+  // slots past the end repeat the last conserved key (see sim_block_products)
+  auto slot_of = [&](int b) { return min(b * 32 + n, S - 1); };
+  int lrow[F];
+#pragma unroll
+  for (int s = 0; s < F; ++s) lrow[s] = less[min(row_base + s * 32 + n, n_less - 1)];
+  int id = sel[slot_of(wave)], id1 = sel[slot_of(wave + NW)];
+  float iv0 = sinv[slot_of(wave)], iv1 = sinv[slot_of(wave + NW)];
+  Frag<T, D> lf[F], cf;
+#pragma unroll
+  for (int s = 0; s < F; ++s) frag_load(lf[s], a.k + (size_t)lrow[s] * TL::kRowBytes, kg);
+  frag_load(cf, a.k + (size_t)id * TL::kRowBytes, kg);
+  RowBest rb[F];
+#pragma unroll
+  for (int s = 0; s < F; ++s) row_best_init(rb[s]);
+
+  int par = 0;
+  for (int b = wave; b < nblocks; b += NW, par ^= 1) {
+    Frag<T, D> cn;
+    frag_load(cn, a.k + (size_t)id1 * TL::kRowBytes, kg);
+    const int id2 = sel[slot_of(b + 2 * NW)];
+    const float iv2 = sinv[slot_of(b + 2 * NW)];
+    if (kg == 0) inv_lds[wave][par][n] = iv0;  // this wave's own copy: LDS operations of a wave stay in order
+    float iv[16];
+    load_inv(iv, &inv_lds[wave][par][kg * 4]);
+    f32x16_t acc[F];
+#pragma unroll
+    for (int s = 0; s < F; ++s) {
+      acc[s] = acc_zero();
+      mma<T, D>(acc[s], cf, lf[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < F; ++s) keep_if_improved(acc[s], scale_max(acc[s], iv), b * 32, rb[s]);
+    cf = cn;
+    id1 = id2;
+    iv0 = iv1;
+    iv1 = iv2;
+  }
+#pragma unroll
+  for (int s = 0; s < F; ++s) {
+    const int bi = row_best_merge(rb[s], kg);
+    const float bv = fmaxf(rb[s].best, __shfl_xor(rb[s].best, 32, kWave));
+    if (kg == 0) {
+      best_v[wave][s * 32 + n] = bv;
+      best_s[wave][s * 32 + n] = bi;
+    }
+  }
+  __syncthreads();
+  if (tid < kRows && row_base + tid < n_less) {
+    float v = best_v[0][tid];
+    int slot = best_s[0][tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float ov = best_v[w][tid];
+      const int os = best_s[w][tid];
+      const bool take = ov > v || (ov == v && os < slot);
+      v = take ? ov : v;
+      slot = take ? os : slot;
+    }
+    a.less_slot[lbase + row_base + tid] = slot;
+    if (a.merge_assign) a.merge_assign[less[row_base + tid]] = slot;
+  }
+}
+
 // ------------------------------------------------------------------------ conserved keys, packed
 // Output row w of the ragged cache is the conserved key sel_idx[w]; the rows of one (layer, head) are
 // consecutive in w.  Copying them once into that order makes every tile of conserved keys the similarity
@@ -933,31 +1031,51 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   return a;
 }
 
+// The direct kernel takes fp32 keys, and short bf16 prompts whose tiled launch would leave most CUs empty: 16 pairs of
+// 500 positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000 53 ->
+// 120 us (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
+constexpr unsigned kSimDirectGroups = 96;
+constexpr int kSimDirectPositions = 2048;
+
+template <typename T, int D, int F, int NW>
+static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStream_t s) {
+  const unsigned nrb = (a.T + 32 * F - 1) / (32 * F);
+  hipLaunchKernelGGL((similarity_direct_kernel<T, D, F, NW>), dim3(8u * nrb * ((pairs + 7u) / 8u)), dim3(NW * 64), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
-  // one resident-set workgroup occupies a whole CU: only worth it with at least one per CU
-  a.use_resident = (resident_capacity<T, D>() > 0 && pairs >= 256u) ? 1 : 0;
-  hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
-                     dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  dim3 grid(8u * nrb * ((pairs + 7u) / 8u));
-  constexpr int kTiledLds = sim_tiled_lds_bytes<T, D>();
-  auto tiled = similarity_argmax_kernel<T, D>;
-  if (kTiledLds > 64 * 1024) {
-    e = allow_dynamic_lds(tiled, kTiledLds);
+  if constexpr (sizeof(T) == 4) {
+    // two fragments per wave halve the key loads once there are enough workgroups of 64 rows for every CU
+    if (D == 64 && pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<T, D, (D == 64 ? 2 : 1), 4>(a, pairs, s);
+    return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
+  } else {
+    if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
+    // one resident-set workgroup occupies a whole CU: only worth it with at least one per CU
+    a.use_resident = pairs >= 256u ? 1 : 0;
+    hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
+                       dim3(256), 0, s, a);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    dim3 grid(8u * nrb * ((pairs + 7u) / 8u));
+    constexpr int kTiledLds = sim_tiled_lds_bytes<T, D>();
+    auto tiled = similarity_argmax_kernel<T, D>;
+    if (kTiledLds > 64 * 1024) {
+      e = allow_dynamic_lds(tiled, kTiledLds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(tiled, grid, dim3(kSimWaves * 64), kTiledLds, s, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (!a.use_resident) return hipSuccess;
+    auto res = similarity_resident_kernel<T, D>;
+    e = allow_dynamic_lds(res, kResLdsBytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(tiled, grid, dim3(kSimWaves * 64), kTiledLds, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (!a.use_resident) return hipSuccess;
-  auto res = similarity_resident_kernel<T, D>;
-  e = allow_dynamic_lds(res, kResLdsBytes);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
-  return hipGetLastError();
 }
 
 hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {
