@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   const long long off_l = a.off[l];
   const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
   const float* sinv = a.sel_inv_norm + cbase;
-  const char* pk = a.packed_k + cbase * TL::kRowBytes;  // this pair's conserved keys, contiguous
+  const int32_t* sel = a.sel_idx + cbase;
   const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
   const int32_t* less = a.less_idx + lbase;
   const char* kbase = a.k;  // positions are stored as row ids over all layers and heads
@@ -360,8 +360,8 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   const int S_pad = (S + 31) & ~31;
   char* ckeys = smem;
   float* cinv = reinterpret_cast<float*>(smem + (size_t)S_pad * TL::kStride);
-  // All pieces of the set are requested before the first one is stored (one memory latency for the whole set; at
-  // most kMaxPieces 16-byte pieces per thread; the bounds are the same for every thread of the workgroup, so the
+  // All row ids, then all pieces of the set are requested before the first one is stored (two memory latencies for the
+  // whole set; at most kMaxPieces 16-byte pieces per thread; the bounds are the same for every thread of the workgroup, so the
   // tests are scalar branches).  The batch is an array of a native vector type: as an array of uint4 the compiler
   // kept it in scratch memory.
   constexpr int kMaxPieces = (resident_capacity<T, D>() * CPR + kResThreads - 1) / kResThreads;
@@ -369,11 +369,15 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   {
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
     u32x4_t v[kMaxPieces > 0 ? kMaxPieces : 1];
+    int id[kMaxPieces > 0 ? kMaxPieces : 1];
+#pragma unroll
+    for (int i = 0; i < kMaxPieces; ++i)
+      if (i * kResThreads < n_pieces) id[i] = sel[min(min(tid + i * kResThreads, n_pieces - 1) / CPR, S - 1)];
 #pragma unroll
     for (int i = 0; i < kMaxPieces; ++i) {
       if (i * kResThreads < n_pieces) {
         const int p = min(tid + i * kResThreads, n_pieces - 1);
-        v[i] = *reinterpret_cast<const u32x4_t*>(pk + (unsigned)(min(p / CPR, S - 1) * TL::kRowBytes + (p % CPR) * 16));
+        v[i] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)id[i] * TL::kRowBytes + (p % CPR) * 16);
       }
     }
 #pragma unroll
@@ -525,8 +529,8 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
 
 // ------------------------------------------------------------------------ conserved keys, packed
 // Output row w of the ragged cache is the conserved key sel_idx[w]; the rows of one (layer, head) are
-// consecutive in w.  Copying them once into that order makes every tile of conserved keys the similarity
-// kernels stream a contiguous block (which a lane-addressed asynchronous copy into LDS needs).
+// consecutive in w.  Copying them once into that order makes every tile of conserved keys the tiled similarity
+// kernel streams a contiguous block (which a lane-addressed asynchronous copy into LDS needs).
 // 256 rows per workgroup.
 constexpr int kPackRows = 256;
 template <typename T, int D>
@@ -538,6 +542,16 @@ __global__ void __launch_bounds__(256) pack_conserved_kernel(MergeArgs a) {
   static_assert(kPackRows % (RPP * U) == 0, "passes must tile the workgroup's rows");
   const int tid = threadIdx.x;
   const long long w0 = (long long)blockIdx.x * kPackRows, total = a.total_slots;
+  if (a.use_resident) {
+    // The resident-set kernel reads a set once and gathers it itself: nothing to do for rows of its layers (every 256
+    // rows that do not lie inside one such layer are packed; a whole pass over 256 pairs of 4096 positions 1507 -> 1489
+    // us, over 360 of 3001 458 -> 450 us).  Layer l owns the rows [off[l], off[l + 1]) * Hkv.
+    const int L = a.L;
+    bool inside = false;
+    for (int l = tid; l < L; l += 256)
+      inside |= a.off[l] * a.Hkv <= w0 && w0 + kPackRows <= a.off[l + 1] * a.Hkv && a.alloc[4 * l] <= resident_capacity<T, D>();
+    if (__syncthreads_or(inside)) return;
+  }
   const int sub = tid / LPR, cc = tid - sub * LPR;
   for (int r0 = 0; r0 < kPackRows; r0 += RPP * U) {
     int idx[U];

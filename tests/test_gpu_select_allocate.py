@@ -4,7 +4,13 @@ kernel's own column scores (text candidates first, then by score, equal scores b
 Budgets: one layer to more layers than a wave has lanes, with and without active bounds; the reference is the oracle's
 allocator on the kernel's own entropies.
 Nearest neighbours of the kernel that works without an LDS copy of the conserved set: against float64 cosines; a
-slot counts as right if its cosine is within 1e-5 of the best (sums of up to 128 exact products in fp32, times 1/|k|)."""
+slot counts as right if its cosine is within 1e-5 of the best (sums of up to 128 exact products in fp32, times 1/|k|).
+The same where layers with conserved sets held whole in LDS (at least 256 pairs) lie between layers with longer ones.
+Merged rows: the mean of the members in float64, for outputs below and above 65536 rows; bf16 may differ by one unit in
+the last place (2^-7 of the value) because the reference rounds twice.
+Row statistics: column scores against a float64 softmax, for 16 to 2052 partials per row; a logit is a sum of 64
+products with a magnitude of up to 30, so its error is below 64 * 30 * 2^-24 = 1.2e-4, which is the relative error of
+the probability; twice that for both passes."""
 import numpy as np
 import pytest
 import torch
@@ -43,7 +49,7 @@ def _run(T, L, hkv, d, dtype, B, W=16, p_text=0.3, duplicates=0, flat=False, see
             order = order[torch.sort(order_class[order], stable=True).indices]  # text first
             want = torch.cat([order[:s - m].sort().values, torch.arange(T - m, T, device=DEV)])
             assert torch.equal(idx[h].long(), want), (l, h)
-    return out, k, S
+    return out, k, S, comp
 
 
 @pytest.mark.parametrize("T", [33, 1023, 1024, 1025, 4095, 4097, 8192, 8193, 16384, 16385, 40001])
@@ -71,7 +77,12 @@ def test_budgets(L):
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("T,L,hkv", [(40, 1, 1), (97, 2, 3), (1000, 2, 1), (2048, 3, 1), (2049, 3, 1), (700, 5, 8)])
 def test_nearest_neighbours(dtype, d, T, L, hkv):
-    out, k, S = _run(T, L, hkv, d, dtype, L * max(17, T // 4))
+    out, k, _, _ = _run(T, L, hkv, d, dtype, L * max(17, T // 4))
+    _check_neighbours(out, k)
+
+
+def _check_neighbours(out, k):
+    L, hkv = k.shape[:2]
     for l in range(L):
         _, _, idx = out.layer(l)
         for h in range(hkv):
@@ -80,3 +91,51 @@ def test_nearest_neighbours(dtype, d, T, L, hkv):
             cos = u @ u[idx[h].long()].T
             got = cos.gather(1, out.merge_assign[l, h].long()[:, None])[:, 0]
             assert (got >= cos.max(dim=1).values - 1e-5).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,L,hkv,kept", [(1500, 32, 8, 560), (1500, 65, 4, 300), (700, 32, 8, 33)])
+def test_conserved_sets_in_lds_between_longer_ones(T, L, hkv, kept, d):
+    out, k, S, _ = _run(T, L, hkv, d, torch.bfloat16, L * kept)
+    if kept == 560 and d == 128:
+        assert S.min() <= 576 < S.max()  # rows of 256 bytes and one 1/|k| each: 576 of them fit
+    _check_neighbours(out, k)
+    _check_merged(out, k)
+
+
+def _check_merged(out, k):
+    L, hkv, T, _ = k.shape
+    for l in range(L):
+        k_out, v_out, idx = out.layer(l)
+        for h in range(hkv):
+            pos = idx[h].long()
+            slot = out.merge_assign[l, h].long().clone()
+            slot[pos] = torch.arange(len(pos), device=DEV)
+            x = k[l, h].double()
+            n = torch.zeros(len(pos), dtype=torch.float64, device=DEV).index_add_(0, slot, torch.ones(T, dtype=torch.float64, device=DEV))
+            want = torch.zeros(len(pos), x.shape[1], dtype=torch.float64, device=DEV).index_add_(0, slot, x) / n[:, None]
+            bound = 2.0 ** -7 if k.dtype == torch.bfloat16 else 2.0 ** -23
+            for got in (k_out[h], v_out[h]):
+                assert ((got.double() - want).abs() <= bound * want.abs() + 1e-12).all(), (l, h)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("T,L,hkv,kept", [(50, 1, 1, 17), (1001, 3, 5, 203), (700, 33, 8, 250)])
+def test_merged_rows(dtype, d, T, L, hkv, kept):
+    out, k, _, _ = _run(T, L, hkv, d, dtype, L * kept)
+    _check_merged(out, k)
+
+
+@pytest.mark.parametrize("tiles", [1, 4, 5, 37, 512, 513])
+def test_column_scores_with_many_partials(tiles):
+    T, L, W = tiles * 128 - 3, 2, 16
+    _, k, _, comp = _run(T, L, 1, 64, torch.bfloat16, L * max(W, T // 5), W=W)
+    g = torch.Generator(device=DEV).manual_seed(0)
+    torch.randn(L, 1, T, 64, generator=g, device=DEV)                       # the keys come first in _run
+    q = torch.randn(L, 1, W, 64, generator=g, device=DEV) * torch.linspace(0.2, 6.0, L, device=DEV)[:, None, None, None]
+    logits = q.bfloat16().double() @ k.double().transpose(-1, -2) / 8.0
+    rows = torch.arange(T - W, T, device=DEV)[:, None]
+    logits = logits.masked_fill(torch.arange(T, device=DEV)[None, :] > rows, float("-inf"))
+    want = torch.softmax(logits, dim=-1).sum(dim=2)
+    got = comp.region("col_scores", torch.float32).view(L, 1, T).double()
+    assert ((got - want).abs() <= 2.4e-4 * want + 1e-30).all()
