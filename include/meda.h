@@ -148,7 +148,8 @@ const char* meda_status_string(meda_status status);
  * for every layer and query head, out = Softmax(q K^T * scale) V over the rows the compression pass
  * kept for that layer (the ragged layout meda_compress writes: layer l holds [Hkv][S_l][d] from row
  * layer_off[l] * Hkv) followed by the rows appended since then, K = [K, k_t], V = [V, v_t].  Query
- * head h reads kv head h / (Hq/Hkv).  The order of the rows has no influence on the result.
+ * head h reads kv head h / (Hq/Hkv).  The order of the rows has no influence on the result beyond its rounding.
+ * A value of +-inf in a row whose weight does not underflow gives +-inf in its column of out.
  */
 typedef struct {
   int32_t n_layers;     /* L                                                                        */

@@ -341,6 +341,7 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
         z1 += p1;
         float p[GP], vf[E];
         row_all_gather<GP, LPR>(p1, p, cc);
+        if (r0 + U * kDecWaves * MS > r_end && !ok[u]) vv[u] = make_uint4(0, 0, 0, 0);  // the last row may hold an infinity
         unpack4(vv[u], vf);
 #pragma unroll
         for (int h = 0; h < GP; ++h)
@@ -392,11 +393,14 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
 // rows (keys) of the chunk.
 //   logits  D[key][col] = sum_d K[key][d] Q[col][d]     2 x d/32 x v_mfma_f32_16x16x32_bf16 (exact products, fp32 sums)
 //   output  O[row][col] += sum_key P[row][key] V[key][col]   d/16 x v_mfma_f32_16x16x32_bf16
-// The softmax weights are not rounded: a weight p in fp32 is the exact sum of three bf16 numbers (the upper 8, the
-// next 8 and the last 8 significant bits), and the second product takes the three parts as rows of its own, which
+// The softmax weights are not rounded: a weight p in fp32 is the exact sum of three bf16 numbers (8 significant bits
+// each), and the second product takes the three parts as rows of its own, which
 // the 16 rows of the instruction have room for: column c of the first product is query head c % GP, so lane column c
 // holds the weights of that head and passes on part c / GP (GP heads, rounded up to a power of two).  Groups of 5 to
-// 8 heads fill the 16 rows with two parts and take a second instruction for the third.
+// 8 heads fill the 16 rows with two parts and take a second instruction for the third, half of it in each.
+// Infinite values: the parts of a weight that is not zero are none of them zero (0 * inf would be NaN, see
+// weight_part) and rows past the end count as zeros, so a value of +-inf under a nonzero weight gives +-inf, as the
+// definition does.
 //
 // Lane (c, g) = (l % 16, l / 16).  First product: it holds, for every k-step, 8 elements of key c (and 16 + c) and the
 // same 8 of query head c % GP (any assignment of elements to (lane group, step) gives the same sum: step k takes
@@ -441,6 +445,12 @@ __device__ __forceinline__ float group_sum(float v) {
   v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
   const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// The upper part of a positive weight: the largest bf16 number BELOW it (0 for 0).  What remains is then exact and
+// never zero: after two parts it has 8 significant bits or less.
+__device__ __forceinline__ float weight_part(float w) {
+  return __uint_as_float(__builtin_elementwise_sub_sat(__float_as_uint(w), 1u) & 0xffff0000u);
 }
 
 // N bytes of a row that is read once, as dwords (see load16_stream)
@@ -524,7 +534,7 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
       for (int i = 0; i < 4; ++i) t[4 * b + i] = s4[i];
     }
   };
-  auto finish = [&](const Rows& rows, int r0, float (&t)[8]) {
+  auto finish = [&](Rows& rows, int r0, float (&t)[8]) {
     float bm = kNegBig;
     float sk[8], sv[8];
     if constexpr (FP8) {
@@ -535,7 +545,12 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
     for (int e = 0; e < 8; ++e) t[e] *= FP8 ? sk[e] : scale_log2;
     if (r0 + kStep > r_end) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = (r0 + 16 * (e >> 2) + 4 * g + (e & 3) < r_end) ? t[e] : kNegBig;
+      for (int e = 0; e < 8; ++e) {
+        const bool in = r0 + 16 * (e >> 2) + 4 * g + (e & 3) < r_end;
+        t[e] = in ? t[e] : kNegBig;
+#pragma unroll
+        for (uint32_t& x : rows.v[e]) x = in ? x : 0u;  // the last row, which they repeat, may hold an infinity
+      }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) bm = fmaxf(bm, t[e]);
@@ -552,7 +567,7 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
         for (int j = 0; j < PE; ++j) st.acc[j][r] *= cr;
       }
     }
-    // the weights, their parts as packed bf16 (parts past the third do not exist: zeros)
+    // the weights, their parts as packed bf16 (rows past the third part repeat it and are dropped)
     uint32_t pa[4], pl[4];
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
@@ -560,16 +575,20 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         float p = __builtin_amdgcn_exp2f(t[e + u] - st.m_run);
-        if (r0 + kStep > r_end) p = (r0 + 16 * ((e + u) >> 2) + 4 * g + ((e + u) & 3) < r_end) ? p : 0.f;
+        float w = FP8 ? fmaf(p, sv[e + u], 0.f) : p;  // the sum takes the sign of a zero
+        if (r0 + kStep > r_end) {
+          const bool in = r0 + 16 * ((e + u) >> 2) + 4 * g + ((e + u) & 3) < r_end;
+          p = in ? p : 0.f;
+          w = in ? w : 0.f;
+        }
         st.z_run += p;
-        const float w = FP8 ? p * sv[e + u] : p;
-        const float hi = __uint_as_float(__float_as_uint(w) & 0xffff0000u), r1 = w - hi;
-        const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u), lo = r1 - mid;
+        const float hi = weight_part(w), r1 = w - hi;
+        const float mid = weight_part(r1), lo = r1 - mid;
         if constexpr (GP == 8) {
           x[u] = __float_as_uint(part == 0 ? hi : mid);
-          y[u] = __float_as_uint(part == 0 ? lo : 0.f);
+          y[u] = __float_as_uint(0.5f * lo);
         } else {
-          x[u] = __float_as_uint(part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : 0.f)));
+          x[u] = __float_as_uint(part == 0 ? hi : (part == 1 ? mid : lo));
           y[u] = 0u;
         }
       }
@@ -683,22 +702,22 @@ __global__ void __launch_bounds__(kDecThreads, 3) decode_matrix_kernel(DecodeArg
 #pragma unroll
   for (int j = 0; j < PE; ++j) {
     float* dst = &red_o[wave][0][PE * c + j];
-    if constexpr (GP == 8) {  // rows 0..7: first and third part, rows 8..15: second part
+    if constexpr (GP == 8) {  // rows 0..7: first part and half of the third, rows 8..15: second part and the other half
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.acc[j][r]), __float_as_uint(st.acc[j][r]), false, false);
         if (grp < 2) dst[(4 * grp + r) * D] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
       }
-    } else if constexpr (GP == 4) {  // lane groups 0, 1, 2: the three parts, 3: zeros
+    } else if constexpr (GP == 4) {  // lane groups 0, 1, 2: the three parts; 3: dropped
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float s = group_sum(st.acc[j][r]);
+        const float s = group_sum(grp < 3 ? st.acc[j][r] : 0.f);
         if (grp == 0) dst[r * D] = s;
       }
     } else if constexpr (GP == 2) {  // rows 0, 1 | 2, 3 in group 0, rows 4, 5 in group 1
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const float s = group_sum(st.acc[j][h] + st.acc[j][2 + h]);
+        const float s = group_sum(grp == 0 ? st.acc[j][h] + st.acc[j][2 + h] : (grp == 1 ? st.acc[j][h] : 0.f));
         if (grp == 0) dst[h * D] = s;
       }
     } else {  // rows 0, 1, 2 in group 0
@@ -728,7 +747,7 @@ __global__ void __launch_bounds__(D) decode_combine_kernel(DecodeArgs a) {
       const float* p = a.part + ((size_t)id * a.Hq + h) * (D + 2);
       m[u] = (s0 + u < n) ? p[D] : kNegBig;
       z[u] = (s0 + u < n) ? p[D + 1] : 0.f;
-      o[u] = p[j];
+      o[u] = (s0 + u < n) ? p[j] : 0.f;
     }
     float top = mn;
 #pragma unroll
