@@ -747,7 +747,7 @@ __global__ void __launch_bounds__(D) decode_combine_kernel(DecodeArgs a) {
       const float* p = a.part + ((size_t)id * a.Hq + h) * (D + 2);
       m[u] = (s0 + u < n) ? p[D] : kNegBig;
       z[u] = (s0 + u < n) ? p[D + 1] : 0.f;
-      o[u] = (s0 + u < n) ? p[j] : 0.f;
+      o[u] = p[j];  // always: a load under a condition would wait for itself
     }
     float top = mn;
 #pragma unroll
@@ -757,9 +757,9 @@ __global__ void __launch_bounds__(D) decode_combine_kernel(DecodeArgs a) {
     os *= c0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float c = (s0 + u < n) ? __builtin_amdgcn_exp2f(m[u] - top) : 0.f;
+      const float c = __builtin_amdgcn_exp2f(m[u] - top);
       zs = fmaf(z[u], c, zs);
-      os = fmaf(o[u], c, os);
+      os = s0 + u < n ? fmaf(o[u], c, os) : os;
     }
     mn = top;
   }
