@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/meda.h"
 #include "device_utils.hpp"
@@ -76,13 +77,13 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
 __device__ __forceinline__ LayerChunks find_chunks(const DecodeArgs& a, int by_layer, int id) {
   const int lane = threadIdx.x & 63;
   LayerChunks out{-1, 0, 0, 0, 0};
-  for (int R = a.R;; R *= 2) {
+  for (unsigned R = a.R;; R = R < (1u << 30) ? 2u * R : 1u << 31) {  // 2^31: one chunk per layer, which always fits
     int total = 0;
     for (int base = 0; base < a.L; base += 64) {
       const int lc = min(base + lane, a.L - 1);
       const int s = (base + lane < a.L) ? a.layer_len[lc] : 0;
       const long long off = a.layer_off[lc];
-      const int n = base + lane < a.L ? max(1, (int)(((unsigned)s + (unsigned)R - 1u) / (unsigned)R)) : 0;
+      const int n = base + lane < a.L ? max(1, (int)(((unsigned)s + R - 1u) / R)) : 0;
       const int inc = wave_inclusive_sum(n);
       const int first = total + inc - n;
       const bool mine = by_layer >= 0 ? base + lane == by_layer : (id >= first && id < first + n);
@@ -98,7 +99,7 @@ __device__ __forceinline__ LayerChunks find_chunks(const DecodeArgs& a, int by_l
       }
       total += __builtin_amdgcn_readlane(inc, 63);
     }
-    if (total <= a.NC || R > (1 << 29)) return out;
+    if (total <= a.NC || R == 1u << 31) return out;
     out.layer = -1;
   }
 }
@@ -305,14 +306,17 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
 
   auto walk = [&](const char* k, const char* v, size_t row0, int r_end) {
     const char *kb = k + row0 * TL::kRowBytes + cc * 16, *vb = v + row0 * TL::kRowBytes + cc * 16;
-    for (int r0 = wave * MS; r0 < r_end; r0 += U * kDecWaves * MS) {
+    // TAIL: some of the rows lie past the end.  They repeat the last one with weight zero, and their values, among
+    // which an infinity can be, count as zeros.
+    auto step = [&](int r0, auto tail) {
+      constexpr bool TAIL = decltype(tail)::value;
       uint4 kv[U], vv[U];
       bool ok[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int r = r0 + u * kDecWaves * MS + sub;
-        ok[u] = r < r_end;
-        const size_t ro = (size_t)min(r, r_end - 1) * TL::kRowBytes;  // rows past the end repeat the last one
+        ok[u] = !TAIL || r < r_end;
+        const size_t ro = (size_t)(TAIL ? min(r, r_end - 1) : r) * TL::kRowBytes;
         kv[u] = load16_stream(kb + ro);
         vv[u] = load16_stream(vb + ro);
       }
@@ -341,14 +345,18 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
         z1 += p1;
         float p[GP], vf[E];
         row_all_gather<GP, LPR>(p1, p, cc);
-        if (r0 + U * kDecWaves * MS > r_end && !ok[u]) vv[u] = make_uint4(0, 0, 0, 0);  // the last row may hold an infinity
         unpack4(vv[u], vf);
+#pragma unroll
+        for (int e = 0; e < E; ++e) vf[e] = ok[u] ? vf[e] : 0.f;
 #pragma unroll
         for (int h = 0; h < GP; ++h)
 #pragma unroll
           for (int e = 0; e < E; ++e) o[h][e] = fmaf(p[h], vf[e], o[h][e]);
       }
-    }
+    };
+    int r0 = wave * MS;
+    for (; r0 + ((U - 1) * kDecWaves + 1) * MS <= r_end; r0 += U * kDecWaves * MS) step(r0, std::false_type());
+    if (r0 < r_end) step(r0, std::true_type());
   };
   if (ch.fresh) {
     walk(a.k_new, a.v_new, ch.row0 + g * ch.head, ch.rows);
@@ -495,29 +503,35 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
     float scale;
   };
   const float* sc = c < 8 ? ksc : vsc;
+  // A step's first row has a 64-bit offset (a chunk can be longer than 4 GiB), the same for the wave; inside a step the
+  // offsets are 32-bit.  Rows past the end repeat the last one (their weights are zero).
   auto load_keys = [&](Rows& t, int r0) {
+    const char* base = kb + (size_t)r0 * kRowBytes;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      // rows past the end repeat the last one (their weights are zero).  No streaming hint here: a load instruction
-      // takes half a cache line of every row (with the hint the line was fetched again for the other half: 5.3
-      // instead of 5.6 TB/s)
-      const unsigned ro = (unsigned)min(r0 + 16 * b + c, r_end - 1) * (unsigned)kRowBytes + (unsigned)(16 * g);
+      // No streaming hint here: a load instruction takes half a cache line of every row (with the hint the line was
+      // fetched again for the other half: 5.3 instead of 5.6 TB/s)
+      const unsigned ro = (unsigned)(min(16 * b + c, r_end - 1 - r0) * kRowBytes + 16 * g);
 #pragma unroll
       for (int k = 0; k < KL; ++k) {
-        const uint4 x = *reinterpret_cast<const uint4*>(kb + (ro + 64 * k));
+        const uint4 x = *reinterpret_cast<const uint4*>(base + ro + 64 * k);
         t.k[b][k][0] = x.x; t.k[b][k][1] = x.y; t.k[b][k][2] = x.z; t.k[b][k][3] = x.w;
       }
     }
   };
-  auto load_values = [&](Rows& t, int r0) {
+  auto load_values = [&](Rows& t, int r0, auto tail) {
+    constexpr bool TAIL = decltype(tail)::value;
+    const char* base = vb + (size_t)r0 * kRowBytes;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const unsigned ro = (unsigned)min(r0 + 16 * (e >> 2) + 4 * g + (e & 3), r_end - 1) * (unsigned)kRowBytes;
-      load_piece<PE * kEl>(vb + (ro + c * PE * kEl), t.v[e]);
+      const int row = 16 * (e >> 2) + 4 * g + (e & 3);
+      const unsigned ro = (unsigned)((TAIL ? min(row, r_end - 1 - r0) : row) * kRowBytes + c * PE * kEl);
+      load_piece<PE * kEl>(base + ro, t.v[e]);
     }
     // the scales of the 8 keys this row of 16 lanes has logits and weights for: lanes 0..7 the keys', 8..15 the
     // values', handed to the other lanes of the row by broadcasts
-    if constexpr (FP8) t.scale = sc[min(r0 + 16 * ((c >> 2) & 1) + 4 * g + (c & 3), r_end - 1)];
+    const int row = r0 + 16 * ((c >> 2) & 1) + 4 * g + (c & 3);
+    if constexpr (FP8) t.scale = sc[TAIL ? min(row, r_end - 1) : row];
   };
   auto logits = [&](const Rows& rows, float (&t)[8]) {
 #pragma unroll
@@ -534,7 +548,9 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
       for (int i = 0; i < 4; ++i) t[4 * b + i] = s4[i];
     }
   };
-  auto finish = [&](Rows& rows, int r0, float (&t)[8]) {
+  // TAIL: some of the step's rows lie past the end
+  auto finish = [&](Rows& rows, int r0, float (&t)[8], auto tail) {
+    constexpr bool TAIL = decltype(tail)::value;
     float bm = kNegBig;
     float sk[8], sv[8];
     if constexpr (FP8) {
@@ -543,7 +559,7 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) t[e] *= FP8 ? sk[e] : scale_log2;
-    if (r0 + kStep > r_end) {
+    if constexpr (TAIL) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const bool in = r0 + 16 * (e >> 2) + 4 * g + (e & 3) < r_end;
@@ -576,7 +592,7 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
       for (int u = 0; u < 2; ++u) {
         float p = __builtin_amdgcn_exp2f(t[e + u] - st.m_run);
         float w = FP8 ? fmaf(p, sv[e + u], 0.f) : p;  // the sum takes the sign of a zero
-        if (r0 + kStep > r_end) {
+        if constexpr (TAIL) {
           const bool in = r0 + 16 * ((e + u) >> 2) + 4 * g + ((e + u) & 3) < r_end;
           p = in ? p : 0.f;
           w = in ? w : 0.f;
@@ -626,22 +642,21 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
   if (r0 >= r_end) return;
   float t[8];
   Rows rows;
-  if constexpr (LEAN) {
-    for (; r0 < r_end; r0 += kStride) {
+  if constexpr (!LEAN) load_keys(rows, r0);
+  auto step = [&](auto tail) {
+    if constexpr (LEAN) {
       load_keys(rows, r0);
       logits(rows, t);
-      load_values(rows, r0);
-      finish(rows, r0, t);
-    }
-  } else {
-    load_keys(rows, r0);
-    for (; r0 < r_end; r0 += kStride) {
-      load_values(rows, r0);
+      load_values(rows, r0, tail);
+    } else {
+      load_values(rows, r0, tail);
       logits(rows, t);
       if (r0 + kStride < r_end) load_keys(rows, r0 + kStride);  // in flight while this step is finished
-      finish(rows, r0, t);
     }
-  }
+    finish(rows, r0, t, tail);
+  };
+  for (; r0 + kStep <= r_end; r0 += kStride) step(std::false_type());
+  if (r0 < r_end) step(std::true_type());
 }
 
 // Three waves per SIMD (145 registers with rows of 256 bytes; four spill, and took twice the time).

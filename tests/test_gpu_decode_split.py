@@ -77,3 +77,30 @@ def test_lengths_beyond_the_budget_of_the_launch():
 def test_rows_enough_for_chunks_of_several_hundred_rows():
     # 2 kv heads, 500000 rows: chunks of 384 rows at 1536 workgroups
     _case([120000, 70000, 33333, 26667], 8, 2, 64, torch.bfloat16, 0)
+
+
+@pytest.mark.parametrize("fp8,dtype,d,rows", [(False, torch.bfloat16, 128, 1 << 24), (True, torch.bfloat16, 128, 1 << 25),
+                                              (False, torch.float32, 64, 1 << 24)])
+def test_a_chunk_of_more_than_4_gib(fp8, dtype, d, rows):
+    # One layer sized for one row is one chunk: its rows from the 2^32nd byte on are the only ones with keys, values and a
+    # weight; rows read from anywhere else give zero.  The softmax over them is uniform: out = 1.
+    import paper_2502_17599_amd as pkg
+    print(f"\n[decode split] {rows} rows and 40 more, d={d} {dtype} fp8={fp8}", flush=True)
+    dev, tail = torch.device("cuda:0"), 40
+    el = torch.uint8 if fp8 else dtype
+    k, v = (torch.zeros(rows + tail, d, dtype=el, device=dev) for _ in range(2))
+    k[rows:] = 0x38 if fp8 else 1.0   # 0x38 is the code of 1
+    v[rows:] = 0x38 if fp8 else 1.0
+    q = torch.full((1, 1, d), 4.0, dtype=dtype, device=dev)       # logits of 4 sqrt(d): the others' weights vanish
+    s = torch.tensor([rows + tail], dtype=torch.int32, device=dev)
+    off = torch.tensor([0, rows + tail], dtype=torch.int64, device=dev)
+    p = pkg.make_decode_params(1, 1, 1, d, 1, dtype, 0)
+    dec = pkg.Decoder(p, dev)
+    if fp8:
+        ones = torch.ones(rows + tail, device=dev)
+        out = dec.fp8(q, k, v, ones, ones, s, off)
+    else:
+        out = dec(q, k, v, s, off)
+    torch.cuda.synchronize()
+    # the 2^24 and more other rows weigh exp(-4 sqrt(d)) each: 2^25 * exp(-45.2) and 2^24 * exp(-32) over 40 rows
+    assert (out.float() - 1).abs().max() < 1e-6 + (2.0 ** -8 if dtype == torch.bfloat16 else 0.0)
