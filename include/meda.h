@@ -162,7 +162,8 @@ typedef struct {
   float softmax_scale;  /* 0 -> 1/sqrt(head_dim)                                                    */
 } meda_decode_params;
 
-/* Bytes of workspace meda_decode_attention needs (multiple of 256); 0 if the parameters are invalid. */
+/* Bytes of workspace meda_decode_attention needs (multiple of 256); 0 if the parameters are invalid.  Never less for a
+ * larger total_budget or n_new, all else equal: a workspace for the largest step serves every smaller one. */
 size_t meda_decode_workspace_bytes(const meda_decode_params* params);
 
 /*

@@ -53,8 +53,8 @@ struct DecodeArgs {
 };
 
 // The chunks of the cached rows are numbered layer after layer: layer l has ceil(S_l / R) of them, at least one.  The host sizes
-// the launch for NC = floor(B / R) + L ids, which bounds their number for S_1 + .. + S_L <= B; should the lengths
-// exceed B, R is doubled until they fit (every workgroup computes the same R).  Evaluated by every wave on its own:
+// the launch for NC ids, at least floor(B / R) + L in general, which bounds their number for S_1 + .. + S_L <= B; should
+// the lengths exceed B, R is doubled until they fit (every workgroup computes the same R).  Evaluated by every wave on its own:
 // lane i holds layer base + i.
 struct LayerChunks {
   int layer;      // the layer asked for, or the one that owns the chunk id asked for (-1: id past the last chunk)
@@ -801,21 +801,43 @@ static meda_status make_decode_plan(const meda_decode_params* p, DecodePlan* pl)
   pl->L = p->n_layers; pl->Hq = p->n_q_heads; pl->Hkv = p->n_kv_heads; pl->G = G; pl->d = p->head_dim;
   pl->GP = G <= 1 ? 1 : (G <= 2 ? 2 : (G <= 4 ? 4 : 8));
   pl->dtype = p->dtype; pl->n_new = p->n_new;
-  int64_t rows = p->total_budget * p->n_kv_heads / kDecTargetGroups;
+  // lengths are 32-bit, so a larger budget bounds nothing more
+  const int64_t L = pl->L, most = L * INT32_MAX, B = p->total_budget < most ? p->total_budget : most;
+  int64_t rows = (B * pl->Hkv + kDecTargetGroups - 1) / kDecTargetGroups;
   rows = (rows + 127) / 128 * 128;
   rows = rows < kDecMinRows ? kDecMinRows : (rows > kDecMaxRows ? kDecMaxRows : rows);
   // at most kDecMaxSplit chunks per layer on average (the chunk partials are workspace)
-  const int64_t least = p->total_budget / ((int64_t)(kDecMaxSplit - 1) * p->n_layers) + 1;
+  const int64_t least = B / ((kDecMaxSplit - 1) * L) + 1;
   if (rows < least) rows = least;
-  if (rows > (1 << 28)) return MEDA_ERR_UNSUPPORTED;
+  // The workspace is sized so that one for a larger budget and more appended rows always serves a smaller step: for
+  // `extra` chunks beyond one per layer, the most that any budget up to B is cut into, and for the appended rows in
+  // chunks of the least size.
+  const int64_t extra_small = B / kDecMinRows, extra_mid = kDecTargetGroups / pl->Hkv, extra_large = B / kDecMaxRows;
+  int64_t extra = extra_small < extra_mid ? extra_small : extra_mid;
+  extra = extra > extra_large ? extra : extra_large;
+  extra = extra < (kDecMaxSplit - 1) * L ? extra : (kDecMaxSplit - 1) * L;
+  const bool own = p->n_new > kDecInlineNew;  // the appended rows have chunks of their own
+  int64_t new_chunks = own ? ((int64_t)p->n_new + kDecMinRows - 1) / kDecMinRows : 0;
+  new_chunks = new_chunks < kDecMaxSplit ? new_chunks : kDecMaxSplit;
+  // Where every layer cut into equally many chunks of 128 rows per query head of the group (up to 4) at the average
+  // length fits the built-in scratch array, the chunks are made long enough to fit it too.
+  const int even_rows = kDecMinRows * (pl->GP < 4 ? pl->GP : 4);
+  int64_t even = (B / L + even_rows - 1) / even_rows;
+  even = even < kDecMaxSplit ? even : kDecMaxSplit;
+  const int64_t partial_bytes = (int64_t)pl->Hq * (pl->d + 2) * (int64_t)sizeof(float);
+  const int64_t room = (int64_t)MEDA_DECODE_NOALLOC_MAX_BYTES / partial_bytes, least_chunks = L * (1 + new_chunks);
+  if (L * (even + new_chunks) <= room && least_chunks + extra > room) {
+    extra = room - least_chunks;
+    if (rows < B / (extra + 1) + 1) rows = B / (extra + 1) + 1;
+  }
+  if (rows > 1 << 30) rows = 1 << 30;  // find_chunks goes on from there
   pl->R = (int)rows;
-  pl->NC = (int)(p->total_budget / rows) + p->n_layers;
-  const int64_t nsn = p->n_new <= kDecInlineNew ? 0 : ((int64_t)p->n_new + rows - 1) / rows;
-  pl->NSN = (int)(nsn > kDecMaxSplit ? kDecMaxSplit : nsn);
+  pl->NC = (int)(L + (B / rows < extra ? B / rows : extra));
+  const int64_t nsn = own ? ((int64_t)p->n_new + rows - 1) / rows : 0;
+  pl->NSN = (int)(nsn < kDecMaxSplit ? nsn : kDecMaxSplit);
+  pl->ws_bytes = (size_t)(((least_chunks + extra) * partial_bytes + 255) / 256 * 256);
   const double scale = p->softmax_scale > 0.0f ? (double)p->softmax_scale : 1.0 / sqrt((double)p->head_dim);
   pl->scale_log2 = (float)(scale * 1.4426950408889634074);
-  const size_t chunks = (size_t)pl->NC + (size_t)pl->L * pl->NSN;
-  pl->ws_bytes = (chunks * pl->Hq * (pl->d + 2) * sizeof(float) + 255) / 256 * 256;
   return MEDA_OK;
 }
 

@@ -104,3 +104,24 @@ def test_a_chunk_of_more_than_4_gib(fp8, dtype, d, rows):
     torch.cuda.synchronize()
     # the 2^24 and more other rows weigh exp(-4 sqrt(d)) each: 2^25 * exp(-45.2) and 2^24 * exp(-32) over 40 rows
     assert (out.float() - 1).abs().max() < 1e-6 + (2.0 ** -8 if dtype == torch.bfloat16 else 0.0)
+
+
+def test_chunks_made_longer_to_fit_the_built_in_scratch():
+    # 150 layers, 512 query heads: 157 partials per head fit, 174 would be cut without that bound.  The entry point without
+    # a workspace gives the same bits.
+    import paper_2502_17599_amd as pkg
+    lens = [200 if l % 9 == 0 else 10 + l % 7 for l in range(150)]
+    p = pkg.make_decode_params(150, 512, 64, 128, sum(lens), torch.bfloat16, 0)
+    assert pkg.DECODE_NOALLOC_MAX_BYTES - 512 * 130 * 4 < pkg.meda_decode_workspace_bytes(p) <= pkg.DECODE_NOALLOC_MAX_BYTES
+    _case(lens, 512, 64, 128, torch.bfloat16, 0)
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(0)
+    k, v = (torch.randn(sum(lens) * 64, 128, generator=g, device=dev).bfloat16() for _ in range(2))
+    q = torch.randn(150, 512, 128, generator=g, device=dev).bfloat16()
+    s = torch.tensor(lens, dtype=torch.int32, device=dev)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64, device=dev)
+    out = pkg.Decoder(p, dev)(q, k, v, s, off).clone()
+    got = torch.empty_like(out)
+    pkg.meda_decode_attention_noalloc(p, q, k, v, s, off, got)
+    torch.cuda.synchronize()
+    assert torch.equal(out, got)
