@@ -485,7 +485,12 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
     frag_load(cn, a.k + (size_t)id1 * TL::kRowBytes, kg);
     const int id2 = sel[slot_of(b + 2 * NW)];
     const float iv2 = sinv[slot_of(b + 2 * NW)];
-    if (kg == 0) inv_lds[wave][par][n] = iv0;  // this wave's own copy: LDS operations of a wave stay in order
+    // This wave's own copy: its LDS operations stay in order in hardware, and the fences (no instructions at this scope)
+    // keep the compiler from moving the loads, which other lanes' stores feed, before them.
+    if (kg == 0) inv_lds[wave][par][n] = iv0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     float iv[16];
     load_inv(iv, &inv_lds[wave][par][kg * 4]);
     f32x16_t acc[F];
