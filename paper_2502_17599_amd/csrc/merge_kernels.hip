@@ -38,9 +38,9 @@ __device__ __forceinline__ size_t less_base_of(int l, int g, int T, int Hkv, lon
 }
 
 // ------------------------------------------------------------------------ similarity + argmax
-// Layers whose conserved set fits into LDS go to the resident-set kernel (one workgroup of 8 waves per
-// (layer, head) part, all 160 KB of LDS), the others to the tiled kernel; both are launched and every
-// workgroup looks up its layer's budget.
+// Small problems go to the direct kernel (direct_pays).  Of the others, bf16 layers whose conserved set fits into LDS go
+// to the resident-set kernel (one workgroup of 8 waves per (layer, head) part, all 160 KB of LDS), the rest to the tiled
+// kernel; both are launched and every workgroup looks up its layer's budget.
 constexpr int kResWaves = 8;
 constexpr int kResThreads = kResWaves * 64;
 constexpr int kResLdsBytes = 160 * 1024;
@@ -50,8 +50,7 @@ constexpr int kResSplit = 1;  // 2 and 3 parts per pair (more, shorter workgroup
 // conserved keys (a multiple of 32) that fit: one padded row and one 1/|k| each
 template <typename T, int D>
 constexpr int resident_capacity() {
-  // rows above 256 bytes would need more registers per wave than eight waves per CU leave
-  return Tile<T, D>::kRowBytes > 256 ? 0 : kResLdsBytes / (Tile<T, D>::kStride + 4) / 32 * 32;
+  return kResLdsBytes / (Tile<T, D>::kStride + 4) / 32 * 32;
 }
 
 // u_ij = (k_i . k_j)/(|k_i| |k_j|): the raw keys are multiplied (bf16 products are exact in the fp32
@@ -368,8 +367,8 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   const int n_pieces = S_pad * CPR;
   {
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-    u32x4_t v[kMaxPieces > 0 ? kMaxPieces : 1];
-    int id[kMaxPieces > 0 ? kMaxPieces : 1];
+    u32x4_t v[kMaxPieces];
+    int id[kMaxPieces];
 #pragma unroll
     for (int i = 0; i < kMaxPieces; ++i)
       if (i * kResThreads < n_pieces) id[i] = sel[min(min(tid + i * kResThreads, n_pieces - 1) / CPR, S - 1)];
@@ -432,10 +431,9 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
 // Direct kernel: no conserved set in LDS, no packed copy.  grid over (row block of 32 F, kv head, layer), XCD-aware
 // as the tiled kernel; the NW waves of a workgroup take the same 32 F rows and every NW-th block of 32 conserved keys,
 // whose fragments come from the key cache itself (L2), one block ahead; the waves' bests are merged at the end.
-// For fp32 keys, whose matrix instructions are sixteen times slower than bf16's per byte, so that the loads hide
-// behind them (256 pairs of 1024 positions: 110 us, against 105 for one workgroup per pair with its set in LDS plus
-// 16 for packing the set and an empty launch), and for problems that leave CUs empty with 256 rows per workgroup, where
-// the serial chain of one wave bounds the kernel (8 pairs of 1024 positions, fp32: 27 + 6 us for packing -> 9.6 us).
+// For problems that leave CUs empty with 256 rows per workgroup, where the serial chain of one wave bounds the kernel
+// (8 pairs of 1024 positions, fp32: 27 + 6 us for packing -> 9.6 us).  Every 32 F rows read the whole set again, eight
+// (four) times as often as in the tiled kernel, so with the chip full it loses: see direct_pays.
 template <typename T, int D, int F, int NW>
 __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs a) {
   using TL = Tile<T, D>;
@@ -1050,11 +1048,31 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   return a;
 }
 
-// The direct kernel takes fp32 keys, and short bf16 prompts whose tiled launch would leave most CUs empty: 16 pairs of
-// 500 positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000 53 ->
-// 120 us (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
+// Which problems go to the direct kernel.  bf16: short prompts whose tiled launch would leave most CUs empty: 16 pairs
+// of 500 positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000
+// 53 -> 120 us (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
+// fp32: a workgroup of the tiled kernel walks the whole conserved set, so the longer that is, the more workgroups it
+// takes to beat the direct kernel: the line lies at a number of positions over all pairs that grows with the share
+// kept, at a length that does too, and below the number of pairs from which even one row block each fills the chip.
+// Direct / tiled (with packing) in us, equal budgets, in brackets budgets as uneven as entropies make them:
+//                    a tenth kept                                       three tenths kept
+// rows of 256 bytes  64 pairs of 1024   26 /  27  (24 /  43)            64 pairs of 3072  197 / 244  (110 / 243)
+//                    256 of 1024        75 /  60  (69 /  62)            256 of 2048       352 / 354  (278 / 269)
+// rows of 512 bytes  32 of 1024         32 /  44  (34 /  82)            48 of 2048        195 / 205  (118 / 261)
+//                    128 of 512         48 /  38  (48 /  46)            128 of 2048       506 / 384  (360 / 283)
+// and one pair of 8192 positions, a tenth kept, 108 / 73 (rows of 256 bytes); over 1394 shapes the rule costs
+// 1.1 % against the better one of the two, the direct kernel everywhere 12 %, the tiled one everywhere 48 %.
 constexpr unsigned kSimDirectGroups = 96;
 constexpr int kSimDirectPositions = 2048;
+
+template <typename T, int D>
+static bool direct_pays(const Plan& p, unsigned pairs) {
+  if (sizeof(T) == 2) return pairs * ((p.T + kSimRows - 1) / kSimRows) <= kSimDirectGroups && p.T <= kSimDirectPositions;
+  const double positions = (double)pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
+  const bool few = pairs <= (D == 64 ? 256u : 96u) || positions <= (D == 64 ? 163840.0 : 49152.0);
+  const double longest = (pairs == 1 ? 4.1e4 : D == 64 ? 1.64e5 : 6.15e4) * kept;
+  return few && positions <= (D == 64 ? 1.5e6 : 5e5) * kept && p.T <= longest && p.T <= 16384;
+}
 
 template <typename T, int D, int F, int NW>
 static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStream_t s) {
@@ -1066,35 +1084,38 @@ static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStrea
 template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
-  if constexpr (sizeof(T) == 4) {
+  if (direct_pays<T, D>(p, pairs)) {
     // two fragments per wave halve the key loads once there are enough workgroups of 64 rows for every CU
-    if (D == 64 && pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<T, D, (D == 64 ? 2 : 1), 4>(a, pairs, s);
+    if constexpr (sizeof(T) == 4 && D == 64)
+      if (pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<T, D, 2, 4>(a, pairs, s);
     return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
-  } else {
-    if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
-    // one resident-set workgroup occupies a whole CU: only worth it with at least one per CU
-    a.use_resident = pairs >= 256u ? 1 : 0;
-    hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
-                       dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
+  }
+  // One resident-set workgroup occupies a whole CU: only worth it with at least one per CU.  bf16 only: with the sixteen
+  // times slower fp32 instructions a workgroup with a long set outlives the others (256 pairs of 2048, a tenth kept
+  // under uneven budgets: 218 us against 150 tiled; 1024 pairs 492 against 545).
+  a.use_resident = sizeof(T) == 2 && pairs >= 256u ? 1 : 0;
+  hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
+                     dim3(256), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  dim3 grid(8u * nrb * ((pairs + 7u) / 8u));
+  constexpr int kTiledLds = sim_tiled_lds_bytes<T, D>();
+  auto tiled = similarity_argmax_kernel<T, D>;
+  if (kTiledLds > 64 * 1024) {
+    e = allow_dynamic_lds(tiled, kTiledLds);
     if (e != hipSuccess) return e;
-    dim3 grid(8u * nrb * ((pairs + 7u) / 8u));
-    constexpr int kTiledLds = sim_tiled_lds_bytes<T, D>();
-    auto tiled = similarity_argmax_kernel<T, D>;
-    if (kTiledLds > 64 * 1024) {
-      e = allow_dynamic_lds(tiled, kTiledLds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(tiled, grid, dim3(kSimWaves * 64), kTiledLds, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (!a.use_resident) return hipSuccess;
+  }
+  hipLaunchKernelGGL(tiled, grid, dim3(kSimWaves * 64), kTiledLds, s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess || !a.use_resident) return e;
+  if constexpr (sizeof(T) == 2) {
     auto res = similarity_resident_kernel<T, D>;
     e = allow_dynamic_lds(res, kResLdsBytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
-    return hipGetLastError();
+    e = hipGetLastError();
   }
+  return e;
 }
 
 hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {

@@ -81,6 +81,15 @@ def test_nearest_neighbours(dtype, d, T, L, hkv):
     _check_neighbours(out, k)
 
 
+# fp32 keys of enough pairs that 256 rows per workgroup fill the chip: the tiled kernel
+@pytest.mark.parametrize("d,T,L,hkv,kept", [(64, 1500, 32, 8, 150), (64, 701, 33, 9, 97), (64, 257, 40, 16, 50), (128, 1500, 16, 8, 300),
+                                            (128, 385, 13, 11, 40), (128, 6500, 3, 2, 1300)])
+def test_nearest_neighbours_of_many_fp32_pairs(d, T, L, hkv, kept):
+    out, k, _, _ = _run(T, L, hkv, d, torch.float32, L * kept)
+    _check_neighbours(out, k)
+    _check_merged(out, k)
+
+
 def _check_neighbours(out, k):
     L, hkv = k.shape[:2]
     for l in range(L):
