@@ -90,6 +90,55 @@ def test_nearest_neighbours_of_many_fp32_pairs(d, T, L, hkv, kept):
     _check_merged(out, k)
 
 
+# Ties: one key stands at four conserved positions more than 32 slots apart (different blocks, and different waves of the
+# kernels whose waves share the blocks) and at five dropped ones, which have to go to the lowest of the four slots.
+# Kept are exactly the text positions and the window (uniform budgets, no recent part), so the slots are known.
+@pytest.mark.parametrize("dtype,d,T,L,hkv,kept", [
+    (torch.float32, 64, 1000, 2, 2, 300),       # direct, one fragment per wave
+    (torch.float32, 64, 1000, 8, 8, 300),       # direct, two
+    (torch.float32, 128, 1000, 2, 2, 300),      # direct
+    (torch.float32, 64, 600, 32, 16, 200),      # tiled
+    (torch.float32, 128, 600, 16, 8, 200),
+    (torch.bfloat16, 64, 1000, 2, 2, 300),      # direct
+    (torch.bfloat16, 128, 1000, 2, 2, 300),
+    (torch.bfloat16, 64, 1000, 8, 8, 300),      # tiled
+    (torch.bfloat16, 128, 1000, 8, 8, 300),
+    (torch.bfloat16, 64, 600, 32, 8, 200),      # the whole set in LDS
+    (torch.bfloat16, 128, 600, 32, 8, 200)])
+def test_equal_keys_go_to_the_lowest_slot(dtype, d, T, L, hkv, kept):
+    import paper_2502_17599_amd as pkg
+    print(f"\n[ties] {dtype} d={d} T={T} L={L} Hkv={hkv} kept={kept}", flush=True)
+    W = 16
+    g = torch.Generator().manual_seed(d + L)
+    k = torch.randn(L, hkv, T, d, generator=g).to(dtype)
+    text = torch.randperm(T - W, generator=g)[:kept - W].sort().values    # slots 0 .. kept - W - 1
+    mask = torch.ones(T, dtype=torch.uint8)
+    mask[text] = 0
+    dropped = torch.tensor(sorted(set(range(T - W)) - set(text.tolist())))
+    lowest = torch.empty(L, hkv, dtype=torch.int64)
+    copies = torch.empty(L, hkv, 5, dtype=torch.int64)
+    for l in range(L):
+        for h in range(hkv):
+            first = int(torch.randint(0, kept - W - 3 * 50, (1,), generator=g))
+            slots = torch.tensor([first, first + 33, first + 83, first + 3 * 50 - 1])
+            copies[l, h] = dropped[torch.randperm(len(dropped), generator=g)[:5]]
+            key = torch.randn(d, generator=g).to(dtype)
+            k[l, h, text[slots]] = key
+            k[l, h, copies[l, h]] = key
+            lowest[l, h] = first
+    q = torch.randn(L, hkv, W, d, generator=g).to(dtype)
+    p = pkg.make_params(L, hkv, hkv, d, T, W, L * kept, dtype, 0, 1, flags=pkg.FLAG_UNIFORM_BUDGET)
+    comp = pkg.Compressor(p, DEV, want_merge_assign=True)
+    k = k.to(DEV)
+    out = comp(q.to(DEV), k, k.clone(), mask.to(DEV))
+    torch.cuda.synchronize()
+    for l in range(L):
+        _, _, idx = out.layer(l)
+        assert torch.equal(idx[:, :kept - W].cpu().long(), text.expand(hkv, -1))
+    got = out.merge_assign.cpu().long().gather(2, copies)
+    assert torch.equal(got, lowest[:, :, None].expand_as(got))
+
+
 def _check_neighbours(out, k):
     L, hkv = k.shape[:2]
     for l in range(L):
