@@ -203,19 +203,20 @@ struct SelectArgs {
 
 constexpr int kSelMaxThreads = 1024;
 constexpr int kSelMaxWaves = kSelMaxThreads / 64;
-constexpr int kSelBins = 2048;  // 11-bit digits
 
+template <int BITS>
 struct SelectShared {
-  int hist[2][kSelBins];      // text, vision (the later digits use the first half)
+  int hist[2][1 << BITS];     // text, vision (the later digits use the first half)
   int wsum[2][kSelMaxWaves];
   int bin, rest;
 };
 
 // The digit of the `want`-th largest key of a histogram (want >= 1, at most the histogram's total) and how many of
-// that digit's keys are still wanted.  Every thread takes kSelBins / threads adjacent bins, from the top.
-__device__ __forceinline__ void find_digit(SelectShared& sh, const int* hist, int want) {
+// that digit's keys are still wanted.  Every thread takes the same number of adjacent bins, from the top.
+template <int BITS>
+__device__ __forceinline__ void find_digit(SelectShared<BITS>& sh, const int* hist, int want) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
-  const int per = kSelBins / (int)blockDim.x, top = kSelBins - 1 - tid * per;
+  const int per = (1 << BITS) / (int)blockDim.x, top = (1 << BITS) - 1 - tid * per;
   int own = 0;
   for (int b = 0; b < per; ++b) own += hist[top - b];
   int inc = own;
@@ -241,8 +242,8 @@ __device__ __forceinline__ void find_digit(SelectShared& sh, const int* hist, in
 // candidates and keeps the order inside each modality, so the Top-N of the boosted scores is:
 // all text candidates plus the best vision ones if N exceeds the number of text candidates, else
 // the best N text candidates.  The order inside one modality is found exactly on the unboosted
-// fp32 scores (no bits are lost to the addition) with a radix select over their bit patterns, 11 + 11 + 10 bits
-// (scores are >= 0, so the unsigned order of the bits is the order of the values); equal scores go to the smaller
+// fp32 scores (no bits are lost to the addition) with a radix select over their bit patterns, 11 + 11 + 10 bits or four
+// times 8 for short prompts (scores are >= 0, so the unsigned order of the bits is the order of the values); equal scores go to the smaller
 // position.  The first sweep counts both modalities, so the number of text candidates needs no sweep of its own.
 //
 // Bound by the latency of its sweeps and, before, by histogram atomics: with 8-bit digits the first one (two octaves
@@ -251,10 +252,11 @@ __device__ __forceinline__ void find_digit(SelectShared& sh, const int* hist, in
 // thread (SINGLE) the scores are read once and stay in registers.  One barrier per iteration of the output sweep:
 // the positions a tie may take before p are min(ties before p, ties taken), so one prefix over (certain, tied)
 // counts places everything.  Before and now, in us: 256 (layer, head) pairs of 131072 positions 370 / 233, 112 of 37376
-// 92 / 64, 256 of 16384 45 / 32, 1024 of 4096 31 / 29, 360 of 3001 23 / 16.5.
-template <int ITEMS, bool SINGLE>
+// 92 / 64, 256 of 16384 45 / 32, 1024 of 4096 31 / 29, 360 of 3001 23 / 16.5, 256 of 300 and of 100 11 / 10 and 10 / 9.4.
+template <int ITEMS, bool SINGLE, int BITS>
 __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
-  __shared__ SelectShared sh;
+  constexpr int kBins = 1 << BITS;
+  __shared__ SelectShared<BITS> sh;
   const int g = blockIdx.x, l = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_thr = blockDim.x, n_waves = n_thr >> 6;
@@ -291,12 +293,12 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
   };
   if (SINGLE) load(0);
 
-  for (int b = tid; b < 2 * kSelBins; b += n_thr) (&sh.hist[0][0])[b] = 0;
+  for (int b = tid; b < 2 * kBins; b += n_thr) (&sh.hist[0][0])[b] = 0;
   __syncthreads();
-  sweep([&](unsigned k, int c) { atomicAdd(&sh.hist[c][k >> 21], 1); });
+  sweep([&](unsigned k, int c) { atomicAdd(&sh.hist[c][k >> (32 - BITS)], 1); });
   __syncthreads();
   int n_text = 0;
-  for (int b = tid; b < kSelBins; b += n_thr) n_text += sh.hist[0][b];
+  for (int b = tid; b < kBins; b += n_thr) n_text += sh.hist[0][b];
   n_text = wave_sum(n_text);
   if (lane == 0) sh.wsum[1][wave] = n_text;
   __syncthreads();
@@ -315,9 +317,9 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
     unsigned prefix = (unsigned)sh.bin;
     int want = sh.rest;
 #pragma unroll
-    for (int step = 0; step < 2; ++step) {
-      const int shift = step == 0 ? 10 : 0, bits = step == 0 ? 11 : 10;
-      for (int b = tid; b < kSelBins; b += n_thr) sh.hist[0][b] = 0;
+    for (int left = 32 - BITS; left > 0; left -= BITS) {
+      const int bits = left < BITS ? left : BITS, shift = left - bits;
+      for (int b = tid; b < kBins; b += n_thr) sh.hist[0][b] = 0;
       __syncthreads();
       sweep([&](unsigned k, int c) {
         if (c == cls && (k >> (shift + bits)) == prefix) atomicAdd(&sh.hist[0][(k >> shift) & ((1u << bits) - 1u)], 1);
@@ -419,11 +421,23 @@ hipError_t launch_select(const Plan& p, const Buffers& b, hipStream_t s) {
   a.L = p.L; a.Hkv = p.Hkv; a.T = p.T; a.no_merge = (p.flags & MEDA_FLAG_NO_MERGE) ? 1 : 0;
   a.Lseq = p.Lseq;
   const dim3 grid(p.Hkv, p.L);
-  if (p.T <= 1024) hipLaunchKernelGGL((select_kernel<4, true>), grid, dim3(256), 0, s, a);
-  else if (p.T <= 4096) hipLaunchKernelGGL((select_kernel<8, true>), grid, dim3(512), 0, s, a);
-  else if (p.T <= 8192) hipLaunchKernelGGL((select_kernel<8, true>), grid, dim3(1024), 0, s, a);
-  else if (p.T <= 16384) hipLaunchKernelGGL((select_kernel<16, true>), grid, dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL((select_kernel<8, false>), grid, dim3(1024), 0, s, a);
+  // Short prompts: one sweep costs less than clearing and searching 2048 bins, so 8-bit digits and as few positions per
+  // thread as cover the prompt (256 pairs of 300 positions 12.1 -> 10.1 us, 1024 pairs 16.4 -> 12.1).  Longer ones: the
+  // workgroup is as large as the CUs can hold for the number of pairs (of 1024 threads a CU holds one): 1024 pairs of
+  // 4100 positions 57 us with 1024 threads, 37 with 512, 34 with 256, but 256 pairs 18.4, 18.7 and 22 us.  From 8192
+  // positions on the scores are read again in every sweep (8 registers of them per thread hide the loads as well).
+  const int pairs = p.L * p.Hkv;
+  if (p.T <= 256) hipLaunchKernelGGL((select_kernel<1, true, 8>), grid, dim3(256), 0, s, a);
+  else if (p.T <= 512) hipLaunchKernelGGL((select_kernel<2, true, 8>), grid, dim3(256), 0, s, a);
+  else if (p.T <= 1024) hipLaunchKernelGGL((select_kernel<4, true, 8>), grid, dim3(256), 0, s, a);
+  else if (p.T <= 2048 && pairs <= 512) hipLaunchKernelGGL((select_kernel<4, true, 11>), grid, dim3(512), 0, s, a);
+  else if (p.T <= 2048) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(256), 0, s, a);
+  else if (p.T <= 4096) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(512), 0, s, a);
+  else if (p.T <= 8192 && pairs <= 256) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(1024), 0, s, a);
+  else {
+    const int n_thr = pairs <= 256 ? (p.T < 16384 ? 512 : 1024) : (pairs > 512 && p.T <= 16384 ? 256 : 512);
+    hipLaunchKernelGGL((select_kernel<8, false, 11>), grid, dim3(n_thr), 0, s, a);
+  }
   return hipGetLastError();
 }
 

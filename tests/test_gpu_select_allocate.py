@@ -59,6 +59,15 @@ def test_selection_around_the_shapes(T, p_text):
     _run(T, 2, 1, 64, torch.bfloat16, 2 * max(16, T // 5), p_text=p_text, duplicates=T // 3)
 
 
+# short prompts, and the workgroups chosen for more than 256 and 512 pairs
+@pytest.mark.parametrize("T,L,hkv", [(17, 2, 2), (256, 2, 2), (257, 2, 2), (512, 2, 2), (513, 2, 2), (2048, 3, 1), (2049, 3, 1),
+                                     (300, 33, 20), (1025, 33, 20), (2048, 33, 20), (4097, 33, 20), (4100, 20, 20), (16385, 33, 20),
+                                     (12000, 3, 1)])
+@pytest.mark.parametrize("duplicates", [False, True])
+def test_selection_of_short_prompts_and_many_pairs(T, L, hkv, duplicates):
+    _run(T, L, hkv, 64, torch.bfloat16, L * max(16, T // 5), p_text=0.1, duplicates=T // 3 if duplicates else 0)
+
+
 def test_selection_of_one_modality_and_of_nearly_everything():
     for p in (0.0, 1.0):
         _run(1500, 2, 1, 64, torch.float32, 2 * 300, p_text=p)
