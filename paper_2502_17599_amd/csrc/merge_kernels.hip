@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(256) pack_conserved_kernel(MergeArgs a) {
 }
 
 // ------------------------------------------------------------------------------- segment sort
-// grid (Hkv, L), 1024 threads.  Stable least-significant-digit radix sort (at most 8 bits per pass) of the pairs
+// grid (Hkv, L), WAVES waves.  Stable least-significant-digit radix sort (at most 8 bits per pass) of the pairs
 // (slot, row id) of one (layer, head) by slot; row ids enter ascending, so every slot's members come
 // out ascending and the merge adds them in one fixed order.  Then seg_beg / seg_end of every slot = its range in the
 // sorted array (sort_val[0]).
@@ -582,14 +582,13 @@ __global__ void __launch_bounds__(256) pack_conserved_kernel(MergeArgs a) {
 // position travel as one 32-bit word where their bits fit (PACKED: slot above position), which halves them.
 // Before (5 bits per pass, a barrier-separated prefix over the waves per 1024 elements) and now, in us: 256 pairs of
 // 118000 rows 781 / 621, 256 of 13000 91 / 50, 1024 of 3600 62 / 52, 360 of 2300 39 / 21, 8 of 770 12 / 8.
-constexpr int kSortThreads = 1024;
-constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortBits = 8;
 constexpr int kSortDigits = 1 << kSortBits;
 constexpr int kSortItems = 8;  // groups of 64 elements whose loads are issued together
 
+template <int WAVES>
 struct SortShared {
-  int cnt[kSortWaves][kSortDigits];
+  int cnt[WAVES][kSortDigits];
   int wave_total[kSortDigits / 64];
 };
 
@@ -609,8 +608,8 @@ __device__ __forceinline__ unsigned long long digit_peers(int dgt, int bits, boo
 
 __device__ __forceinline__ int bits_below(int n) { return n > 1 ? 32 - __clz(n - 1) : 1; }  // bits of 0 .. n-1
 
-template <bool PACKED>
-__device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh, int S, size_t lbase, int row0, int32_t* beg,
+template <int WAVES, bool PACKED>
+__device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared<WAVES>& sh, int S, size_t lbase, int row0, int32_t* beg,
                                              int32_t* end) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -619,7 +618,7 @@ __device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh,
   const int slot_bits = bits_below(S), pos_bits = PACKED ? bits_below(a.T) : 0;
   const int passes = (slot_bits + kSortBits - 1) / kSortBits;
   const int bits = (slot_bits + passes - 1) / passes, digit_mask = (1 << bits) - 1;
-  const int part = ((n + kSortWaves - 1) / kSortWaves + 63) & ~63;  // elements per wave
+  const int part = ((n + WAVES - 1) / WAVES + 63) & ~63;  // elements per wave
   const int p_beg = min(wave * part, n), p_end = min(p_beg + part, n);
   volatile int* mine = sh.cnt[wave];  // the wave's histogram, later the next output position per digit
 
@@ -644,10 +643,10 @@ __device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh,
     }
     __syncthreads();
     // exclusive prefix in the order (digit, wave): thread q < 256 has digit q
-    int c[kSortWaves], total = 0, inc = 0;
+    int c[WAVES], total = 0, inc = 0;
     if (tid < kSortDigits) {
 #pragma unroll
-      for (int w = 0; w < kSortWaves; ++w) {
+      for (int w = 0; w < WAVES; ++w) {
         c[w] = sh.cnt[w][tid];
         total += c[w];
       }
@@ -665,7 +664,7 @@ __device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh,
 #pragma unroll
       for (int w = 0; w < kSortDigits / 64; ++w) pos += (w < wave) ? sh.wave_total[w] : 0;
 #pragma unroll
-      for (int w = 0; w < kSortWaves; ++w) {
+      for (int w = 0; w < WAVES; ++w) {
         sh.cnt[w][tid] = pos;
         pos += c[w];
       }
@@ -703,7 +702,7 @@ __device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh,
   // member range of every slot, as absolute indices into the sorted array
   const int ib = (int)lbase;
   auto slot_at = [&](int i) { return PACKED ? (int)((unsigned)in_key[i] >> pos_bits) : in_key[i]; };
-  for (int i = tid; i < n; i += kSortThreads) {
+  for (int i = tid; i < n; i += WAVES * 64) {
     const int kcur = slot_at(i);
     const int kprev = (i > 0) ? slot_at(i - 1) : -1;
     if (PACKED) a.sort_val[0][lbase + i] = row0 + (int)((unsigned)in_key[i] & ((1u << pos_bits) - 1u));
@@ -711,12 +710,13 @@ __device__ __forceinline__ void segment_sort(const MergeArgs& a, SortShared& sh,
     for (int s = max(kprev, 0); s < kcur; ++s) end[s] = ib + i;
   }
   const int klast = (n > 0) ? slot_at(n - 1) : -1;
-  for (int s = klast + 1 + tid; s < S; s += kSortThreads) beg[s] = ib + n;
-  for (int s = max(klast, 0) + tid; s < S; s += kSortThreads) end[s] = ib + n;
+  for (int s = klast + 1 + tid; s < S; s += WAVES * 64) beg[s] = ib + n;
+  for (int s = max(klast, 0) + tid; s < S; s += WAVES * 64) end[s] = ib + n;
 }
 
-__global__ void __launch_bounds__(kSortThreads, 8) segment_sort_kernel(MergeArgs a) {
-  __shared__ SortShared sh;
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, 8) segment_sort_kernel(MergeArgs a) {
+  __shared__ SortShared<WAVES> sh;
   const int g = blockIdx.x, l = blockIdx.y;
   const int S = a.alloc[4 * l];
   const long long off_l = a.off[l];
@@ -724,9 +724,9 @@ __global__ void __launch_bounds__(kSortThreads, 8) segment_sort_kernel(MergeArgs
   const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
   const int row0 = (l * a.Hkv + g) * a.T;  // row id of position 0
   if (bits_below(S) + bits_below(a.T) <= 32)
-    segment_sort<true>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
+    segment_sort<WAVES, true>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
   else
-    segment_sort<false>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
+    segment_sort<WAVES, false>(a, sh, S, lbase, row0, a.seg_beg + cbase, a.seg_end + cbase);
 }
 
 // ------------------------------------------------------------------------------ merge + write
@@ -1126,7 +1126,14 @@ hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {
 
 hipError_t launch_segment_sort(const Plan& p, const Buffers& b, hipStream_t s) {
   const MergeArgs a = make_args(p, b);
-  hipLaunchKernelGGL(segment_sort_kernel, dim3(p.Hkv, p.L), dim3(kSortThreads), 0, s, a);
+  // One workgroup of 16 waves fills half a CU: fewer waves where the parts would be short or the pairs many (1024 pairs of
+  // 100 and of 1000 positions 13.4 and 18 us with 16 waves, 8.6 and 13.4 with 4; of 2000 23.5 and 20 with 8; but 256 of
+  // 2000 11.6 us with 16, 11.8 with 8, 14.8 with 4).
+  const dim3 grid(p.Hkv, p.L);
+  const int pairs = p.L * p.Hkv;
+  if (p.T <= 128 || (pairs >= 512 && p.T <= 768)) hipLaunchKernelGGL(segment_sort_kernel<4>, grid, dim3(256), 0, s, a);
+  else if (pairs >= 1024 && p.T <= 4096) hipLaunchKernelGGL(segment_sort_kernel<8>, grid, dim3(512), 0, s, a);
+  else hipLaunchKernelGGL(segment_sort_kernel<16>, grid, dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

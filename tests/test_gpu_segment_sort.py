@@ -48,6 +48,11 @@ def test_passes_and_ragged_parts(T, B, dtype, d):
     _case(T, B, d, dtype)
 
 
+@pytest.mark.parametrize("T,B,L,hkv", [(129, 33, 2, 3), (128, 33, 2, 3), (700, 100, 32, 16), (300, 90, 64, 16), (2000, 300, 64, 16)])
+def test_waves_chosen_by_length_and_pairs(T, B, L, hkv):
+    _case(T, L * B, 64, torch.bfloat16, n_layers=L, hkv=hkv)
+
+
 def test_long_lists():
     _case(6000, 300, 64, torch.bfloat16, one_cluster=True)
     _case(3000, 40, 64, torch.float32, one_cluster=True)
