@@ -830,6 +830,10 @@ struct OutConv<float> {
 constexpr int kMergeRowsPerWave = 16;
 constexpr int kMergeRowsPerWaveShort = 4;
 constexpr long long kMergeShortRows = 65536;
+// Rows of 128 bytes: one load per step makes twice the steps of a long list, and a wave's chain of them is what a layer
+// with few slots waits for, so fewer rows per wave for longer (96000 rows of 30000 positions a pair under uneven budgets:
+// 578 us with 16 rows, 160 with 4; 209920 rows of 8200: 197 and 129 with 8; even budgets within 7 %).
+constexpr long long kMergeRows128Four = 131072, kMergeRows128Eight = 1 << 20;
 
 // Where a wave is in the flat sequence of load steps of its output rows: row r of the wave, element t
 // of that row's list (element 0 is the conserved row itself, the others its members), and the row's
@@ -1138,12 +1142,14 @@ hipError_t launch_segment_sort(const Plan& p, const Buffers& b, hipStream_t s) {
 }
 
 template <typename T, int D>
-static hipError_t launch_merge_t(const Plan& p, const MergeArgs& a, hipStream_t s) {
+static hipError_t launch_merge_t(const Plan& p, MergeArgs a, hipStream_t s) {
   if (!a.merge_members) {
     const long long pieces = a.total_slots * Tile<T, D>::kChunksPerRow;
     hipLaunchKernelGGL((copy_rows_kernel<T, D>), dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
   }
+  if (Tile<T, D>::kRowBytes == 128 && a.merge_rows == kMergeRowsPerWave)
+    a.merge_rows = a.total_slots < kMergeRows128Four ? 4 : (a.total_slots < kMergeRows128Eight ? 8 : kMergeRowsPerWave);
   const long long waves = (a.total_slots + a.merge_rows - 1) / a.merge_rows;
   hipLaunchKernelGGL((merge_write_kernel<T, D>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a);
   return hipGetLastError();
