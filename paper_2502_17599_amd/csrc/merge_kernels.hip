@@ -1064,7 +1064,9 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
 //                    256 of 1024        75 /  60  (69 /  62)            256 of 2048       352 / 354  (278 / 269)
 // rows of 512 bytes  32 of 1024         32 /  44  (34 /  82)            48 of 2048        195 / 205  (118 / 261)
 //                    128 of 512         48 /  38  (48 /  46)            128 of 2048       506 / 384  (360 / 283)
-// and one pair of 8192 positions, a tenth kept, 108 / 73 (rows of 256 bytes); over 1394 shapes the rule costs
+// With rows of 256 bytes and a quarter or more kept the two are even at any number of pairs (within 15 %), and the merge
+// after the direct kernel finds more of the keys in the caches (1024 pairs of 300 and 3000, three tenths kept, whole
+// pass: 245 / 285 and 3490 / 3850 us).  One pair of 8192 positions, a tenth kept: 108 / 73 us (rows of 256 bytes).  Over 1394 shapes the rule costs
 // 1.1 % against the better one of the two, the direct kernel everywhere 12 %, the tiled one everywhere 48 %.
 constexpr unsigned kSimDirectGroups = 96;
 constexpr int kSimDirectPositions = 2048;
@@ -1075,7 +1077,8 @@ static bool direct_pays(const Plan& p, unsigned pairs) {
   const double positions = (double)pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
   const bool few = pairs <= (D == 64 ? 256u : 96u) || positions <= (D == 64 ? 163840.0 : 49152.0);
   const double longest = (pairs == 1 ? 4.1e4 : D == 64 ? 1.64e5 : 6.15e4) * kept;
-  return few && positions <= (D == 64 ? 1.5e6 : 5e5) * kept && p.T <= longest && p.T <= 16384;
+  const bool many_kept = D == 64 && kept >= 0.25;
+  return p.T <= longest && p.T <= 16384 && (many_kept || (few && positions <= (D == 64 ? 1.5e6 : 5e5) * kept));
 }
 
 template <typename T, int D, int F, int NW>
