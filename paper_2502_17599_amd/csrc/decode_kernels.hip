@@ -44,7 +44,7 @@ struct DecodeArgs {
   char* out;                // [L][Hq][d]
   float* part;              // [NC + L*NSN][Hq][d + 2]: weighted value sum, maximum (base-2 logits), normaliser
   int L, Hq, Hkv, G, n_new;
-  int R;                    // rows per chunk aimed at
+  unsigned R, R_inv;        // rows per chunk aimed at, floor(2^32 / R)
   int NC, NSN;              // chunk ids of the cached rows (at most), chunks of a layer's appended rows
   float scale_log2;
   // 8-bit cache (FP8 instantiation): k_cache / v_cache hold E4M3 codes, one scale per row
@@ -54,8 +54,7 @@ struct DecodeArgs {
 
 // The chunks of the cached rows are numbered layer after layer: layer l has ceil(S_l / R) of them, at least one.  The host sizes
 // the launch for NC ids, at least floor(B / R) + L in general, which bounds their number for S_1 + .. + S_L <= B; should
-// the lengths exceed B, R is doubled until they fit (every workgroup computes the same R).  Evaluated by every wave on its own:
-// lane i holds layer base + i.
+// the lengths exceed B, R is doubled until they fit (every workgroup computes the same R).  Evaluated by every wave on its own.
 struct LayerChunks {
   int layer;      // the layer asked for, or the one that owns the chunk id asked for (-1: id past the last chunk)
   int first;      // id of its first chunk
@@ -73,35 +72,83 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2, 3
   return v;
 }
-// by_layer >= 0: the chunks of that layer; otherwise the owner of chunk `id`
+// max(1, ceil(s / R)), inv = floor(2^32 / R): the estimate is the quotient or one less.  (A division here was most of
+// what the search cost with many layers: every workgroup of both kernels walks them all.)
+__device__ __forceinline__ int chunks_of(int s, unsigned R, unsigned inv) {
+  const unsigned x = (unsigned)s + R - 1u, q = __umulhi(x, inv);
+  return max(1, (int)(q + (x - q * R >= R ? 1u : 0u)));
+}
+// by_layer >= 0: the chunks of that layer; otherwise the owner of chunk `id`.  A lane holds one layer of 64; with more
+// layers the lengths of kDecScan x 64 are loaded together and the offset only of the layer found.
+constexpr int kDecScan = 4;
 __device__ __forceinline__ LayerChunks find_chunks(const DecodeArgs& a, int by_layer, int id) {
   const int lane = threadIdx.x & 63;
   LayerChunks out{-1, 0, 0, 0, 0};
-  for (unsigned R = a.R;; R = R < (1u << 30) ? 2u * R : 1u << 31) {  // 2^31: one chunk per layer, which always fits
+  unsigned R = a.R, inv = a.R_inv;
+  while (true) {
     int total = 0;
-    for (int base = 0; base < a.L; base += 64) {
-      const int lc = min(base + lane, a.L - 1);
-      const int s = (base + lane < a.L) ? a.layer_len[lc] : 0;
-      const long long off = a.layer_off[lc];
-      const int n = base + lane < a.L ? max(1, (int)(((unsigned)s + R - 1u) / R)) : 0;
+    // the layers base .. base + 63, of which this lane has one of s rows
+    auto search = [&](int base, int s) {
+      const int n = base + lane < a.L ? chunks_of(s, R, inv) : 0;
       const int inc = wave_inclusive_sum(n);
       const int first = total + inc - n;
-      const bool mine = by_layer >= 0 ? base + lane == by_layer : (id >= first && id < first + n);
-      const unsigned long long b = __ballot(mine);
-      if (b != 0ull) {
-        const int src = __ffsll((unsigned long long)b) - 1;
-        out.layer = base + src;
-        out.first = __builtin_amdgcn_readlane(first, src);
-        out.n = __builtin_amdgcn_readlane(n, src);
-        out.rows = __builtin_amdgcn_readlane(s, src);
+      const unsigned long long b = __ballot(by_layer >= 0 ? base + lane == by_layer : (id >= first && id < first + n));
+      total += __builtin_amdgcn_readlane(inc, 63);
+      if (b == 0ull) return -1;
+      const int src = __ffsll((unsigned long long)b) - 1;
+      out.layer = base + src;
+      out.first = __builtin_amdgcn_readlane(first, src);
+      out.n = __builtin_amdgcn_readlane(n, src);
+      out.rows = __builtin_amdgcn_readlane(s, src);
+      return src;
+    };
+    if (a.L <= 64) {
+      const int lc = min(lane, a.L - 1);
+      const int s = a.layer_len[lc];
+      const long long off = a.layer_off[lc];
+      const int src = search(0, s);
+      if (src >= 0)
         out.off = (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(off >> 32), src) << 32) |
                               (unsigned)__builtin_amdgcn_readlane((int)off, src));
+    } else {
+      for (int base = 0; base < a.L; base += 64 * kDecScan) {
+        int s[kDecScan];
+#pragma unroll
+        for (int j = 0; j < kDecScan; ++j) s[j] = a.layer_len[min(base + 64 * j + lane, a.L - 1)];
+#pragma unroll
+        for (int j = 0; j < kDecScan; ++j)
+          if (base + 64 * j < a.L) search(base + 64 * j, s[j]);
       }
-      total += __builtin_amdgcn_readlane(inc, 63);
     }
-    if (total <= a.NC || R == 1u << 31) return out;
+    if (total <= a.NC || R == 1u << 31) break;
     out.layer = -1;
+    inv = R < (1u << 30) ? inv >> 1 : 2u;
+    R = R < (1u << 30) ? 2u * R : 1u << 31;  // 2^31: one chunk per layer, which always fits
   }
+  if (a.L > 64 && out.layer >= 0) out.off = a.layer_off[out.layer];
+  return out;
+}
+
+// The same for a workgroup: with more layers than a wave holds at once its first wave searches for all.  512 and 2000
+// layers of 64 rows, one kv head and eight query heads: 19 and 109 us with every wave searching and dividing, 16 and 73
+// now; an equal number of chunks per layer (no search) 15 and 32, but with lengths of 100 to 1800 rows 57 and 214
+// against 44 and 207.
+__device__ __forceinline__ LayerChunks find_chunks_of_group(const DecodeArgs& a, int by_layer, int id) {
+  if (a.L <= 64) return find_chunks(a, by_layer, id);
+  __shared__ LayerChunks found;
+  if (threadIdx.x < 64) {
+    const LayerChunks lc = find_chunks(a, by_layer, id);
+    if (threadIdx.x == 0) found = lc;
+  }
+  __syncthreads();
+  LayerChunks out;
+  out.layer = __builtin_amdgcn_readfirstlane(found.layer);
+  out.first = __builtin_amdgcn_readfirstlane(found.first);
+  out.n = __builtin_amdgcn_readfirstlane(found.n);
+  out.rows = __builtin_amdgcn_readfirstlane(found.rows);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)found.off);
+  out.off = (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(found.off >> 32)) << 32) | lo);
+  return out;
 }
 
 // What one workgroup works on.
@@ -126,7 +173,7 @@ __device__ __forceinline__ bool chunk_of_group(const DecodeArgs& a, int id, Deco
     c.last = false;
     return true;
   }
-  const LayerChunks lc = find_chunks(a, -1, id);
+  const LayerChunks lc = find_chunks_of_group(a, -1, id);
   if (lc.layer < 0) return false;
   const int per = (lc.rows + lc.n - 1) / lc.n;
   const int rows = (per + 31) & ~31;  // whole steps of a wave
@@ -744,12 +791,14 @@ __global__ void __launch_bounds__(kDecThreads, 3) decode_matrix_kernel(DecodeArg
   write_partial<GP, D>(a, id, l, g, red_o, red_m, red_z);
 }
 
-// grid (Hq, L), D threads: merges the chunks of one query head and writes the output row.  Four chunks are in flight
-// together.
+// grid (Hq / H, L), H * D threads: merges the chunks of H query heads, one per D threads, and writes their output rows.
+// Four chunks are in flight together.  H = 4 with more than 64 layers: one search for four heads.
+constexpr int kDecCombineHeads = 4;
 template <typename T, int D>
-__global__ void __launch_bounds__(D) decode_combine_kernel(DecodeArgs a) {
-  const int h = blockIdx.x, l = blockIdx.y, j = threadIdx.x;
-  const LayerChunks lc = find_chunks(a, l, 0);
+__global__ void __launch_bounds__(kDecCombineHeads * D) decode_combine_kernel(DecodeArgs a) {
+  const int h = blockIdx.x * (blockDim.x / D) + threadIdx.x / D, l = blockIdx.y, j = threadIdx.x % D;
+  const LayerChunks lc = find_chunks_of_group(a, l, 0);
+  if (h >= a.Hq) return;
   const int n = lc.n + a.NSN;
   constexpr int U = 4;
   float mn = kNegBig, zs = 0.f, os = 0.f;
@@ -852,7 +901,8 @@ static hipError_t launch_decode_g(const DecodePlan& pl, const DecodeArgs& a, hip
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(pl.Hq, pl.L), dim3(D), 0, s, a);
+  const int heads = pl.L > 64 ? kDecCombineHeads : 1;
+  hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3((pl.Hq + heads - 1) / heads, pl.L), dim3(heads * D), 0, s, a);
   return hipGetLastError();
 }
 
@@ -936,7 +986,7 @@ static meda_status decode_common(const meda_decode_params* params, const void* q
   a.out = static_cast<char*>(out);
   a.part = static_cast<float*>(workspace);
   a.L = pl.L; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.n_new = pl.n_new;
-  a.R = pl.R; a.NC = pl.NC; a.NSN = pl.NSN;
+  a.R = (unsigned)pl.R; a.R_inv = (unsigned)((1ull << 32) / (unsigned)pl.R); a.NC = pl.NC; a.NSN = pl.NSN;
   a.scale_log2 = pl.scale_log2;
   a.k_scale = fp8 ? k_scale : nullptr;
   a.v_scale = fp8 ? v_scale : nullptr;

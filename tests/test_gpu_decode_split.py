@@ -67,6 +67,15 @@ def test_more_layers_than_lanes_and_uneven_lengths():
     _case(lens, 2, 1, 64, torch.float32, 0)
 
 
+@pytest.mark.parametrize("L", [63, 64, 65, 511, 512, 513, 1030])
+def test_layers_around_the_steps_of_the_chunk_search(L):
+    lens = [1 + (53 * i * i) % 300 for i in range(L)]
+    lens[L - 1], lens[L // 2] = 700, 1
+    _case(lens, 2, 1, 64, torch.bfloat16, 0)
+    _case(lens, 2, 1, 64, torch.bfloat16, 140, budget=L)       # R doubled until the chunks fit, appended rows of their own
+    _case(lens, 2, 1, 64, torch.float32, 2)
+
+
 def test_lengths_beyond_the_budget_of_the_launch():
     # 20 layers of up to 2000 rows, sized for 20 rows: the chunks grow until their number fits
     lens = [2000, 1, 700] * 6 + [129, 128]
