@@ -50,20 +50,21 @@ def test_what_fits_in_an_even_split_fits():
         even = _even_split_bytes(*shape)
         near += LIMIT * 3 // 4 < even <= LIMIT
         if even <= LIMIT:
-            assert 0 < _bytes(*shape) <= LIMIT, (shape, even)
+            assert 0 < _bytes(*shape) <= LIMIT and 0 < _bytes(*shape, torch.float32) <= LIMIT, (shape, even)
     assert near > 300
 
 
 def test_a_workspace_for_more_serves_less():
-    for L, hq, hkv, d, B, n_new in _shapes(400, 2):
+    for i, (L, hq, hkv, d, B, n_new) in enumerate(_shapes(400, 2)):
+        dtype = (torch.bfloat16, torch.float32)[i % 2]
         last = 0
         for b in sorted({L, 2 * L, B // 2 + L, B, B + 1, *(B + i * max(1, B // 37) for i in range(60)), 200 * B}):
-            now = _bytes(L, hq, hkv, d, b, n_new)
-            assert now >= last > -1, (L, hq, hkv, d, b, n_new)
+            now = _bytes(L, hq, hkv, d, b, n_new, dtype)
+            assert now >= last, (L, hq, hkv, d, b, n_new)
             last = now
         last = 0
-        for m in (0, 1, 127, 128, 129, 256, 257, 300, 1000, 1025, 5000, 8192, 9000, 20000, 10 ** 6):
-            now = _bytes(L, hq, hkv, d, B, m)
+        for m in (0, 1, 32, 33, 127, 128, 129, 256, 257, 300, 1000, 1025, 5000, 8192, 9000, 20000, 10 ** 6):
+            now = _bytes(L, hq, hkv, d, B, m, dtype)
             assert now >= last, (L, hq, hkv, d, B, m)
             last = now
     sizes = [_bytes(32, 32, 8, 128, b, 0) for b in range(20000, 40000, 16)]

@@ -56,8 +56,8 @@ def test_lengths_around_the_steps(hq, hkv, d):
         _case(EDGES, hq, hkv, d, torch.bfloat16, n_new)
     _case(EDGES, hq, hkv, d, torch.bfloat16, 5, fp8=True)
     _case(EDGES, hq, hkv, d, torch.bfloat16, 140, fp8=True)
-    _case(EDGES, hq, hkv, d, torch.float32, 5)
-    _case(EDGES, hq, hkv, d, torch.float32, 140)
+    for n_new in (5, 32, 33, 140):
+        _case(EDGES, hq, hkv, d, torch.float32, n_new)
 
 
 def test_more_layers_than_lanes_and_uneven_lengths():
