@@ -831,9 +831,10 @@ constexpr int kMergeRowsPerWave = 16;
 constexpr int kMergeRowsPerWaveShort = 4;
 constexpr long long kMergeShortRows = 65536;
 // Rows of 128 bytes: one load per step makes twice the steps of a long list, and a wave's chain of them is what a layer
-// with few slots waits for, so fewer rows per wave for longer (96000 rows of 30000 positions a pair under uneven budgets:
-// 578 us with 16 rows, 160 with 4; 209920 rows of 8200: 197 and 129 with 8; even budgets within 7 %).
-constexpr long long kMergeRows128Four = 131072, kMergeRows128Eight = 1 << 20;
+// with few slots waits for where the pairs are too few to cover it, so fewer rows per wave there (uneven budgets: 32 pairs
+// of 30000, 96000 rows, 578 us with 16 rows and 160 with 4; 128 pairs of 8200, 104960 rows, 179 and 100 with 8; even
+// budgets within 5 %, 14 % with 4 rows; from 256 pairs on 16 rows lose nothing: 360 pairs of 3001 124 us, 127 with 8).
+constexpr int kMergeRows128Four = 64, kMergeRows128Eight = 128;  // up to so many pairs
 
 // Where a wave is in the flat sequence of load steps of its output rows: row r of the wave, element t
 // of that row's list (element 0 is the conserved row itself, the others its members), and the row's
@@ -1152,7 +1153,7 @@ static hipError_t launch_merge_t(const Plan& p, MergeArgs a, hipStream_t s) {
     return hipGetLastError();
   }
   if (Tile<T, D>::kRowBytes == 128 && a.merge_rows == kMergeRowsPerWave)
-    a.merge_rows = a.total_slots < kMergeRows128Four ? 4 : (a.total_slots < kMergeRows128Eight ? 8 : kMergeRowsPerWave);
+    a.merge_rows = p.L * p.Hkv <= kMergeRows128Four ? 4 : (p.L * p.Hkv <= kMergeRows128Eight ? 8 : kMergeRowsPerWave);
   const long long waves = (a.total_slots + a.merge_rows - 1) / a.merge_rows;
   hipLaunchKernelGGL((merge_write_kernel<T, D>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a);
   return hipGetLastError();
