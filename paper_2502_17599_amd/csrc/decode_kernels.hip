@@ -471,11 +471,11 @@ __global__ void __launch_bounds__(kDecThreads, 2) decode_partial_kernel(DecodeAr
 // FP8: the cached rows are E4M3 codes with one scale per row, converted to packed bf16 on arrival (exact); the key's
 // scale multiplies the logit and the value's scale the weight.  The appended rows of a step are bf16 in either case.
 //
-// Bound by HBM: 524288 bf16 rows, one head per kv head, in 47 us (5.7 TB/s); 650000 rows, seven heads, in 62 us
-// (5.4 TB/s); 838856 8-bit rows, four heads, in 50 us (4.6 TB/s).  The kernels this one replaced took 47, 79 and 90 us:
-// they spent about 160 vector instructions per 16 rows and wave (up to four heads) or 32 fp32 matrix instructions of
-// 32 clocks (five to eight), and cut every layer into the same number of chunks, so that the layer with the largest
-// budget had the longest ones.
+// Bound by HBM.  Whole steps (both launches) over caches not read before: 524288 bf16 rows, one head per kv head, 50 us
+// (5.3 TB/s); 650000 rows, seven heads, 67 us (5.0 TB/s); 838856 8-bit rows, four heads, 51 us (4.5 TB/s).  With the
+// kernels this one replaced 52, 86 and 90 us: they spent about 160 vector instructions per 16 rows and wave (up to four
+// heads) or 32 fp32 matrix instructions of 32 clocks (five to eight), and cut every layer into the same number of chunks,
+// so that the layer with the largest budget had the longest ones.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // out[i] = the value of lane FIRST + i of this lane's row of 16 lanes, i = 0..7 (0x150 + n: broadcast of lane n)
@@ -709,7 +709,7 @@ __device__ __forceinline__ void decode_rows(DecodeState<D>& st, const uint4 (&qp
   if (r0 < r_end) step(std::true_type());
 }
 
-// Three waves per SIMD (145 registers with rows of 256 bytes; four spill, and took twice the time).
+// Three waves per SIMD (138 to 152 registers with rows of 256 bytes; four spill, and took twice the time).
 template <int D, int GP, bool FP8>
 __global__ void __launch_bounds__(kDecThreads, 3) decode_matrix_kernel(DecodeArgs a) {
   constexpr int PE = D / 16;
