@@ -1,10 +1,15 @@
 // Pass B of the scoring (Sections 3.2 and 3.3) for grouped query heads and observation windows of up to 96 rows: the
-// arithmetic of score_accum_kernel, instruction for instruction (same products, same order of every sum, so the
-// results are bit-identical), with another way of feeding it.  A workgroup walks over all query heads against one
+// sums of score_accum_kernel with another way of feeding it.  A workgroup walks over all query heads against one
 // column tile of 128 keys; per head it needs the window's query rows and row statistics, per kv head the key tile.
 // Here they come by asynchronous global-to-LDS copies (no staging registers, no LDS store instructions): the copies
 // of head h+1 (and of the next kv head's key tile, when h+1 starts a new group) are issued when head h starts, so a
 // head costs one wait and one barrier and no load is waited for where it is issued.
+//
+// The keys are operand A and the query rows operand B, so a lane owns one query row and 16 keys per block: the row's
+// statistics are three registers of the lane (with a column per lane they were twelve 16-byte LDS reads per block of
+// 32 x 32), and the column sums of a kv head are reduced over the lanes once per kv head.  Bound by the vector unit: a
+// probability costs a multiply-add, an exponential and two multiply-adds.  32 layers of 16384 keys, 4 heads per kv head,
+// 64 rows: 518 -> 423 us; 28 of 37376, 7 heads per kv head: 820 -> 679 us.
 //
 // One key tile buffer is enough with at least two query heads per kv head: every wave takes its key fragment out of
 // the buffer in the first head of a group, and the next tile is requested in the last head of the group, at least one
@@ -54,10 +59,7 @@ __global__ void __launch_bounds__(kDmaThreads, 2) score_accum_dma_kernel(ScoreAr
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kg = lane >> 5;
   const int cw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j0 = tile * kScoreTile;
-  const int j = j0 + cw * 32 + n;  // this lane's key column
-  const bool col_ok = j < a.T;
-  const bool col_is_vision = col_ok && a.mask[(size_t)(l / a.Lseq) * a.Tk + j] != 0;
-  const int coef_plane = col_is_vision ? 2 : 3;
+  const int jw = j0 + cw * 32;  // the wave's first key
   // rows past the window (W not a multiple of 32) repeat the last query row and have zero weights; the masked path
   // also drops their exponentials, which the plain path would multiply by zero (not safe if one overflowed)
   const bool full = j0 + kScoreTile - 1 <= a.T - a.W && a.W == Wp;
@@ -78,10 +80,10 @@ __global__ void __launch_bounds__(kDmaThreads, 2) score_accum_dma_kernel(ScoreAr
   }
   const unsigned lds0 = (unsigned)(size_t)smem;
   const float* stats_f = reinterpret_cast<const float*>(a.stats);
-  auto issue = [&](int h) {
-    const int g = h / a.G;
+  // the query rows and statistics of head h; with g >= 0 the key tile of kv head g too
+  auto issue = [&](int h, int g) {
     const unsigned stage = lds0 + (unsigned)(kTileBytes + (h & 1) * kStageBytes);
-    if (h - g * a.G == 0) {
+    if (g >= 0) {
       const char* ksrc = uniform_ptr(a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt);
 #pragma unroll
       for (int c = 0; c < PFK; ++c) async_copy16_to_lds_stream(ksrc, koff[c], lds0 + (unsigned)((cw * PFK + c) * 1024));
@@ -115,78 +117,81 @@ __global__ void __launch_bounds__(kDmaThreads, 2) score_accum_dma_kernel(ScoreAr
 #pragma unroll
     for (int r = 0; r < 16; ++r) pbar[rb][r] = 0.f;
   Frag<T, D> kf;
-  float colsum = 0.f;
+  float colsum[16];
 
-  issue(0);
-  for (int h = 0; h < a.Hq; ++h) {
-    async_copy_wait<0>();  // this wave's pieces of the head have landed
-    __syncthreads();       // every wave's have; and nobody reads the other stage (the previous head) any more
-    if (h + 1 < a.Hq) issue(h + 1);
-    const int g = h / a.G, hg = h - g * a.G;
-    const char* stage = smem + kTileBytes + (h & 1) * kStageBytes;
-    const float* st = reinterpret_cast<const float*>(stage + kQBytes);  // planes: maximum, 1/Z, the two cross-modal 1/Z
-    if (hg == 0) {
-      frag_from(kf, smem + cw * 32 * RBt);  // the key tile of this kv head
-      colsum = 0.f;
-    }
-    // One query head against the wave's key columns.  MASKED: the tile touches the causal diagonal or the end
-    // of the sequence, so every probability is checked against its row; all other tiles take the plain path.
-    auto head_block = [&](auto masked_tag) {
-      constexpr bool MASKED = decltype(masked_tag)::value;
-      // Row r (without the lane group's offset kg*4) counts for this lane's column iff row_min <= r < row_end:
-      // the row exists (r + kg*4 < W) and sees the column (j <= T - W + r + kg*4).  The bounds are made opaque
-      // here so that the 16 comparisons per row block are redone per head instead of being kept in registers.
-      int row_min = col_ok ? j - (a.T - a.W) - kg * 4 : (1 << 30);
-      int row_end = a.W - kg * 4;
-      if (MASKED) asm volatile("" : "+v"(row_min), "+v"(row_end));
+  // The walk over the heads.  MASKED: the tile touches the causal diagonal or the end of the sequence, so every
+  // probability is checked against its row; all other tiles take the plain walk.  (The two are separate loops: a branch
+  // inside one loop made the compiler copy all accumulators around it, 48 moves beside the 64 instructions that a block
+  // of 32 x 32 needs.)
+  auto walk = [&](auto masked_tag) {
+    constexpr bool MASKED = decltype(masked_tag)::value;
+    int g = 0, hg = 0;
+    for (int h = 0; h < a.Hq; ++h) {
+      async_copy_wait<0>();  // this wave's pieces of the head have landed
+      __syncthreads();       // every wave's have; and nobody reads the other stage (the previous head) any more
+      if (h + 1 < a.Hq) issue(h + 1, hg + 1 == a.G ? g + 1 : -1);
+      const char* stage = smem + kTileBytes + (h & 1) * kStageBytes;
+      const float* st = reinterpret_cast<const float*>(stage + kQBytes);  // planes: maximum, 1/Z, the two cross-modal 1/Z
+      if (hg == 0) {
+        frag_from(kf, smem + cw * 32 * RBt);  // the key tile of this kv head
+#pragma unroll
+        for (int r = 0; r < 16; ++r) colsum[r] = 0.f;
+      }
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         Frag<T, D> qf;
         frag_from(qf, stage + rb * 32 * RBt);
+        const float m = st[rb * 32 + n], rz = st[Wp + rb * 32 + n];
+        // a row is of one modality, so one of its two weights is zero: the sum is its weight on the other modality's keys
+        const float coef = st[2 * Wp + rb * 32 + n] + st[3 * Wp + rb * 32 + n];
         f32x16_t acc = acc_zero();
-        mma<T, D>(acc, qf, kf);
+        mma<T, D>(acc, kf, qf);
+        // The row sees the wave's key i iff i <= T - W + row - jw; rows past the window see none.  The bound is made
+        // opaque so that the 16 comparisons per row block are redone per head instead of being kept in registers.
+        int seen = rb * 32 + n < a.W ? a.T - a.W + rb * 32 + n - jw - kg * 4 : -1;
+        if (MASKED) asm volatile("" : "+v"(seen));
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int row0 = rb * 32 + r4 * 8 + kg * 4;  // rows of acc[r4*4 .. r4*4+3]
-          const float4 m4 = *reinterpret_cast<const float4*>(st + row0);
-          const float4 z4 = *reinterpret_cast<const float4*>(st + Wp + row0);
-          const float4 c4 = *reinterpret_cast<const float4*>(st + coef_plane * Wp + row0);
-          const float mm[4] = {m4.x, m4.y, m4.z, m4.w};
-          const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
-          const float cc[4] = {c4.x, c4.y, c4.z, c4.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float e = fast_exp2(fmaf(acc[r4 * 4 + i], a.c, -mm[i]));
-            if (MASKED) e = (rb * 32 + r4 * 8 + i >= row_min && rb * 32 + r4 * 8 + i < row_end) ? e : 0.f;
-            colsum = fmaf(e, zz[i], colsum);
-            pbar[rb][r4 * 4 + i] = fmaf(e, cc[i], pbar[rb][r4 * 4 + i]);
-          }
+        for (int r = 0; r < 16; ++r) {
+          float e = fast_exp2(fmaf(acc[r], a.c, -m));
+          if (MASKED) e = acc_row(r, 0) <= seen ? e : 0.f;
+          colsum[r] = fmaf(e, rz, colsum[r]);
+          pbar[rb][r] = fmaf(e, coef, pbar[rb][r]);
         }
       }
-    };
-    if (full)
-      head_block(std::false_type{});
-    else
-      head_block(std::true_type{});
-    if (hg == a.G - 1) {
-      const float tot = colsum + __shfl_xor(colsum, 32, kWave);
-      if (kg == 0 && col_ok) a.col_scores[(size_t)(l * a.Hkv + g) * a.Tk + j] = tot;  // one writer per column
+      if (++hg == a.G) {
+        const float tot = reduce_lanes32(colsum, lane);  // of the key in register n / 2
+        const int j = jw + acc_row(n >> 1, kg);
+        if ((n & 1) == 0 && j < a.T) a.col_scores[(size_t)(l * a.Hkv + g) * a.Tk + j] = tot;  // one writer per column
+        hg = 0;
+        ++g;
+      }
     }
-  }
+  };
+  issue(0, 0);
+  if (full)
+    walk(std::false_type{});
+  else
+    walk(std::true_type{});
 
-  // entropy terms of the head-averaged cross-modal probabilities.  A vision column only receives
-  // probability from text rows (text -> vision direction) and a text column only from vision rows.
+  // Entropy terms of the head-averaged cross-modal probabilities: text rows on vision keys, vision rows on text keys
+  // (the sums of a row over keys of its own modality are dropped here).
+  const uint8_t* mask = a.mask + (size_t)(l / a.Lseq) * a.Tk;
+  const unsigned key_vision = (unsigned)__ballot(mask[min(jw + n, a.T - 1)] != 0);
   const float inv_heads = 1.0f / (float)a.Hq;
-  float s = 0.f;
+  float s_tv = 0.f, s_vt = 0.f;
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int rb = 0; rb < RB; ++rb) {
+    const bool row_vision = mask[a.T - a.W + min(rb * 32 + n, a.W - 1)] != 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
+      const bool vision = ((key_vision >> acc_row(r, kg)) & 1u) != 0;
       const float p = pbar[rb][r] * inv_heads;
-      s += (p > 0.f) ? p * __logf(p) : 0.f;
+      const float t = (p > 0.f && vision != row_vision) ? p * __logf(p) : 0.f;
+      s_tv += vision ? t : 0.f;
+      s_vt += vision ? 0.f : t;
     }
-  const double tv = wave_sum(col_is_vision ? (double)s : 0.0);
-  const double vt = wave_sum((col_ok && !col_is_vision) ? (double)s : 0.0);
+  }
+  const double tv = wave_sum((double)s_tv), vt = wave_sum((double)s_vt);
   if (lane == 0) {
     red[cw * 2 + 0] = tv;
     red[cw * 2 + 1] = vt;
