@@ -58,44 +58,27 @@ __device__ __forceinline__ void frag_load(Frag<T, D>& f, const char* row_ptr, in
   for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) f.c[i] = p[i];
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void mma(f32x16_t& acc, const Frag<T, D>& a, const Frag<T, D>& b);
-
+// one 16-byte chunk of both operands
+template <typename T>
+__device__ __forceinline__ void mma_chunk(f32x16_t& acc, const uint4& a, const uint4& b);
 template <>
-__device__ __forceinline__ void mma<bf16_t, 128>(f32x16_t& acc, const Frag<bf16_t, 128>& a,
-                                                 const Frag<bf16_t, 128>& b) {
-#pragma unroll
-  for (int i = 0; i < Tile<bf16_t, 128>::kFragChunks; ++i)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a.c[i]),
-                                                  __builtin_bit_cast(bf16x8_t, b.c[i]), acc, 0, 0, 0);
+__device__ __forceinline__ void mma_chunk<bf16_t>(f32x16_t& acc, const uint4& a, const uint4& b) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
 }
 template <>
-__device__ __forceinline__ void mma<bf16_t, 64>(f32x16_t& acc, const Frag<bf16_t, 64>& a,
-                                                const Frag<bf16_t, 64>& b) {
-#pragma unroll
-  for (int i = 0; i < Tile<bf16_t, 64>::kFragChunks; ++i)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a.c[i]),
-                                                  __builtin_bit_cast(bf16x8_t, b.c[i]), acc, 0, 0, 0);
-}
-
-__device__ __forceinline__ void mma_f32_chunk(f32x16_t& acc, const uint4& a, const uint4& b) {
+__device__ __forceinline__ void mma_chunk<float>(f32x16_t& acc, const uint4& a, const uint4& b) {
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
-template <>
-__device__ __forceinline__ void mma<float, 64>(f32x16_t& acc, const Frag<float, 64>& a,
-                                               const Frag<float, 64>& b) {
+
+template <typename T, int D>
+__device__ __forceinline__ void mma(f32x16_t& acc, const Frag<T, D>& a, const Frag<T, D>& b) {
 #pragma unroll
-  for (int i = 0; i < Tile<float, 64>::kFragChunks; ++i) mma_f32_chunk(acc, a.c[i], b.c[i]);
+  for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) mma_chunk<T>(acc, a.c[i], b.c[i]);
 }
-template <>
-__device__ __forceinline__ void mma<float, 128>(f32x16_t& acc, const Frag<float, 128>& a,
-                                                const Frag<float, 128>& b) {
-#pragma unroll
-  for (int i = 0; i < Tile<float, 128>::kFragChunks; ++i) mma_f32_chunk(acc, a.c[i], b.c[i]);
-}
+
 
 __device__ __forceinline__ f32x16_t acc_zero() {
   f32x16_t z;
@@ -158,19 +141,32 @@ __device__ __forceinline__ int swizzle_of_row(int r) {
   return Tile<T, D>::kRowBytes >= 256 ? (r & 15) : ((r >> 1) & 7);
 }
 
-// Copy `rows` consecutive rows (contiguous in global memory) into a padded LDS tile; rows at or
-// beyond `rows_valid` are zero-filled.
+// LDS tile filled by copies of 64 x 16 bytes (rows of at most 256 bytes).  What one copy brings, a piece, is contiguous;
+// 64 bytes of padding after every piece and an xor of the two low bits of the chunk number inside it spread the 16 rows
+// that a fragment load touches in one pass over all banks.  Unlike an xor of the whole chunk number this leaves only four
+// different addresses per lane in a fragment, the rest are constant offsets: 4 address registers instead of 8.
 template <typename T, int D>
-__device__ __forceinline__ void tile_load_contiguous(char* lds, const char* gsrc, int rows, int rows_valid,
-                                                     int tid, int n_threads) {
-  constexpr int CPR = Tile<T, D>::kChunksPerRow;
-  const int total = rows * CPR;
-  for (int c = tid; c < total; c += n_threads) {
-    const int row = c / CPR, cc = c - row * CPR;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row < rows_valid) v = *reinterpret_cast<const uint4*>(gsrc + (size_t)row * Tile<T, D>::kRowBytes + cc * 16);
-    *reinterpret_cast<uint4*>(lds + row * Tile<T, D>::kStride + cc * 16) = v;
+struct CopyTile {
+  static constexpr int kPiece = 1024 + 64;
+  static constexpr int kRows = 1024 / Tile<T, D>::kRowBytes;  // rows per piece
+  static_assert(Tile<T, D>::kRowBytes <= 256, "longer rows would need other bits in the xor");
+  static constexpr int bytes(int rows) { return rows / kRows * kPiece; }
+  static __device__ __forceinline__ int swizzle(int r) { return kRows == 4 ? (r & 3) : ((r >> 1) & 3); }
+  // byte offset (inside its row) of the chunk that lane `lane` brings of row r of a piece (r = lane / chunks per row)
+  static __device__ __forceinline__ unsigned source_chunk(int lane) {
+    return (unsigned)(((lane % Tile<T, D>::kChunksPerRow) ^ swizzle(lane / Tile<T, D>::kChunksPerRow)) * 16);
   }
+  // this lane's first chunk of row n of a block of 32 rows; chunk c of its fragment is at (this ^ 16 (c % 4)) + 64 (c / 4)
+  static __device__ __forceinline__ unsigned frag_base(int n, int lane_group) {
+    return (unsigned)((n / kRows) * kPiece + (n % kRows) * Tile<T, D>::kRowBytes + lane_group * Tile<T, D>::kHalfBytes +
+                      swizzle(n % kRows) * 16);
+  }
+};
+template <typename T, int D>
+__device__ __forceinline__ void frag_from_tile(Frag<T, D>& f, const char* block, unsigned base) {
+#pragma unroll
+  for (int c = 0; c < Tile<T, D>::kFragChunks; ++c)
+    f.c[c] = *reinterpret_cast<const uint4*>(block + (base ^ (unsigned)((c & 3) * 16)) + (c >> 2) * 64);
 }
 
 // A tile of ROWS consecutive rows, cut in 16-byte pieces that are dealt round-robin to the threads of
@@ -273,28 +269,35 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sums 16 values per lane over the 32 lanes of each half of the wave: lane n of a half ends with the sum of v[n / 2].
-// A reduce-scatter: each exchange halves the values a lane is responsible for (the upper lanes of a pair keep the upper
-// half); the pairs are 16, 8, 4 (mirrored inside 8 lanes) and 2 apart, the last exchange adds the two lanes of a value.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, false));
+// For the accumulator registers r = R .. R+3 of a lane: sum += x_r e_r (in this order) and p_r += y_r e_r, where lane r of
+// each 16 lanes holds x_r and y_r and every lane of the 16 uses them (DPP row broadcast).  One rounding per term, as fmaf.
+// In assembly because the compiler makes separate moves of the broadcasts; the s_nop covers the wait states after an
+// exponential whose result is used (one) and after a vector instruction that wrote a register read through DPP (two).
+template <int R>
+__device__ __forceinline__ void fma_rows4(float& sum, float& p0, float& p1, float& p2, float& p3, float x, float y, float e0, float e1,
+                                          float e2, float e3) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %5, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %6, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %6, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %6, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %5, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, %6, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+      : "+&v"(sum), "+&v"(p0), "+&v"(p1), "+&v"(p2), "+&v"(p3)
+      : "v"(x), "v"(y), "v"(e0), "v"(e1), "v"(e2), "v"(e3), "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3));
 }
-__device__ __forceinline__ float reduce_lanes32(const float (&v)[16], int lane) {
-  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4e, kXor1 = 0xb1;
-  float a[8], b[4], c[2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
-    a[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0, up2 = (lane & 2) != 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) b[i] = (up8 ? a[i + 4] : a[i]) + dpp_move<kRor8>(up8 ? a[i] : a[i + 4]);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) c[i] = (up4 ? b[i + 2] : b[i]) + dpp_move<kHalfMirror>(up4 ? b[i] : b[i + 2]);
-  const float d = (up2 ? c[1] : c[0]) + dpp_move<kXor2>(up2 ? c[0] : c[1]);
-  return d + dpp_move<kXor1>(d);
+// The same without the sum.
+template <int R>
+__device__ __forceinline__ void fma_rows4(float& p0, float& p1, float& p2, float& p3, float y, float e0, float e1, float e2, float e3) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
+      : "+&v"(p0), "+&v"(p1), "+&v"(p2), "+&v"(p3)
+      : "v"(y), "v"(e0), "v"(e1), "v"(e2), "v"(e3), "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3));
 }
 
 }  // namespace meda

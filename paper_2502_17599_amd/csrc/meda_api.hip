@@ -32,7 +32,9 @@ static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) 
   pl->n_blocks_a = single_chunk ? (rows + pl->row_block_a - 1) / pl->row_block_a : 1;
   const int combos = pl->G * pl->RBa;
   if (combos > 32 || pl->RB > 4) return false;
-  pl->NQ = combos <= 4 ? 1 : (combos <= 16 ? 2 : 4);  // (head, row block) pairs a wave keeps in registers
+  // (head, row block) pairs a wave keeps in registers: four waves at work where they can be, which leaves two workgroups
+  // per CU, one computing while the other waits at its barrier
+  pl->NQ = combos <= 4 ? 1 : (combos <= 8 ? 2 : (combos <= 12 ? 3 : 4));
   pl->NCG = (combos + pl->NQ - 1) / pl->NQ;
   pl->CS = (pl->NCG <= 4) ? 4 / pl->NCG : 1;
   const int tiles = (t + kScoreTile - 1) / kScoreTile;

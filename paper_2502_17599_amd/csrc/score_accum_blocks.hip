@@ -16,7 +16,11 @@
 // ends.  The column sums of a kv head go to an LDS array [Hkv][128] that the workgroup alone adds to, in a fixed
 // order, and that is written out once at the end: no read-modify-write of global memory, deterministic sums.
 //
-// LDS tiles filled by the copies are unpadded and xor-swizzled (swizzle_of_row in device_utils.hpp).
+// Row blocks wholly below the tile's diagonal are walked in a loop of their own (a branch inside one loop made the
+// compiler copy all accumulators around it), and the rows' cross-modal weights reach the multiply-adds through DPP
+// (fma_rows4) instead of four 16-byte LDS reads per block of 32 x 32: 70 vector instructions per block where there were
+// 140.  32 layers, 32 heads, 4096 positions: 4700 -> 4020 us; what is left waits at the barriers (one workgroup per CU).
+// LDS tiles filled by the copies are laid out as CopyTile (device_utils.hpp).
 #include "score_common.hpp"
 
 namespace meda {
@@ -28,28 +32,31 @@ constexpr int kBlkHalf = 128;            // rows of a half: what the waves of a 
 constexpr int kBlkRows = 2 * kBlkHalf;   // rows of a row block of this kernel (counted from the end of the prompt)
 
 template <typename T, int D>
-constexpr int blocks_stage_bytes() {  // one half: its query rows and four planes of row statistics (three in use)
-  return kBlkHalf * Tile<T, D>::kRowBytes + 4 * kBlkHalf * (int)sizeof(float);
+constexpr int blocks_stage_bytes() {  // one half: its query rows and four planes of row statistics
+  return CopyTile<T, D>::bytes(kBlkHalf) + 4 * kBlkHalf * (int)sizeof(float);
 }
 
 // one key tile, two stages, the column sums, the second row group's share (two buffers), the entropy reduction
 template <typename T, int D>
 static size_t blocks_lds_bytes(int Hkv) {
-  return (size_t)kScoreTile * Tile<T, D>::kRowBytes + 2 * (size_t)blocks_stage_bytes<T, D>() +
+  return (size_t)CopyTile<T, D>::bytes(kScoreTile) + 2 * (size_t)blocks_stage_bytes<T, D>() +
          (size_t)Hkv * kScoreTile * sizeof(float) + 2 * kScoreTile * sizeof(float) + kBlkWaves * 2 * sizeof(double);
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(kBlkThreads, 2) score_accum_blocks_kernel(ScoreArgs a) {
+__global__ void __launch_bounds__(kBlkThreads, kBlkWaves / 4) score_accum_blocks_kernel(ScoreArgs a) {
   using TL = Tile<T, D>;
+  using CT = CopyTile<T, D>;
   static_assert(kScoreTile == 128 && kBlkHalf == 128, "the wave layout assumes 128 x 128 patches");
   constexpr int RBt = TL::kRowBytes;
   constexpr int CPR = TL::kChunksPerRow;
-  constexpr int NC = TL::kFragChunks;
   constexpr int RPI = 64 / CPR;                     // rows one copy instruction fills
   constexpr int PF = kScoreTile / RPI / kBlkWaves;  // copy instructions per wave and tile
-  constexpr int kTileBytes = kScoreTile * RBt;
+  constexpr int kTileBytes = CT::bytes(kScoreTile);
   constexpr int kStageBytes = blocks_stage_bytes<T, D>();
+  constexpr int kRowGroups = kBlkWaves / 4;
+  constexpr int F = kBlkHalf / 32 / kRowGroups;  // 32-row fragments of a half that a wave takes
+  static_assert(kRowGroups == 2, "two row groups share a column");
   static_assert(64 % CPR == 0 && kScoreTile % (RPI * kBlkWaves) == 0, "the copy instructions must tile a tile evenly");
   extern __shared__ __align__(16) char smem[];
   // smem: the key tile, then the two stages
@@ -66,11 +73,10 @@ __global__ void __launch_bounds__(kBlkThreads, 2) score_accum_blocks_kernel(Scor
   const int cw = wave & 3, rh = wave >> 2;
   const int j0 = tile * kScoreTile;
   const int j = j0 + cw * 32 + n;  // this lane's key column
-  const bool col_is_vision = j < a.Tk && a.mask[(size_t)(l / a.Lseq) * a.Tk + j] != 0;
-  const int coef_plane = col_is_vision ? 1 : 2;  // text rows weigh vision columns, vision rows text columns
+  const uint8_t* mask = a.mask + (size_t)(l / a.Lseq) * a.Tk;
+  const bool col_is_vision = j < a.Tk && mask[j] != 0;
   // row blocks that exist (the scoring rows are the last q_rows positions) and see this tile
   const int n_bi = min((a.Tk - j0 + kBlkRows - 1) / kBlkRows, (a.q_rows + kBlkRows - 1) / kBlkRows);
-  const int n_items = n_bi * a.Hq * 2;                     // (row block, head, half), the half running fastest
 
   for (int i = tid; i < a.Hkv * kScoreTile; i += kBlkThreads) colacc[i] = 0.f;  // published by the first barrier
 
@@ -78,62 +84,50 @@ __global__ void __launch_bounds__(kBlkThreads, 2) score_accum_blocks_kernel(Scor
   // 16-byte chunk of the row crow + c * RPI.  Key rows past the end of the sequence repeat the last key, query and
   // statistics rows past it the last row: such columns and rows are masked below, they only have to be readable.
   const int crow = wave * PF * RPI + lane / CPR;
-  unsigned koff[PF];    // byte offset of this lane's piece inside the keys of a (layer, kv head): the same for all items
-  unsigned qchunk[PF];  // its chunk offset inside a query row
+  const unsigned chunk = CT::source_chunk(lane);
+  unsigned koff[PF];  // byte offset of this lane's piece inside the keys of a (layer, kv head): the same for all items
 #pragma unroll
-  for (int c = 0; c < PF; ++c) {
-    const int r = crow + c * RPI;
-    qchunk[c] = (unsigned)(((lane % CPR) ^ swizzle_of_row<T, D>(r)) * 16);
-    koff[c] = (unsigned)min(j0 + r, a.Tk - 1) * RBt + qchunk[c];
-  }
+  for (int c = 0; c < PF; ++c) koff[c] = (unsigned)min(j0 + crow + c * RPI, a.Tk - 1) * RBt + chunk;
   const unsigned lds0 = (unsigned)(size_t)smem;
   const float* stats_f = reinterpret_cast<const float*>(a.stats);
   // Row block bi holds the positions [Tb - Wb, Tb), Tb = Tk - bi * 256, Wb = min(256, q_rows - bi * 256): the scoring
   // rows are the last q_rows positions, row r of the query and statistics buffers is the position Tk - q_rows + r.
   // Half hf of a block starts at the position Tb - Wb + hf * 128 (the last block may leave the second half short or
   // empty: its rows are masked).
-  auto issue = [&](int item) {
-    const int hf = item & 1, hh = item >> 1;
-    const int bi = hh / a.Hq, h = hh - bi * a.Hq;
-    const int g = h / a.G;
+  // This brings half hf of the row block bi of head h to stage hf, and with key_tile the key tile of its kv head.
+  auto issue = [&](int bi, int h, int hf, bool key_tile) {
     const int row0 = a.q_rows - bi * kBlkRows - min(kBlkRows, a.q_rows - bi * kBlkRows) + hf * kBlkHalf;  // in the buffers
-    const unsigned stage = lds0 + (unsigned)(kTileBytes + (item & 1) * kStageBytes);
-    if (hf == 0 && h - g * a.G == 0) {
+    const unsigned stage = lds0 + (unsigned)(kTileBytes + hf * kStageBytes);
+    if (key_tile) {
+      const int g = h / a.G;
       // The key tile changes with the kv head.  One buffer is enough: every wave took its key fragment out of it
       // in the first half of the previous kv head, at least one barrier ago.
       const char* ksrc = uniform_ptr(a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt);
 #pragma unroll
-      for (int c = 0; c < PF; ++c) async_copy16_to_lds_stream(ksrc, koff[c], lds0 + (unsigned)((wave * PF + c) * 1024));
+      for (int c = 0; c < PF; ++c) async_copy16_to_lds_stream(ksrc, koff[c], lds0 + (unsigned)((wave * PF + c) * CT::kPiece));
     }
     const char* qsrc = uniform_ptr(a.q + (size_t)(l * a.Hq + h) * a.q_rows * RBt);
 #pragma unroll
     for (int c = 0; c < PF; ++c) {
-      const unsigned goff = (unsigned)min(row0 + crow + c * RPI, a.q_rows - 1) * RBt + qchunk[c];
-      async_copy16_to_lds(qsrc, goff, stage + (unsigned)((wave * PF + c) * 1024));
+      const unsigned goff = (unsigned)min(row0 + crow + c * RPI, a.q_rows - 1) * RBt + chunk;
+      async_copy16_to_lds(qsrc, goff, stage + (unsigned)((wave * PF + c) * CT::kPiece));
     }
-    // wave w brings the rows (w & 1) * 64 .. + 63 of plane w >> 1 of the row statistics
+    // wave w < 8 brings the rows (w & 1) * 64 .. + 63 of plane w >> 1 of the row statistics
+    if (wave >= 8) return;
     const float* ssrc = uniform_ptr(stats_f + ((size_t)(l * a.Hq + h) * 4 + (wave >> 1)) * a.stats_rows);
     const unsigned soff = (unsigned)min(row0 + (wave & 1) * 64 + lane, a.q_rows - 1) * 4u;
     async_copy4_to_lds(ssrc, soff, stage + (unsigned)(kTileBytes + ((wave >> 1) * kBlkHalf + (wave & 1) * 64) * 4));
   };
 
-  // chunk c of this lane's fragment (chunk kg * NC + c of row n of a 32-row block) sits at (n * row bytes) +
-  // 16 * ((kg * NC + c) ^ swz(n)) inside the block; the swizzle of a row does not depend on its block
-  unsigned coff[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) coff[c] = (unsigned)(n * RBt + (((kg * NC + c) ^ swizzle_of_row<T, D>(n)) * 16));
-  auto frag_from = [&](Frag<T, D>& f, const char* block) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) f.c[c] = *reinterpret_cast<const uint4*>(block + coff[c]);
-  };
+  const unsigned fbase = CT::frag_base(n, kg);
 
-  float pbar[2][2][16];  // [half][fragment of the wave][accumulator register]
+  float pbar[2][F][16];  // [half][fragment of the wave][accumulator register]
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-    for (int rbl = 0; rbl < 2; ++rbl)
+    for (int f = 0; f < F; ++f)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) pbar[hf][rbl][r] = 0.f;
+      for (int r = 0; r < 16; ++r) pbar[hf][f][r] = 0.f;
   double ent = 0.0;  // - sum of p log p over this lane's column, all row blocks
   Frag<T, D> kf;
   float colsum = 0.f;
@@ -146,107 +140,113 @@ __global__ void __launch_bounds__(kBlkThreads, 2) score_accum_blocks_kernel(Scor
     pending_g = -1;
   };
 
-  // one half of a (row block, head) item; hf is a compile-time constant so that pbar stays in registers
-  auto half_item = [&](int hh, auto hf_tag) {
-    constexpr int hf = decltype(hf_tag)::value;
-    const int item = hh * 2 + hf;
-    async_copy_wait<0>();  // this wave's pieces of the half have landed
-    __syncthreads();       // every wave's have; and nobody reads the other stage (the previous half) any more
-    flush_pending();
-    if (item + 1 < n_items) issue(item + 1);
-
-    const int bi = hh / a.Hq, h = hh - bi * a.Hq;
-    const int g = h / a.G, hg = h - g * a.G;
-    const int Tb = a.Tk - bi * kBlkRows, Wb = min(kBlkRows, a.q_rows - bi * kBlkRows);
-    const int pos0 = Tb - Wb + hf * kBlkHalf;          // position of the half's first row
-    const int rows = min(kBlkHalf, Wb - hf * kBlkHalf);  // rows the half really has (may be <= 0)
-    const char* stage = smem + kTileBytes + (item & 1) * kStageBytes;
-    const float* st = reinterpret_cast<const float*>(stage + kTileBytes);
-    if (hf == 0 && hg == 0) {
-      frag_from(kf, smem + cw * 32 * RBt);  // the key tile of this kv head
-      colsum = 0.f;
-    }
-    const bool col_ok = j < Tb;
-    const bool full = rows == kBlkHalf && j0 + kScoreTile - 1 <= pos0;  // below the causal diagonal of every row
-    // One query head against the wave's key columns.  MASKED: the tile touches the causal diagonal or the end of
-    // the sequence, or the half is short, so every probability is checked against its row; all other tiles take
-    // the plain path.
-    auto head_block = [&](auto masked_tag) {
-      constexpr bool MASKED = decltype(masked_tag)::value;
-      // Row r of the half (without the lane group's offset kg*4) counts for this lane's column iff
-      // row_min <= r < row_end: the row exists (r + kg*4 < rows) and sees the column (j <= pos0 + r + kg*4).
-      int row_min = col_ok ? j - pos0 - kg * 4 : (1 << 30);
-      int row_end = rows - kg * 4;
-      if (MASKED) asm volatile("" : "+v"(row_min), "+v"(row_end));
-#pragma unroll
-      for (int rbl = 0; rbl < 2; ++rbl) {
-        const int rb = rh * 2 + rbl;
-        Frag<T, D> qf;
-        frag_from(qf, stage + rb * 32 * RBt);
-        // the accumulators start at the rows' biases, so that the products come out as log2 p / c
-        f32x16_t acc;
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 b4 = *reinterpret_cast<const float4*>(st + rb * 32 + r4 * 8 + kg * 4);
-          acc[r4 * 4 + 0] = b4.x;
-          acc[r4 * 4 + 1] = b4.y;
-          acc[r4 * 4 + 2] = b4.z;
-          acc[r4 * 4 + 3] = b4.w;
-        }
-        mma<T, D>(acc, qf, kf);
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int row0 = rb * 32 + r4 * 8 + kg * 4;  // rows of acc[r4*4 .. r4*4+3]
-          const float4 c4 = *reinterpret_cast<const float4*>(st + coef_plane * kBlkHalf + row0);
-          const float cc[4] = {c4.x, c4.y, c4.z, c4.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float e = fast_exp2(acc[r4 * 4 + i] * a.c);
-            // rows past the block carry another row's bias and weight (finite): the select drops them
-            if (MASKED) e = (rb * 32 + r4 * 8 + i >= row_min && rb * 32 + r4 * 8 + i < row_end) ? e : 0.f;
-            colsum += e;
-            pbar[hf][rbl][r4 * 4 + i] = fmaf(e, cc[i], pbar[hf][rbl][r4 * 4 + i]);
+  // The row blocks bi_beg .. bi_end-1.  MASKED: they touch the causal diagonal, the end of the sequence or the first
+  // scoring row, so every probability is checked against its row; the others take the plain walk.  (Two loops: a branch
+  // inside one made the compiler copy all accumulators around it.)
+  auto walk = [&](int bi_beg, int bi_end, auto masked_tag) {
+    constexpr bool MASKED = decltype(masked_tag)::value;
+    for (int bi = bi_beg; bi < bi_end; ++bi) {
+      const int Tb = a.Tk - bi * kBlkRows, Wb = min(kBlkRows, a.q_rows - bi * kBlkRows);
+      const bool col_ok = j < Tb;
+      int g = 0, hg = 0;
+      for (int h = 0; h < a.Hq; ++h) {
+        const bool last_of_group = hg == a.G - 1;
+        auto half = [&](auto hf_tag) {  // hf is a compile-time constant so that pbar stays in registers
+          constexpr int hf = decltype(hf_tag)::value;
+          async_copy_wait<0>();  // this wave's pieces of the half have landed
+          __syncthreads();       // every wave's have; and nobody reads the other stage (the previous half) any more
+          flush_pending();
+          if (hf == 0)
+            issue(bi, h, 1, false);
+          else if (h + 1 < a.Hq)
+            issue(bi, h + 1, 0, last_of_group);
+          else if (bi + 1 < n_bi)
+            issue(bi + 1, 0, 0, true);
+          if (hf == 0 && hg == 0) {
+            frag_from_tile(kf, smem + CT::bytes(32) * cw, fbase);  // the key tile of this kv head
+            colsum = 0.f;
           }
+          const char* stage = smem + kTileBytes + hf * kStageBytes;
+          const float* st = reinterpret_cast<const float*>(stage + kTileBytes);
+          const int rows = min(kBlkHalf, Wb - hf * kBlkHalf);  // rows the half really has (may be <= 0)
+          // Row r of the half (without the lane group's offset kg*4) counts for this lane's column iff row_min <= r < row_end:
+          // the row exists (r + kg*4 < rows) and sees the column (j <= position of the half's first row + r + kg*4).
+          int row_min = col_ok ? j - (Tb - Wb + hf * kBlkHalf) - kg * 4 : (1 << 30);
+          int row_end = rows - kg * 4;
+          if (MASKED) asm volatile("" : "+v"(row_min), "+v"(row_end));
+          static_for<F>([&](auto f_tag) {
+            constexpr int f = decltype(f_tag)::value;
+            const int rb = rh * F + f;
+            Frag<T, D> qf;
+            frag_from_tile(qf, stage + CT::bytes(32) * rb, fbase);
+            // the accumulators start at the rows' biases, so that the products come out as log2 p / c
+            f32x16_t acc;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+              const float4 b4 = *reinterpret_cast<const float4*>(st + rb * 32 + r4 * 8 + kg * 4);
+              acc[r4 * 4 + 0] = b4.x;
+              acc[r4 * 4 + 1] = b4.y;
+              acc[r4 * 4 + 2] = b4.z;
+              acc[r4 * 4 + 3] = b4.w;
+            }
+            // the weight of the row of register n % 16: a row is of one modality, so one of its two weights is zero
+            const int row = rb * 32 + acc_row(n & 15, kg);
+            const float coef = st[kBlkHalf + row] + st[2 * kBlkHalf + row];
+            mma<T, D>(acc, qf, kf);
+            static_for<4>([&](auto r4_tag) {
+              constexpr int r4 = decltype(r4_tag)::value;
+              float e[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                e[i] = fast_exp2(acc[r4 * 4 + i] * a.c);
+                // rows past the block carry another row's bias and weight (finite): the select drops them
+                if (MASKED) e[i] = (rb * 32 + r4 * 8 + i >= row_min && rb * 32 + r4 * 8 + i < row_end) ? e[i] : 0.f;
+                colsum += e[i];
+              }
+              float* pb = &pbar[hf][f][r4 * 4];
+              fma_rows4<r4 * 4>(pb[0], pb[1], pb[2], pb[3], coef, e[0], e[1], e[2], e[3]);
+            });
+          });
+        };
+        half(std::integral_constant<int, 0>{});
+        half(std::integral_constant<int, 1>{});
+        if (last_of_group) {  // the kv head is complete for this row block
+          const int buf = (bi * a.Hkv + g) & 1;  // written again two kv heads later, read after the next barrier
+          const float tot = colsum + __shfl_xor(colsum, 32, kWave);
+          if (rh == 1 && kg == 0) colred[buf * kScoreTile + cw * 32 + n] = tot;
+          pending = tot;
+          pending_g = g++;
+          pending_buf = buf;
+          hg = 0;
+        } else {
+          ++hg;
         }
       }
-    };
-    if (full)
-      head_block(std::false_type{});
-    else
-      head_block(std::true_type{});
-
-    if (hf == 1 && hg == a.G - 1) {  // the kv head is complete for this row block
-      const int buf = (bi * a.Hkv + g) & 1;  // written again two kv heads later, read after the next barrier
-      const float tot = colsum + __shfl_xor(colsum, 32, kWave);
-      if (rh == 1 && kg == 0) colred[buf * kScoreTile + cw * 32 + n] = tot;
-      pending = tot;
-      pending_g = g;
-      pending_buf = buf;
-    }
-    if (hf == 1 && h == a.Hq - 1) {
-      // entropy terms of the head-averaged cross-modal probabilities of this row block.  A vision column only
-      // receives probability from text rows (text -> vision direction) and a text column only from vision rows.
+      // Entropy terms of the head-averaged cross-modal probabilities of this row block: text rows on vision keys, vision
+      // rows on text keys (what a row gathered over keys of its own modality is dropped here).
       const float inv_heads = 1.0f / (float)a.Hq;
       float s = 0.f;
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
+      for (int i = 0; i < 2 * F; ++i) {
+        const int hf = i / F, f = i % F, row0 = hf * kBlkHalf + (rh * F + f) * 32;
+        const unsigned rows_vision = (unsigned)__ballot(mask[Tb - Wb + min(row0 + n, Wb - 1)] != 0);
 #pragma unroll
-        for (int rbl = 0; rbl < 2; ++rbl)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float p = pbar[f][rbl][r] * inv_heads;
-            s += (p > 0.f) ? p * __logf(p) : 0.f;
-            pbar[f][rbl][r] = 0.f;
-          }
+        for (int r = 0; r < 16; ++r) {
+          const bool row_is_vision = ((rows_vision >> acc_row(r, kg)) & 1u) != 0;
+          const float p = pbar[hf][f][r] * inv_heads;
+          const float t = p * __logf(p);  // (no branch around the logarithm)
+          s += (p > 0.f) & (row_is_vision != col_is_vision) ? t : 0.f;
+          pbar[hf][f][r] = 0.f;
+        }
+      }
       ent -= (double)s;
     }
   };
-
-  issue(0);
-  for (int hh = 0; hh < n_bi * a.Hq; ++hh) {
-    half_item(hh, std::integral_constant<int, 0>{});
-    half_item(hh, std::integral_constant<int, 1>{});
-  }
+  // plain row blocks: complete ones whose first row lies below the tile's last key (the position falls with bi)
+  const int n_plain = max(0, min(min(n_bi, a.q_rows / kBlkRows), (a.Tk - (j0 + kScoreTile - 1)) / kBlkRows));
+  issue(0, 0, 0, true);
+  walk(0, n_plain, std::false_type{});
+  walk(n_plain, n_bi, std::true_type{});
   __syncthreads();
   flush_pending();
   const double tv = wave_sum(col_is_vision ? ent : 0.0);

@@ -13,22 +13,15 @@ namespace meda {
 // operand B, so a lane owns one query row and 16 keys per block: the running (max, Z_vision, Z_text)
 // of the row live in three registers per fragment and need no cross-lane traffic until the end.
 //
-// Two ways of bringing the key tiles into LDS.  Through registers (DMA false): the next tile is fetched into registers
-// while the current one is processed, and written to a padded LDS tile between two barriers.  By asynchronous
-// global-to-LDS copies (DMA true, rows of at most 256 bytes): two unpadded, xor-swizzled tiles (swizzle_of_row in
-// device_utils.hpp); the copies of tile t+1 are issued when tile t starts, one wait and one barrier per tile, no
-// staging registers; the modality bits of a tile's keys are ballots of two bytes per lane that every wave loads for
-// itself one tile ahead.  The arithmetic is the same instruction for instruction, so the results are bit-identical.
-template <typename T, int D, int NQ, int NW, bool BLOCKS, bool DMA>
+// The next tile is fetched into registers while the current one is processed, and written to a padded LDS tile between
+// two barriers.  Grouped heads and the row-block mode, with rows of at most 256 bytes, go to score_stats_dma.hip.
+template <typename T, int D, int NQ, int NW, bool BLOCKS>
 __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2) ? 3 : 2) score_stats_kernel(ScoreArgs a) {
   using TL = Tile<T, D>;
-  constexpr int RBt = TL::kRowBytes;
-  constexpr int CPR = TL::kChunksPerRow;
   constexpr int NC = TL::kFragChunks;
-  constexpr int kTileBytes = kScoreTile * RBt;
   extern __shared__ __align__(16) char smem[];
   char* ktile = smem;
-  uint8_t* lmask = reinterpret_cast<uint8_t*>(smem + kScoreTile * TL::kStride);  // (DMA false)
+  uint8_t* lmask = reinterpret_cast<uint8_t*>(smem + kScoreTile * TL::kStride);
 
   const int ch = blockIdx.x, l = blockIdx.z;
   int g = blockIdx.y, bi = 0;
@@ -81,75 +74,30 @@ __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2
   const char* kbase = a.k + (size_t)(l * a.Hkv + g) * a.Tk * TL::kRowBytes;
   float* invn_out = a.inv_norm + (size_t)(l * a.Hkv + g) * a.Tk;
 
-  TileStage<T, D, DMA ? 1 : kScoreTile, nthr> stage;
+  TileStage<T, D, kScoreTile, nthr> stage;
   uint8_t mreg = 0;
-  // DMA: copy instruction c of this wave fills the rows (wave * PF + c) * RPI .. + RPI-1 of a tile, this lane brings
-  // one 16-byte chunk; rows past the end of the sequence repeat the last key (their columns are masked below)
-  constexpr int RPI = 64 / CPR;
-  constexpr int PF = DMA ? kScoreTile / RPI / NW : 1;
-  static_assert(!DMA || (64 % CPR == 0 && kScoreTile % (RPI * NW) == 0), "the copy instructions must tile a tile evenly");
-  unsigned crow[PF], cchunk[PF], coff[NC];
-  uint8_t mk0 = 0, mk1 = 0;            // modality bytes of the keys lane and 64 + lane of the next tile
-  unsigned long long cur0 = 0, cur1 = 0;  // modality bits of the current tile's keys 0..63 and 64..127
-  const unsigned lds0 = (unsigned)(size_t)smem;
-  const char* kbase_u = uniform_ptr(kbase);
-  auto issue = [&](int jt, int slot) {
-#pragma unroll
-    for (int c = 0; c < PF; ++c)
-      async_copy16_to_lds_stream(kbase_u, (unsigned)min(jt + (int)crow[c], a.T - 1) * RBt + cchunk[c],
-                                 lds0 + (unsigned)(slot * kTileBytes + (wave * PF + c) * 1024));
-    mk0 = (jt + lane < a.T) ? mask[jt + lane] : 0;
-    mk1 = (jt + 64 + lane < a.T) ? mask[jt + 64 + lane] : 0;
-  };
-  if (DMA) {
-#pragma unroll
-    for (int c = 0; c < PF; ++c) {
-      crow[c] = (unsigned)((wave * PF + c) * RPI + lane / CPR);
-      cchunk[c] = (unsigned)(((lane % CPR) ^ swizzle_of_row<T, D>((int)crow[c])) * 16);
-    }
-    // chunk c of this lane's fragment (chunk kg * NC + c of row n of a 32-row block)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) coff[c] = (unsigned)(n * RBt + (((kg * NC + c) ^ swizzle_of_row<T, D>(n)) * 16));
-    if (jbeg < jend) issue(jbeg, 0);
-  } else if (jbeg < jend) {
+  if (jbeg < jend) {
     stage.template fetch<true>(kbase + (size_t)jbeg * TL::kRowBytes, min(kScoreTile, a.T - jbeg), tid, nthr);
     if (tid < kScoreTile) mreg = (jbeg + tid < a.T) ? mask[jbeg + tid] : 0;
   }
-  int slot = 0;
-  for (int j0 = jbeg; j0 < jend; j0 += kScoreTile, slot ^= 1) {
+  for (int j0 = jbeg; j0 < jend; j0 += kScoreTile) {
     const int rows_valid = min(kScoreTile, a.T - j0);
-    if (DMA) {
-      async_copy_wait<0>();  // this wave's pieces of the tile have landed
-      __syncthreads();       // every wave's have; and nobody reads the other tile (the previous one) any more
-      cur0 = __ballot(mk0 != 0);
-      cur1 = __ballot(mk1 != 0);
-      if (j0 + kScoreTile < jend) issue(j0 + kScoreTile, slot ^ 1);
-      ktile = smem + slot * kTileBytes;
-    } else {
-      __syncthreads();  // the previous tile is no longer read
-      stage.commit(ktile, tid, nthr);
-      if (tid < kScoreTile) lmask[tid] = mreg;
-      __syncthreads();
-      if (j0 + kScoreTile < jend) {  // next tile's loads are in flight while this one is processed
-        const int jn = j0 + kScoreTile;
-        stage.template fetch<true>(kbase + (size_t)jn * TL::kRowBytes, min(kScoreTile, a.T - jn), tid, nthr);
-        if (tid < kScoreTile) mreg = (jn + tid < a.T) ? mask[jn + tid] : 0;
-      }
+    __syncthreads();  // the previous tile is no longer read
+    stage.commit(ktile, tid, nthr);
+    if (tid < kScoreTile) lmask[tid] = mreg;
+    __syncthreads();
+    if (j0 + kScoreTile < jend) {  // next tile's loads are in flight while this one is processed
+      const int jn = j0 + kScoreTile;
+      stage.template fetch<true>(kbase + (size_t)jn * TL::kRowBytes, min(kScoreTile, a.T - jn), tid, nthr);
+      if (tid < kScoreTile) mreg = (jn + tid < a.T) ? mask[jn + tid] : 0;
     }
 
     // 1/|k| of the tile's keys: two threads per row (the first row block sees every key; the others skip this)
     for (int row = tid >> 1; bi == 0 && row < kScoreTile; row += nthr >> 1) {
       float ss = 0.f;
-      if (DMA) {
+      const uint4* p = reinterpret_cast<const uint4*>(ktile + row * TL::kStride + (tid & 1) * TL::kHalfBytes);
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
-          ss += chunk_sumsq<T>(*reinterpret_cast<const uint4*>(
-              ktile + row * RBt + ((((tid & 1) * NC + i) ^ swizzle_of_row<T, D>(row)) * 16)));
-      } else {
-        const uint4* p = reinterpret_cast<const uint4*>(ktile + row * TL::kStride + (tid & 1) * TL::kHalfBytes);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) ss += chunk_sumsq<T>(p[i]);
-      }
+      for (int i = 0; i < NC; ++i) ss += chunk_sumsq<T>(p[i]);
       ss += __shfl_xor(ss, 1, kWave);
       if ((tid & 1) == 0 && row < rows_valid) invn_out[j0 + row] = 1.0f / fmaxf(sqrtf(ss), 1e-30f);
     }
@@ -158,15 +106,8 @@ __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2
       const int jb = j0 + sb * 32;
       if (jb >= a.T || (BLOCKS && jb > wave_last)) break;  // past the sequence, or past every row of this wave
       Frag<T, D> kf;
-      uint32_t mword;
-      if (DMA) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) kf.c[c] = *reinterpret_cast<const uint4*>(ktile + sb * 32 * RBt + coff[c]);
-        mword = (uint32_t)((sb & 2 ? cur1 : cur0) >> ((sb & 1) * 32));
-      } else {
-        frag_load(kf, ktile + (sb * 32 + n) * TL::kStride, kg);
-        mword = (uint32_t)__ballot(lmask[sb * 32 + n] != 0);
-      }
+      frag_load(kf, ktile + (sb * 32 + n) * TL::kStride, kg);
+      const uint32_t mword = (uint32_t)__ballot(lmask[sb * 32 + n] != 0);
       const bool tail = jb + 31 >= a.T;  // the block runs past the end of the sequence
       const bool one_modality = mword == 0u || mword == 0xffffffffu;
       const bool full_all = jb + 31 <= a.T - a.W;  // every key of the block is visible to every row of the window
@@ -340,10 +281,10 @@ __global__ void __launch_bounds__(kCombineThreads) stats_combine_kernel(ScoreArg
 
 // ------------------------------------------------------------------------------------------ launch
 
-template <typename T, int D, int NQ, int NW, bool BLOCKS, bool DMA>
+template <typename T, int D, int NQ, int NW, bool BLOCKS>
 static hipError_t launch_stats_b(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  const size_t lds = DMA ? 2 * (size_t)kScoreTile * Tile<T, D>::kRowBytes : (size_t)kScoreTile * Tile<T, D>::kStride + kScoreTile;
-  auto kern = score_stats_kernel<T, D, NQ, NW, BLOCKS, DMA>;
+  const size_t lds = (size_t)kScoreTile * Tile<T, D>::kStride + kScoreTile;
+  auto kern = score_stats_kernel<T, D, NQ, NW, BLOCKS>;
   if (lds > 64 * 1024) {
     hipError_t e = allow_dynamic_lds(kern, (int)lds);
     if (e != hipSuccess) return e;
@@ -355,15 +296,12 @@ static hipError_t launch_stats_b(const Plan& p, const ScoreArgs& a, hipStream_t 
 
 template <typename T, int D, int NQ, int NW>
 static hipError_t launch_stats_w(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  // Asynchronous copies where the pass is not already at the memory's rate: grouped heads, and every prompt row
-  // scoring.  With one query head per kv head and a window of 32 rows the pass streams the keys at the rate a plain
-  // read reaches, and three workgroups per CU of the small register-staged form do that best.
-  constexpr bool kCanDma = Tile<T, D>::kRowBytes <= 256;
-  if constexpr (kCanDma) {
-    if (p.blocks) return launch_stats_b<T, D, NQ, NW, true, true>(p, a, s);
-    if (p.G >= 2) return launch_stats_b<T, D, NQ, NW, false, true>(p, a, s);
+  // With one query head per kv head and a window the pass streams the keys at the rate a plain read reaches, and three
+  // workgroups per CU of the small register-staged form do that best; rows of 512 bytes take it in every mode.
+  if constexpr (Tile<T, D>::kRowBytes > 256) {
+    if (p.blocks) return launch_stats_b<T, D, NQ, NW, true>(p, a, s);
   }
-  return p.blocks ? launch_stats_b<T, D, NQ, NW, true, false>(p, a, s) : launch_stats_b<T, D, NQ, NW, false, false>(p, a, s);
+  return launch_stats_b<T, D, NQ, NW, false>(p, a, s);
 }
 
 template <typename T, int D, int NQ>
@@ -376,11 +314,13 @@ static hipError_t launch_stats_d(const Plan& p, const ScoreArgs& a, hipStream_t 
   switch (p.NQ) {
     case 1: return launch_stats_t<T, D, 1>(p, a, s);
     case 2: return launch_stats_t<T, D, 2>(p, a, s);
+    case 3: return launch_stats_t<T, D, 3>(p, a, s);
     default: return launch_stats_t<T, D, 4>(p, a, s);
   }
 }
 
 hipError_t launch_score_stats(const Plan& p, const Buffers& b, hipStream_t s) {
+  if (score_stats_dma_supported(p)) return launch_score_stats_dma(p, b, s);
   const ScoreArgs a = make_args(p, b, true);
   if (p.dtype == MEDA_BF16) return p.d == 128 ? launch_stats_d<bf16_t, 128>(p, a, s) : launch_stats_d<bf16_t, 64>(p, a, s);
   return p.d == 128 ? launch_stats_d<float, 128>(p, a, s) : launch_stats_d<float, 64>(p, a, s);
