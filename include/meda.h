@@ -100,7 +100,7 @@ size_t meda_workspace_bytes(const meda_params* params);
  * ABSOLUTE offsets (layer_off[n][0] = n*B, layer_off[n][L] = (n+1)*B), so the slices of sequence n can be
  * handed to meda_decode_attention as they are; entropy [N][L]; sel_idx [N*B*Hkv]; merge_assign [N][L][Hkv][T].
  * The result of every sequence is that of a call of its own up to the rounding of fp32 sums: into how many chunks the
- * keys are cut for the row statistics, and which similarity kernel runs, follows the size of the whole batch.
+ * keys are cut for the row statistics, and which scoring and similarity kernels run, follows the size of the whole batch.
  */
 meda_status meda_compress(const meda_params* params, const void* q_win, const void* k, const void* v,
                           const uint8_t* modality, void* k_out, void* v_out, int32_t* layer_len,

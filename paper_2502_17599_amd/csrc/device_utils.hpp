@@ -300,4 +300,29 @@ __device__ __forceinline__ void fma_rows4(float& p0, float& p1, float& p2, float
       : "v"(y), "v"(e0), "v"(e1), "v"(e2), "v"(e3), "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3));
 }
 
+// The value of another lane of the same 16 lanes (or its mirror image), as an operand of the instruction that uses it.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+// Sums 16 values per lane over the 32 lanes of each half of the wave: lane n of a half ends with the sum of v[n / 2].
+// A reduce-scatter: each exchange halves the values a lane is responsible for (the upper lanes of a pair keep the upper
+// half); the pairs are 16, 8, 4 (mirrored inside 8 lanes) and 2 apart, the last exchange adds the two lanes of a value.
+__device__ __forceinline__ float reduce_lanes32(const float (&v)[16], int lane) {
+  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4e, kXor1 = 0xb1;
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    a[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0, up2 = (lane & 2) != 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = (up8 ? a[i + 4] : a[i]) + dpp_move<kRor8>(up8 ? a[i] : a[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = (up4 ? b[i + 2] : b[i]) + dpp_move<kHalfMirror>(up4 ? b[i] : b[i + 2]);
+  const float d = (up2 ? c[1] : c[0]) + dpp_move<kXor2>(up2 ? c[0] : c[1]);
+  return d + dpp_move<kXor1>(d);
+}
+
 }  // namespace meda

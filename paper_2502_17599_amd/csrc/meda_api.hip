@@ -9,6 +9,16 @@
 
 namespace meda {
 
+// Which windows go to the direct scoring kernels: those with few column tiles of 128 keys over all layers.  Both passes
+// and the merge of the statistics, in us (kernels over LDS tiles / direct), 60 to 120 shapes at each number of tiles:
+//   6 tiles   geometric mean of the ratio 1.87 (2 layers of 300, 8 heads per kv head, fp32: 139 / 45)
+//   16        1.68 (2 layers of 1024 keys, 28 heads, bf16: 49 / 42), 32  1.67, 64  1.51 (0.95 at worst)
+//   128       1.10: 0.73 to 1.04 for few heads and grouped bf16 rows of 256 bytes, 1.03 to 1.6 for the others
+//   256       0.79 (a tile of 128 keys shares what a workgroup of 32 keys reads again), 512  0.69
+// A sequence of a small batch goes the way it would go alone, so that its sums are the same.
+constexpr int64_t kDirectTiles = 64, kDirectTilesAll = 128;
+constexpr int kDirectManyHeads = 28;
+
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Tiling of the two scoring passes for w query rows (the last w positions) of a sequence of t keys.  With
@@ -101,6 +111,24 @@ meda_status make_plan(const meda_params* p, Plan* out) {
   pl.accumulate = 0;
   const int w_score = (pl.blocks || pl.R > kScoreRowBlock) ? kScoreRowBlock : pl.R;
   if (!score_geometry(&pl, pl.T, w_score, pl.R, pl.blocks)) return MEDA_ERR_UNSUPPORTED;
+  // Few column tiles over all layers: the kernels that cut the work finer (score_direct.hip).
+  const bool direct_fits = !pl.blocks && pl.Hq * (pl.RB * 384 + 128) <= 130944;  // its LDS
+  const bool many_heads = pl.Hq >= kDirectManyHeads && (pl.G == 1 || pl.d == 64 || pl.dtype == MEDA_F32);
+  const int64_t seq_tiles = (int64_t)pl.NT * pl.Lseq, all_tiles = (int64_t)pl.NT * pl.L;
+  pl.direct = direct_fits && all_tiles <= kDirectTilesAll && (many_heads || seq_tiles <= kDirectTiles) ? 1 : 0;
+  if (pl.direct) {
+    const int tiles = (pl.T + 31) / 32;
+    pl.NTk = tiles;
+    // chunks of pass A: about 2048 waves for one sequence (the sums of a sequence then do not depend on the batch), at
+    // most kDirParts partials per row
+    const int64_t waves = (int64_t)pl.Lseq * pl.Hq * pl.RB;
+    int64_t chunks = (2048 + waves - 1) / waves;
+    if (chunks > kDirParts) chunks = kDirParts;
+    if (chunks > tiles) chunks = tiles;
+    pl.CH = (int)((tiles + chunks - 1) / chunks) * 32;
+    pl.NCH = (pl.T + pl.CH - 1) / pl.CH;
+    pl.NPART = pl.NCH;
+  }
   const size_t stats_rows = pl.blocks ? (size_t)pl.R : (size_t)pl.Wp;
 
   pl.n_less_total = (size_t)((int64_t)pl.L * pl.T - pl.B) * pl.Hkv;

@@ -16,6 +16,7 @@ constexpr int kSimWaves = 4;
 constexpr int kSimRows = kSimRowsPerWave * kSimWaves;  // less-important rows per workgroup
 constexpr int kSimSlotTile = 64;                       // conserved slots staged in LDS per step
 constexpr int kMaxLayers = 256;
+constexpr int kDirParts = 16;    // statistics partials per row of the direct scoring kernels, at most
 constexpr int kScoreRowBlock = 128;  // query rows per row block of pass B when every prompt row scores
 
 struct Plan {
@@ -43,9 +44,10 @@ struct Plan {
   int Tb, Wb;        // keys and query rows of the scoring launch (T and W; in the row-block mode: T and 128)
   int R;             // scoring rows in total; rows per (layer, head) in the query buffer
   int blocks;        // row-block mode
+  int direct;        // both scoring passes by the kernels for few keys (score_direct.hip)
   int Tk;            // key rows per (layer, kv head) in memory (T of the whole sequence)
   int q_row0;        // first row of the block inside the query buffer
-  int NTk;           // column tiles of the whole sequence (stride of the per-tile entropy partials)
+  int NTk;           // entropy partials per layer: column tiles of the whole sequence (of 32 keys with `direct`)
   int accumulate;    // add to column scores / entropy partials instead of storing (every block but the first)
   // workspace regions (byte offsets)
   size_t off_stats_part, off_stats, off_inv_norm, off_col_scores, off_ent_part, off_alloc, off_layer_off,

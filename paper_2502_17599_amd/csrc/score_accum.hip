@@ -273,6 +273,7 @@ static hipError_t launch_accum_d(const Plan& p, const ScoreArgs& a, hipStream_t 
 }
 
 hipError_t launch_score_accum(const Plan& p, const Buffers& b, hipStream_t s) {
+  if (p.direct) return launch_score_accum_direct(p, b, s);
   if (score_accum_blocks_supported(p)) return launch_score_accum_blocks(p, b, s);
   if (score_accum_dma_supported(p)) return launch_score_accum_dma(p, b, s);
   const ScoreArgs a = make_args(p, b);

@@ -175,6 +175,10 @@ inline ScoreArgs make_args(const Plan& p, const Buffers& b, bool pass_a = false)
   return a;
 }
 
+// Both passes for windows over few keys (score_direct.hip); the statistics are merged by pass B itself.
+hipError_t launch_score_stats_direct(const Plan& p, const Buffers& b, hipStream_t s);
+hipError_t launch_score_accum_direct(const Plan& p, const Buffers& b, hipStream_t s);
+
 // Pass A for grouped heads and the row-block mode, fed by asynchronous copies (score_stats_dma.hip).
 bool score_stats_dma_supported(const Plan& p);
 hipError_t launch_score_stats_dma(const Plan& p, const Buffers& b, hipStream_t s);

@@ -320,6 +320,7 @@ static hipError_t launch_stats_d(const Plan& p, const ScoreArgs& a, hipStream_t 
 }
 
 hipError_t launch_score_stats(const Plan& p, const Buffers& b, hipStream_t s) {
+  if (p.direct) return launch_score_stats_direct(p, b, s);
   if (score_stats_dma_supported(p)) return launch_score_stats_dma(p, b, s);
   const ScoreArgs a = make_args(p, b, true);
   if (p.dtype == MEDA_BF16) return p.d == 128 ? launch_stats_d<bf16_t, 128>(p, a, s) : launch_stats_d<bf16_t, 64>(p, a, s);
@@ -327,6 +328,7 @@ hipError_t launch_score_stats(const Plan& p, const Buffers& b, hipStream_t s) {
 }
 
 hipError_t launch_stats_combine(const Plan& p, const Buffers& b, hipStream_t s) {
+  if (p.direct) return hipSuccess;  // pass B merges the partials itself
   const ScoreArgs a = make_args(p, b);
   const int total = p.L * p.Hq * (p.blocks ? p.R : p.Wp);
   if (a.NPART > kCombineDirect && a.NPART <= kCombineStaged) {
