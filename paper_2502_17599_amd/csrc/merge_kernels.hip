@@ -38,9 +38,9 @@ __device__ __forceinline__ size_t less_base_of(int l, int g, int T, int Hkv, lon
 }
 
 // ------------------------------------------------------------------------ similarity + argmax
-// Small problems go to the direct kernel (direct_pays).  Of the others, bf16 layers whose conserved set fits into LDS go
-// to the resident-set kernel (one workgroup of 8 waves per (layer, head) part, all 160 KB of LDS), the rest to the tiled
-// kernel; both are launched and every workgroup looks up its layer's budget.
+// fp32 keys go to the split kernel.  bf16: small problems go to the direct kernel; of the others, layers whose conserved
+// set fits into LDS go to the resident-set kernel (one workgroup of 8 waves per (layer, head) part, all 160 KB of LDS),
+// the rest to the tiled kernel; both are launched and every workgroup looks up its layer's budget.
 constexpr int kResWaves = 8;
 constexpr int kResThreads = kResWaves * 64;
 constexpr int kResLdsBytes = 160 * 1024;
@@ -431,9 +431,9 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
 // Direct kernel: no conserved set in LDS, no packed copy.  grid over (row block of 32 F, kv head, layer), XCD-aware
 // as the tiled kernel; the NW waves of a workgroup take the same 32 F rows and every NW-th block of 32 conserved keys,
 // whose fragments come from the key cache itself (L2), one block ahead; the waves' bests are merged at the end.
-// For problems that leave CUs empty with 256 rows per workgroup, where the serial chain of one wave bounds the kernel
-// (8 pairs of 1024 positions, fp32: 27 + 6 us for packing -> 9.6 us).  Every 32 F rows read the whole set again, eight
-// (four) times as often as in the tiled kernel, so with the chip full it loses: see direct_pays.
+// For problems that leave CUs empty with 256 rows per workgroup, where the serial chain of one wave bounds the kernel.
+// Every 32 rows read the whole set again, eight times as often as in the tiled kernel, so with the chip full it loses:
+// see kSimDirectGroups.
 template <typename T, int D, int F, int NW>
 __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs a) {
   using TL = Tile<T, D>;
@@ -527,6 +527,263 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
     }
     a.less_slot[lbase + row_base + tid] = slot;
     if (a.merge_assign) a.merge_assign[less[row_base + tid]] = slot;
+  }
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs in launch order: all row blocks of one (layer, head) run on the same XCD
+// (they stream the same conserved keys and then share one L2), consecutive pairs go to different XCDs; the last pairs,
+// fewer than 8, are spread over all XCDs, which would otherwise wait for the few that had one pair more.
+__device__ __forceinline__ void pair_and_row_block(unsigned block, unsigned pairs, unsigned row_blocks, unsigned& pair, unsigned& rblock) {
+  const unsigned full = pairs & ~7u;
+  if (block < full * row_blocks) {
+    const unsigned seq = block >> 3;
+    pair = (block & 7u) + 8u * (seq / row_blocks);
+    rblock = seq % row_blocks;
+  } else {
+    const unsigned r = block - full * row_blocks, rest = pairs - full;
+    pair = full + r % rest;
+    rblock = r / rest;
+  }
+}
+
+// ------------------------------------------------------------------------ fp32 keys in three bf16 parts
+// x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m, each rounded to nearest: 8 + 8 + 8 significant bits hold
+// all 24 of x, and every subtraction is exact.  Two elements per call; `rest` collects what is left, which is a NaN where
+// x has no such parts (infinite, NaN, or so large that h overflows) and a small number everywhere else.
+__device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& m, unsigned& l, float& rest) {
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  auto pack = [](float p, float q) { return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2_t){p, q}, bf16x2_t)); };
+  h = pack(x, y);
+  x -= __uint_as_float(h << 16);
+  y -= __uint_as_float(h & 0xffff0000u);
+  m = pack(x, y);
+  x -= __uint_as_float(m << 16);
+  y -= __uint_as_float(m & 0xffff0000u);
+  l = pack(x, y);
+  rest += x;
+  rest += y;
+}
+// 8 consecutive elements: one 16-byte chunk of each part.
+__device__ __forceinline__ void split8(const uint4& a, const uint4& b, uint4 (&part)[3], float& rest) {
+  const unsigned x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  unsigned h[4], m[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) split2(__uint_as_float(x[2 * i]), __uint_as_float(x[2 * i + 1]), h[i], m[i], l[i], rest);
+  part[0] = make_uint4(h[0], h[1], h[2], h[3]);
+  part[1] = make_uint4(m[0], m[1], m[2], m[3]);
+  part[2] = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// Split kernel: fp32 keys on the bf16 matrix instructions.  A product of two keys is h h' + (h m' + m h') + (m m' + h l' +
+// l h') of their parts, added from the smallest terms to the largest in the fp32 accumulator; the three products left out
+// are below 2^-26 of the keys' lengths.  6 x 32 matrix clocks per 32 x 32 x 16 products instead of 512, and a sixteenth of
+// the fp32 instruction's roundings at the size of the result: keys that differ by 3e-4 of their size, so that the
+// similarities differ in their last bits, lose 6 to 14 % less against the nearest key in float64 than with that
+// instruction (mean loss 2.0e-8 to 3.0e-8 against 2.3e-8 to 3.4e-8).
+// grid over (row block of 32 F NW / SW, kv head, layer); a wave keeps F fragments of 32 less-important rows split in
+// registers, SW waves share the same rows and take every SW-th block of a tile; the conserved keys come from the key cache
+// in tiles: a thread loads its pieces of the next tile before it multiplies the present one, splits them after it and
+// stores the parts into the other of two LDS tiles (one barrier per tile).
+// Bound by the bf16 matrix instructions where the sets are long (256 pairs of 3126, a third kept: 1.97 PFLOP/s), by the
+// first loads and the splitting of rows and tiles where they are short.  Against the direct and tiled kernels with the
+// fp32 instruction that this replaces: 256 pairs of 1024 110 -> 40 us, of 3126 487 -> 222, 1024 of 969 (rows of 512 bytes) 737 -> 353.
+template <int D, int SW>
+struct SplitTile {
+  static constexpr int kSlots = SW > 2 ? 32 * SW : 64;
+  static constexpr int kPart = D * 2;             // bytes of one part of a key
+  static constexpr int kStride = 3 * kPart + 16;  // three parts and padding: bank pattern as Tile<bf16_t, D>::kStride
+  static constexpr int kTileBytes = kSlots * kStride;
+  static constexpr int kLdsBytes = 2 * kTileBytes + 2 * kSlots * (int)sizeof(float) + 16;
+};
+
+template <int D, int F, int NW, int SW>
+__global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs a) {
+  using TF = Tile<float, D>;
+  using ST = SplitTile<D, SW>;
+  constexpr int kSplitSlots = ST::kSlots;
+  constexpr int kRows = 32 * F * NW / SW;
+  constexpr int NT = NW * 64;
+  constexpr int NC = D / 16;                     // chunks per lane, fragment and part
+  constexpr int GPR = D / 8;                     // pieces of 8 elements per key
+  constexpr int NG = kSplitSlots * GPR / NT;     // pieces per thread and tile
+  static_assert(NG * NT == kSplitSlots * GPR, "the pieces of a tile must come out even");
+  extern __shared__ __align__(16) char smem[];
+  float* inv_lds = reinterpret_cast<float*>(smem + 2 * ST::kTileBytes);  // [2][kSplitSlots]
+  int* bad_lds = reinterpret_cast<int*>(inv_lds + 2 * kSplitSlots);
+
+  unsigned pair, rblock;
+  pair_and_row_block(blockIdx.x, (unsigned)(a.L * a.Hkv), (a.T + kRows - 1) / kRows, pair, rblock);
+  const int l = a.alloc[4 * (pair / a.Hkv) + 3], g = pair % a.Hkv;  // layers by decreasing budget
+  const int S = a.alloc[4 * l];
+  const int n_less = a.T - S;
+  const int row_base = rblock * kRows;
+  if (row_base >= n_less) return;
+
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long long off_l = a.off[l];
+  const size_t cbase = (size_t)off_l * a.Hkv + (size_t)g * S;
+  const int32_t* sel = a.sel_idx + cbase;
+  const float* sinv = a.sel_inv_norm + cbase;
+  const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
+  const int32_t* less = a.less_idx + lbase;
+
+  // slots past the end repeat the last conserved key (see sim_block_products)
+  const int ntiles = (S + kSplitSlots - 1) / kSplitSlots, nblocks = (S + 31) / 32;
+  auto load_ids = [&](int t, int (&id)[NG]) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) id[i] = sel[min(t * kSplitSlots + (tid + i * NT) / GPR, S - 1)];
+  };
+  uint4 piece[NG][2];
+  float piece_inv = 0.f;
+  auto load_tile = [&](int t, const int (&id)[NG]) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      const uint4* src = reinterpret_cast<const uint4*>(a.k + (size_t)id[i] * TF::kRowBytes + (tid + i * NT) % GPR * 32);
+      piece[i][0] = src[0];
+      piece[i][1] = src[1];
+    }
+    if (tid < kSplitSlots) piece_inv = sinv[min(t * kSplitSlots + tid, S - 1)];
+  };
+  float rest = 0.f;  // NaN once a key without three parts has been seen
+  auto store_tile = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      uint4 part[3];
+      split8(piece[i][0], piece[i][1], part, rest);
+      char* dst = smem + buf * ST::kTileBytes + (tid + i * NT) / GPR * ST::kStride + (tid + i * NT) % GPR * 16;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(dst + p * ST::kPart) = part[p];
+    }
+    if (tid < kSplitSlots) inv_lds[buf * kSplitSlots + tid] = piece_inv;
+  };
+
+  // rows past the end repeat the last one and are never stored
+  const int r0 = row_base + wave / SW * 32 * F;
+  int id[NG], lrow[F];
+  load_ids(0, id);
+#pragma unroll
+  for (int s = 0; s < F; ++s) lrow[s] = less[min(r0 + s * 32 + n, n_less - 1)];
+  load_tile(0, id);
+  load_ids(1, id);
+  uint4 rows[F][3][NC];
+#pragma unroll
+  for (int s = 0; s < F; ++s) {
+    const uint4* src = reinterpret_cast<const uint4*>(a.k + (size_t)lrow[s] * TF::kRowBytes + kg * TF::kHalfBytes);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      uint4 part[3];
+      split8(src[2 * c], src[2 * c + 1], part, rest);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) rows[s][p][c] = part[p];
+    }
+  }
+  if (tid == 0) *bad_lds = 0;
+  store_tile(0);
+  RowBest rb[F];
+#pragma unroll
+  for (int s = 0; s < F; ++s) row_best_init(rb[s]);
+  __syncthreads();
+
+  for (int t = 0; t < ntiles; ++t) {
+    const bool more = t + 1 < ntiles;
+    if (more) {
+      load_tile(t + 1, id);
+      load_ids(t + 2, id);
+    }
+#pragma unroll
+    for (int i = 0; i < kSplitSlots / 32 / SW; ++i) {
+      const int cb = i * SW + wave % SW, b = t * (kSplitSlots / 32) + cb;
+      if (b >= nblocks) break;
+      const char* src = smem + (t & 1) * ST::kTileBytes + (cb * 32 + n) * ST::kStride + kg * (ST::kPart / 2);
+      uint4 keys[3][NC];
+#pragma unroll
+      for (int p = 2; p >= 0; --p)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) keys[p][c] = *reinterpret_cast<const uint4*>(src + p * ST::kPart + c * 16);
+      f32x16_t acc[F];
+#pragma unroll
+      for (int s = 0; s < F; ++s) acc[s] = acc_zero();
+      auto product = [&](int pk, int pr) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int s = 0; s < F; ++s) mma_chunk<bf16_t>(acc[s], keys[pk][c], rows[s][pr][c]);
+      };
+      product(2, 0);
+      product(1, 1);
+      product(0, 2);
+      product(1, 0);
+      product(0, 1);
+      product(0, 0);
+      float iv[16];
+      load_inv(iv, inv_lds + (t & 1) * kSplitSlots + cb * 32 + kg * 4);
+#pragma unroll
+      for (int s = 0; s < F; ++s) keep_if_improved(acc[s], scale_max(acc[s], iv), b * 32, rb[s]);
+    }
+    if (more) store_tile((t + 1) & 1);
+    __syncthreads();
+  }
+  if (rest != rest) *bad_lds = 1;
+  __syncthreads();
+  if (*bad_lds != 0) {
+    // A key of this workgroup has no three bf16 parts: the fp32 instruction, operands straight from the key cache.
+#pragma unroll
+    for (int s = 0; s < F; ++s) {
+      row_best_init(rb[s]);
+      Frag<float, D> lf;
+      frag_load(lf, a.k + (size_t)lrow[s] * TF::kRowBytes, kg);
+      for (int b = wave % SW; b < nblocks; b += SW) {
+        Frag<float, D> cf;
+        frag_load(cf, a.k + (size_t)sel[min(b * 32 + n, S - 1)] * TF::kRowBytes, kg);
+        float iv[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) iv[r] = sinv[min(b * 32 + acc_row(r, kg), S - 1)];
+        f32x16_t acc = acc_zero();
+        mma<float, D>(acc, cf, lf);
+        keep_if_improved(acc, scale_max(acc, iv), b * 32, rb[s]);
+      }
+    }
+  }
+  if constexpr (SW > 1) {  // the bests of the waves that share rows, over the tiles (nobody reads those any more)
+    float* best_v = reinterpret_cast<float*>(smem);                  // [NW][32 F]
+    int* best_s = reinterpret_cast<int*>(smem + NW * 32 * F * 4);    // [NW][32 F]
+#pragma unroll
+    for (int s = 0; s < F; ++s) {
+      const int bi = row_best_merge(rb[s], kg);
+      const float bv = fmaxf(rb[s].best, __shfl_xor(rb[s].best, 32, kWave));
+      if (kg == 0) {
+        best_v[(wave * F + s) * 32 + n] = bv;
+        best_s[(wave * F + s) * 32 + n] = bi;
+      }
+    }
+    __syncthreads();
+    if (tid < kRows && row_base + tid < n_less) {
+      const int at = tid / (32 * F) * SW * 32 * F + tid % (32 * F);
+      float v = best_v[at];
+      int slot = best_s[at];
+#pragma unroll
+      for (int w = 1; w < SW; ++w) {
+        const float ov = best_v[at + w * 32 * F];
+        const int os = best_s[at + w * 32 * F];
+        const bool take = ov > v || (ov == v && os < slot);
+        v = take ? ov : v;
+        slot = take ? os : slot;
+      }
+      a.less_slot[lbase + row_base + tid] = slot;
+      if (a.merge_assign) a.merge_assign[less[row_base + tid]] = slot;
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < F; ++s) {
+      const int bi = row_best_merge(rb[s], kg);
+      const int ri = r0 + s * 32 + n;
+      if (kg == 0 && ri < n_less) {
+        a.less_slot[lbase + ri] = bi;
+        if (a.merge_assign) a.merge_assign[lrow[s]] = bi;
+      }
+    }
   }
 }
 
@@ -1053,34 +1310,11 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   return a;
 }
 
-// Which problems go to the direct kernel.  bf16: short prompts whose tiled launch would leave most CUs empty: 16 pairs
-// of 500 positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000
-// 53 -> 120 us (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
-// fp32: a workgroup of the tiled kernel walks the whole conserved set, so the longer that is, the more workgroups it
-// takes to beat the direct kernel: the line lies at a number of positions over all pairs that grows with the share
-// kept, at a length that does too, and below the number of pairs from which even one row block each fills the chip.
-// Direct / tiled (with packing) in us, equal budgets, in brackets budgets as uneven as entropies make them:
-//                    a tenth kept                                       three tenths kept
-// rows of 256 bytes  64 pairs of 1024   26 /  27  (24 /  43)            64 pairs of 3072  197 / 244  (110 / 243)
-//                    256 of 1024        75 /  60  (69 /  62)            256 of 2048       352 / 354  (278 / 269)
-// rows of 512 bytes  32 of 1024         32 /  44  (34 /  82)            48 of 2048        195 / 205  (118 / 261)
-//                    128 of 512         48 /  38  (48 /  46)            128 of 2048       506 / 384  (360 / 283)
-// With rows of 256 bytes and a quarter or more kept the two are even at any number of pairs (within 15 %), and the merge
-// after the direct kernel finds more of the keys in the caches (1024 pairs of 300 and 3000, three tenths kept, whole
-// pass: 245 / 285 and 3490 / 3850 us).  One pair of 8192 positions, a tenth kept: 108 / 73 us (rows of 256 bytes).  Over 1394 shapes the rule costs
-// 1.1 % against the better one of the two, the direct kernel everywhere 12 %, the tiled one everywhere 48 %.
+// bf16 problems for the direct kernel: short prompts whose tiled launch would leave most CUs empty: 16 pairs of 500
+// positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000 53 -> 120 us
+// (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
 constexpr unsigned kSimDirectGroups = 96;
 constexpr int kSimDirectPositions = 2048;
-
-template <typename T, int D>
-static bool direct_pays(const Plan& p, unsigned pairs) {
-  if (sizeof(T) == 2) return pairs * ((p.T + kSimRows - 1) / kSimRows) <= kSimDirectGroups && p.T <= kSimDirectPositions;
-  const double positions = (double)pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
-  const bool few = pairs <= (D == 64 ? 256u : 96u) || positions <= (D == 64 ? 163840.0 : 49152.0);
-  const double longest = (pairs == 1 ? 4.1e4 : D == 64 ? 1.64e5 : 6.15e4) * kept;
-  const bool many_kept = D == 64 && kept >= 0.25;
-  return p.T <= longest && p.T <= 16384 && (many_kept || (few && positions <= (D == 64 ? 1.5e6 : 5e5) * kept));
-}
 
 template <typename T, int D, int F, int NW>
 static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStream_t s) {
@@ -1089,19 +1323,52 @@ static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStrea
   return hipGetLastError();
 }
 
+template <int D, int F, int NW, int SW>
+static hipError_t launch_sim_split(const MergeArgs& a, hipStream_t s) {
+  constexpr int kRows = 32 * F * NW / SW;
+  const unsigned nrb = (a.T + kRows - 1) / kRows;
+  auto split = similarity_split_kernel<D, F, NW, SW>;
+  constexpr int kLds = SplitTile<D, SW>::kLdsBytes;
+  if (kLds > 64 * 1024) {
+    const hipError_t e = allow_dynamic_lds(split, kLds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(split, dim3(nrb * (unsigned)(a.L * a.Hkv)), dim3(NW * 64), kLds, s, a);
+  return hipGetLastError();
+}
+
+// fp32 problems: waves per workgroup and how many of them share the same rows.  Where 128 rows per workgroup leave CUs
+// empty, the chain of tiles that one wave walks bounds the kernel, above all in the layers with the longest sets: waves
+// that take every SW-th block shorten it, at the price of splitting the set for fewer rows.  us, by events around the
+// phase (with about 5 us of them), NW x SW = 4 x 1 / 8 x 4 / 4 x 4 (rows of 256 bytes), 4 x 1 / 8 x 1 / 4 x 2 (of 512):
+//   256 bytes  8 pairs of 704, 2 layers 13.6 / 11.8 / 10.5      18 of 1674, 18 layers 38 / 24 / 30
+//              10 of 3835, 5 layers     82 / 47 / 47            30 of 3851, 15 layers 103 / 90 / 135
+//              32 of 800, 1 layer       11.5 / 17.9 / 20.2      256 of 829, 8 layers  30 / 79 / 115
+//   512 bytes  5 of 1272, 5 layers      28 / 38 / 21            16 of 1718, 4 layers  32 / 43 / 25
+//              32 of 1157, 1 layer      17.7 / 21.7 / 23.7      35 of 2715, 35 layers 106 / 140 / 97
+//              256 of 310               26 / 32 / 36            224 of 660, 28 layers 46 / 38 / 64
+// The fp32 instruction in the direct / tiled kernel before (tiled with its packing launch): 256 pairs of 829 107 / 71,
+// 8 of 704 12.3 / 19, 224 of 660 (512 bytes) 111 / 91.
+template <int D>
+static hipError_t launch_sim_fp32(const Plan& p, const MergeArgs& a, hipStream_t s) {
+  const long long pairs = (long long)p.L * p.Hkv, groups128 = pairs * ((p.T + 127) / 128);
+  if constexpr (D == 64) {
+    const double groups32 = (double)pairs * ((double)p.T - (double)p.B / p.L) / 32;  // of rows that merge, equal budgets
+    if (pairs <= 32 && groups32 <= 256) return launch_sim_split<D, 1, 4, 4>(a, s);
+    if (p.L >= 3 && p.T >= 256 && groups128 <= 320) return launch_sim_split<D, 1, 8, 4>(a, s);
+  } else {
+    if (groups128 <= 160 || (p.L >= 3 && groups128 <= 256)) return launch_sim_split<D, 1, 4, 2>(a, s);
+    if (p.T > 128 && pairs * ((p.T + 255) / 256) >= 576) return launch_sim_split<D, 1, 8, 1>(a, s);
+  }
+  return launch_sim_split<D, 1, 4, 1>(a, s);
+}
+
 template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
-  if (direct_pays<T, D>(p, pairs)) {
-    // two fragments per wave halve the key loads once there are enough workgroups of 64 rows for every CU
-    if constexpr (sizeof(T) == 4 && D == 64)
-      if (pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<T, D, 2, 4>(a, pairs, s);
-    return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
-  }
-  // One resident-set workgroup occupies a whole CU: only worth it with at least one per CU.  bf16 only: with the sixteen
-  // times slower fp32 instructions a workgroup with a long set outlives the others (256 pairs of 2048, a tenth kept
-  // under uneven budgets: 218 us against 150 tiled; 1024 pairs 492 against 545).
-  a.use_resident = sizeof(T) == 2 && pairs >= 256u ? 1 : 0;
+  if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
+  // One resident-set workgroup occupies a whole CU: only worth it with at least one per CU.
+  a.use_resident = pairs >= 256u ? 1 : 0;
   hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
                      dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
@@ -1116,20 +1383,17 @@ static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   hipLaunchKernelGGL(tiled, grid, dim3(kSimWaves * 64), kTiledLds, s, a);
   e = hipGetLastError();
   if (e != hipSuccess || !a.use_resident) return e;
-  if constexpr (sizeof(T) == 2) {
-    auto res = similarity_resident_kernel<T, D>;
-    e = allow_dynamic_lds(res, kResLdsBytes);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
-    e = hipGetLastError();
-  }
-  return e;
+  auto res = similarity_resident_kernel<T, D>;
+  e = allow_dynamic_lds(res, kResLdsBytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {
   const MergeArgs a = make_args(p, b);
   if (p.dtype == MEDA_BF16) return p.d == 128 ? launch_sim_t<bf16_t, 128>(p, a, s) : launch_sim_t<bf16_t, 64>(p, a, s);
-  return p.d == 128 ? launch_sim_t<float, 128>(p, a, s) : launch_sim_t<float, 64>(p, a, s);
+  return p.d == 128 ? launch_sim_fp32<128>(p, a, s) : launch_sim_fp32<64>(p, a, s);
 }
 
 hipError_t launch_segment_sort(const Plan& p, const Buffers& b, hipStream_t s) {

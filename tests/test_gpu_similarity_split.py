@@ -1,0 +1,73 @@
+"""Nearest conserved key of fp32 keys (multiplied in three bf16 parts) against float64, at sizes that reach every workgroup
+shape of the kernel: one and several tiles, a part of a tile, rows that do not fill a block."""
+import pytest
+import torch
+
+import paper_2502_17599_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(L, hkv, T, d, kept, k, q0):
+    dev = torch.device("cuda:0")
+    W = min(T, 16)
+    B = max(L * W, int(kept * L * T))
+    g = torch.Generator().manual_seed(5)
+    q = torch.randn(L, hkv, W, d, generator=g) * torch.linspace(0.3, 3.0, L)[:, None, None, None]
+    q[..., 0] *= q0
+    mask = torch.zeros(T, dtype=torch.uint8)
+    mask[T // 4:T // 2] = 1
+    comp = pkg.Compressor(pkg.make_params(L, hkv, hkv, d, T, W, B, torch.float32), dev, want_merge_assign=True)
+    out = comp(q.to(dev), k.to(dev), k.to(dev), mask.to(dev))
+    S, off = out.layer_len.cpu().tolist(), out.layer_off.cpu().tolist()
+    sel, slot = out.sel_idx.cpu().long(), out.merge_assign.cpu().long().reshape(L, hkv, T)
+    for l in range(L):
+        for h in range(hkv):
+            at = off[l] * hkv + h * S[l]
+            yield l, h, sel[at:at + S[l]], slot[l, h]
+
+
+SHAPES = [  # layers, kv heads, positions, head dimension, share kept
+    (1, 1, 33, 64, 0.5), (2, 4, 257, 64, 0.3), (3, 8, 700, 64, 0.25), (2, 20, 300, 64, 0.2),
+    (1, 2, 65, 128, 0.5), (2, 24, 500, 128, 0.1), (8, 32, 600, 128, 0.12),
+]
+
+
+@pytest.mark.parametrize("near", [0.0, 3e-4], ids=["spread", "near_ties"])
+@pytest.mark.parametrize("L,hkv,T,d,kept", SHAPES)
+def test_nearest_key_of_fp32_keys(L, hkv, T, d, kept, near):
+    k = torch.randn(L, hkv, T, d, generator=torch.Generator().manual_seed(T))
+    if near:
+        k = k[:, :, :1] + near * k
+    # Two similarities, each with at most d / 16 accumulations of the leading products and 12 more roundings (smaller
+    # products, norm, root, reciprocal, scaling) of 2^-24
+    bound = 2 * (d / 16 + 12) * 2.0 ** -24
+    for l, h, sel, slot in _run(L, hkv, T, d, kept, k, 1.0):
+        u = torch.nn.functional.normalize(k[l, h].double(), dim=1)
+        less = torch.ones(T, dtype=torch.bool)
+        less[sel] = False
+        if not bool(less.any()):
+            continue
+        sim = u[less] @ u[sel].T
+        got = sim.gather(1, slot[less][:, None])[:, 0]
+        assert float((sim.max(1).values - got).max()) <= bound, (l, h)
+
+
+@pytest.mark.parametrize("L,hkv,T,d,kept", SHAPES)
+def test_keys_that_have_no_three_parts(L, hkv, T, d, kept):
+    """An element that rounds to an infinite bf16: its (finite) products still decide where the row goes."""
+    # elements of 0.1: the raw product with a large row, at most 3.4e38 * 0.6, stays below the largest float
+    k = 0.1 * torch.randn(L, hkv, T, d, generator=torch.Generator().manual_seed(T + 1))
+    big = torch.arange(0, T, 5)
+    k[:, :, big, 0] = 3.4e38
+    for l, h, sel, slot in _run(L, hkv, T, d, kept, k, 0.0):
+        x = k[l, h].double()
+        # 1 / |k| of a key whose sum of squares overflows is 0: it can win only where every other similarity is negative
+        inv = x[sel].norm(dim=1).reciprocal() * (x[sel, 0] < 1e38)
+        less = torch.ones(T, dtype=torch.bool)
+        less[sel] = False
+        rows = torch.nonzero(less & (x[:, 0] > 1e38)).flatten()
+        for r in rows.tolist():
+            sim = (x[sel] @ x[r]) * inv
+            sim[x[sel, 0] > 1e38] = -1.0     # their product with this row overflows, times 0: no similarity
+            assert sim[slot[r]] >= sim.max() * (1 - 1e-5), (l, h, r)
