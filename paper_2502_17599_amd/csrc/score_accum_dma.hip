@@ -15,9 +15,13 @@
 // kv head: 830 -> 640 us.
 //
 // The query rows and statistics of head h+1 are requested when head h starts.  A wave's key rows are used by no other
-// wave, so they go straight to its registers; the next kv head's are requested when the last product with the present
-// ones is done, before its probabilities are formed.  Without a key tile in LDS the workgroups of a CU are four (three
-// with their registers) instead of two.
+// wave, so with much work per kv head they go straight to its registers; the next kv head's are requested when the last
+// product with the present ones is done, before its probabilities are formed.  Without a key tile in LDS the workgroups
+// of a CU are four (three with their registers) instead of two.  With little work per kv head (KEYS: one row block, or
+// two and two heads) the stream of keys bounds the kernel, and fragment loads, which touch 64 lines each, and their late
+// request cost more than the tile: there every wave has its key rows in LDS too, brought by copies of whole rows that
+// start as soon as the present ones are in registers.  16 layers of 20000 keys, 2 kv heads, 32 rows, 2 / 4 / 8 heads per kv
+// head: 54 / 65 / 87 us from registers, 41 / 55 / 83 from LDS; 64 rows, 2 heads: 66 and 63.
 //
 // LDS tiles filled by the copies are laid out as CopyTile (device_utils.hpp).
 // grid (NT, L) x 4 waves: wave cw owns the 32 keys cw*32.. of the tile and all RB 32-row blocks of the window.
@@ -33,12 +37,12 @@ constexpr int dma_stage_bytes() {  // the window's query rows and the four plane
   return CopyTile<T, D>::bytes(RB * 32) + 4 * RB * 32 * (int)sizeof(float);
 }
 
-template <typename T, int D, int RB>
-constexpr size_t dma_lds_bytes() {  // two stages, the entropy reduction
-  return 2 * (size_t)dma_stage_bytes<T, D, RB>() + kDmaWaves * 2 * sizeof(double);
+template <typename T, int D, int RB, bool KEYS>
+constexpr size_t dma_lds_bytes() {  // two stages, the entropy reduction, the waves' key rows
+  return 2 * (size_t)dma_stage_bytes<T, D, RB>() + kDmaWaves * 2 * sizeof(double) + (KEYS ? CopyTile<T, D>::bytes(kScoreTile) : 0);
 }
 
-template <typename T, int D, int RB>
+template <typename T, int D, int RB, bool KEYS>
 __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_kernel(ScoreArgs a) {
   using TL = Tile<T, D>;
   using CT = CopyTile<T, D>;
@@ -51,7 +55,8 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
   constexpr int kQBytes = CT::bytes(Wp);
   constexpr int kStageBytes = dma_stage_bytes<T, D, RB>();
   static_assert(RPI == CT::kRows && (RB * 32) % RPI == 0, "the copy instructions must tile the window evenly");
-  extern __shared__ __align__(16) char smem[];  // stage 0, stage 1, reduction
+  constexpr int KI = 32 / RPI;                           // copy instructions of a wave's key rows
+  extern __shared__ __align__(16) char smem[];  // stage 0, stage 1, reduction, key rows
   double* red = reinterpret_cast<double*>(smem + 2 * kStageBytes);  // [waves][2]
 
   // layers are walked in the opposite order of pass A, so the keys pass A touched last (still in the
@@ -77,6 +82,16 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
     qoff[c] = (unsigned)(a.q_row0 + min(r, a.W - 1)) * RBt + CT::source_chunk(lane);
   }
   const unsigned koff = (unsigned)min(j, a.Tk - 1) * RBt;  // this lane's key inside a (layer, kv head)
+  char* key_rows = smem + 2 * kStageBytes + kDmaWaves * 2 * sizeof(double) + cw * CT::bytes(32);  // this wave's
+  unsigned kcopy[KI];  // KEYS: the chunk this lane brings with copy c (keys past the end repeat the last one)
+#pragma unroll
+  for (int c = 0; c < KI; ++c)
+    kcopy[c] = (unsigned)min(j0 + cw * 32 + c * RPI + lane / CPR, a.Tk - 1) * RBt + CT::source_chunk(lane);
+  auto issue_keys = [&](int g) {
+    const char* ksrc = uniform_ptr(a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt);
+#pragma unroll
+    for (int c = 0; c < KI; ++c) async_copy16_to_lds_stream(ksrc, kcopy[c], (unsigned)(size_t)key_rows + c * CT::kPiece);
+  };
   auto load_keys = [&](Frag<T, D>& f, int g) { frag_load(f, uniform_ptr(a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt) + koff, kg); };
   // this lane's value of the first kDmaThreads statistics (the plane of the maxima is among them)
   const unsigned soff = 4u * (unsigned)(tid < Wp ? min(tid, a.W - 1) : tid);
@@ -101,7 +116,10 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
 
   issue(0);
   Frag<T, D> kf;
-  load_keys(kf, 0);
+  if constexpr (KEYS)
+    issue_keys(0);
+  else
+    load_keys(kf, 0);
   float pbar[RB][16];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -115,14 +133,18 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
     constexpr bool MASKED = decltype(masked_tag)::value;
     int g = 0, hg = 0;
     for (int h = 0; h < a.Hq; ++h) {
-      // this wave's pieces of the head have landed (younger than them: the loads of its keys, at the start of a group)
-      if (hg == 0)
+      // this wave's pieces of the head have landed (younger than them: the loads of its keys, at the start of a group, or
+      // the copies of the next group's keys, which the first head of a group issues behind those of the second)
+      if (!KEYS && hg == 0)
         async_copy_wait<TL::kFragChunks>();
+      else if (KEYS && hg == 1 && g + 1 < a.Hkv)
+        async_copy_wait<KI>();
       else
         async_copy_wait<0>();
       __syncthreads();  // every wave's have; and nobody reads the other stage (the previous head) any more
       const char* stage = smem + (h & 1) * kStageBytes;
       const float* st = reinterpret_cast<const float*>(stage + kQBytes);  // planes: maximum, 1/Z, the two cross-modal 1/Z
+      if (KEYS && hg == 0) frag_from_tile(kf, key_rows, fbase);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         Frag<T, D> qf;
@@ -133,9 +155,12 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
         mma<T, D>(acc, qf, kf);
         // (behind the first product, so that the wait for the keys there does not wait for these copies)
         if (rb == 0 && h + 1 < a.Hq) issue(h + 1);
-        if (rb == RB - 1 && hg == a.G - 1) {  // the next kv head's keys (past the last one: the same again)
-          load_keys(kf, min(g + 1, a.Hkv - 1));
+        if (KEYS && rb == 0 && hg == 0 && g + 1 < a.Hkv) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the present key rows have left LDS
+          issue_keys(g + 1);
         }
+        if (!KEYS && rb == RB - 1 && hg == a.G - 1)  // the next kv head's keys (past the last one: the same again)
+          load_keys(kf, min(g + 1, a.Hkv - 1));
         // Row r (without the lane group's offset kg*4) counts for this lane's column iff row_min <= r < row_end: the row
         // exists and sees the column (j <= T - W + r + kg*4).  Opaque, so that the comparisons are redone per head instead
         // of being kept in registers.
@@ -202,10 +227,10 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
 
 // ------------------------------------------------------------------------------------------ launch
 
-template <typename T, int D, int RB>
+template <typename T, int D, int RB, bool KEYS>
 static hipError_t launch_dma_k(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  constexpr size_t lds = dma_lds_bytes<T, D, RB>();
-  auto kern = score_accum_dma_kernel<T, D, RB>;
+  constexpr size_t lds = dma_lds_bytes<T, D, RB, KEYS>();
+  auto kern = score_accum_dma_kernel<T, D, RB, KEYS>;
   if (lds > 64 * 1024) {
     hipError_t e = allow_dynamic_lds(kern, (int)lds);
     if (e != hipSuccess) return e;
@@ -217,9 +242,9 @@ static hipError_t launch_dma_k(const Plan& p, const ScoreArgs& a, hipStream_t s)
 template <typename T, int D>
 static hipError_t launch_dma_t(const Plan& p, const ScoreArgs& a, hipStream_t s) {
   switch (p.RB) {
-    case 1: return launch_dma_k<T, D, 1>(p, a, s);
-    case 2: return launch_dma_k<T, D, 2>(p, a, s);
-    default: return launch_dma_k<T, D, 3>(p, a, s);
+    case 1: return launch_dma_k<T, D, 1, true>(p, a, s);
+    case 2: return p.G == 2 ? launch_dma_k<T, D, 2, true>(p, a, s) : launch_dma_k<T, D, 2, false>(p, a, s);
+    default: return launch_dma_k<T, D, 3, false>(p, a, s);
   }
 }
 
