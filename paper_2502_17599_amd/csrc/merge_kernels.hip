@@ -167,6 +167,23 @@ __device__ __forceinline__ void sim_block_simple(const char* block, const unsign
   keep_if_improved(acc[1], bm1, slot0, rb[1]);
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs in launch order: all row blocks of one (layer, head) run on the same XCD
+// (they stream the same conserved keys and then share one L2), consecutive pairs go to different XCDs; the last pairs,
+// fewer than 8, are spread over all XCDs, which would otherwise wait for the few that had one pair more (similarity of 9
+// pairs of 60000 positions 1238 -> 1071 us, 10 of 100000 3310 -> 3020, 17 of 30000 674 -> 658, 5 of 1500 17 -> 12).
+__device__ __forceinline__ void pair_and_row_block(unsigned block, unsigned pairs, unsigned row_blocks, unsigned& pair, unsigned& rblock) {
+  const unsigned full = pairs & ~7u;
+  if (block < full * row_blocks) {
+    const unsigned seq = block >> 3;
+    pair = (block & 7u) + 8u * (seq / row_blocks);
+    rblock = seq % row_blocks;
+  } else {
+    const unsigned r = block - full * row_blocks, rest = pairs - full;
+    pair = full + r % rest;
+    rblock = r / rest;
+  }
+}
+
 // Tiled kernel: grid over (row block of 256, kv head, layer); 4 waves x 64 less-important rows.  The conserved
 // keys stream through a ring of four LDS tiles of 64 slots, filled by asynchronous copies that go from global
 // memory straight into LDS (no registers, no LDS store instructions): while tile t is multiplied, tile t+1 has
@@ -203,18 +220,13 @@ __global__ void __launch_bounds__(kSimWaves * 64, (Tile<T, D>::kRowBytes <= 256 
   char* ctile = smem;                                                       // [kSimRing][64 rows]
   float* cinv = reinterpret_cast<float*>(smem + kSimRing * kTileBytes);     // [kSimInvRing][waves][64]
 
-  // Workgroups are dealt round-robin to the 8 XCDs in launch order.  The launch index is remapped so
-  // that all row blocks of one (layer, head) run on the same XCD (they stream the same conserved keys
-  // and then share one L2), while consecutive (layer, head) pairs go to different XCDs.
-  const unsigned nrb = (a.T + kSimRows - 1) / kSimRows;
-  const unsigned xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
-  const unsigned pair = xcd + 8u * (seq / nrb);
-  if (pair >= (unsigned)(a.L * a.Hkv)) return;
+  unsigned pair, rblock;
+  pair_and_row_block(blockIdx.x, (unsigned)(a.L * a.Hkv), (a.T + kSimRows - 1) / kSimRows, pair, rblock);
   const int l = a.alloc[4 * (pair / a.Hkv) + 3], g = pair % a.Hkv;  // layers by decreasing budget
   const int S = a.alloc[4 * l];
   if (a.use_resident && S <= resident_capacity<T, D>()) return;  // the resident-set kernel below takes this layer
   const int n_less = a.T - S;
-  const int row_base = (seq % nrb) * kSimRows;
+  const int row_base = rblock * kSimRows;
   if (row_base >= n_less) return;
 
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kg = lane >> 5;
@@ -442,14 +454,12 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
   __shared__ float best_v[NW][kRows];
   __shared__ int best_s[NW][kRows];
 
-  const unsigned nrb = (a.T + kRows - 1) / kRows;
-  const unsigned xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
-  const unsigned pair = xcd + 8u * (seq / nrb);
-  if (pair >= (unsigned)(a.L * a.Hkv)) return;
+  unsigned pair, rblock;
+  pair_and_row_block(blockIdx.x, (unsigned)(a.L * a.Hkv), (a.T + kRows - 1) / kRows, pair, rblock);
   const int l = a.alloc[4 * (pair / a.Hkv) + 3], g = pair % a.Hkv;  // layers by decreasing budget
   const int S = a.alloc[4 * l];
   const int n_less = a.T - S;
-  const int row_base = (seq % nrb) * kRows;
+  const int row_base = rblock * kRows;
   if (row_base >= n_less) return;
 
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kg = lane >> 5;
@@ -527,22 +537,6 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
     }
     a.less_slot[lbase + row_base + tid] = slot;
     if (a.merge_assign) a.merge_assign[less[row_base + tid]] = slot;
-  }
-}
-
-// Workgroups are dealt round-robin to the 8 XCDs in launch order: all row blocks of one (layer, head) run on the same XCD
-// (they stream the same conserved keys and then share one L2), consecutive pairs go to different XCDs; the last pairs,
-// fewer than 8, are spread over all XCDs, which would otherwise wait for the few that had one pair more.
-__device__ __forceinline__ void pair_and_row_block(unsigned block, unsigned pairs, unsigned row_blocks, unsigned& pair, unsigned& rblock) {
-  const unsigned full = pairs & ~7u;
-  if (block < full * row_blocks) {
-    const unsigned seq = block >> 3;
-    pair = (block & 7u) + 8u * (seq / row_blocks);
-    rblock = seq % row_blocks;
-  } else {
-    const unsigned r = block - full * row_blocks, rest = pairs - full;
-    pair = full + r % rest;
-    rblock = r / rest;
   }
 }
 
@@ -1319,7 +1313,7 @@ constexpr int kSimDirectPositions = 2048;
 template <typename T, int D, int F, int NW>
 static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStream_t s) {
   const unsigned nrb = (a.T + 32 * F - 1) / (32 * F);
-  hipLaunchKernelGGL((similarity_direct_kernel<T, D, F, NW>), dim3(8u * nrb * ((pairs + 7u) / 8u)), dim3(NW * 64), 0, s, a);
+  hipLaunchKernelGGL((similarity_direct_kernel<T, D, F, NW>), dim3(nrb * pairs), dim3(NW * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1373,7 +1367,7 @@ static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
                      dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid(8u * nrb * ((pairs + 7u) / 8u));
+  dim3 grid(nrb * pairs);
   constexpr int kTiledLds = sim_tiled_lds_bytes<T, D>();
   auto tiled = similarity_argmax_kernel<T, D>;
   if (kTiledLds > 64 * 1024) {
