@@ -15,7 +15,8 @@ namespace meda {
 //   16        1.68 (2 layers of 1024 keys, 28 heads, bf16: 49 / 42), 32  1.67, 64  1.51 (0.95 at worst)
 //   128       1.10: 0.73 to 1.04 for few heads and grouped bf16 rows of 256 bytes, 1.03 to 1.6 for the others
 //   256       0.79 (a tile of 128 keys shares what a workgroup of 32 keys reads again), 512  0.69
-// A sequence of a small batch goes the way it would go alone, so that its sums are the same.
+// Up to four sequences go the way one of them would go alone, so that its sums are the same; 7 of 4 layers of 487 keys,
+// 4 heads, 2 kv heads, 80 rows (112 tiles; whole pass) 77 / 91.
 constexpr int64_t kDirectTiles = 64, kDirectTilesAll = 128;
 constexpr int kDirectManyHeads = 28;
 
@@ -115,7 +116,8 @@ meda_status make_plan(const meda_params* p, Plan* out) {
   const bool direct_fits = !pl.blocks && pl.Hq * (pl.RB * 384 + 128) <= 130944;  // its LDS
   const bool many_heads = pl.Hq >= kDirectManyHeads && (pl.G == 1 || pl.d == 64 || pl.dtype == MEDA_F32);
   const int64_t seq_tiles = (int64_t)pl.NT * pl.Lseq, all_tiles = (int64_t)pl.NT * pl.L;
-  pl.direct = direct_fits && all_tiles <= kDirectTilesAll && (many_heads || seq_tiles <= kDirectTiles) ? 1 : 0;
+  const bool few = all_tiles <= kDirectTiles || (pl.N <= 4 && seq_tiles <= kDirectTiles);
+  pl.direct = direct_fits && all_tiles <= kDirectTilesAll && (many_heads || few) ? 1 : 0;
   if (pl.direct) {
     const int tiles = (pl.T + 31) / 32;
     pl.NTk = tiles;
