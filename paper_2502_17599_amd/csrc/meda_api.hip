@@ -20,6 +20,16 @@ namespace meda {
 constexpr int64_t kDirectTiles = 64, kDirectTilesAll = 128;
 constexpr int kDirectManyHeads = 28;
 
+// (Head, 32-row block) pairs in all, every prompt row scoring, from which a pass-A workgroup takes more than four of them
+// (bf16 rows of 256 bytes).  Pass A in us, workgroups of 4 / 8 / 12 / 16 pairs:
+//   bf16, 256 bytes   1600 pairs (8 layers of 780, 8 heads)  28 / 34 / 43 / 59    9600 (24 of 1600, 8)   137 / 139 / 174 / 219
+//                     16128 (8 of 2000, 32)  244 / 245 / 250 / 290                19200 (24 of 1600, 16 in 4) 225 / 205 / 211 / 215
+//                     56000 (28 of 4000, 16 in 8) 1408 / 1347 / 1217 / 1366       131072 (32 of 4096, 32)  3370 / 3039 / 2858 / 2893
+//                     110544 (28 of 4500, 28 in 4: 12 and 8 hold one row block)   2838 / 2814 / 2823 / 2632
+//   bf16, 128 bytes   4800 (24 of 780, 8)  42 / 54 / 51 / 71    110544 (28 of 4500, 28 in 4)  1811 / 1824 / 1831 / 1996
+//   fp32, 512 bytes   16128 (8 of 2000, 32)  1389 / 2385 / 2819 / 3021
+constexpr int64_t kLargePairs = 12000;
+
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Tiling of the two scoring passes for w query rows (the last w positions) of a sequence of t keys.  With
@@ -30,13 +40,15 @@ static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) 
   pl->Wb = w;
   pl->RB = (w + 31) / 32;
   pl->Wp = pl->RB * 32;
-  // Row blocks of one pass-A workgroup.  When every prompt row scores (single_chunk), pass A cuts the rows into its
-  // own, larger blocks: about 16 (head, 32-row block) pairs per workgroup, so a key tile staged in LDS serves 512
-  // rows without head grouping (the keys are re-read once per row block of pass A).
+  // Row blocks of one pass-A workgroup.  When every prompt row scores (single_chunk), pass A cuts the rows into its own
+  // blocks: a workgroup of few (head, 32-row block) pairs walks the keys in a short chain and there are many of them, one
+  // of many pairs re-reads the keys less often, which counts for long rows once the chip is full.
   pl->RBa = pl->RB;
   if (single_chunk) {
-    const int want = pl->G >= 16 ? 1 : 16 / pl->G;
     const int have = (rows + 31) / 32;
+    const bool large = pl->dtype == MEDA_BF16 && pl->d == 128 && (int64_t)pl->L * pl->Hq * have > kLargePairs;
+    const int pairs = !large ? 4 : pl->G >= 7 ? 16 : 12;
+    const int want = pl->G >= pairs ? 1 : pairs / pl->G;
     pl->RBa = want < have ? want : have;
   }
   pl->row_block_a = pl->RBa * 32;
