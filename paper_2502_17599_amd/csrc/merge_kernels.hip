@@ -1357,12 +1357,21 @@ static hipError_t launch_sim_fp32(const Plan& p, const MergeArgs& a, hipStream_t
   return launch_sim_split<D, 1, 4, 1>(a, s);
 }
 
+// Where the resident-set kernel takes the layers that fit: a workgroup of it occupies a whole CU, so with one or two per CU
+// its last round leaves most of the chip empty, and with long sets its few layers do not cover their own launch.  Tiled
+// alone / both kernels, similarity in us, mean budget of a layer in brackets:
+//   256 bytes  256 pairs [375] 60 / 76, [750] 159 / 185, [1125] 297 / 334    384 [240] 148 / 139, [375] 91 / 101, [1125] 439 / 475
+//              512 [240] 190 / 163, [675] 468 / 436, [1125] 576 / 622        1024 [240] 364 / 304, [750] 603 / 566, [1125] 1024 / 1025
+//   128 bytes  256 [375] 37 / 44, [750] 93 / 125, 360 [701] 133 / 163        384 [240] 80 / 78, [750] 135 / 140, [1125] 241 / 270
+//              512 [450] 146 / 142, [750] 180 / 174, [1125] 334 / 366        1024 [240] 209 / 198, [675] 481 / 475, [1125] 566 / 586
+constexpr unsigned kResidentPairs = 512;
+constexpr long long kResidentKept = 900;
+
 template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
   if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
-  // One resident-set workgroup occupies a whole CU: only worth it with at least one per CU.
-  a.use_resident = pairs >= 256u ? 1 : 0;
+  a.use_resident = pairs >= kResidentPairs && p.B <= kResidentKept * p.L ? 1 : 0;
   hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
                      dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
