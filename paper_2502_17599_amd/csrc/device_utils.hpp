@@ -251,6 +251,25 @@ __device__ __forceinline__ uint32_t double_to_bf16_bits(double x) {
   return float_to_bf16_rne(double_to_float_round_odd(x));
 }
 
+// ---- order of the workgroups ------------------------------------------------------------------------
+
+// Workgroups are dealt round-robin to the 8 XCDs in launch order: all row blocks of one (layer, head) run on the same XCD
+// (they stream the same keys and then share one L2), consecutive pairs go to different XCDs; the last pairs,
+// fewer than 8, are spread over all XCDs, which would otherwise wait for the few that had one pair more (similarity of 9
+// pairs of 60000 positions 1238 -> 1071 us, 10 of 100000 3310 -> 3020, 17 of 30000 674 -> 658, 5 of 1500 17 -> 12).
+__device__ __forceinline__ void pair_and_row_block(unsigned block, unsigned pairs, unsigned row_blocks, unsigned& pair, unsigned& rblock) {
+  const unsigned full = pairs & ~7u;
+  if (block < full * row_blocks) {
+    const unsigned seq = block >> 3;
+    pair = (block & 7u) + 8u * (seq / row_blocks);
+    rblock = seq % row_blocks;
+  } else {
+    const unsigned r = block - full * row_blocks, rest = pairs - full;
+    pair = full + r % rest;
+    rblock = r / rest;
+  }
+}
+
 // ---- wave helpers ----------------------------------------------------------------------------------
 
 __device__ __forceinline__ float wave_sum(float v) {

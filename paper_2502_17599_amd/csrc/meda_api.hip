@@ -28,6 +28,10 @@ constexpr int kDirectManyHeads = 28;
 //                     110544 (28 of 4500, 28 in 4: 12 and 8 hold one row block)   2838 / 2814 / 2823 / 2632
 //   bf16, 128 bytes   4800 (24 of 780, 8)  42 / 54 / 51 / 71    110544 (28 of 4500, 28 in 4)  1811 / 1824 / 1831 / 1996
 //   fp32, 512 bytes   16128 (8 of 2000, 32)  1389 / 2385 / 2819 / 3021
+// With a multiple of 8 kv heads 12 pairs are between 0.8 and 1.35 of the time of 16 (250 layers of 2000 and 1458, 8 heads: 1926 /
+// 2545, 1435 / 1059), so those keep 16; the others, (layer, kv head) pairs dealt to the XCDs: 250 layers, 8 heads in 2, of 600,
+// 1458, 2000, 3000: 12 pairs 214, 966, 1507, 3223, 16 pairs 216, 1000, 1674, 3243; in the order of the grid 12 pairs 213, 1428,
+// 1477, 4076, 16 pairs 220, 1030, 2394, 3632.
 constexpr int64_t kLargePairs = 12000;
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -47,7 +51,7 @@ static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) 
   if (single_chunk) {
     const int have = (rows + 31) / 32;
     const bool large = pl->dtype == MEDA_BF16 && pl->d == 128 && (int64_t)pl->L * pl->Hq * have > kLargePairs;
-    const int pairs = !large ? 4 : pl->G >= 7 ? 16 : 12;
+    const int pairs = !large ? 4 : (pl->Hkv % 8 == 0 || pl->G >= 7) ? 16 : 12;
     const int want = pl->G >= pairs ? 1 : pairs / pl->G;
     pl->RBa = want < have ? want : have;
   }

@@ -23,11 +23,19 @@ __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2
   char* ktile = smem;
   uint8_t* lmask = reinterpret_cast<uint8_t*>(smem + kScoreTile * TL::kStride);
 
-  const int ch = blockIdx.x, l = blockIdx.z;
-  int g = blockIdx.y, bi = 0;
-  if (BLOCKS) {  // row-block mode: this workgroup's row block (the largest blocks are dispatched first)
-    bi = blockIdx.y / a.Hkv;
-    g = blockIdx.y - bi * a.Hkv;
+  const int ch = blockIdx.x;
+  int l = blockIdx.z, g = blockIdx.y, bi = 0;
+  if (BLOCKS) {  // row-block mode (one chunk): this workgroup's row block, the largest ones first
+    if ((a.Hkv & 7) == 0) {
+      bi = blockIdx.y / a.Hkv;
+      g = blockIdx.y - bi * a.Hkv;
+    } else {  // row blocks by XCD in the order of the grid would give some XCDs all the long ones
+      unsigned pair, rblock;
+      pair_and_row_block(blockIdx.z * gridDim.y + blockIdx.y, (unsigned)(a.L * a.Hkv), gridDim.y / (unsigned)a.Hkv, pair, rblock);
+      l = pair / (unsigned)a.Hkv;
+      g = pair - (unsigned)(l * a.Hkv);
+      bi = rblock;
+    }
     select_row_block(a, bi);
   }
   constexpr int nthr = NW * 64;

@@ -34,11 +34,19 @@ __global__ void __launch_bounds__(NW * 64, 2) score_stats_dma_kernel(ScoreArgs a
   static_assert(NI % NW == 0, "the copy instructions must tile a tile evenly");
   extern __shared__ __align__(16) char smem[];  // two tiles
 
-  const int ch = blockIdx.x, l = blockIdx.z;
-  int g = blockIdx.y, bi = 0;
-  if (BLOCKS) {  // row-block mode: this workgroup's row block (the largest blocks are dispatched first)
-    bi = blockIdx.y / a.Hkv;
-    g = blockIdx.y - bi * a.Hkv;
+  const int ch = blockIdx.x;
+  int l = blockIdx.z, g = blockIdx.y, bi = 0;
+  if (BLOCKS) {  // row-block mode (one chunk): this workgroup's row block, the largest ones first
+    if ((a.Hkv & 7) == 0) {
+      bi = blockIdx.y / a.Hkv;
+      g = blockIdx.y - bi * a.Hkv;
+    } else {  // row blocks by XCD in the order of the grid would give some XCDs all the long ones
+      unsigned pair, rblock;
+      pair_and_row_block(blockIdx.z * gridDim.y + blockIdx.y, (unsigned)(a.L * a.Hkv), gridDim.y / (unsigned)a.Hkv, pair, rblock);
+      l = pair / (unsigned)a.Hkv;
+      g = pair - (unsigned)(l * a.Hkv);
+      bi = rblock;
+    }
     select_row_block(a, bi);
   }
   const int tid = threadIdx.x;
