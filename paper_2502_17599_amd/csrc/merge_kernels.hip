@@ -30,6 +30,7 @@ struct MergeArgs {
   long long total_slots;    // B * Hkv
   int merge_rows;           // output rows a wave of the merge walks
   int use_resident;         // layers whose conserved set fits into LDS go to the resident-set kernel
+  int adjacent_order;       // layers whose conserved set fits into LDS sum their products in adjacent order
   int n_members;            // keys that are not conserved, all layers and heads: (L * T - B) * Hkv
 };
 
@@ -51,6 +52,26 @@ constexpr int kResSplit = 1;  // 2 and 3 parts per pair (more, shorter workgroup
 template <typename T, int D>
 constexpr int resident_capacity() {
   return kResLdsBytes / (Tile<T, D>::kStride + 4) / 32 * 32;
+}
+
+// Order of the k-steps of a product.  Halves: step i takes the bytes [16 i, + 16) of each half of a row, the lane groups one
+// half each.  Adjacent: step i takes the bytes [32 i, + 32), the lane groups 16 of them each, so that a load instruction
+// touches 32 cache lines instead of 64; the resident-set kernel, which loads rows all the time, works that way.  The two
+// round differently and decide near ties differently (1e-6 to 1e-5 of the rows of clustered keys), so the order is a
+// property of the problem and the layer, not of the kernel that a rule of speed picks for them: adjacent for a set that
+// fits into LDS among at least kAdjacentPairs (layer, head) pairs, halves for every other one.
+constexpr unsigned kAdjacentPairs = 256;
+template <typename T, int D>
+struct StepOrder {
+  int group, step;  // chunk of step i in lane group kg: kg * group + i * step
+  __device__ __forceinline__ explicit StepOrder(bool adjacent)
+      : group(adjacent ? 1 : Tile<T, D>::kFragChunks), step(adjacent ? 2 : 1) {}
+  __device__ __forceinline__ int chunk(int i, int kg) const { return kg * group + i * step; }
+};
+template <typename T, int D>
+__device__ __forceinline__ void frag_load(Frag<T, D>& f, const char* row_ptr, int kg, const StepOrder<T, D>& order) {
+#pragma unroll
+  for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) f.c[i] = *reinterpret_cast<const uint4*>(row_ptr + order.chunk(i, kg) * 16);
 }
 
 // u_ij = (k_i . k_j)/(|k_i| |k_j|): the raw keys are multiplied (bf16 products are exact in the fp32
@@ -207,7 +228,9 @@ __global__ void __launch_bounds__(kSimWaves * 64, (Tile<T, D>::kRowBytes <= 256 
   pair_and_row_block(blockIdx.x, (unsigned)(a.L * a.Hkv), (a.T + kSimRows - 1) / kSimRows, pair, rblock);
   const int l = a.alloc[4 * (pair / a.Hkv) + 3], g = pair % a.Hkv;  // layers by decreasing budget
   const int S = a.alloc[4 * l];
-  if (a.use_resident && S <= resident_capacity<T, D>()) return;  // the resident-set kernel below takes this layer
+  const bool fits = S <= resident_capacity<T, D>();
+  if (a.use_resident && fits) return;  // the resident-set kernel below takes this layer
+  const StepOrder<T, D> order(a.adjacent_order && fits);
   const int n_less = a.T - S;
   const int row_base = rblock * kSimRows;
   if (row_base >= n_less) return;
@@ -235,7 +258,7 @@ __global__ void __launch_bounds__(kSimWaves * 64, (Tile<T, D>::kRowBytes <= 256 
   row_best_init(rb[1]);
   Frag<T, D> lf[2];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) frag_load(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes, kg);
+  for (int s = 0; s < 2; ++s) frag_load(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes, kg, order);
 
   // Copy instruction j of this wave fills the rows (wave * PF + j) * RPI .. + RPI-1 of a tile: this lane brings
   // one 16-byte chunk of row crow_r + j * RPI.  Slots past the end of the set repeat the last conserved key (see
@@ -261,11 +284,10 @@ __global__ void __launch_bounds__(kSimWaves * 64, (Tile<T, D>::kRowBytes <= 256 
   issue_tile(1, 1);
   issue_tile(2, 2);
 
-  // chunk c of this lane's fragment (chunk kg * NC + c of row n of a block) sits at (n * row bytes) +
-  // 16 * ((kg * NC + c) ^ swz(n)) inside a block of 32 rows
+  // chunk x of row n of a block sits at (n * row bytes) + 16 * (x ^ swz(n)) inside a block of 32 rows
   unsigned coff[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) coff[c] = (unsigned)(n * TL::kRowBytes + (((kg * NC + c) ^ swizzle_of_row<T, D>(n)) * 16));
+  for (int c = 0; c < NC; ++c) coff[c] = (unsigned)(n * TL::kRowBytes + ((order.chunk(c, kg) ^ swizzle_of_row<T, D>(n)) * 16));
   // block cb of the tile in ring slot rs: its rows and where its 1/|k_j| start in this wave's copy
   auto block_rows = [&](int rs, int cb) { return ctile + (rs % kSimRing) * kTileBytes + cb * 32 * TL::kRowBytes; };
   auto inv_index = [&](int rs, int cb) { return ((rs % kSimInvRing) * kSimWaves + wave) * kSimSlotTile + cb * 32; };
@@ -337,14 +359,8 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   int lrow[2], nrow[2];
   chunk_rows(c, lrow);
   chunk_rows(c + kChunkStep, nrow);
-  // k-step i of a fragment takes the bytes [32 i + 16 kg, + 16) of its row: the two lane groups read adjacent
-  // pieces, so a load instruction touches 32 cache lines instead of the 64 of the half-row mapping (this kernel
-  // loads 64 rows per wave and chunk, all the time).  The conserved keys are read from LDS with the same mapping,
-  // and any fixed order of the k-steps gives the same products.
-  auto row_frag = [&](Frag<T, D>& f, const char* row_ptr) {
-#pragma unroll
-    for (int i = 0; i < TL::kFragChunks; ++i) f.c[i] = *reinterpret_cast<const uint4*>(row_ptr + i * 32 + kg * 16);
-  };
+  const StepOrder<T, D> order(true);  // this kernel loads 64 rows per wave and chunk, all the time
+  auto row_frag = [&](Frag<T, D>& f, const char* row_ptr) { frag_load(f, row_ptr, kg, order); };
   Frag<T, D> lf[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) row_frag(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes);
@@ -388,7 +404,7 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   const int nblocks = S_pad / 32;
   unsigned coff[TL::kFragChunks];   // chunk c of this lane's fragment inside a block of 32 padded rows
 #pragma unroll
-  for (int c = 0; c < TL::kFragChunks; ++c) coff[c] = (unsigned)(n * TL::kStride + c * 32 + kg * 16);
+  for (int c = 0; c < TL::kFragChunks; ++c) coff[c] = (unsigned)(n * TL::kStride + order.chunk(c, kg) * 16);
   auto block_base = [&](int b) { return ckeys + b * 32 * TL::kStride; };
   auto block_inv = [&](int b) { return cinv + b * 32 + kg * 4; };
   while (c < n_chunks) {
@@ -1282,6 +1298,7 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   a.total_slots = (long long)p.B * p.Hkv;
   a.merge_rows = a.total_slots < kMergeShortRows ? kMergeRowsPerWaveShort : kMergeRowsPerWave;
   a.use_resident = 0;
+  a.adjacent_order = 0;
   a.merge_members = !((p.flags & MEDA_FLAG_NO_MERGE) || p.B == (int64_t)p.L * p.T);
   a.n_members = (int)(((int64_t)p.L * p.T - p.B) * p.Hkv);
   return a;
@@ -1354,7 +1371,9 @@ template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
   if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
+  static_assert(kSimDirectGroups < kAdjacentPairs && kAdjacentPairs <= kResidentPairs, "each kernel with one order keeps to it");
   a.use_resident = pairs >= kResidentPairs && p.B <= kResidentKept * p.L ? 1 : 0;
+  a.adjacent_order = pairs >= kAdjacentPairs ? 1 : 0;
   hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
                      dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
