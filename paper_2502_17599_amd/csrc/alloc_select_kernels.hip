@@ -199,6 +199,8 @@ struct SelectArgs {
   int32_t* merge_assign;    // may be null, [L][Hkv][T]
   int L, Hkv, T, no_merge;
   int Lseq;                 // layers per sequence (the mask is per sequence)
+  const char* k;            // the keys, row_bytes each (COPIES)
+  int row_bytes;
 };
 
 constexpr int kSelMaxThreads = 1024;
@@ -210,6 +212,20 @@ struct SelectShared {
   int wsum[2][kSelMaxWaves];
   int bin, rest;
 };
+
+// Copies of a key (COPIES, fp32 keys that are to be merged): of the conserved keys that are equal bit for bit the lowest
+// slot stands for all in the similarity search, the 1/|k| of the others becomes kNoSlot.  They are found by their equal
+// 1/|k|: an entry of the table holds the smallest (bits of 1/|k|, position) that falls on it.  A copy is missed where a key
+// with a smaller 1/|k| falls on its entry and where a workgroup finds more than kMaxCopies candidates; the search then
+// decides that tie by itself, which costs time and nothing else.
+constexpr int kCopyEntries = 2048, kMaxCopies = 512;
+struct CopyShared {
+  unsigned long long first[kCopyEntries];
+  int at[kMaxCopies], of[kMaxCopies], slot[kMaxCopies];  // positions of a candidate and of its first, its slot
+  int n;
+};
+__device__ __forceinline__ unsigned copy_entry(unsigned inv_bits) { return inv_bits * 2654435769u >> 21; }
+static_assert(kCopyEntries == 1 << (32 - 21), "the shift leaves the bits of an entry");
 
 // The digit of the `want`-th largest key of a histogram (want >= 1, at most the histogram's total) and how many of
 // that digit's keys are still wanted.  Every thread takes the same number of adjacent bins, from the top.
@@ -253,10 +269,12 @@ __device__ __forceinline__ void find_digit(SelectShared<BITS>& sh, const int* hi
 // the positions a tie may take before p are min(ties before p, ties taken), so one prefix over (certain, tied)
 // counts places everything.  Before and now, in us: 256 (layer, head) pairs of 131072 positions 370 / 233, 112 of 37376
 // 92 / 64, 256 of 16384 45 / 32, 1024 of 4096 31 / 29, 360 of 3001 23 / 16.5, 256 of 300 and of 100 11 / 10 and 10 / 9.4.
-template <int ITEMS, bool SINGLE, int BITS>
+template <int ITEMS, bool SINGLE, int BITS, bool COPIES>
 __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
   constexpr int kBins = 1 << BITS;
   __shared__ SelectShared<BITS> sh;
+  struct Nothing {};
+  __shared__ std::conditional_t<COPIES, CopyShared, Nothing> copies;
   const int g = blockIdx.x, l = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_thr = blockDim.x, n_waves = n_thr >> 6;
@@ -293,6 +311,10 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
   };
   if (SINGLE) load(0);
 
+  if constexpr (COPIES) {  // published by the barriers of the sweeps
+    for (int b = tid; b < kCopyEntries; b += n_thr) copies.first[b] = ~0ull;
+    if (tid == 0) copies.n = 0;
+  }
   for (int b = tid; b < 2 * kBins; b += n_thr) (&sh.hist[0][0])[b] = 0;
   __syncthreads();
   sweep([&](unsigned k, int c) { atomicAdd(&sh.hist[c][k >> (32 - BITS)], 1); });
@@ -374,6 +396,10 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
       if (sel) {
         a.sel_idx[c_base + pos_c] = head_row0 + j;
         a.sel_inv_norm[c_base + pos_c] = inv[i];
+        if constexpr (COPIES) {
+          const unsigned bits = __float_as_uint(inv[i]);
+          atomicMin(&copies.first[copy_entry(bits)], (unsigned long long)bits << 32 | (unsigned)j);
+        }
         if (a.sel_idx_user) a.sel_idx_user[c_base + pos_c] = j;
         if (a.merge_assign) a.merge_assign[head_row0 + j] = pos_c;
       } else if (j < T) {
@@ -385,6 +411,31 @@ __global__ void __launch_bounds__(kSelMaxThreads) select_kernel(SelectArgs a) {
     }
     run_sure += total & 0xffff;
     run_tie += total >> 16;
+  }
+  if constexpr (COPIES) {
+    __syncthreads();  // the table and this workgroup's sel_idx, sel_inv_norm are complete
+    for (int slot = tid; slot < S; slot += n_thr) {
+      const unsigned bits = __float_as_uint(a.sel_inv_norm[c_base + slot]);
+      const int j = a.sel_idx[c_base + slot] - head_row0;
+      const unsigned long long first = copies.first[copy_entry(bits)];
+      if ((unsigned)(first >> 32) != bits || (int)(unsigned)first == j) continue;
+      const int n = atomicAdd(&copies.n, 1);
+      if (n >= kMaxCopies) break;
+      copies.at[n] = j;
+      copies.of[n] = (int)(unsigned)first;
+      copies.slot[n] = slot;
+    }
+    __syncthreads();
+    const int pieces = a.row_bytes / 16, piece = tid % pieces;  // 16 or 32 adjacent lanes compare two keys
+    const char* keys = a.k + (size_t)head_row0 * a.row_bytes + piece * 16;
+    const int n_copies = min(copies.n, kMaxCopies);
+    for (int i = tid / pieces; i < n_copies; i += n_thr / pieces) {
+      const uint4 x = *reinterpret_cast<const uint4*>(keys + (size_t)copies.at[i] * a.row_bytes);
+      const uint4 y = *reinterpret_cast<const uint4*>(keys + (size_t)copies.of[i] * a.row_bytes);
+      unsigned differ = (x.x ^ y.x) | (x.y ^ y.y) | (x.z ^ y.z) | (x.w ^ y.w);
+      for (int o = pieces / 2; o > 0; o >>= 1) differ |= __shfl_xor((int)differ, o, kWave);
+      if (piece == 0 && differ == 0) a.sel_inv_norm[c_base + copies.slot[i]] = __uint_as_float(kNoSlot);
+    }
   }
 }
 
@@ -420,6 +471,8 @@ hipError_t launch_select(const Plan& p, const Buffers& b, hipStream_t s) {
   a.merge_assign = b.merge_assign;
   a.L = p.L; a.Hkv = p.Hkv; a.T = p.T; a.no_merge = (p.flags & MEDA_FLAG_NO_MERGE) ? 1 : 0;
   a.Lseq = p.Lseq;
+  a.k = static_cast<const char*>(b.k);
+  a.row_bytes = p.d * p.elt;
   const dim3 grid(p.Hkv, p.L);
   // Short prompts: one sweep costs less than clearing and searching 2048 bins, so 8-bit digits and as few positions per
   // thread as cover the prompt (256 pairs of 300 positions 12.1 -> 10.1 us, 1024 pairs 16.4 -> 12.1).  Longer ones: the
@@ -427,17 +480,22 @@ hipError_t launch_select(const Plan& p, const Buffers& b, hipStream_t s) {
   // 4100 positions 57 us with 1024 threads, 37 with 512, 34 with 256, but 256 pairs 18.4, 18.7 and 22 us.  From 8192
   // positions on the scores are read again in every sweep (8 registers of them per thread hide the loads as well).
   const int pairs = p.L * p.Hkv;
-  if (p.T <= 256) hipLaunchKernelGGL((select_kernel<1, true, 8>), grid, dim3(256), 0, s, a);
-  else if (p.T <= 512) hipLaunchKernelGGL((select_kernel<2, true, 8>), grid, dim3(256), 0, s, a);
-  else if (p.T <= 1024) hipLaunchKernelGGL((select_kernel<4, true, 8>), grid, dim3(256), 0, s, a);
-  else if (p.T <= 2048 && pairs <= 512) hipLaunchKernelGGL((select_kernel<4, true, 11>), grid, dim3(512), 0, s, a);
-  else if (p.T <= 2048) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(256), 0, s, a);
-  else if (p.T <= 4096) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(512), 0, s, a);
-  else if (p.T <= 8192 && pairs <= 256) hipLaunchKernelGGL((select_kernel<8, true, 11>), grid, dim3(1024), 0, s, a);
-  else {
-    const int n_thr = pairs <= 256 ? (p.T < 16384 ? 512 : 1024) : (pairs > 512 && p.T <= 16384 ? 256 : 512);
-    hipLaunchKernelGGL((select_kernel<8, false, 11>), grid, dim3(n_thr), 0, s, a);
-  }
+  auto launch = [&](auto copies_tag) {
+    constexpr bool C = decltype(copies_tag)::value;
+    if (p.T <= 256) hipLaunchKernelGGL((select_kernel<1, true, 8, C>), grid, dim3(256), 0, s, a);
+    else if (p.T <= 512) hipLaunchKernelGGL((select_kernel<2, true, 8, C>), grid, dim3(256), 0, s, a);
+    else if (p.T <= 1024) hipLaunchKernelGGL((select_kernel<4, true, 8, C>), grid, dim3(256), 0, s, a);
+    else if (p.T <= 2048 && pairs <= 512) hipLaunchKernelGGL((select_kernel<4, true, 11, C>), grid, dim3(512), 0, s, a);
+    else if (p.T <= 2048) hipLaunchKernelGGL((select_kernel<8, true, 11, C>), grid, dim3(256), 0, s, a);
+    else if (p.T <= 4096) hipLaunchKernelGGL((select_kernel<8, true, 11, C>), grid, dim3(512), 0, s, a);
+    else if (p.T <= 8192 && pairs <= 256) hipLaunchKernelGGL((select_kernel<8, true, 11, C>), grid, dim3(1024), 0, s, a);
+    else {
+      const int n_thr = pairs <= 256 ? (p.T < 16384 ? 512 : 1024) : (pairs > 512 && p.T <= 16384 ? 256 : 512);
+      hipLaunchKernelGGL((select_kernel<8, false, 11, C>), grid, dim3(n_thr), 0, s, a);
+    }
+  };
+  if (p.sim_split) launch(std::true_type{});
+  else launch(std::false_type{});
   return hipGetLastError();
 }
 

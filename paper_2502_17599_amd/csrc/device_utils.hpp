@@ -25,6 +25,7 @@ struct bf16_t {
 
 constexpr int kWave = 64;
 constexpr float kNegBig = -1.0e30f;
+constexpr unsigned kNoSlot = 0x7fc00000u;  // the 1/|k| (a NaN) of a conserved slot that no row goes to
 
 template <typename T, int D>
 struct Tile {

@@ -34,6 +34,28 @@ constexpr int kDirectManyHeads = 28;
 // 1477, 4076, 16 pairs 220, 1030, 2394, 3632.
 constexpr int64_t kLargePairs = 12000;
 
+// Which problems with fp32 keys go to the similarity kernel that splits them (merge_kernels.hip): from a number of positions
+// over all (layer, head) pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads,
+// would walk too long a share of the set.  Below it the waves that take their blocks again, and the search for copies in
+// the selection (2 to 8 us), cost more than the matrix instructions save.  Selection and similarity in us, direct kernel /
+// split kernel, a tenth and three tenths kept:
+//   rows of 256 bytes  32 pairs of 1200  31 / 34, 40 / 45   of 2000   46 / 42, 64 / 63   of 3000  72 / 57, 106 / 86
+//                      128 of 300        25 / 25, 26 / 29   of 700    37 / 32, 45 / 43   of 1200  65 / 43, 81 / 63
+//                      8 of 3000         46 / 39, 58 / 65   of 5000   71 / 54, 116 / 94
+//                      1 of 5000         65 / 45, 43 / 71   of 16000  153 / 91, 355 / 177
+//   rows of 512 bytes  32 pairs of 700   33 / 39, 39 / 55   of 1200   55 / 50, 67 / 74   of 2000  118 / 71, 123 / 108
+//                      64 of 300         28 / 30, 30 / 38   of 700    49 / 43, 57 / 56   of 1200  73 / 58, 113 / 79
+//                      8 of 2000         44 / 46, 59 / 73   of 5000   136 / 110, 201 / 158
+static bool similarity_splits(const Plan& p) {
+  if (p.dtype != MEDA_F32 || (p.flags & MEDA_FLAG_NO_MERGE)) return false;
+  const double pairs = (double)p.L * p.Hkv, positions = pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
+  const bool small = p.d == 64;
+  const double from = small ? (kept < 0.2 ? 46000 : 64000) : (kept < 0.2 ? 24000 : 50000);
+  const double longest = (pairs == 1 ? 4.1e4 : small ? 1.64e5 : 6.15e4) * kept;
+  return positions >= from || (pairs <= 8 && positions >= 36000) || p.T > longest || p.T > 16384 ||
+         positions > (small ? 1.5e6 : 5e5) * kept;
+}
+
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Tiling of the two scoring passes for w query rows (the last w positions) of a sequence of t keys.  With
@@ -147,6 +169,7 @@ meda_status make_plan(const meda_params* p, Plan* out) {
     pl.NCH = (pl.T + pl.CH - 1) / pl.CH;
     pl.NPART = pl.NCH;
   }
+  pl.sim_split = similarity_splits(pl) ? 1 : 0;
   const size_t stats_rows = pl.blocks ? (size_t)pl.R : (size_t)pl.Wp;
 
   pl.n_less_total = (size_t)((int64_t)pl.L * pl.T - pl.B) * pl.Hkv;

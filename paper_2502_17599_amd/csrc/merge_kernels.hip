@@ -39,9 +39,9 @@ __device__ __forceinline__ size_t less_base_of(int l, int g, int T, int Hkv, lon
 }
 
 // ------------------------------------------------------------------------ similarity + argmax
-// fp32 keys go to the split kernel.  bf16: small problems go to the direct kernel; of the others, layers whose conserved
-// set fits into LDS go to the resident-set kernel (one workgroup of 8 waves per (layer, head) part, all 160 KB of LDS),
-// the rest to the tiled kernel; both are launched and every workgroup looks up its layer's budget.
+// Small problems go to the direct kernel, larger ones with fp32 keys to the split kernel (Plan::sim_split), with bf16 keys
+// to the tiled kernel; layers whose conserved set fits into LDS may go to the resident-set kernel (one workgroup of 8 waves
+// per (layer, head) part, all 160 KB of LDS): then both are launched and every workgroup looks up its layer's budget.
 constexpr int kResWaves = 8;
 constexpr int kResThreads = kResWaves * 64;
 constexpr int kResLdsBytes = 160 * 1024;
@@ -541,9 +541,8 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs
 
 // ------------------------------------------------------------------------ fp32 keys in three bf16 parts
 // x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m, each rounded to nearest: 8 + 8 + 8 significant bits hold
-// all 24 of x, and every subtraction is exact.  Two elements per call; `rest` collects what is left, which is a NaN where
-// x has no such parts (infinite, NaN, or so large that h overflows) and a small number everywhere else.
-__device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& m, unsigned& l, float& rest) {
+// all 24 of x, and every subtraction is exact (for finite x whose h does not overflow).  Two elements per call.
+__device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& m, unsigned& l) {
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
   auto pack = [](float p, float q) { return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2_t){p, q}, bf16x2_t)); };
@@ -554,50 +553,64 @@ __device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& 
   x -= __uint_as_float(m << 16);
   y -= __uint_as_float(m & 0xffff0000u);
   l = pack(x, y);
-  rest += x;
-  rest += y;
 }
 // 8 consecutive elements: one 16-byte chunk of each part.
-__device__ __forceinline__ void split8(const uint4& a, const uint4& b, uint4 (&part)[3], float& rest) {
+__device__ __forceinline__ void split8(const uint4& a, const uint4& b, uint4 (&part)[3]) {
   const unsigned x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
   unsigned h[4], m[4], l[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) split2(__uint_as_float(x[2 * i]), __uint_as_float(x[2 * i + 1]), h[i], m[i], l[i], rest);
+  for (int i = 0; i < 4; ++i) split2(__uint_as_float(x[2 * i]), __uint_as_float(x[2 * i + 1]), h[i], m[i], l[i]);
   part[0] = make_uint4(h[0], h[1], h[2], h[3]);
   part[1] = make_uint4(m[0], m[1], m[2], m[3]);
   part[2] = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
+// Twice what the two sums of a product may lie apart, as a share of the lengths of both keys (which bound every partial
+// sum): D fused multiply-adds of the fp32 instruction and at most D additions of the leading bf16 products, each rounded to
+// 2^-24 of what it returns, and below 8 + D / 16 of that unit for the smaller products, those left out, 1/|k| and scaling.
+template <int D>
+constexpr float split_margin() {
+  return 5 * D * 5.9604645e-8f;
+}
+// 1/|k| of a key of length 2^-40 to 2^60: its parts exist and no product or sum leaves the normal range.
+__device__ __forceinline__ bool splits(float inv_norm) { return inv_norm >= 8.6736174e-19f && inv_norm <= 1.0995116e12f; }
+
 // Split kernel: fp32 keys on the bf16 matrix instructions.  A product of two keys is h h' + (h m' + m h') + (m m' + h l' +
 // l h') of their parts, added from the smallest terms to the largest in the fp32 accumulator; the three products left out
-// are below 2^-26 of the keys' lengths.  6 x 32 matrix clocks per 32 x 32 x 16 products instead of 512, and a sixteenth of
-// the fp32 instruction's roundings at the size of the result: keys that differ by 3e-4 of their size, so that the
-// similarities differ in their last bits, lose 6 to 14 % less against the nearest key in float64 than with that
-// instruction (mean loss 2.0e-8 to 3.0e-8 against 2.3e-8 to 3.4e-8).
-// grid over (row block of 32 F NW / SW, kv head, layer); a wave keeps F fragments of 32 less-important rows split in
-// registers, SW waves share the same rows and take every SW-th block of a tile; the conserved keys come from the key cache
-// in tiles: a thread loads its pieces of the next tile before it multiplies the present one, splits them after it and
-// stores the parts into the other of two LDS tiles (one barrier per tile).
-// Bound by the bf16 matrix instructions where the sets are long (256 pairs of 3126, a third kept: 1.97 PFLOP/s), by the
-// first loads and the splitting of rows and tiles where they are short.  Against the direct and tiled kernels with the
-// fp32 instruction that this replaces: 256 pairs of 1024 110 -> 40 us, of 3126 487 -> 222, 1024 of 969 (rows of 512 bytes) 737 -> 353.
-template <int D, int SW>
+// are below 2^-23 of the keys' lengths (2^-26 as a rule).  6 x 32 matrix clocks per 32 x 32 x 16 products instead of 512.
+//
+// These sums find the slots that can win, those of the fp32 instruction decide: a row with more than one slot within
+// split_margin of its best takes the products of the blocks they are in once more, with the fp32 instruction, so that near
+// ties fall as they do with that instruction alone.  For that a lane keeps, beside the best block, two others that came
+// within the margin of it, and the maximum of all further ones; where that is inside the margin too, its wave goes over
+// its whole share of the set.  One row in two thousand of clustered keys needs it, with two blocks as a rule.  Copies of
+// a lower slot's key, which would tie in both sums, have been taken out by the selection: their 1/|k| is a NaN, which no
+// maximum takes.  A workgroup with a key that splits() excludes goes over everything with the fp32 instruction.
+//
+// grid over (row block of 32 NW, kv head, layer); a wave keeps a fragment of 32 less-important rows split in registers;
+// the conserved keys come from the key cache in tiles of 64: a thread loads its pieces of the next tile before it multiplies
+// the present one, splits them after it and stores the parts into the other of two LDS tiles (one barrier per tile).
+// Bound by the bf16 matrix instructions (1.9 PFLOP/s of them where the sets are long) and, in short launches, by the waves
+// that take their blocks again, 3 to 10 us.  Selection and similarity together, against the direct and tiled kernels, in
+// us, three tenths kept: rows of 256 bytes 256 pairs of 700 69 -> 50, of 2000 290 -> 163, 32 of 8000 456 -> 279; rows of 512
+// bytes 116 -> 81, 593 -> 333, 886 -> 503.
+template <int D>
 struct SplitTile {
-  static constexpr int kSlots = SW > 2 ? 32 * SW : 64;
+  static constexpr int kSlots = 64;
   static constexpr int kPart = D * 2;             // bytes of one part of a key
   static constexpr int kStride = 3 * kPart + 16;  // three parts and padding: bank pattern as Tile<bf16_t, D>::kStride
   static constexpr int kTileBytes = kSlots * kStride;
   static constexpr int kLdsBytes = 2 * kTileBytes + 2 * kSlots * (int)sizeof(float) + 16;
 };
 
-template <int D, int F, int NW, int SW>
+template <int D, int NW>
 __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs a) {
   using TF = Tile<float, D>;
-  using ST = SplitTile<D, SW>;
+  using ST = SplitTile<D>;
   constexpr int kSplitSlots = ST::kSlots;
-  constexpr int kRows = 32 * F * NW / SW;
+  constexpr int kRows = 32 * NW;
   constexpr int NT = NW * 64;
-  constexpr int NC = D / 16;                     // chunks per lane, fragment and part
+  constexpr int NC = D / 16;                     // chunks per lane and part
   constexpr int GPR = D / 8;                     // pieces of 8 elements per key
   constexpr int NG = kSplitSlots * GPR / NT;     // pieces per thread and tile
   static_assert(NG * NT == kSplitSlots * GPR, "the pieces of a tile must come out even");
@@ -622,7 +635,7 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs 
   const size_t lbase = less_base_of(l, g, a.T, a.Hkv, off_l, S);
   const int32_t* less = a.less_idx + lbase;
 
-  // slots past the end repeat the last conserved key (see sim_block_products)
+  // slots past the end repeat the last conserved key, and their 1/|k| is a NaN as well
   const int ntiles = (S + kSplitSlots - 1) / kSplitSlots, nblocks = (S + 31) / 32;
   auto load_ids = [&](int t, int (&id)[NG]) {
 #pragma unroll
@@ -637,46 +650,56 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs 
       piece[i][0] = src[0];
       piece[i][1] = src[1];
     }
-    if (tid < kSplitSlots) piece_inv = sinv[min(t * kSplitSlots + tid, S - 1)];
+    if (tid < kSplitSlots) {
+      const int s = t * kSplitSlots + tid;
+      piece_inv = sinv[min(s, S - 1)];
+      piece_inv = s < S ? piece_inv : __uint_as_float(kNoSlot);
+    }
   };
-  float rest = 0.f;  // NaN once a key without three parts has been seen
+  bool bad = false;  // a key that splits() excludes has been seen
   auto store_tile = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       uint4 part[3];
-      split8(piece[i][0], piece[i][1], part, rest);
+      split8(piece[i][0], piece[i][1], part);
       char* dst = smem + buf * ST::kTileBytes + (tid + i * NT) / GPR * ST::kStride + (tid + i * NT) % GPR * 16;
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(dst + p * ST::kPart) = part[p];
     }
-    if (tid < kSplitSlots) inv_lds[buf * kSplitSlots + tid] = piece_inv;
+    if (tid < kSplitSlots) {
+      inv_lds[buf * kSplitSlots + tid] = piece_inv;
+      bad |= piece_inv == piece_inv && !splits(piece_inv);
+    }
   };
 
   // rows past the end repeat the last one and are never stored
-  const int r0 = row_base + wave / SW * 32 * F;
-  int id[NG], lrow[F];
+  const int r0 = row_base + wave * 32;
+  int id[NG];
   load_ids(0, id);
-#pragma unroll
-  for (int s = 0; s < F; ++s) lrow[s] = less[min(r0 + s * 32 + n, n_less - 1)];
+  const int lrow = less[min(r0 + n, n_less - 1)];
   load_tile(0, id);
   load_ids(1, id);
-  uint4 rows[F][3][NC];
-#pragma unroll
-  for (int s = 0; s < F; ++s) {
-    const uint4* src = reinterpret_cast<const uint4*>(a.k + (size_t)lrow[s] * TF::kRowBytes + kg * TF::kHalfBytes);
+  const float row_inv = a.inv_norm[lrow];
+  bad |= !splits(row_inv);
+  uint4 rows[3][NC];
+  {
+    const uint4* src = reinterpret_cast<const uint4*>(a.k + (size_t)lrow * TF::kRowBytes + kg * TF::kHalfBytes);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       uint4 part[3];
-      split8(src[2 * c], src[2 * c + 1], part, rest);
+      split8(src[2 * c], src[2 * c + 1], part);
 #pragma unroll
-      for (int p = 0; p < 3; ++p) rows[s][p][c] = part[p];
+      for (int p = 0; p < 3; ++p) rows[p][c] = part[p];
     }
   }
   if (tid == 0) *bad_lds = 0;
   store_tile(0);
-  RowBest rb[F];
-#pragma unroll
-  for (int s = 0; s < F; ++s) row_best_init(rb[s]);
+  RowBest rb;
+  row_best_init(rb);
+  // Blocks beside the best one that came within the margin of it: the best two of them and the maximum of all others.
+  float second = -INFINITY, third = -INFINITY, further = -INFINITY;
+  int second_slot0 = 0, third_slot0 = 0;
+  const float margin = split_margin<D>() / row_inv;
   __syncthreads();
 
   for (int t = 0; t < ntiles; ++t) {
@@ -686,8 +709,8 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs 
       load_ids(t + 2, id);
     }
 #pragma unroll
-    for (int i = 0; i < kSplitSlots / 32 / SW; ++i) {
-      const int cb = i * SW + wave % SW, b = t * (kSplitSlots / 32) + cb;
+    for (int cb = 0; cb < kSplitSlots / 32; ++cb) {
+      const int b = t * (kSplitSlots / 32) + cb;
       if (b >= nblocks) break;
       const char* src = smem + (t & 1) * ST::kTileBytes + (cb * 32 + n) * ST::kStride + kg * (ST::kPart / 2);
       uint4 keys[3][NC];
@@ -695,14 +718,10 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs 
       for (int p = 2; p >= 0; --p)
 #pragma unroll
         for (int c = 0; c < NC; ++c) keys[p][c] = *reinterpret_cast<const uint4*>(src + p * ST::kPart + c * 16);
-      f32x16_t acc[F];
-#pragma unroll
-      for (int s = 0; s < F; ++s) acc[s] = acc_zero();
+      f32x16_t acc = acc_zero();
       auto product = [&](int pk, int pr) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-          for (int s = 0; s < F; ++s) mma_chunk<bf16_t>(acc[s], keys[pk][c], rows[s][pr][c]);
+        for (int c = 0; c < NC; ++c) mma_chunk<bf16_t>(acc, keys[pk][c], rows[pr][c]);
       };
       product(2, 0);
       product(1, 1);
@@ -712,71 +731,94 @@ __global__ void __launch_bounds__(NW * 64, 2) similarity_split_kernel(MergeArgs 
       product(0, 0);
       float iv[16];
       load_inv(iv, inv_lds + (t & 1) * kSplitSlots + cb * 32 + kg * 4);
-#pragma unroll
-      for (int s = 0; s < F; ++s) keep_if_improved(acc[s], scale_max(acc[s], iv), b * 32, rb[s]);
+      const float bm = scale_max(acc, iv);
+      // (one that is further behind the best so far, or is left further behind, cannot hold the nearest slot)
+      const bool close = fabsf(bm - rb.best) <= margin;
+      if (__ballot(close) != 0ull) {
+        const float lower = close ? fminf(bm, rb.best) : -INFINITY;
+        const int lower_slot0 = bm > rb.best ? rb.slot0 : b * 32;
+        const bool is_second = lower > second, is_third = lower > third;
+        further = fmaxf(further, is_third ? third : lower);
+        third = is_second ? second : is_third ? lower : third;
+        third_slot0 = is_second ? second_slot0 : is_third ? lower_slot0 : third_slot0;
+        second = is_second ? lower : second;
+        second_slot0 = is_second ? lower_slot0 : second_slot0;
+      }
+      keep_if_improved(acc, bm, b * 32, rb);
     }
     if (more) store_tile((t + 1) & 1);
     __syncthreads();
   }
-  if (rest != rest) *bad_lds = 1;
+
+  if (bad) *bad_lds = 1;
   __syncthreads();
-  if (*bad_lds != 0) {
-    // A key of this workgroup has no three bf16 parts: the fp32 instruction, operands straight from the key cache.
+  const bool all_fp32 = *bad_lds != 0;
+
+  // The best slot by these sums.  The two lane groups saw disjoint slots of the same row: the better one, ties -> lower slot.
+  float best = rb.best;
+  int slot = row_best_slot(rb, kg);
+  auto keep_better = [&](float ov, int os) {
+    const bool take = ov > best || (ov == best && os < slot);
+    best = take ? ov : best;
+    slot = take ? os : slot;
+  };
+  auto merge_lane_groups = [&]() {
+    const float ov = __shfl_xor(best, 32, kWave);
+    const int os = __shfl_xor(slot, 32, kWave);
+    keep_better(ov, os);
+  };
+  merge_lane_groups();
+
+  // Which rows have another slot within the margin.
+  const float limit = best - margin;
+  int undecided = all_fp32 || second >= limit ? 1 : 0;
 #pragma unroll
-    for (int s = 0; s < F; ++s) {
-      row_best_init(rb[s]);
-      Frag<float, D> lf;
-      frag_load(lf, a.k + (size_t)lrow[s] * TF::kRowBytes, kg);
-      for (int b = wave % SW; b < nblocks; b += SW) {
-        Frag<float, D> cf;
-        frag_load(cf, a.k + (size_t)sel[min(b * 32 + n, S - 1)] * TF::kRowBytes, kg);
-        float iv[16];
+  for (int r = 0; r < 16; ++r) undecided |= rb.u[r] >= limit && rb.slot0 + acc_row(r, kg) != slot ? 1 : 0;
+  undecided |= __shfl_xor(undecided, 32, kWave);
+  if (__ballot(undecided) != 0ull) {
+    // The fp32 instruction, operands straight from the key cache: the blocks that hold a slot within the margin, or all
+    // blocks.  (More blocks than a row asked for change nothing: they are compared by the same sums.)
+    const int nearest = slot;
+    best = -INFINITY;
+    slot = 0;
+    Frag<float, D> lf;
+    frag_load(lf, a.k + (size_t)lrow * TF::kRowBytes, kg);
+    auto take_block = [&](int b) {
+      Frag<float, D> cf;
+      frag_load(cf, a.k + (size_t)sel[min(b * 32 + n, S - 1)] * TF::kRowBytes, kg);
+      float iv[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) iv[r] = sinv[min(b * 32 + acc_row(r, kg), S - 1)];
-        f32x16_t acc = acc_zero();
-        mma<float, D>(acc, cf, lf);
-        keep_if_improved(acc, scale_max(acc, iv), b * 32, rb[s]);
+      for (int r = 0; r < 16; ++r) iv[r] = sinv[min(b * 32 + acc_row(r, kg), S - 1)];
+      f32x16_t acc = acc_zero();
+      mma<float, D>(acc, cf, lf);
+      const float bm = scale_max(acc, iv);
+      int ridx = 15;
+#pragma unroll
+      for (int r = 14; r >= 0; --r) ridx = acc[r] == bm ? r : ridx;
+      keep_better(bm, b * 32 + acc_row(ridx, kg));
+    };
+    if (all_fp32 || __ballot(undecided && further >= limit) != 0ull) {
+      for (int b = 0; b < nblocks; ++b) take_block(b);
+    } else {
+      int first = undecided && rb.best >= limit ? rb.slot0 >> 5 : -1;
+      int other = undecided && second >= limit ? second_slot0 >> 5 : -1;
+      int last = undecided && third >= limit ? third_slot0 >> 5 : -1;
+      while (true) {
+        const unsigned long long waiting = __ballot(first >= 0 || other >= 0 || last >= 0);
+        if (waiting == 0ull) break;
+        const int b = __builtin_amdgcn_readlane(first >= 0 ? first : other >= 0 ? other : last, __ffsll(waiting) - 1);
+        take_block(b);
+        first = first == b ? -1 : first;
+        other = other == b ? -1 : other;
+        last = last == b ? -1 : last;
       }
     }
+    merge_lane_groups();
+    slot = undecided ? slot : nearest;
   }
-  if constexpr (SW > 1) {  // the bests of the waves that share rows, over the tiles (nobody reads those any more)
-    float* best_v = reinterpret_cast<float*>(smem);                  // [NW][32 F]
-    int* best_s = reinterpret_cast<int*>(smem + NW * 32 * F * 4);    // [NW][32 F]
-#pragma unroll
-    for (int s = 0; s < F; ++s) {
-      const int bi = row_best_merge(rb[s], kg);
-      const float bv = fmaxf(rb[s].best, __shfl_xor(rb[s].best, 32, kWave));
-      if (kg == 0) {
-        best_v[(wave * F + s) * 32 + n] = bv;
-        best_s[(wave * F + s) * 32 + n] = bi;
-      }
-    }
-    __syncthreads();
-    if (tid < kRows && row_base + tid < n_less) {
-      const int at = tid / (32 * F) * SW * 32 * F + tid % (32 * F);
-      float v = best_v[at];
-      int slot = best_s[at];
-#pragma unroll
-      for (int w = 1; w < SW; ++w) {
-        const float ov = best_v[at + w * 32 * F];
-        const int os = best_s[at + w * 32 * F];
-        const bool take = ov > v || (ov == v && os < slot);
-        v = take ? ov : v;
-        slot = take ? os : slot;
-      }
-      a.less_slot[lbase + row_base + tid] = slot;
-      if (a.merge_assign) a.merge_assign[less[row_base + tid]] = slot;
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < F; ++s) {
-      const int bi = row_best_merge(rb[s], kg);
-      const int ri = r0 + s * 32 + n;
-      if (kg == 0 && ri < n_less) {
-        a.less_slot[lbase + ri] = bi;
-        if (a.merge_assign) a.merge_assign[lrow[s]] = bi;
-      }
-    }
+  if (kg == 0 && r0 + n < n_less) {
+    a.less_slot[lbase + r0 + n] = slot;
+    if (a.merge_assign) a.merge_assign[lrow] = slot;
   }
 }
 
@@ -1317,44 +1359,18 @@ static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStrea
   return hipGetLastError();
 }
 
-template <int D, int F, int NW, int SW>
+template <int D, int NW>
 static hipError_t launch_sim_split(const MergeArgs& a, hipStream_t s) {
-  constexpr int kRows = 32 * F * NW / SW;
+  constexpr int kRows = 32 * NW;
   const unsigned nrb = (a.T + kRows - 1) / kRows;
-  auto split = similarity_split_kernel<D, F, NW, SW>;
-  constexpr int kLds = SplitTile<D, SW>::kLdsBytes;
+  auto split = similarity_split_kernel<D, NW>;
+  constexpr int kLds = SplitTile<D>::kLdsBytes;
   if (kLds > 64 * 1024) {
     const hipError_t e = allow_dynamic_lds(split, kLds);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(split, dim3(nrb * (unsigned)(a.L * a.Hkv)), dim3(NW * 64), kLds, s, a);
   return hipGetLastError();
-}
-
-// fp32 problems: waves per workgroup and how many of them share the same rows.  Where 128 rows per workgroup leave CUs
-// empty, the chain of tiles that one wave walks bounds the kernel, above all in the layers with the longest sets: waves
-// that take every SW-th block shorten it, at the price of splitting the set for fewer rows.  us, by events around the
-// phase (with about 5 us of them), NW x SW = 4 x 1 / 8 x 4 / 4 x 4 (rows of 256 bytes), 4 x 1 / 8 x 1 / 4 x 2 (of 512):
-//   256 bytes  8 pairs of 704, 2 layers 13.6 / 11.8 / 10.5      18 of 1674, 18 layers 38 / 24 / 30
-//              10 of 3835, 5 layers     82 / 47 / 47            30 of 3851, 15 layers 103 / 90 / 135
-//              32 of 800, 1 layer       11.5 / 17.9 / 20.2      256 of 829, 8 layers  30 / 79 / 115
-//   512 bytes  5 of 1272, 5 layers      28 / 38 / 21            16 of 1718, 4 layers  32 / 43 / 25
-//              32 of 1157, 1 layer      17.7 / 21.7 / 23.7      35 of 2715, 35 layers 106 / 140 / 97
-//              256 of 310               26 / 32 / 36            224 of 660, 28 layers 46 / 38 / 64
-// The fp32 instruction in the direct / tiled kernel before (tiled with its packing launch): 256 pairs of 829 107 / 71,
-// 8 of 704 12.3 / 19, 224 of 660 (512 bytes) 111 / 91.
-template <int D>
-static hipError_t launch_sim_fp32(const Plan& p, const MergeArgs& a, hipStream_t s) {
-  const long long pairs = (long long)p.L * p.Hkv, groups128 = pairs * ((p.T + 127) / 128);
-  if constexpr (D == 64) {
-    const double groups32 = (double)pairs * ((double)p.T - (double)p.B / p.L) / 32;  // of rows that merge, equal budgets
-    if (pairs <= 32 && groups32 <= 256) return launch_sim_split<D, 1, 4, 4>(a, s);
-    if (p.L >= 3 && p.T >= 256 && groups128 <= 320) return launch_sim_split<D, 1, 8, 4>(a, s);
-  } else {
-    if (groups128 <= 160 || (p.L >= 3 && groups128 <= 256)) return launch_sim_split<D, 1, 4, 2>(a, s);
-    if (p.T > 128 && pairs * ((p.T + 255) / 256) >= 576) return launch_sim_split<D, 1, 8, 1>(a, s);
-  }
-  return launch_sim_split<D, 1, 4, 1>(a, s);
 }
 
 // Where the resident-set kernel takes the layers that fit: a workgroup of it occupies a whole CU, so with one or two per CU
@@ -1393,6 +1409,20 @@ static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(res, dim3(pairs * kResSplit), dim3(kResThreads), kResLdsBytes, s, a);
   return hipGetLastError();
+}
+
+// fp32 problems (Plan::sim_split).  Split kernel: workgroups of eight waves share a tile's pieces among more rows, which pays
+// for rows of 512 bytes once two of them per CU are there (224 pairs of 660 46 -> 38 us, 35 of 2715 106 -> 140).  Direct
+// kernel: two fragments per wave halve the key loads once there are enough workgroups of 64 rows for every CU.
+template <int D>
+static hipError_t launch_sim_fp32(const Plan& p, const MergeArgs& a, hipStream_t s) {
+  const unsigned pairs = (unsigned)(p.L * p.Hkv);
+  if constexpr (D == 128) {
+    if (p.sim_split && pairs * ((p.T + 255u) / 256u) >= 576u) return launch_sim_split<D, 8>(a, s);
+  } else {
+    if (!p.sim_split && pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<float, D, 2, 4>(a, pairs, s);
+  }
+  return p.sim_split ? launch_sim_split<D, 4>(a, s) : launch_sim_direct<float, D, 1, 8>(a, pairs, s);
 }
 
 hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {

@@ -30,6 +30,8 @@ def _run(L, hkv, T, d, kept, k, q0):
 SHAPES = [  # layers, kv heads, positions, head dimension, share kept
     (1, 1, 33, 64, 0.5), (2, 4, 257, 64, 0.3), (3, 8, 700, 64, 0.25), (2, 20, 300, 64, 0.2),
     (1, 2, 65, 128, 0.5), (2, 24, 500, 128, 0.1), (8, 32, 600, 128, 0.12),
+    # the kernel that splits: sets of one and of many tiles, row blocks of 128 and 256 with a remainder, few and many pairs
+    (32, 32, 65, 64, 0.5), (1, 4, 9001, 64, 0.05), (8, 8, 1111, 64, 0.35), (48, 32, 33, 128, 0.55), (2, 24, 553, 128, 0.15),
 ]
 
 
@@ -51,6 +53,27 @@ def test_nearest_key_of_fp32_keys(L, hkv, T, d, kept, near):
         sim = u[less] @ u[sel].T
         got = sim.gather(1, slot[less][:, None])[:, 0]
         assert float((sim.max(1).values - got).max()) <= bound, (l, h)
+
+
+@pytest.mark.parametrize("near", [0.0, 3e-4, 3e-3], ids=["spread", "all_near", "many_near"])
+@pytest.mark.parametrize("L,hkv,T,d,kept", SHAPES)
+def test_near_ties_fall_as_with_the_fp32_instruction(L, hkv, T, d, kept, near):
+    """The same keys twice: as they are, and with a last key (always conserved) that has no three parts and is the nearest
+    of no row, which sends every workgroup over the whole set with the fp32 instruction."""
+    g = torch.Generator().manual_seed(3 * T)
+    centres = torch.randn(L, hkv, 1 if near else 4, d, generator=g)
+    k = centres.repeat(1, 1, T // centres.shape[2] + 1, 1)[:, :, :T] + (near or 0.3) * torch.randn(L, hkv, T, d, generator=g)
+    if not near:  # copies of two keys, as the selection finds them, and of one that is the nearest of many rows
+        k[:, :, 5::7], k[:, :, 6::11] = k[:, :, 5:6], k[:, :, 6:7]
+        k[:, :, 3::9] = centres[:, :, 3:4]
+    k[..., 0] = 0.1
+    k[:, :, -1] = -3.0 * centres.sum(2)
+    plain, fp32 = k.clone(), k.clone()
+    plain[:, :, -1, 0] = -0.1
+    fp32[:, :, -1, 0] = 3.4e38
+    for (l, h, sel, slot), (_, _, sel32, slot32) in zip(_run(L, hkv, T, d, kept, plain, 0.0), _run(L, hkv, T, d, kept, fp32, 0.0)):
+        assert torch.equal(sel, sel32) and int(sel[-1]) == T - 1
+        assert torch.equal(slot, slot32), (l, h, int((slot != slot32).sum()))
 
 
 @pytest.mark.parametrize("L,hkv,T,d,kept", SHAPES)
