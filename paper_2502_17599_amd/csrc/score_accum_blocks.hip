@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(kBlkThreads, kBlkWaves / 4) score_accum_blocks
           const bool row_is_vision = ((rows_vision >> acc_row(r, kg)) & 1u) != 0;
           const float p = pbar[hf][f][r] * inv_heads;
           const float t = p * __logf(p);  // (no branch around the logarithm)
-          s += (p > 0.f) & (row_is_vision != col_is_vision) ? t : 0.f;
+          s += ((p > 0.f) & (row_is_vision != col_is_vision)) ? t : 0.f;
           pbar[hf][f][r] = 0.f;
         }
       }

@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
 #pragma unroll
     for (int c = 0; c < KI; ++c) async_copy16_to_lds_stream(ksrc, kcopy[c], (unsigned)(size_t)key_rows + c * CT::kPiece);
   };
-  auto load_keys = [&](Frag<T, D>& f, int g) { frag_load(f, uniform_ptr(a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt) + koff, kg); };
+  // (the base straight from the kernel's arguments: through uniform_ptr it would lose its address space, and FLAT loads, which
+  // count as LDS accesses too and come back in no order, cannot be waited for by number)
+  auto load_keys = [&](Frag<T, D>& f, int g) { frag_load(f, a.k + (size_t)(l * a.Hkv + g) * a.Tk * RBt + koff, kg); };
   // this lane's value of the first kDmaThreads statistics (the plane of the maxima is among them)
   const unsigned soff = 4u * (unsigned)(tid < Wp ? min(tid, a.W - 1) : tid);
   const unsigned lds0 = (unsigned)(size_t)smem;
@@ -208,7 +210,7 @@ __global__ void __launch_bounds__(kDmaThreads, RB <= 2 ? 3 : 2) score_accum_dma_
       const bool row_is_vision = ((rows_vision[rb] >> acc_row(r, kg)) & 1u) != 0;
       const float p = pbar[rb][r] * inv_heads;
       const float t = p * __logf(p);  // (no branch around the logarithm)
-      s += (p > 0.f) & (row_is_vision != col_is_vision) ? t : 0.f;
+      s += ((p > 0.f) & (row_is_vision != col_is_vision)) ? t : 0.f;
     }
   const double tv = wave_sum(col_is_vision ? (double)s : 0.0);
   const double vt = wave_sum((col_ok && !col_is_vision) ? (double)s : 0.0);
