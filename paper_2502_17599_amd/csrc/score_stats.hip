@@ -6,7 +6,7 @@
 namespace meda {
 
 // ------------------------------------------------------------------------------------------ pass A
-// grid (NCH, Hkv, L), or (1, Hkv * row blocks, L) in the row-block mode (more than 128 scoring rows); NCG*CS waves.
+// grid (NCH, Hkv, L), or (Hkv * row blocks, 1, L) in the row-block mode (more than 128 scoring rows); NCG*CS waves.
 // Wave (cg, cs) keeps NQ query fragments ((head of the group, row
 // block) pairs cg*NQ .. cg*NQ+NQ-1) in registers and visits the 32-key blocks sb = cs, cs+CS, ... of
 // every tile of its chunk.  The product is taken with the keys as operand A and the queries as
@@ -23,15 +23,15 @@ __global__ void __launch_bounds__(NW * 64, (NQ == 1 && NW == 4 && sizeof(T) == 2
   char* ktile = smem;
   uint8_t* lmask = reinterpret_cast<uint8_t*>(smem + kScoreTile * TL::kStride);
 
-  const int ch = blockIdx.x;
+  const int ch = BLOCKS ? 0 : blockIdx.x;
   int l = blockIdx.z, g = blockIdx.y, bi = 0;
   if (BLOCKS) {  // row-block mode (one chunk): this workgroup's row block, the largest ones first
     if ((a.Hkv & 7) == 0) {
-      bi = blockIdx.y / a.Hkv;
-      g = blockIdx.y - bi * a.Hkv;
+      bi = blockIdx.x / a.Hkv;
+      g = blockIdx.x - bi * a.Hkv;
     } else {  // row blocks by XCD in the order of the grid would give some XCDs all the long ones
       unsigned pair, rblock;
-      pair_and_row_block(blockIdx.z * gridDim.y + blockIdx.y, (unsigned)(a.L * a.Hkv), gridDim.y / (unsigned)a.Hkv, pair, rblock);
+      pair_and_row_block(blockIdx.z * gridDim.x + blockIdx.x, (unsigned)(a.L * a.Hkv), gridDim.x / (unsigned)a.Hkv, pair, rblock);
       l = pair / (unsigned)a.Hkv;
       g = pair - (unsigned)(l * a.Hkv);
       bi = rblock;
@@ -297,7 +297,8 @@ static hipError_t launch_stats_b(const Plan& p, const ScoreArgs& a, hipStream_t 
     hipError_t e = allow_dynamic_lds(kern, (int)lds);
     if (e != hipSuccess) return e;
   }
-  dim3 grid(p.NCH, p.Hkv * p.n_blocks_a, p.L), block(NW * 64);
+  // (row blocks along x: the device promises 65536 workgroups along y)
+  const dim3 grid = BLOCKS ? dim3(p.Hkv * p.n_blocks_a, 1, p.L) : dim3(p.NCH, p.Hkv, p.L), block(NW * 64);
   hipLaunchKernelGGL(kern, grid, block, lds, s, a);
   return hipGetLastError();
 }

@@ -1,7 +1,7 @@
 // Pass A of the scoring (Sections 3.2 and 3.3) for grouped query heads and for the row-block mode: row maxima and softmax
 // normalisers of the scoring rows, and 1/|k| of every key, with the key tiles brought into LDS by asynchronous copies.
 //
-// grid (NCH, Hkv, L), or (1, Hkv * row blocks, L) in the row-block mode; NCG * CS waves at work.  Wave (cg, cs) keeps NQ
+// grid (NCH, Hkv, L), or (Hkv * row blocks, 1, L) in the row-block mode; NCG * CS waves at work.  Wave (cg, cs) keeps NQ
 // query fragments ((head of the group, row block) pairs cg*NQ .. cg*NQ+NQ-1) in registers and visits the 32-key blocks
 // sb = cs, cs+CS, ... of every tile of its chunk.  The keys are operand A, the queries operand B, so a lane owns one
 // query row and 16 keys per block: the running (max, Z_vision, Z_text) of the row are three registers per fragment and
@@ -34,15 +34,15 @@ __global__ void __launch_bounds__(NW * 64, 2) score_stats_dma_kernel(ScoreArgs a
   static_assert(NI % NW == 0, "the copy instructions must tile a tile evenly");
   extern __shared__ __align__(16) char smem[];  // two tiles
 
-  const int ch = blockIdx.x;
+  const int ch = BLOCKS ? 0 : blockIdx.x;
   int l = blockIdx.z, g = blockIdx.y, bi = 0;
   if (BLOCKS) {  // row-block mode (one chunk): this workgroup's row block, the largest ones first
     if ((a.Hkv & 7) == 0) {
-      bi = blockIdx.y / a.Hkv;
-      g = blockIdx.y - bi * a.Hkv;
+      bi = blockIdx.x / a.Hkv;
+      g = blockIdx.x - bi * a.Hkv;
     } else {  // row blocks by XCD in the order of the grid would give some XCDs all the long ones
       unsigned pair, rblock;
-      pair_and_row_block(blockIdx.z * gridDim.y + blockIdx.y, (unsigned)(a.L * a.Hkv), gridDim.y / (unsigned)a.Hkv, pair, rblock);
+      pair_and_row_block(blockIdx.z * gridDim.x + blockIdx.x, (unsigned)(a.L * a.Hkv), gridDim.x / (unsigned)a.Hkv, pair, rblock);
       l = pair / (unsigned)a.Hkv;
       g = pair - (unsigned)(l * a.Hkv);
       bi = rblock;
@@ -160,7 +160,8 @@ __global__ void __launch_bounds__(NW * 64, 2) score_stats_dma_kernel(ScoreArgs a
 template <typename T, int D, int NQ, int NW>
 static hipError_t launch_dma_w(const Plan& p, const ScoreArgs& a, hipStream_t s) {
   constexpr int kLds = 2 * CopyTile<T, D>::bytes(kStatTile);
-  const dim3 grid(p.NCH, p.Hkv * p.n_blocks_a, p.L), block(NW * 64);
+  // (row blocks along x: the device promises 65536 workgroups along y)
+  const dim3 grid = p.blocks ? dim3(p.Hkv * p.n_blocks_a, 1, p.L) : dim3(p.NCH, p.Hkv, p.L), block(NW * 64);
   auto kern = p.blocks ? score_stats_dma_kernel<T, D, NQ, NW, true> : score_stats_dma_kernel<T, D, NQ, NW, false>;
   if (kLds > 64 * 1024) {
     hipError_t e = allow_dynamic_lds(kern, kLds);

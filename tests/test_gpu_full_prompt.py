@@ -95,3 +95,28 @@ def test_full_prompt_llava7b_shape_two_layers():
     comp, gpu = run_gpu(wl, data)
     stats = check_all(wl, data, gpu, heads=[(0, 0), (0, 17), (1, 31)], threads=2)
     assert stats["layers_passing_only_by_entropy_floor"] == 0
+
+
+def test_full_prompt_with_more_than_65535_row_blocks_in_pass_a():
+    # 1024 kv heads x 65 row blocks of 32 rows (four heads per kv head): more than the device promises along y (65536).  The column
+    # scores of some kv heads against float64 softmax, and of all against the rows they sum (a row's probabilities add
+    # up to 1): a logit is a sum of 64 products with a magnitude of up to 10, so its error is below 64 * 10 * 2^-24 =
+    # 3.9e-5, the relative error of the probability; twice that for both passes.
+    import torch
+    import paper_2502_17599_amd as pkg
+    hkv, G, T, d = 1024, 4, 2080, 64
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(4)
+    q = torch.randn(1, hkv * G, T, d, generator=gen, device=dev, dtype=torch.bfloat16)
+    k = torch.randn(1, hkv, T, d, generator=gen, device=dev, dtype=torch.bfloat16)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[100:1500] = 1
+    comp = pkg.Compressor(pkg.make_params(1, hkv * G, hkv, d, T, 32, 32, torch.bfloat16, flags=pkg.FLAG_FULL_PROMPT), dev)
+    comp(q, k, k, mask)
+    got = comp.region("col_scores", torch.float32).view(hkv, T).double()
+    assert float((got.sum(1) / (G * T) - 1).abs().max()) <= 8e-5
+    causal = torch.ones(T, T, dtype=torch.bool, device=dev).triu(1)
+    for g in (0, 517, 1023):
+        logits = q[0, g * G:(g + 1) * G].double() @ k[0, g].double().T / d ** 0.5
+        want = torch.softmax(logits.masked_fill(causal, float("-inf")), dim=-1).sum(dim=(0, 1))
+        assert float(((got[g] - want).abs() / want).max()) <= 8e-5
