@@ -83,7 +83,12 @@ static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) 
   if (combos > 32 || pl->RB > 4) return false;
   // (head, row block) pairs a wave keeps in registers: four waves at work where they can be, which leaves two workgroups
   // per CU, one computing while the other waits at its barrier
-  pl->NQ = combos <= 4 ? 1 : (combos <= 8 ? 2 : (combos <= 12 ? 3 : 4));
+  // (rows of 512 bytes do not fit the registers more than twice: G 8, 64 rows, 64 pairs of 3000 keys 335 us with two per wave
+  // and eight waves, 530 with four and four)
+  if (pl->d * pl->elt > 256)
+    pl->NQ = combos <= 4 ? 1 : (combos <= 16 ? 2 : 4);
+  else
+    pl->NQ = combos <= 4 ? 1 : (combos <= 8 ? 2 : (combos <= 12 ? 3 : 4));
   pl->NCG = (combos + pl->NQ - 1) / pl->NQ;
   pl->CS = (pl->NCG <= 4) ? 4 / pl->NCG : 1;
   const int tiles = (t + kScoreTile - 1) / kScoreTile;
