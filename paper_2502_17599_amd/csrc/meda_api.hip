@@ -20,7 +20,7 @@ namespace meda {
 constexpr int64_t kDirectTiles = 64, kDirectTilesAll = 128;
 constexpr int kDirectManyHeads = 28;
 
-// (Head, 32-row block) pairs in all, every prompt row scoring, from which a pass-A workgroup takes more than four of them
+// (Head, 32-row block) pairs in all, every prompt row scoring, above which a pass-A workgroup takes more than four of them
 // (bf16 rows of 256 bytes).  Pass A in us, workgroups of 4 / 8 / 12 / 16 pairs:
 //   bf16, 256 bytes   1600 pairs (8 layers of 780, 8 heads)  28 / 34 / 43 / 59    9600 (24 of 1600, 8)   137 / 139 / 174 / 219
 //                     16128 (8 of 2000, 32)  244 / 245 / 250 / 290                19200 (24 of 1600, 16 in 4) 225 / 205 / 211 / 215
@@ -33,6 +33,13 @@ constexpr int kDirectManyHeads = 28;
 // 1458, 2000, 3000: 12 pairs 214, 966, 1507, 3223, 16 pairs 216, 1000, 1674, 3243; in the order of the grid 12 pairs 213, 1428,
 // 1477, 4076, 16 pairs 220, 1030, 2394, 3632.
 constexpr int64_t kLargePairs = 12000;
+// The same for observation windows of more than 128 rows, whose row blocks all walk nearly the whole prompt: up to which
+// number of pairs a workgroup takes four, and eight, of them.  Pass A in us, workgroups of 4 / 8 / 16 pairs, 20000 keys:
+//   bf16, 256 bytes   2048 pairs (64 pairs of kv heads, 1000 rows)   505 / 559 / 957    2240 (28 layers, 16 heads in 4, 129)  736 / 747 / 960
+//                     3584 (28, 16 in 4, 256) 881 / 797 / 958         4096 (8, 32 in 8, 512)    907 / 833 / 953
+//                     7168 (28, 16 in 4, 512) 1590 / 1485 / 1386      8192 (8, 32 in 8, 1000)   1684 / 1519 / 1449
+//   bf16, 128 bytes   4096 659 / 645 / 783, 7168 1021 / 1097 / 1127, 8192 1132 / 1113 / 1136
+constexpr int64_t kLongWindowPairs[2] = {2300, 6500};
 
 // Which problems with fp32 keys go to the similarity kernel that splits them (merge_kernels.hip): from a number of positions
 // over all (layer, head) pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads,
@@ -72,8 +79,9 @@ static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) 
   pl->RBa = pl->RB;
   if (single_chunk) {
     const int have = (rows + 31) / 32;
-    const bool large = pl->dtype == MEDA_BF16 && pl->d == 128 && (int64_t)pl->L * pl->Hq * have > kLargePairs;
-    const int pairs = !large ? 4 : (pl->Hkv % 8 == 0 || pl->G >= 7) ? 16 : 12;
+    const int64_t all = pl->dtype == MEDA_BF16 && pl->d == 128 ? (int64_t)pl->L * pl->Hq * have : 0;
+    int pairs = all <= kLargePairs ? 4 : (pl->Hkv % 8 == 0 || pl->G >= 7) ? 16 : 12;
+    if (rows < t) pairs = all <= kLongWindowPairs[0] ? 4 : all <= kLongWindowPairs[1] ? 8 : 16;
     const int want = pl->G >= pairs ? 1 : pairs / pl->G;
     pl->RBa = want < have ? want : have;
   }
