@@ -494,7 +494,7 @@ hipError_t launch_select(const Plan& p, const Buffers& b, hipStream_t s) {
       hipLaunchKernelGGL((select_kernel<8, false, 11, C>), grid, dim3(n_thr), 0, s, a);
     }
   };
-  if (p.sim_split) launch(std::true_type{});
+  if (p.sim == kSimSplit && !a.no_merge) launch(std::true_type{});
   else launch(std::false_type{});
   return hipGetLastError();
 }

@@ -15,8 +15,8 @@ namespace meda {
 //   16        1.68 (2 layers of 1024 keys, 28 heads, bf16: 49 / 42), 32  1.67, 64  1.51 (0.95 at worst)
 //   128       1.10: 0.73 to 1.04 for few heads and grouped bf16 rows of 256 bytes, 1.03 to 1.6 for the others
 //   256       0.79 (a tile of 128 keys shares what a workgroup of 32 keys reads again), 512  0.69
-// Up to four sequences go the way one of them would go alone, so that its sums are the same; 7 of 4 layers of 487 keys,
-// 4 heads, 2 kv heads, 80 rows (112 tiles; whole pass) 77 / 91.
+// Up to four sequences, and no more than 128 tiles in all, go the way one of them would go alone, so that its sums are the
+// same; 7 of 4 layers of 487 keys, 4 heads, 2 kv heads, 80 rows (112 tiles; whole pass) 77 / 91.
 constexpr int64_t kDirectTiles = 64, kDirectTilesAll = 128;
 constexpr int kDirectManyHeads = 28;
 
@@ -41,8 +41,35 @@ constexpr int64_t kLargePairs = 12000;
 //   bf16, 128 bytes   4096 659 / 645 / 783, 7168 1021 / 1097 / 1127, 8192 1132 / 1113 / 1136
 constexpr int64_t kLongWindowPairs[2] = {2300, 6500};
 
-// Which problems with fp32 keys go to the similarity kernel that splits them (merge_kernels.hip): from a number of positions
-// over all (layer, head) pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads,
+// ---- similarity kernels
+
+// bf16 problems for the direct kernel: short prompts whose tiled launch would leave most CUs empty: 16 pairs of 500
+// positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000 53 -> 120 us
+// (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
+constexpr int kSimDirectPositions = 2048;
+
+// Where the resident-set kernel takes the layers that fit: a workgroup of it occupies a whole CU, so with one or two per CU
+// its last round leaves most of the chip empty, and with long sets its few layers do not cover their own launch.  Tiled
+// alone / both kernels, similarity in us, mean budget of a layer in brackets, prompts of 1000 to 3000:
+//   256 bytes  256 pairs [375] 60 / 76, [750] 159 / 185, [1125] 297 / 334    384 [240] 148 / 139, [375] 91 / 101, [1125] 439 / 475
+//              512 [240] 190 / 163, [675] 468 / 436, [1125] 576 / 622        1024 [240] 364 / 304, [750] 603 / 566, [1125] 1024 / 1025
+//   128 bytes  256 [375] 37 / 44, [750] 93 / 125, 360 [701] 133 / 163        384 [240] 80 / 78, [750] 135 / 140, [1125] 241 / 270
+//              512 [450] 146 / 142, [750] 180 / 174, [1125] 334 / 366        1024 [240] 209 / 198, [675] 481 / 475, [1125] 566 / 586
+// Below 512 pairs it takes prompts long enough against the sets that its workgroups walk the rows for long:
+//   256 bytes  448 of 3000 [120] 121 / 107, [330] 176 / 166, [600] 224 / 223, of 8000 [240] 356 / 303, [600] 585 / 567
+//              384 of 3000 [120] 108 / 98, [240] 130 / 130, of 8000 [330] 359 / 333, [600] 505 / 521
+//              256 of 3000 [60] 69 / 65, [120] 76 / 77, of 8000 [240] 219 / 211, [330] 243 / 250
+//   128 bytes  448 of 3000 [330] 104 / 99, of 8000 [240] 206 / 199, [600] 342 / 347   384 of 8000 [120] 143 / 133, [330] 210 / 219
+//              256 of 8000 [60] 89 / 85, [120] 100 / 104
+constexpr long long kResidentKept = 900;
+static bool resident_pays(const Plan& p, int64_t pairs) {
+  if (pairs >= 512) return p.B <= kResidentKept * p.L;
+  const int64_t times = pairs >= 448 ? 9 : p.d == 128 ? (pairs >= 384 ? 16 : 32) : (pairs >= 384 ? 32 : 100);
+  return pairs >= kResidentPairs && p.B * times <= (int64_t)p.T * p.L;  // mean budget against positions
+}
+
+// fp32 problems for the split kernel, the others go to the direct one: from a number of positions over all (layer, head)
+// pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads,
 // would walk too long a share of the set.  Below it the waves that take their blocks again, and the search for copies in
 // the selection (2 to 8 us), cost more than the matrix instructions save.  Selection and similarity in us, direct kernel /
 // split kernel, a tenth and three tenths kept:
@@ -53,21 +80,26 @@ constexpr int64_t kLongWindowPairs[2] = {2300, 6500};
 //   rows of 512 bytes  32 pairs of 700   33 / 39, 39 / 55   of 1200   55 / 50, 67 / 74   of 2000  118 / 71, 123 / 108
 //                      64 of 300         28 / 30, 30 / 38   of 700    49 / 43, 57 / 56   of 1200  73 / 58, 113 / 79
 //                      8 of 2000         44 / 46, 59 / 73   of 5000   136 / 110, 201 / 158
-static bool similarity_splits(const Plan& p) {
-  if (p.dtype != MEDA_F32 || (p.flags & MEDA_FLAG_NO_MERGE)) return false;
-  const double pairs = (double)p.L * p.Hkv, positions = pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
+static SimRoute similarity_route(const Plan& p) {
+  const int64_t pairs = (int64_t)p.L * p.Hkv;
+  if (p.dtype == MEDA_BF16) {
+    if (pairs * ((p.T + kSimRows - 1) / kSimRows) <= kSimDirectGroups && p.T <= kSimDirectPositions) return kSimDirect;
+    return resident_pays(p, pairs) ? kSimResident : kSimTiled;
+  }
+  const double positions = (double)pairs * p.T, kept = (double)p.B / ((double)p.L * p.T);
   const bool small = p.d == 64;
   const double from = small ? (kept < 0.2 ? 46000 : 64000) : (kept < 0.2 ? 24000 : 50000);
   const double longest = (pairs == 1 ? 4.1e4 : small ? 1.64e5 : 6.15e4) * kept;
-  return positions >= from || (pairs <= 8 && positions >= 36000) || p.T > longest || p.T > 16384 ||
-         positions > (small ? 1.5e6 : 5e5) * kept;
+  const bool split = positions >= from || (pairs <= 8 && positions >= 36000) || p.T > longest || p.T > 16384 ||
+                     positions > (small ? 1.5e6 : 5e5) * kept;
+  return split ? kSimSplit : kSimDirect;
 }
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Tiling of the two scoring passes for w query rows (the last w positions) of a sequence of t keys.  With
-// `single_chunk` a pass-A workgroup walks all keys its rows see (used when every prompt row scores: the row blocks
-// already give that launch tens of thousands of workgroups).
+// `single_chunk` a pass-A workgroup walks all keys its rows see (the row-block mode, whose row blocks give that launch its
+// workgroups).
 static bool score_geometry(Plan* pl, int t, int w, int rows, bool single_chunk) {
   pl->Tb = t;
   pl->Wb = w;
@@ -182,7 +214,7 @@ meda_status make_plan(const meda_params* p, Plan* out) {
     pl.NCH = (pl.T + pl.CH - 1) / pl.CH;
     pl.NPART = pl.NCH;
   }
-  pl.sim_split = similarity_splits(pl) ? 1 : 0;
+  pl.sim = similarity_route(pl);
   const size_t stats_rows = pl.blocks ? (size_t)pl.R : (size_t)pl.Wp;
 
   pl.n_less_total = (size_t)((int64_t)pl.L * pl.T - pl.B) * pl.Hkv;

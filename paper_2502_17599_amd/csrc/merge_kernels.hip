@@ -39,9 +39,10 @@ __device__ __forceinline__ size_t less_base_of(int l, int g, int T, int Hkv, lon
 }
 
 // ------------------------------------------------------------------------ similarity + argmax
-// Small problems go to the direct kernel, larger ones with fp32 keys to the split kernel (Plan::sim_split), with bf16 keys
-// to the tiled kernel; layers whose conserved set fits into LDS may go to the resident-set kernel (one workgroup of 8 waves
-// per (layer, head) part, all 160 KB of LDS): then both are launched and every workgroup looks up its layer's budget.
+// Small problems go to the direct kernel, larger ones with fp32 keys to the split kernel, with bf16 keys to the tiled
+// kernel; layers whose conserved set fits into LDS may go to the resident-set kernel (one workgroup of 8 waves per (layer,
+// head) part, all 160 KB of LDS): then both are launched and every workgroup looks up its layer's budget.  The rules that
+// choose (Plan::sim) stand beside the plan.
 constexpr int kResWaves = 8;
 constexpr int kResThreads = kResWaves * 64;
 constexpr int kResLdsBytes = 160 * 1024;
@@ -61,6 +62,7 @@ constexpr int resident_capacity() {
 // property of the problem and the layer, not of the kernel that a rule of speed picks for them: adjacent for a set that
 // fits into LDS among at least kAdjacentPairs (layer, head) pairs, halves for every other one.
 constexpr unsigned kAdjacentPairs = 256;
+static_assert(kSimDirectGroups < kAdjacentPairs && kAdjacentPairs <= kResidentPairs, "each kernel with one order keeps to it");
 template <typename T, int D>
 struct StepOrder {
   int group, step;  // chunk of step i in lane group kg: kg * group + i * step
@@ -444,7 +446,7 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
 // whose fragments come from the key cache itself (L2), one block ahead; the waves' bests are merged at the end.
 // For problems that leave CUs empty with 256 rows per workgroup, where the serial chain of one wave bounds the kernel.
 // Every 32 rows read the whole set again, eight times as often as in the tiled kernel, so with the chip full it loses:
-// see kSimDirectGroups.
+// see similarity_route.
 template <typename T, int D, int F, int NW>
 __global__ void __launch_bounds__(NW * 64, 2) similarity_direct_kernel(MergeArgs a) {
   using TL = Tile<T, D>;
@@ -1346,12 +1348,6 @@ static MergeArgs make_args(const Plan& p, const Buffers& b) {
   return a;
 }
 
-// bf16 problems for the direct kernel: short prompts whose tiled launch would leave most CUs empty: 16 pairs of 500
-// positions 16 (packing 8) -> 6 us, of 1000 21 -> 13 us, of 2000 (128 workgroups) 27 -> 29 us; 2 pairs of 8000 53 -> 120 us
-// (its key loads are not shared by the waves, so long sets stay with the tiled kernel).
-constexpr unsigned kSimDirectGroups = 96;
-constexpr int kSimDirectPositions = 2048;
-
 template <typename T, int D, int F, int NW>
 static hipError_t launch_sim_direct(const MergeArgs& a, unsigned pairs, hipStream_t s) {
   const unsigned nrb = (a.T + 32 * F - 1) / (32 * F);
@@ -1373,22 +1369,11 @@ static hipError_t launch_sim_split(const MergeArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Where the resident-set kernel takes the layers that fit: a workgroup of it occupies a whole CU, so with one or two per CU
-// its last round leaves most of the chip empty, and with long sets its few layers do not cover their own launch.  Tiled
-// alone / both kernels, similarity in us, mean budget of a layer in brackets:
-//   256 bytes  256 pairs [375] 60 / 76, [750] 159 / 185, [1125] 297 / 334    384 [240] 148 / 139, [375] 91 / 101, [1125] 439 / 475
-//              512 [240] 190 / 163, [675] 468 / 436, [1125] 576 / 622        1024 [240] 364 / 304, [750] 603 / 566, [1125] 1024 / 1025
-//   128 bytes  256 [375] 37 / 44, [750] 93 / 125, 360 [701] 133 / 163        384 [240] 80 / 78, [750] 135 / 140, [1125] 241 / 270
-//              512 [450] 146 / 142, [750] 180 / 174, [1125] 334 / 366        1024 [240] 209 / 198, [675] 481 / 475, [1125] 566 / 586
-constexpr unsigned kResidentPairs = 512;
-constexpr long long kResidentKept = 900;
-
 template <typename T, int D>
 static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   const unsigned nrb = (p.T + kSimRows - 1) / kSimRows, pairs = (unsigned)(p.L * p.Hkv);
-  if (pairs * nrb <= kSimDirectGroups && p.T <= kSimDirectPositions) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
-  static_assert(kSimDirectGroups < kAdjacentPairs && kAdjacentPairs <= kResidentPairs, "each kernel with one order keeps to it");
-  a.use_resident = pairs >= kResidentPairs && p.B <= kResidentKept * p.L ? 1 : 0;
+  if (p.sim == kSimDirect) return launch_sim_direct<T, D, 1, 8>(a, pairs, s);
+  a.use_resident = p.sim == kSimResident ? 1 : 0;
   a.adjacent_order = pairs >= kAdjacentPairs ? 1 : 0;
   hipLaunchKernelGGL((pack_conserved_kernel<T, D>), dim3((unsigned)((a.total_slots + kPackRows - 1) / kPackRows)),
                      dim3(256), 0, s, a);
@@ -1411,18 +1396,18 @@ static hipError_t launch_sim_t(const Plan& p, MergeArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// fp32 problems (Plan::sim_split).  Split kernel: workgroups of eight waves share a tile's pieces among more rows, which pays
+// fp32 problems.  Split kernel: workgroups of eight waves share a tile's pieces among more rows, which pays
 // for rows of 512 bytes once two of them per CU are there (224 pairs of 660 46 -> 38 us, 35 of 2715 106 -> 140).  Direct
 // kernel: two fragments per wave halve the key loads once there are enough workgroups of 64 rows for every CU.
 template <int D>
 static hipError_t launch_sim_fp32(const Plan& p, const MergeArgs& a, hipStream_t s) {
   const unsigned pairs = (unsigned)(p.L * p.Hkv);
   if constexpr (D == 128) {
-    if (p.sim_split && pairs * ((p.T + 255u) / 256u) >= 576u) return launch_sim_split<D, 8>(a, s);
+    if (p.sim == kSimSplit && pairs * ((p.T + 255u) / 256u) >= 576u) return launch_sim_split<D, 8>(a, s);
   } else {
-    if (!p.sim_split && pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<float, D, 2, 4>(a, pairs, s);
+    if (p.sim == kSimDirect && pairs * ((p.T + 63u) / 64u) >= 512u) return launch_sim_direct<float, D, 2, 4>(a, pairs, s);
   }
-  return p.sim_split ? launch_sim_split<D, 4>(a, s) : launch_sim_direct<float, D, 1, 8>(a, pairs, s);
+  return p.sim == kSimSplit ? launch_sim_split<D, 4>(a, s) : launch_sim_direct<float, D, 1, 8>(a, pairs, s);
 }
 
 hipError_t launch_similarity(const Plan& p, const Buffers& b, hipStream_t s) {

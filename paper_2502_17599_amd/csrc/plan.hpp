@@ -19,6 +19,10 @@ constexpr int kMaxLayers = 256;
 constexpr int kDirParts = 16;    // statistics partials per row of the direct scoring kernels, at most
 constexpr int kScoreRowBlock = 128;  // query rows per row block of pass B when every prompt row scores
 
+// Which similarity kernels run (merge_kernels.hip; the rules and their figures: similarity_route).
+enum SimRoute { kSimDirect, kSimTiled, kSimResident /* tiled, and resident-set for layers that fit */, kSimSplit };
+constexpr unsigned kSimDirectGroups = 96, kResidentPairs = 256;
+
 struct Plan {
   // problem.  A batch of N sequences is laid out as N * Lseq "layers": every kernel but the budget
   // allocation treats layers independently, so L and B below are totals over the batch and only the
@@ -49,7 +53,7 @@ struct Plan {
   int q_row0;        // first row of the block inside the query buffer
   int NTk;           // entropy partials per layer: column tiles of the whole sequence (of 32 keys with `direct`)
   int accumulate;    // add to column scores / entropy partials instead of storing (every block but the first)
-  int sim_split;     // fp32 keys: similarity by the kernel that splits them in bf16 parts; the selection marks copies
+  int sim;           // similarity kernel (SimRoute); with kSimSplit the selection marks copies of a key
   // workspace regions (byte offsets)
   size_t off_stats_part, off_stats, off_inv_norm, off_col_scores, off_ent_part, off_alloc, off_layer_off,
       off_sel_idx, off_sel_inv, off_packed_k, off_less_idx, off_less_slot, off_sort_a, off_sort_b, off_sort_c, off_sort_d, off_seg_beg, off_seg_end, total_bytes;
