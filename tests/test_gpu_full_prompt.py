@@ -62,7 +62,7 @@ def test_full_prompt_sixteen_query_heads_per_kv_head():
 
 
 def test_full_prompt_three_query_heads_per_kv_head_d64():
-    # 5 row blocks of 32 rows per pass-A workgroup (15 (head, row block) pairs), head dimension 64
+    # a pass-A workgroup of one row block of three heads, head dimension 64
     layout = (("t", 33, -1), ("v", 200, 0), ("t", 17, -1), ("v", 150, 1), ("t", 50, -1))
     _case(variant(TINY, name="fp_g3", n_layers=2, n_q_heads=6, n_kv_heads=2, head_dim=64, dtype="bf16",
                   layout=layout, window=16, total_budget=2 * 120, seed=13, score_rows=450))
@@ -85,8 +85,9 @@ def test_full_prompt_mid_size_bf16_one_head_per_kv_head():
 
 
 def test_full_prompt_llava7b_shape_two_layers():
-    # the shape the full-prompt mode is benchmarked on (32 heads without grouping, 4096 positions, 32 row blocks),
-    # two layers with different temperatures; the oracle takes a few minutes for them, run side by side
+    # two layers of the shape the full-prompt mode is benchmarked on (32 heads without grouping, 4096 positions), with
+    # different temperatures; the oracle takes a few minutes for them, run side by side.  (So few layers take pass-A
+    # workgroups of four row blocks; all 32 take those of 16: test_large_full_prompts.)
     base = get_workload("llava7b_multi_image")
     wl = variant(base, name="fp_llava7b_2_layers", n_layers=2, total_budget=2 * 512, score_rows=base.seq_len)
     print(f"\n[full-prompt case] {wl.name}: L={wl.n_layers} Hq={wl.n_q_heads} Hkv={wl.n_kv_heads} d={wl.head_dim} "
@@ -95,6 +96,22 @@ def test_full_prompt_llava7b_shape_two_layers():
     comp, gpu = run_gpu(wl, data)
     stats = check_all(wl, data, gpu, heads=[(0, 0), (0, 17), (1, 31)], threads=2)
     assert stats["layers_passing_only_by_entropy_floor"] == 0
+
+
+# More than 12000 (head, 32-row block) pairs: pass-A workgroups of 12 and 16 of them.  layers, positions, kv heads, query
+# heads per kv head, row blocks of a workgroup, pairs per wave, pass-A row blocks
+LARGE = [
+    (24, 520, 32, 1, 16, 4, 2),   # the heads of the benchmarked shape, a second row block of eight rows
+    (38, 300, 8, 4, 4, 4, 3), (38, 300, 4, 8, 2, 4, 5), (34, 300, 12, 3, 4, 3, 3), (26, 390, 36, 1, 12, 3, 2), (40, 333, 7, 4, 3, 3, 4),
+]
+
+
+@pytest.mark.parametrize("L,T,hkv,G,row_blocks,fragments,groups", LARGE)
+def test_large_full_prompts(L, T, hkv, G, row_blocks, fragments, groups):
+    layout = (("t", 33, -1), ("v", 100, 0), ("t", 17, -1), ("v", 80, 1), ("t", T - 230, -1))
+    _case(variant(TINY, name="fp_large", n_layers=L, n_q_heads=hkv * G, n_kv_heads=hkv, head_dim=128, dtype="bf16", layout=layout,
+                  window=16, total_budget=L * 60, seed=T, score_rows=T), heads=[(l, (l * 5) % hkv) for l in (0, L - 1)],
+          verbose=False, threads=8)
 
 
 def test_full_prompt_with_more_than_65535_row_blocks_in_pass_a():

@@ -166,13 +166,13 @@ def test_random_shape_with_flags(wl, flags):
 
 
 def _many_pairs_configs():
-    """At least 256 (layer, kv head) pairs, which is when the similarity search sends layers whose conserved set fits
-    into LDS to its resident-set kernel; average budgets on both sides of that capacity (576 rows of 256 bytes, 1184
-    rows of 128 bytes), so that most cases run both kernels."""
+    """512 (layer, kv head) pairs with bf16 keys, which is when the similarity search sends layers whose conserved set fits
+    into LDS to its resident-set kernel (average budgets up to 900); average budgets on both sides of that capacity (576
+    rows of 256 bytes, 1184 rows of 128 bytes).  With fp32 keys: the kernel that splits them."""
     r = np.random.Generator(np.random.Philox(key=[2024, 9]))
     out = []
     for i in range(6):
-        L, hkv = [(8, 32), (16, 16), (32, 8), (64, 4), (16, 32), (64, 8)][i]
+        L, hkv = [(16, 32), (32, 16), (32, 8), (128, 4), (64, 8), (64, 8)][i]
         G = int(r.choice([1, 2, 4]))
         T = int(r.choice([640, 1000, 1537, 2048]))
         W = int(r.choice([8, 32, 64]))

@@ -5,7 +5,7 @@ Budgets: one layer to more layers than a wave has lanes, with and without active
 allocator on the kernel's own entropies.
 Nearest neighbours of the kernel that works without an LDS copy of the conserved set: against float64 cosines; a
 slot counts as right if its cosine is within 1e-5 of the best (sums of up to 128 exact products in fp32, times 1/|k|).
-The same where layers with conserved sets held whole in LDS (at least 256 pairs) lie between layers with longer ones.
+The same where layers with conserved sets held whole in LDS (512 pairs and more) lie between layers with longer ones.
 Merged rows: the mean of the members in float64, for outputs below and above 65536 rows; bf16 may differ by one unit in
 the last place (2^-7 of the value) because the reference rounds twice.
 Row statistics: column scores against a float64 softmax, for 16 to 2052 partials per row; a logit is a sum of 64
@@ -90,9 +90,12 @@ def test_nearest_neighbours(dtype, d, T, L, hkv):
     _check_neighbours(out, k)
 
 
-# fp32 keys of enough pairs that 256 rows per workgroup fill the chip: the tiled kernel
-@pytest.mark.parametrize("d,T,L,hkv,kept", [(64, 1500, 32, 8, 150), (64, 701, 33, 9, 97), (64, 257, 40, 16, 50), (128, 1500, 16, 8, 300),
-                                            (128, 385, 13, 11, 40), (128, 6500, 3, 2, 1300)])
+# fp32 keys of many positions over all pairs: the kernel that splits them
+MANY_FP32 = [(64, 1500, 32, 8, 150), (64, 701, 33, 9, 97), (64, 257, 40, 16, 50), (128, 1500, 16, 8, 300), (128, 385, 13, 11, 40),
+             (128, 6500, 3, 2, 1300)]
+
+
+@pytest.mark.parametrize("d,T,L,hkv,kept", MANY_FP32)
 def test_nearest_neighbours_of_many_fp32_pairs(d, T, L, hkv, kept):
     out, k, _, _ = _run(T, L, hkv, d, torch.float32, L * kept)
     _check_neighbours(out, k)
@@ -102,19 +105,26 @@ def test_nearest_neighbours_of_many_fp32_pairs(d, T, L, hkv, kept):
 # Ties: one key stands at four conserved positions more than 32 slots apart (different blocks, and different waves of the
 # kernels whose waves share the blocks) and at five dropped ones, which have to go to the lowest of the four slots.
 # Kept are exactly the text positions and the window (uniform budgets, no recent part), so the slots are known.
-@pytest.mark.parametrize("dtype,d,T,L,hkv,kept", [
-    (torch.float32, 64, 1000, 2, 2, 300),       # direct, one fragment per wave
-    (torch.float32, 64, 1000, 8, 8, 300),       # direct, two
-    (torch.float32, 128, 1000, 2, 2, 300),      # direct
-    (torch.float32, 64, 600, 32, 16, 200),      # tiled
-    (torch.float32, 128, 600, 16, 8, 200),
-    (torch.bfloat16, 64, 1000, 2, 2, 300),      # direct
-    (torch.bfloat16, 128, 1000, 2, 2, 300),
-    (torch.bfloat16, 64, 1000, 8, 8, 300),      # tiled
-    (torch.bfloat16, 128, 1000, 8, 8, 300),
-    (torch.bfloat16, 64, 600, 32, 8, 200),      # the whole set in LDS
-    (torch.bfloat16, 128, 600, 32, 8, 200)])
-def test_equal_keys_go_to_the_lowest_slot(dtype, d, T, L, hkv, kept):
+TIES = [
+    (torch.float32, 64, 1000, 2, 2, 300, "direct"),       # one fragment per wave
+    (torch.float32, 64, 990, 8, 8, 300, "direct"),        # two
+    (torch.float32, 128, 1000, 2, 2, 300, "direct"),
+    (torch.float32, 64, 1000, 8, 8, 300, "split"),
+    (torch.float32, 64, 600, 32, 16, 200, "split"),
+    (torch.float32, 128, 600, 16, 8, 200, "split"),
+    (torch.float32, 128, 600, 48, 8, 200, "split"),       # eight waves
+    (torch.bfloat16, 64, 1000, 2, 2, 300, "direct"),
+    (torch.bfloat16, 128, 1000, 2, 2, 300, "direct"),
+    (torch.bfloat16, 64, 1000, 8, 8, 300, "tiled"),
+    (torch.bfloat16, 128, 1000, 8, 8, 300, "tiled"),
+    (torch.bfloat16, 64, 600, 32, 8, 200, "tiled"),       # in the order of the sums of sets in LDS
+    (torch.bfloat16, 128, 600, 32, 8, 200, "tiled"),
+    (torch.bfloat16, 64, 600, 64, 8, 200, "resident"),    # the whole set in LDS
+    (torch.bfloat16, 128, 600, 64, 8, 200, "resident")]
+
+
+@pytest.mark.parametrize("dtype,d,T,L,hkv,kept,kernel", TIES)
+def test_equal_keys_go_to_the_lowest_slot(dtype, d, T, L, hkv, kept, kernel):
     import paper_2502_17599_amd as pkg
     print(f"\n[ties] {dtype} d={d} T={T} L={L} Hkv={hkv} kept={kept}", flush=True)
     W = 16
@@ -160,8 +170,11 @@ def _check_neighbours(out, k):
             assert (got >= cos.max(dim=1).values - 1e-5).all()
 
 
+SETS_IN_LDS = [(1500, 64, 8, 560), (1500, 130, 4, 300), (700, 64, 8, 33), (3000, 28, 16, 64)]
+
+
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("T,L,hkv,kept", [(1500, 32, 8, 560), (1500, 65, 4, 300), (700, 32, 8, 33)])
+@pytest.mark.parametrize("T,L,hkv,kept", SETS_IN_LDS)
 def test_conserved_sets_in_lds_between_longer_ones(T, L, hkv, kept, d):
     out, k, S, _ = _run(T, L, hkv, d, torch.bfloat16, L * kept)
     if kept == 560 and d == 128:
