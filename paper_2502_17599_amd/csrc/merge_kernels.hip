@@ -212,7 +212,7 @@ constexpr int sim_tiled_lds_bytes() {
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(kSimWaves * 64, (Tile<T, D>::kRowBytes <= 256 ? 2 : 1)) similarity_argmax_kernel(MergeArgs a) {
+__global__ void __launch_bounds__(kSimWaves * 64, 2) similarity_argmax_kernel(MergeArgs a) {
   using TL = Tile<T, D>;
   constexpr int CPR = TL::kChunksPerRow;
   constexpr int NC = TL::kFragChunks;

@@ -258,8 +258,12 @@ static hipError_t launch_accum_t(const Plan& p, const ScoreArgs& a, hipStream_t 
       return launch_accum_k<T, D, RB, false, NW, true>(p, a, s);
     }
   }
-  if (p.G == 1 && !kThreeGroups) return launch_accum_k<T, D, RB, true, NW>(p, a, s);
-  return launch_accum_k<T, D, RB, false, NW>(p, a, s);
+  if constexpr (Tile<T, D>::kRowBytes <= 256 && RB <= 3) {  // (grouped heads go to score_accum_dma_kernel)
+    return launch_accum_k<T, D, RB, !kThreeGroups, NW>(p, a, s);
+  } else {
+    if (p.G == 1 && !kThreeGroups) return launch_accum_k<T, D, RB, true, NW>(p, a, s);
+    return launch_accum_k<T, D, RB, false, NW>(p, a, s);
+  }
 }
 
 template <typename T, int D>

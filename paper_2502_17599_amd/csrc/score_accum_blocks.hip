@@ -112,8 +112,7 @@ __global__ void __launch_bounds__(kBlkThreads, kBlkWaves / 4) score_accum_blocks
       const unsigned goff = (unsigned)min(row0 + crow + c * RPI, a.q_rows - 1) * RBt + chunk;
       async_copy16_to_lds(qsrc, goff, stage + (unsigned)((wave * PF + c) * CT::kPiece));
     }
-    // wave w < 8 brings the rows (w & 1) * 64 .. + 63 of plane w >> 1 of the row statistics
-    if (wave >= 8) return;
+    // wave w brings the rows (w & 1) * 64 .. + 63 of plane w >> 1 of the row statistics
     const float* ssrc = uniform_ptr(stats_f + ((size_t)(l * a.Hq + h) * 4 + (wave >> 1)) * a.stats_rows);
     const unsigned soff = (unsigned)min(row0 + (wave & 1) * 64 + lane, a.q_rows - 1) * 4u;
     async_copy4_to_lds(ssrc, soff, stage + (unsigned)(kTileBytes + ((wave >> 1) * kBlkHalf + (wave & 1) * 64) * 4));

@@ -3,7 +3,8 @@
 // Here every operand comes straight from memory (L2) into the fragments, no LDS tile and no barrier in the loops, and
 // the work is cut finer: pass A into waves of one (head, 32-row block) pair and a chunk of keys, pass B into workgroups of
 // 32 keys whose waves share the query heads.  Bound by latency: a wave's chain is a few blocks of 32 x 32.
-// A lane owns one query row, as in score_stats_dma.hip and score_accum_dma.hip.
+// A lane owns one query row, as in pass A of score_stats_dma.hip; here in pass B too, so that the statistics of a row are one
+// value per lane.
 #include "score_common.hpp"
 
 namespace meda {

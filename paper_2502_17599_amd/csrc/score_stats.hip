@@ -305,26 +305,23 @@ static hipError_t launch_stats_b(const Plan& p, const ScoreArgs& a, hipStream_t 
 
 template <typename T, int D, int NQ, int NW>
 static hipError_t launch_stats_w(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  // With one query head per kv head and a window the pass streams the keys at the rate a plain read reaches, and three
-  // workgroups per CU of the small register-staged form do that best; rows of 512 bytes take it in every mode.
-  if constexpr (Tile<T, D>::kRowBytes > 256) {
-    if (p.blocks) return launch_stats_b<T, D, NQ, NW, true>(p, a, s);
-  }
-  return launch_stats_b<T, D, NQ, NW, false>(p, a, s);
+  return p.blocks ? launch_stats_b<T, D, NQ, NW, true>(p, a, s) : launch_stats_b<T, D, NQ, NW, false>(p, a, s);
 }
 
-template <typename T, int D, int NQ>
-static hipError_t launch_stats_t(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  return p.NCG * p.CS <= 4 ? launch_stats_w<T, D, NQ, 4>(p, a, s) : launch_stats_w<T, D, NQ, 8>(p, a, s);
-}
-
+// With one query head per kv head and a window the pass streams the keys at the rate a plain read reaches, and three
+// workgroups per CU of the small register-staged form do that best (up to four pairs of one head and a row block: one per
+// wave); rows of 512 bytes take it in every mode.
 template <typename T, int D>
 static hipError_t launch_stats_d(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  switch (p.NQ) {
-    case 1: return launch_stats_t<T, D, 1>(p, a, s);
-    case 2: return launch_stats_t<T, D, 2>(p, a, s);
-    case 3: return launch_stats_t<T, D, 3>(p, a, s);
-    default: return launch_stats_t<T, D, 4>(p, a, s);
+  if constexpr (Tile<T, D>::kRowBytes <= 256) {
+    return launch_stats_b<T, D, 1, 4, false>(p, a, s);
+  } else {
+    const bool four = p.NCG * p.CS <= 4;
+    switch (p.NQ) {
+      case 1: return launch_stats_w<T, D, 1, 4>(p, a, s);
+      case 2: return four ? launch_stats_w<T, D, 2, 4>(p, a, s) : launch_stats_w<T, D, 2, 8>(p, a, s);
+      default: return launch_stats_w<T, D, 4, 8>(p, a, s);
+    }
   }
 }
 

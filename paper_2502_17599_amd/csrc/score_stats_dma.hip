@@ -7,7 +7,7 @@
 // query row and 16 keys per block: the running (max, Z_vision, Z_text) of the row are three registers per fragment and
 // need no cross-lane traffic until the end.
 //
-// Two LDS tiles of 64 keys (CopyTile in device_utils.hpp): the copies of tile t+1 are issued when tile t starts, one wait
+// Two LDS tiles of 128 keys (CopyTile in device_utils.hpp): the copies of tile t+1 are issued when tile t starts, one wait
 // and one barrier per tile, no staging registers; the modality bits of a tile are a ballot of one byte per lane that
 // every wave loads for itself one tile ahead.  Tiles whose keys every row of the workgroup sees have a loop of their own.
 // Bound by the vector unit (a probability costs a multiply-add, an exponential, an addition and half a maximum) and by the
@@ -173,10 +173,10 @@ static hipError_t launch_dma_w(const Plan& p, const ScoreArgs& a, hipStream_t s)
 
 template <typename T, int D>
 static hipError_t launch_dma_d(const Plan& p, const ScoreArgs& a, hipStream_t s) {
-  const bool four = p.NCG * p.CS <= 4;
+  const bool four = p.NCG * p.CS <= 4;  // (always up to 16 pairs)
   switch (p.NQ) {
-    case 1: return four ? launch_dma_w<T, D, 1, 4>(p, a, s) : launch_dma_w<T, D, 1, 8>(p, a, s);
-    case 2: return four ? launch_dma_w<T, D, 2, 4>(p, a, s) : launch_dma_w<T, D, 2, 8>(p, a, s);
+    case 1: return launch_dma_w<T, D, 1, 4>(p, a, s);
+    case 2: return launch_dma_w<T, D, 2, 4>(p, a, s);
     case 3: return launch_dma_w<T, D, 3, 4>(p, a, s);
     default: return four ? launch_dma_w<T, D, 4, 4>(p, a, s) : launch_dma_w<T, D, 4, 8>(p, a, s);
   }
