@@ -64,16 +64,9 @@ constexpr int resident_capacity() {
 constexpr unsigned kAdjacentPairs = 256;
 static_assert(kSimDirectGroups < kAdjacentPairs && kAdjacentPairs <= kResidentPairs, "each kernel with one order keeps to it");
 template <typename T, int D>
-struct StepOrder {
-  int group, step;  // chunk of step i in lane group kg: kg * group + i * step
-  __device__ __forceinline__ explicit StepOrder(bool adjacent)
-      : group(adjacent ? 1 : Tile<T, D>::kFragChunks), step(adjacent ? 2 : 1) {}
-  __device__ __forceinline__ int chunk(int i, int kg) const { return kg * group + i * step; }
-};
-template <typename T, int D>
-__device__ __forceinline__ void frag_load(Frag<T, D>& f, const char* row_ptr, int kg, const StepOrder<T, D>& order) {
+__device__ __forceinline__ void frag_load_adjacent(Frag<T, D>& f, const char* row_ptr, int kg) {
 #pragma unroll
-  for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) f.c[i] = *reinterpret_cast<const uint4*>(row_ptr + order.chunk(i, kg) * 16);
+  for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) f.c[i] = *reinterpret_cast<const uint4*>(row_ptr + i * 32 + kg * 16);
 }
 
 // u_ij = (k_i . k_j)/(|k_i| |k_j|): the raw keys are multiplied (bf16 products are exact in the fp32
@@ -232,7 +225,7 @@ __global__ void __launch_bounds__(kSimWaves * 64, 2) similarity_argmax_kernel(Me
   const int S = a.alloc[4 * l];
   const bool fits = S <= resident_capacity<T, D>();
   if (a.use_resident && fits) return;  // the resident-set kernel below takes this layer
-  const StepOrder<T, D> order(a.adjacent_order && fits);
+  const bool adjacent = a.adjacent_order && fits;
   const int n_less = a.T - S;
   const int row_base = rblock * kSimRows;
   if (row_base >= n_less) return;
@@ -259,8 +252,13 @@ __global__ void __launch_bounds__(kSimWaves * 64, 2) similarity_argmax_kernel(Me
   row_best_init(rb[0]);
   row_best_init(rb[1]);
   Frag<T, D> lf[2];
+  if (adjacent) {
 #pragma unroll
-  for (int s = 0; s < 2; ++s) frag_load(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes, kg, order);
+    for (int s = 0; s < 2; ++s) frag_load_adjacent(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes, kg);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) frag_load(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes, kg);
+  }
 
   // Copy instruction j of this wave fills the rows (wave * PF + j) * RPI .. + RPI-1 of a tile: this lane brings
   // one 16-byte chunk of row crow_r + j * RPI.  Slots past the end of the set repeat the last conserved key (see
@@ -286,10 +284,13 @@ __global__ void __launch_bounds__(kSimWaves * 64, 2) similarity_argmax_kernel(Me
   issue_tile(1, 1);
   issue_tile(2, 2);
 
-  // chunk x of row n of a block sits at (n * row bytes) + 16 * (x ^ swz(n)) inside a block of 32 rows
+  // chunk x of row n of a block sits at (n * row bytes) + 16 * (x ^ swz(n)) inside a block of 32 rows; step c takes the chunk
+  // kg * NC + c, or 2 c + kg in adjacent order: no bits in common, so the step goes in by another xor
+  const unsigned coff0 = (unsigned)(n * TL::kRowBytes + (((adjacent ? kg : kg * NC) ^ swizzle_of_row<T, D>(n)) * 16));
+  const unsigned step = adjacent ? 32u : 16u;
   unsigned coff[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) coff[c] = (unsigned)(n * TL::kRowBytes + ((order.chunk(c, kg) ^ swizzle_of_row<T, D>(n)) * 16));
+  for (int c = 0; c < NC; ++c) coff[c] = coff0 ^ (c * step);
   // block cb of the tile in ring slot rs: its rows and where its 1/|k_j| start in this wave's copy
   auto block_rows = [&](int rs, int cb) { return ctile + (rs % kSimRing) * kTileBytes + cb * 32 * TL::kRowBytes; };
   auto inv_index = [&](int rs, int cb) { return ((rs % kSimInvRing) * kSimWaves + wave) * kSimSlotTile + cb * 32; };
@@ -361,8 +362,8 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   int lrow[2], nrow[2];
   chunk_rows(c, lrow);
   chunk_rows(c + kChunkStep, nrow);
-  const StepOrder<T, D> order(true);  // this kernel loads 64 rows per wave and chunk, all the time
-  auto row_frag = [&](Frag<T, D>& f, const char* row_ptr) { frag_load(f, row_ptr, kg, order); };
+  // adjacent order: this kernel loads 64 rows per wave and chunk, all the time
+  auto row_frag = [&](Frag<T, D>& f, const char* row_ptr) { frag_load_adjacent(f, row_ptr, kg); };
   Frag<T, D> lf[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) row_frag(lf[s], kbase + (size_t)lrow[s] * TL::kRowBytes);
@@ -406,7 +407,7 @@ __global__ void __launch_bounds__(kResThreads, 2) similarity_resident_kernel(Mer
   const int nblocks = S_pad / 32;
   unsigned coff[TL::kFragChunks];   // chunk c of this lane's fragment inside a block of 32 padded rows
 #pragma unroll
-  for (int c = 0; c < TL::kFragChunks; ++c) coff[c] = (unsigned)(n * TL::kStride + order.chunk(c, kg) * 16);
+  for (int c = 0; c < TL::kFragChunks; ++c) coff[c] = (unsigned)(n * TL::kStride + c * 32 + kg * 16);
   auto block_base = [&](int b) { return ckeys + b * 32 * TL::kStride; };
   auto block_inv = [&](int b) { return cinv + b * 32 + kg * 4; };
   while (c < n_chunks) {
