@@ -4,9 +4,10 @@
 // Fragment convention.  A 32x32 MFMA block multiplies 32 rows of operand A by 32 rows of operand B
 // over the whole head dimension.  Lane l holds, for row (l % 32), the half of the row selected by
 // (l / 32): elements [ (l/32)*D/2, (l/32+1)*D/2 ).  The MFMA pairs element e of A's lane group with
-// element e of B's lane group, so any assignment of row elements to (lane group, step) gives the
-// same dot product as long as both operands use the same one; taking contiguous halves lets every
-// lane fetch its fragment with 16-byte loads from one contiguous run.
+// element e of B's lane group, so any assignment of row elements to (lane group, step) that both operands
+// share gives the same sum of products, up to the rounding of its order (the similarity of bf16 keys,
+// whose nearest neighbours can be a rounding apart, fixes that order per layer); taking contiguous
+// halves lets every lane fetch its fragment with 16-byte loads from one contiguous run.
 // Result layout of a 32x32 block (f32x16 acc): acc[r] is the product of A row
 // (r/4)*8 + (l/32)*4 + (r%4) with B row (l % 32).
 #pragma once
@@ -79,7 +80,6 @@ __device__ __forceinline__ void mma(f32x16_t& acc, const Frag<T, D>& a, const Fr
 #pragma unroll
   for (int i = 0; i < Tile<T, D>::kFragChunks; ++i) mma_chunk<T>(acc, a.c[i], b.c[i]);
 }
-
 
 __device__ __forceinline__ f32x16_t acc_zero() {
   f32x16_t z;

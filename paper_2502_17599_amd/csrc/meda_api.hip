@@ -69,10 +69,10 @@ static bool resident_pays(const Plan& p, int64_t pairs) {
 }
 
 // fp32 problems for the split kernel, the others go to the direct one: from a number of positions over all (layer, head)
-// pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads,
-// would walk too long a share of the set.  Below it the waves that take their blocks again, and the search for copies in
-// the selection (2 to 8 us), cost more than the matrix instructions save.  Selection and similarity in us, direct kernel /
-// split kernel, a tenth and three tenths kept:
+// pairs on that grows with the share kept, and where the direct kernel's waves, which share no loads, would walk too long
+// a share of the set.  Below it the waves that take their blocks again, and the search for copies in the selection (2 to
+// 8 us), cost more than the matrix instructions save.  Selection and similarity in us, direct kernel / split kernel, a
+// tenth and three tenths kept:
 //   rows of 256 bytes  32 pairs of 1200  31 / 34, 40 / 45   of 2000   46 / 42, 64 / 63   of 3000  72 / 57, 106 / 86
 //                      128 of 300        25 / 25, 26 / 29   of 700    37 / 32, 45 / 43   of 1200  65 / 43, 81 / 63
 //                      8 of 3000         46 / 39, 58 / 65   of 5000   71 / 54, 116 / 94
@@ -229,7 +229,7 @@ meda_status make_plan(const meda_params* p, Plan* out) {
   pl.off_layer_off = take((size_t)(pl.L + 1) * 8);
   pl.off_sel_idx = take((size_t)pl.B * pl.Hkv * 4);
   pl.off_sel_inv = take((size_t)pl.B * pl.Hkv * 4);
-  pl.off_packed_k = take((size_t)pl.B * pl.Hkv * pl.d * pl.elt);
+  pl.off_packed_k = take(pl.dtype == MEDA_BF16 ? (size_t)pl.B * pl.Hkv * pl.d * pl.elt : 0);  // no fp32 kernel reads packed keys
   const size_t less_bytes = pl.n_less_total * 4 + 16;
   pl.off_less_idx = take(less_bytes);
   pl.off_less_slot = take(less_bytes);

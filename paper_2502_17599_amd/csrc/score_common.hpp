@@ -11,10 +11,11 @@
 //                                entropies are reduced per tile
 //           score_accum_dma_kernel     the same for grouped heads, fed by asynchronous copies
 //           score_accum_blocks_kernel  the row-block mode (more than 128 scoring rows)
+//   both    score_stats_direct_kernel, score_accum_direct_kernel  windows over few keys (score_direct.hip)
 // Logits are kept in the base-2 domain: t = (q.k) * scale * log2(e), probabilities are exp2(t - max).
 // This header holds what the passes share: the argument block and its filling from the plan.  Pass A and each form
-// of pass B are translation units of their own (score_stats.hip, score_accum.hip, score_accum_dma.hip,
-// score_accum_blocks.hip): they sit at the edge of their register budgets and the compiler's allocation for one
+// of pass B are translation units of their own (score_stats.hip, score_stats_dma.hip, score_accum.hip,
+// score_accum_dma.hip, score_accum_blocks.hip, score_direct.hip): they sit at the edge of their register budgets and the compiler's allocation for one
 // kernel shifted when another lived in the same module.
 #pragma once
 #include <type_traits>
